@@ -45,9 +45,7 @@ using namespace trig;
 namespace {
 
 constexpr int kPlainWaves = 4;      // waves (events) per workgroup, plain form
-constexpr int kChunkMsd = 512;      // layer-2 hits per LDS chunk (2 floats each)
-constexpr int kChunkFit = 256;      // layer-2 hits per LDS chunk (4 floats each)
-constexpr int kChunkZ = 160;        // layer-2 hits per LDS chunk (6 floats each)
+constexpr int kChunk = 512;         // layer-2 hits per LDS chunk of a wave (2 floats each)
 constexpr int kScanBlock = 256;     // threads of the scan/compaction kernels
 constexpr int kCompactItems = 4;    // events per thread in compaction
 constexpr int kPersistWaves = 4;    // waves per workgroup, persistent form
@@ -56,18 +54,24 @@ constexpr int kDefaultTileUnits = 8;  // pair tiles (of 64 pairs) per work unit
 constexpr int kClaimsPerGroup = 8;    // claims per workgroup (pipelined batched form) or per wave (binned)
 constexpr double kRuleFill = 0.85;    // built-in rule: hits per block over the LDS capacity
 
+// Bound of the rejecting test of wave_count over one event (whole wave).
 template <class T>
-struct Chunk;
-template <>
-struct Chunk<MsdBasisTest> { static constexpr int value = kChunkMsd; };
-template <>
-struct Chunk<WindowTest> { static constexpr int value = kChunkMsd; };
-template <>
-struct Chunk<MsdFitTest> { static constexpr int value = kChunkFit; };
-template <>
-struct Chunk<MsdZTest> { static constexpr int value = kChunkZ; };
-template <>
-struct Chunk<WindowZTest> { static constexpr int value = kChunkMsd; };
+__device__ __forceinline__ PreBound pre_bound(const Consts& c, const float* __restrict__ x,
+                                              const float* __restrict__ y, const float* __restrict__ z,
+                                              const EventRange& ev) {
+    if constexpr (std::is_same<T, MsdFitTest>::value) {
+        const float M = layer_mag(GlobalHits{x, y}, ev.o1, ev.n1);
+        return {__builtin_fmaxf(c.fit_b0x + c.fit_b1x * M, c.fit_b0y + c.fit_b1y * M), true};
+    } else if constexpr (std::is_same<T, MsdZTest>::value) {
+        // the slope bound of layers 0 and 2 (it holds for any two layers)
+        const PairBounds b = MsdZPrune::event_bounds(c, SlopeHits{x, y, z}, ev.o0, ev.n0, ev.o2, ev.n2);
+        return {b.pre, b.prune};
+    } else if constexpr (std::is_same<T, MsdBasisTest>::value) {
+        return {c.pre_msd, true};
+    } else {
+        return {c.pre_win, true};
+    }
+}
 
 __device__ __forceinline__ void write_result(int e, int32_t cnt, const Consts& c,
                                              int32_t* counts, uint8_t* accept,
@@ -87,8 +91,7 @@ __global__ __launch_bounds__(WPB * kWave) void k_plain(const int32_t* __restrict
                                                        int32_t* __restrict__ counts,
                                                        uint8_t* __restrict__ accept,
                                                        uint32_t* status) {
-    constexpr int KCH = Chunk<T>::value;
-    __shared__ __align__(16) float lds_all[WPB][KCH * T::HF];
+    __shared__ __align__(16) float lds_all[WPB][2 * kChunk];
     const int w = uniform_i(threadIdx.x / kWave);
     const int e = uniform_i(blockIdx.x) * WPB + w;
     if (e >= n_events) return;
@@ -96,7 +99,8 @@ __global__ __launch_bounds__(WPB * kWave) void k_plain(const int32_t* __restrict
     int32_t cnt = load_event(off, e, c.n_hits, ev);
     if (cnt == 0) {
         const uint32_t tiles = pair_tiles(ev);
-        if (tiles) cnt = (int32_t)wave_count<T, KCH>(x, y, z, ev, 0, tiles, c, lds_all[w]);
+        if (tiles)
+            cnt = (int32_t)wave_count<T, kChunk>(x, y, z, ev, 0, tiles, c, pre_bound<T>(c, x, y, z, ev), lds_all[w]);
     }
     if (lane_id() == 0) write_result(e, cnt, c, counts, accept, status);
 }
@@ -299,8 +303,7 @@ __global__ __launch_bounds__(WPB * kWave) void k_persistent(
     const float* __restrict__ y, const float* __restrict__ z, Consts c, const int64_t* __restrict__ ustart,
     int tile_units,
     unsigned long long* counter, int32_t* counts) {
-    constexpr int KCH = Chunk<T>::value;
-    __shared__ __align__(16) float lds_all[WPB][KCH * T::HF];
+    __shared__ __align__(16) float lds_all[WPB][2 * kChunk];
     __shared__ unsigned long long s_first;
     const int w = uniform_i(threadIdx.x / kWave);
     float* lds = lds_all[w];
@@ -326,7 +329,7 @@ __global__ __launch_bounds__(WPB * kWave) void k_persistent(
                 const uint32_t tiles = pair_tiles(ev);
                 const uint32_t tb = (uint32_t)((u - ustart[e]) * tile_units);
                 const uint32_t te = min(tiles, tb + (uint32_t)tile_units);
-                const uint32_t cnt = wave_count<T, KCH>(x, y, z, ev, tb, te, c, lds);
+                const uint32_t cnt = wave_count<T, kChunk>(x, y, z, ev, tb, te, c, pre_bound<T>(c, x, y, z, ev), lds);
                 if (lane_id() == 0 && cnt) atomicAdd(&counts[e], (int32_t)cnt);
             }
         }
@@ -451,9 +454,8 @@ __global__ __launch_bounds__(kBinWaves * kWave) void k_event_z(const int32_t* __
                                                                const float* __restrict__ z, Consts c,
                                                                int32_t* __restrict__ counts,
                                                                uint8_t* __restrict__ accept, uint32_t* status) {
-    constexpr int KCH = Chunk<T>::value;
-    static_assert(KCH * T::HF >= 2 * kPBuf, "the pruned path's buffers fit in the staging slice");
-    __shared__ __align__(16) float lds_all[kBinWaves][KCH * T::HF];
+    static_assert(kChunk >= kPBuf, "the pruned path's buffers fit in the staging slice");
+    __shared__ __align__(16) float lds_all[kBinWaves][2 * kChunk];
     const int w = uniform_i((int)(threadIdx.x / kWave));
     const int64_t e64 = (int64_t)blockIdx.x * kBinWaves + w;
     if (e64 >= n_events) return;
@@ -478,7 +480,7 @@ __global__ __launch_bounds__(kBinWaves * kWave) void k_event_z(const int32_t* __
                 cnt = (int32_t)wave_event_pruned<P>(c, pb, sh, ev.o0, ev.n0, ev.o1, ev.n1, ev.o2, ev.n2, lds,
                                                     lds + kPBuf);
         } else {
-            cnt = (int32_t)wave_count<T, KCH>(x, y, z, ev, 0, pair_tiles(ev), c, lds);
+            cnt = (int32_t)wave_count<T, kChunk>(x, y, z, ev, 0, pair_tiles(ev), c, pre_bound<T>(c, x, y, z, ev), lds);
         }
     }
     if (lane_id() == 0) write_result(e, cnt, c, counts, accept, status);
@@ -564,6 +566,8 @@ Consts make_consts(const trig_params* p, int n_hits) {
     c.fit_a1y = fy.a1;
     c.fit_b0x = fx.b0;
     c.fit_b1x = fx.b1;
+    c.fit_b0y = fy.b0;
+    c.fit_b1y = fy.b1;
     const SlopeBounds sx = slope_bounds(c.qmax_x), sy = slope_bounds(c.qmax_y);
     c.zs_a0x = sx.a0;
     c.zs_a1x = sx.a1;

@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace trig {
 
 constexpr int kWave = 64;
@@ -37,8 +39,8 @@ struct Consts {
     float zs_a0x, zs_a1x, zs_a0y, zs_a1y;
     // TRIG_TEST_MSD: a triplet that passes a plane has |a| <= a0 + a1 M and
     // |b| <= b0 + b1 M (device evaluation order, M >= |c1| the plane's
-    // layer-1 coordinate), per plane for a, x-z plane for b
-    float fit_a0x, fit_a1x, fit_a0y, fit_a1y, fit_b0x, fit_b1x;
+    // layer-1 coordinate), per plane
+    float fit_a0x, fit_a1x, fit_a0y, fit_a1y, fit_b0x, fit_b1x, fit_b0y, fit_b1y;
     // Pair prefilter of the batched form: (|u| <= bx and |v| <= by) implies
     // max(|u|, |v|) <= max(bx, by).  MSD_BASIS: the larger beta; window: the
     // larger window.
@@ -167,10 +169,21 @@ __device__ __forceinline__ int wave_inclusive_sum(int x) {
 __device__ __forceinline__ uint64_t lanes(bool cmp) { return __builtin_amdgcn_ballot_w64(cmp); }
 
 // ----------------------------------------------------------------------------
-// Test policies.  HF = floats staged in LDS per layer-2 hit; Pair = the part
-// of the test that depends on (i, j) only; pass() completes it with hit k and
-// returns the mask of lanes whose triplet passes.
-// Staged padding and invalid pairs are NaN, which fails every comparison.
+// Test policies.  HF = floats of a layer-2 hit that pass() reads (stage());
+// Pair = the part of the test that depends on (i, j) only; pass() completes it
+// with hit k and returns the mask of lanes whose triplet passes.
+//
+// Rejecting test of the every-triplet loops (wave_count): pre_pair(i, j) and
+// pre_k(k) give one value per plane, and a triplet that passes has
+// |pre_pair + pre_k| <= the loop's bound in both planes, one binary32 sum.
+//   MSD tests: the partial sum b = f32(p + w) of the basis form, p = f32(
+//     f32(V0 c_i) + f32(V1 c_j)), w = f32(V2 c_k).  Basis form: Q =
+//     f32(f32(a^2) + f32(b^2)) >= f32(b^2), so |b| <= beta.  Fit written out:
+//     |b| <= b0 + b1 M (csrc/trig_bounds.hpp).
+//   window: s_k - s_i (as s_k + (-s_i), the same binary32 value) is the
+//     test's own quantity; a pair outside the layer-1 window gives NaN.
+//   per-hit z, MSD: s_k - s_i, |.| <= (a0 + a1 M) / zmin.
+// Invalid pairs and padding are NaN, which fails every comparison.
 // ----------------------------------------------------------------------------
 
 // TRIG_TEST_MSD_BASIS: Q = a^2 + b^2 in the basis (u, v).
@@ -184,9 +197,11 @@ struct MsdBasisTest {
         h[0] = c.V2 * x;
         h[1] = c.V2 * y;
     }
-    __device__ static __forceinline__ void pad(float* h) {
-        h[0] = __builtin_nanf("");
-        h[1] = __builtin_nanf("");
+    __device__ static __forceinline__ float2 pre_k(const Consts& c, float x, float y) {
+        return make_float2(c.V2 * x, c.V2 * y);
+    }
+    __device__ static __forceinline__ float2 pre_pair(const Consts& c, float xi, float yi, float xj, float yj) {
+        return make_float2(c.V0 * xi + c.V1 * xj, c.V0 * yi + c.V1 * yj);
     }
     __device__ static __forceinline__ Pair pair(const Consts& c, float xi, float yi, float xj,
                                                 float yj) {
@@ -226,9 +241,11 @@ struct MsdFitTest {
         h[2] = x * c.z2;
         h[3] = y * c.z2;
     }
-    __device__ static __forceinline__ void pad(float* h) {
-        const float n = __builtin_nanf("");
-        h[0] = n; h[1] = n; h[2] = n; h[3] = n;
+    __device__ static __forceinline__ float2 pre_k(const Consts& c, float x, float y) {
+        return MsdBasisTest::pre_k(c, x, y);
+    }
+    __device__ static __forceinline__ float2 pre_pair(const Consts& c, float xi, float yi, float xj, float yj) {
+        return MsdBasisTest::pre_pair(c, xi, yi, xj, yj);
     }
     __device__ static __forceinline__ Pair pair(const Consts& c, float xi, float yi, float xj,
                                                 float yj) {
@@ -267,9 +284,12 @@ struct WindowTest {
         h[0] = x / c.z2;
         h[1] = y / c.z2;
     }
-    __device__ static __forceinline__ void pad(float* h) {
-        h[0] = __builtin_nanf("");
-        h[1] = __builtin_nanf("");
+    __device__ static __forceinline__ float2 pre_k(const Consts& c, float x, float y) {
+        return make_float2(x / c.z2, y / c.z2);
+    }
+    __device__ static __forceinline__ float2 pre_pair(const Consts& c, float xi, float yi, float xj, float yj) {
+        const Pair p = pair(c, xi, yi, xj, yj);
+        return make_float2(-p.sxi, -p.syi);
     }
     __device__ static __forceinline__ Pair pair(const Consts& c, float xi, float yi, float xj,
                                                 float yj) {
@@ -306,9 +326,12 @@ struct MsdZTest {
         h[4] = y * z;
         h[5] = z * z;
     }
-    __device__ static __forceinline__ void pad(float* h) {
-        const float n = __builtin_nanf("");
-        h[0] = n; h[1] = n; h[2] = n; h[3] = n; h[4] = n; h[5] = n;
+    __device__ static __forceinline__ float2 pre_k(const Consts&, float x, float y, float z) {
+        return make_float2(x / z, y / z);
+    }
+    __device__ static __forceinline__ float2 pre_pair(const Consts&, float xi, float yi, float zi, float, float,
+                                                      float) {
+        return make_float2(-(xi / zi), -(yi / zi));
     }
     __device__ static __forceinline__ Pair pair(const Consts&, float xi, float yi, float zi, float xj, float yj,
                                                 float zj) {
@@ -350,9 +373,13 @@ struct WindowZTest {
         h[0] = x / z;
         h[1] = y / z;
     }
-    __device__ static __forceinline__ void pad(float* h) {
-        h[0] = __builtin_nanf("");
-        h[1] = __builtin_nanf("");
+    __device__ static __forceinline__ float2 pre_k(const Consts&, float x, float y, float z) {
+        return make_float2(x / z, y / z);
+    }
+    __device__ static __forceinline__ float2 pre_pair(const Consts& c, float xi, float yi, float zi, float xj,
+                                                      float yj, float zj) {
+        const Pair p = pair(c, xi, yi, zi, xj, yj, zj);
+        return make_float2(-p.sxi, -p.syi);
     }
     __device__ static __forceinline__ Pair pair(const Consts& c, float xi, float yi, float zi, float xj, float yj,
                                                 float zj) {
@@ -399,65 +426,133 @@ __device__ __forceinline__ uint32_t pair_tiles(const EventRange& ev) {
     return (ev.n2 == 0) ? 0u : (uint32_t)((np + kWave - 1) / kWave);
 }
 
+// Rejecting-test bound of an event (see the test policies): a triplet passes
+// only if both planes' sums are within `bound`; valid = false: no bound holds
+// (per-hit z outside (0, inf) in layers 0 or 2) and every triplet takes the
+// full test.
+struct PreBound {
+    float bound;
+    bool valid;
+};
+
 // Passing triplets of one event over pair tiles [t_begin, t_end); each tile
 // is 64 consecutive (i, j) pairs in row-major order (pair p -> i = p / n1,
 // j = p % n1), one pair per lane, looping over every layer-2 hit staged in
 // this wave's LDS slice (KCH hits per chunk).  Called by a whole wave with
 // uniform arguments; returns the same count on every lane.
+//
+// Every triplet gets the rejecting test of the policy (two sums, a max and
+// half a min3 on the vector unit: 3.5 instructions against 28 of the written-out
+// fit), folded over four layer-2 hits and the lane's NP pairs before one
+// vote; only a group in which some triplet is within the bound is
+// evaluated in full.  NP pairs per lane share one 16-byte LDS read per plane
+// and four layer-2 hits: with one pair per lane those reads (all lanes at one
+// address, still 1 KB each on a 128 B/clock LDS) take longer than the sums.
+// Bound by the vector unit.  100,000 events of 30 hits per layer, whole call:
+// 1.337 ms with the full test per triplet, 0.251 ms now (2.7e9 triplets; 0.15 ms
+// at 3.5 instructions each and the measured 63 T lane operations/s).
 template <class T, int KCH>
 __device__ uint32_t wave_count(const float* __restrict__ x, const float* __restrict__ y,
                                const float* __restrict__ z, const EventRange& ev, uint32_t t_begin,
-                               uint32_t t_end, const Consts& c, float* __restrict__ lds) {
+                               uint32_t t_end, const Consts& c, const PreBound& pb, float* __restrict__ lds) {
     const uint32_t stop = (uint32_t)c.count_cap;  // enough: the result is capped there
     static_assert(KCH % 4 == 0, "chunk must hold whole float4 groups");
     const unsigned lane = lane_id();
     const uint32_t n0 = (uint32_t)ev.n0, n1 = (uint32_t)ev.n1;
     const uint32_t dq = kWave / n1, dr = kWave % n1;
+    const float nan = __builtin_nanf("");
+    float* wx = lds;
+    float* wy = lds + KCH;
     uint32_t cnt = 0;
     for (int k0 = 0; k0 < ev.n2; k0 += KCH) {
         const int nk = min(KCH, ev.n2 - k0);
         const int nk_pad = (nk + 3) & ~3;
         for (int t = (int)lane; t < nk_pad; t += kWave) {
-            float* h = lds + t * T::HF;
-            if (t < nk) {
-                if constexpr (T::kZ)
-                    T::stage(c, x[ev.o2 + k0 + t], y[ev.o2 + k0 + t], z[ev.o2 + k0 + t], h);
-                else
-                    T::stage(c, x[ev.o2 + k0 + t], y[ev.o2 + k0 + t], h);
-            } else {
-                T::pad(h);
-            }
+            const int k = ev.o2 + k0 + min(t, nk - 1);
+            float2 w;
+            if constexpr (T::kZ)
+                w = T::pre_k(c, x[k], y[k], z[k]);
+            else
+                w = T::pre_k(c, x[k], y[k]);
+            wx[t] = t < nk ? w.x : nan;
+            wy[t] = t < nk ? w.y : nan;
         }
         wave_lds_sync();
         const uint32_t p0 = t_begin * (uint32_t)kWave + lane;
-        uint32_t i = p0 / n1, j = p0 - (p0 / n1) * n1;
-        for (uint32_t t = t_begin; t < t_end; ++t) {
-            typename T::Pair pr = T::invalid();
-            if (i < n0) {
+        uint32_t i = p0 / n1, j = p0 - (p0 / n1) * n1;  // the lane's pair of tile t
+        uint32_t t = t_begin;
+        // The full test of NP tiles from t on and layer-2 hits [k, k + 4).
+        auto exact = [&](int np, int k) {
+#pragma unroll 1
+            for (int q = 0; q < np; ++q) {
+                const uint32_t p = (t + (uint32_t)q) * (uint32_t)kWave + lane;
+                const uint32_t pi = p / n1, pj = p - (p / n1) * n1;
+                typename T::Pair pr = T::invalid();
+                if (pi < n0) {
+                    if constexpr (T::kZ)
+                        pr = T::pair(c, x[ev.o0 + pi], y[ev.o0 + pi], z[ev.o0 + pi], x[ev.o1 + pj], y[ev.o1 + pj],
+                                     z[ev.o1 + pj]);
+                    else
+                        pr = T::pair(c, x[ev.o0 + pi], y[ev.o0 + pi], x[ev.o1 + pj], y[ev.o1 + pj]);
+                }
+                const int ke = min(k + 4, nk);
+#pragma unroll 1
+                for (int kk = k; kk < ke; ++kk) {
+                    const int h2 = ev.o2 + k0 + kk;
+                    float h[T::HF];
+                    if constexpr (T::kZ)
+                        T::stage(c, x[h2], y[h2], z[h2], h);
+                    else
+                        T::stage(c, x[h2], y[h2], h);
+                    cnt += (uint32_t)__builtin_popcountll(T::pass(c, pr, h));
+                }
+            }
+        };
+        auto tiles = [&](auto np) {
+            constexpr int NP = decltype(np)::value;
+            float2 p[NP];
+            uint32_t in = i, jn = j;
+#pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                const bool v = in < n0;
+                const int hi = ev.o0 + (int)min(in, n0 - 1), hj = ev.o1 + (int)jn;
                 if constexpr (T::kZ)
-                    pr = T::pair(c, x[ev.o0 + i], y[ev.o0 + i], z[ev.o0 + i], x[ev.o1 + j], y[ev.o1 + j],
-                                 z[ev.o1 + j]);
+                    p[q] = T::pre_pair(c, x[hi], y[hi], z[hi], x[hj], y[hj], z[hj]);
                 else
-                    pr = T::pair(c, x[ev.o0 + i], y[ev.o0 + i], x[ev.o1 + j], y[ev.o1 + j]);
+                    p[q] = T::pre_pair(c, x[hi], y[hi], x[hj], y[hj]);
+                p[q].x = v ? p[q].x : nan;
+                p[q].y = v ? p[q].y : nan;
+                jn += dr;
+                in += dq;
+                if (jn >= n1) {
+                    jn -= n1;
+                    ++in;
+                }
             }
             // nk_pad is a multiple of 4: four layer-2 hits per iteration
             for (int k = 0; k < nk_pad; k += 4) {
-                const float* h = lds + k * T::HF;
-                const uint64_t m0 = T::pass(c, pr, h);
-                const uint64_t m1 = T::pass(c, pr, h + T::HF);
-                const uint64_t m2 = T::pass(c, pr, h + 2 * T::HF);
-                const uint64_t m3 = T::pass(c, pr, h + 3 * T::HF);
-                cnt += (uint32_t)(__builtin_popcountll(m0) + __builtin_popcountll(m1) +
-                                  __builtin_popcountll(m2) + __builtin_popcountll(m3));
+                const float4 vx = *reinterpret_cast<const float4*>(wx + k);
+                const float4 vy = *reinterpret_cast<const float4*>(wy + k);
+                float m = nan;  // fmin drops NaN; all NaN stays NaN and fails
+#pragma unroll
+                for (int q = 0; q < NP; ++q) {
+                    const float s0 = __builtin_fmaxf(__builtin_fabsf(p[q].x + vx.x), __builtin_fabsf(p[q].y + vy.x));
+                    const float s1 = __builtin_fmaxf(__builtin_fabsf(p[q].x + vx.y), __builtin_fabsf(p[q].y + vy.y));
+                    const float s2 = __builtin_fmaxf(__builtin_fabsf(p[q].x + vx.z), __builtin_fabsf(p[q].y + vy.z));
+                    const float s3 = __builtin_fmaxf(__builtin_fabsf(p[q].x + vx.w), __builtin_fabsf(p[q].y + vy.w));
+                    m = __builtin_fminf(__builtin_fminf(m, s0), s1);
+                    m = __builtin_fminf(__builtin_fminf(m, s2), s3);
+                }
+                if (!pb.valid || wave_any(m <= pb.bound)) exact(NP, k);
             }
-            j += dr;
-            i += dq;
-            if (j >= n1) {
-                j -= n1;
-                ++i;
-            }
-            if (cnt >= stop) break;  // wave-uniform
-        }
+            i = in;
+            j = jn;
+            t += NP;
+        };
+        // wave-uniform control flow
+        while (t + 4 <= t_end && cnt < stop) tiles(std::integral_constant<int, 4>{});
+        if (t + 2 <= t_end && cnt < stop) tiles(std::integral_constant<int, 2>{});
+        if (t < t_end && cnt < stop) tiles(std::integral_constant<int, 1>{});
         wave_lds_sync();
         if (cnt >= stop) break;
     }
