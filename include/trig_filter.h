@@ -57,9 +57,11 @@ typedef struct {
                                      the capacity are not written, and the offsets past it are not valid */
 
 /* Device workspace trig_filter_stations needs for n_events events (host-only
- * call; 0 for n_events < 0): per event 16 bytes of layer and record counts
- * and 512 bytes of window records (128 records of 16 bytes per 4 events),
- * plus 8 bytes per 16 events. */
+ * call; 0 for n_events < 0; never less for more events): per event 16 bytes
+ * of layer and record counts and 512 bytes of records, plus 8 bytes per 4
+ * events, each part rounded up.  A workspace with room for 8 bytes per 16
+ * events there (and the events rounded up to 16) is accepted too; batches of
+ * fewer than 32,768 events then run on fewer waves. */
 size_t trig_filter_workspace_bytes(int32_t n_events);
 
 /* Keep the hits of the trigger layers, event by event.
@@ -69,13 +71,16 @@ size_t trig_filter_workspace_bytes(int32_t n_events);
  * the index in out_x/out_y of the first hit of event e in trigger layer l,
  * out_layer_offsets[3*n_events] the total, and the hits of each (event,
  * layer) keep their input order.  Kernels: per-event counts of the three
- * layers and records of the 32-hit windows that hold trigger hits (their
- * start and per-layer bit masks; one pass over the station numbers), an
- * exclusive scan of the workgroup totals, then a stable scatter of the
- * trigger hits through the records (x and y read for trigger hits only).
- * The events of a group of 4 (events w, w + 4, w + 8, w + 12 of each 16)
- * that need more than 128 records together are scattered from a second pass
- * over their station numbers instead.
+ * layers and, per wave (four consecutive events of every 16, or two or one
+ * in batches of fewer than 32,768 or 16,384), a list of its trigger hits, as
+ * 16-byte records of the 32-hit windows that hold some (their start and
+ * per-layer bit masks) or as 4-byte entries per hit, whichever is shorter at
+ * the wave's first trigger hits (one pass over the station numbers); an
+ * exclusive scan of the workgroup totals (in small batches each wave sums
+ * them itself); then a stable scatter of the trigger hits through the lists
+ * (x and y read for trigger hits only).  A wave whose events need more than
+ * 512 bytes of list each on average scatters from a second pass over their
+ * station numbers instead.
  * Errors (returned before anything is enqueued): TRIG_EINVAL for a NULL
  * required pointer, n_events < 0, n_hits < 0, equal layer numbers, a non-zero
  * reserved field, out_capacity < 0, or a workspace that is too small or not

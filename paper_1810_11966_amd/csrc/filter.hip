@@ -4,23 +4,25 @@
 // on the host before the transfer (Sec. 5.3, implementation i3); here the
 // station numbers are streamed once.
 //
-// Partition: a workgroup of 4 waves owns kFilterEvents consecutive events;
-// wave w takes events w, w + 4, ...  A wave reads an event's station numbers
-// 32 per lane (two 16-byte loads of consecutive hits, 2048 hits per step),
-// so the hits of lane L precede those of lane L + 1 in a step.  The count
-// kernel sums each layer's hits and writes one record per lane window (32
-// consecutive hits) that holds a trigger hit: the window's start and its
-// three layer masks, to the wave's list in the workspace.  The scatter kernel
+// Partition: a workgroup of 4 waves owns 4 PER consecutive events; wave w
+// takes events w, w + 4, ... (PER of them).  A wave reads an event's station
+// numbers 32 per lane (two 16-byte loads of consecutive hits, 2048 hits per
+// step), so the hits of lane L precede those of lane L + 1 in a step.  The
+// count kernel sums each layer's hits and writes a list of the wave's trigger
+// hits to the workspace, of one of two kinds (below).  The scatter kernel
 // finds every event's output positions with one lane per event, then each
-// wave takes its list 64 records at a time: a wave scan of the records'
-// layer counts gives each record's first output position per layer, and two
-// records per round, one per half-wave and one lane per hit of the window,
-// move x and y (a hit's rank within its record is the bits below it in the
-// record's mask).  A wave whose events need more records than its list
-// holds leaves the list incomplete, and the scatter then reads those
-// events' station numbers again: a hit's rank in its layer is the exclusive
-// prefix over lanes of the per-lane counts plus the count of the lane's
-// earlier hits.
+// wave takes its list 64 records at a time:
+//   window records (a lane window's start and three layer masks): a wave scan
+//     of the records' layer counts gives each record's first output position
+//     per layer, and two records per round, one per half-wave and one lane
+//     per hit of the window, move x and y (a hit's rank within its record is
+//     the bits below it in the record's mask);
+//   hit entries (offset and layer): a lane per hit, ranked in its layer by
+//     one ballot per layer.
+// A wave whose events need more than its list holds leaves it incomplete, and
+// the scatter then reads those events' station numbers again: a hit's rank in
+// its layer is the exclusive prefix over lanes of the per-lane counts plus
+// the count of the lane's earlier hits.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -35,7 +37,10 @@ namespace {
 
 constexpr int kFilterThreads = 256;
 constexpr int kFilterWaves = kFilterThreads / trig::kWave;
-constexpr int kFilterEvents = 16;  // events per workgroup
+// Events of a wave (PER): 4 where there are enough of them to fill the GPU
+// with waves, else 2 or 1 (filter_per).
+constexpr int kMaxPer = 4;
+constexpr int kEventRecBytes = 512;  // record bytes per event in the workspace
 
 struct Range {
     int64_t a, b;
@@ -164,13 +169,35 @@ __device__ __forceinline__ LaneMatch match_lane_t(const LaneStations& s, uint32_
     return r;
 }
 
-// Records one wave keeps for the scatter: per lane window of kLaneHits
-// consecutive hits that holds a trigger hit of its event, the window's start
+// What one wave keeps for the scatter, in input order, in kEventRecBytes per
+// event of the wave: either window records, per lane window of kLaneHits
+// consecutive hits that holds a trigger hit of its event the window's start
 // relative to the event's first hit and the transposed layer masks (bit
-// tpos(b): hit start + b), in input order.
-constexpr int kWaveRecords = 128;
+// tpos(b): hit start + b); or hit entries, per trigger hit its offset in the
+// event and its layer in the top two bits.  The wave takes the kind that is
+// shorter on its first step with a trigger hit: windows where the trigger
+// layers' hits lie together (detector order: 16 bytes for up to 32 hits),
+// entries where they are scattered (stations in time order: about one hit
+// per window).  5,003 events of 5,000 hits in random station order, whole
+// call: 54 us with windows only (the lists overflowed, so the station numbers
+// were read twice) and four events per wave, 33 us now, of which the gather
+// of x and y takes about 14: its 64-byte sectors hold one hit each.
 typedef unsigned u32x4r __attribute__((ext_vector_type(4)));  // {start, m0, m1, m2}
+template <int PER>
+constexpr int wave_windows() {
+    return PER * kEventRecBytes / 16;
+}
+template <int PER>
+constexpr int wave_entries() {
+    return PER * kEventRecBytes / 4;
+}
+constexpr uint32_t kEntryLayer = 30;  // an entry's layer starts at this bit
+// Per event in ev_recs: its records (at most kRecMax written, more than any
+// list holds) and whether they are entries.
+constexpr int32_t kRecMax = 1 << 20;
+constexpr int32_t kRecEntries = 1 << 30;
 
+template <int PER>
 __global__ __launch_bounds__(kFilterThreads) void k_filter_count(const int64_t* __restrict__ off, int n_events,
                                                                    int64_t n_hits, const uint8_t* __restrict__ st,
                                                                    uint32_t layers, int vec,
@@ -179,7 +206,8 @@ __global__ __launch_bounds__(kFilterThreads) void k_filter_count(const int64_t* 
                                                                    u32x4r* __restrict__ wave_recs,
                                                                    int32_t* __restrict__ ev_recs,
                                                                    uint32_t* status) {
-    constexpr int kPer = kFilterEvents / kFilterWaves;  // events of a wave
+    constexpr int kFilterEvents = PER * kFilterWaves;  // events of a workgroup
+    constexpr int kPer = PER;
     __shared__ int64_t wave_total[kFilterWaves];
     __shared__ uint32_t tup[kLaneHits + 1];  // tupto(h)
     if (threadIdx.x <= (unsigned)kLaneHits) tup[threadIdx.x] = tupto((int)threadIdx.x);
@@ -187,7 +215,8 @@ __global__ __launch_bounds__(kFilterThreads) void k_filter_count(const int64_t* 
     const int w = trig::uniform_i((int)(threadIdx.x / trig::kWave));
     const int lane = (int)trig::lane_id();
     const int e_first = (int)blockIdx.x * kFilterEvents;
-    u32x4r* wrec = wave_recs + ((int64_t)blockIdx.x * kFilterWaves + w) * kWaveRecords;
+    u32x4r* wrec = wave_recs + ((int64_t)blockIdx.x * kFilterWaves + w) * wave_windows<PER>();
+    uint32_t* went = reinterpret_cast<uint32_t*>(wrec);
     // The wave's events (w, w + 4, ...): ranges; empty and malformed ones are
     // written here, the others while their hits stream by.
     int64_t ra[kPer], rb[kPer];
@@ -219,8 +248,9 @@ __global__ __launch_bounds__(kFilterThreads) void k_filter_count(const int64_t* 
             if (q > k && live[q]) n = q;
         return n;
     };
-    int32_t used = 0;   // records of wrec written
-    bool keep = true;   // wrec holds every record of this wave's events so far (wave-uniform)
+    int32_t used = 0;   // records written
+    bool keep = true;   // the list holds every record of this wave's events so far (wave-uniform)
+    bool entries = false, chosen = false;  // the list's kind (wave-uniform)
     int64_t total = 0;
     // One flat stream over the live events' steps: the next step's station
     // numbers (of this event or the next) are in flight while this step's
@@ -263,20 +293,50 @@ __global__ __launch_bounds__(kFilterThreads) void k_filter_count(const int64_t* 
             const LaneMatch m = match_lane_t(cur, in_t, layers);
 #pragma unroll
             for (int l = 0; l < 3; ++l) c[l] += (uint32_t)__builtin_popcount(m.m[l]);
-            cur = nxt;
-            // one record per lane window with a trigger hit, in lane order
-            const bool active = (m.m[0] | m.m[1] | m.m[2]) != 0u;
-            const uint64_t am = trig::lanes(active);
-            const int32_t nrec = (int32_t)__builtin_popcountll(am);
-            recs += nrec;
-            if (keep && used + nrec > kWaveRecords) keep = false;
-            if (keep && active) {
-                const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(am >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)am, 0u));
-                // h0 - ra[k] lies in [-15, rb[k] - ra[k]): an int32
-                wrec[used + rank] = u32x4r{(uint32_t)(int32_t)(h0 - ra[k]), m.m[0], m.m[1], m.m[2]};
+            const uint32_t all = m.m[0] | m.m[1] | m.m[2];
+            const uint64_t am = trig::lanes(all != 0u);
+            if (am) {
+                const int32_t n_win = (int32_t)__builtin_popcountll(am);
+                if (!chosen || entries) {
+                    const int n = __builtin_popcount(all);
+                    const int incl = trig::wave_inclusive_sum(n);
+                    const int32_t n_hit = __builtin_amdgcn_readlane(incl, 63);
+                    if (!chosen) entries = n_hit < 4 * n_win;  // 4 bytes a hit or 16 a window
+                    if (entries) {
+                        // one entry per trigger hit, lane by lane
+                        if (used + n_hit > wave_entries<PER>() || rb[k] - ra[k] >= (1ll << kEntryLayer)) keep = false;
+                        recs = keep ? recs + n_hit : kRecMax;
+                        if (keep) {
+                            int32_t at = used + incl - n;
+                            for (uint32_t left = all; left;) {
+                                // the lane's first hit left: the lowest word q
+                                // with a set bit, then its lowest byte
+                                const uint32_t rows = left | (left >> 16);
+                                const int q = __builtin_ctz((rows | (rows >> 8)) & 0xFFu);
+                                const int bit = __builtin_ctz(left & (0x01010101u << q));
+                                left &= ~(1u << bit);
+                                const uint32_t l = (m.m[0] >> bit) & 1u ? 0u : ((m.m[1] >> bit) & 1u ? 1u : 2u);
+                                went[at++] = (l << kEntryLayer) | (uint32_t)(h0 - ra[k] + 4 * q + (bit >> 3));
+                            }
+                            used += n_hit;
+                        }
+                    }
+                    chosen = true;
+                }
+                if (!entries) {
+                    // one record per lane window with a trigger hit, in lane order
+                    recs += n_win;
+                    if (keep && used + n_win > wave_windows<PER>()) keep = false;
+                    if (keep && all) {
+                        const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(am >> 32),
+                                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)am, 0u));
+                        // h0 - ra[k] lies in [-15, rb[k] - ra[k]): an int32
+                        wrec[used + rank] = u32x4r{(uint32_t)(int32_t)(h0 - ra[k]), m.m[0], m.m[1], m.m[2]};
+                    }
+                    if (keep) used += n_win;
+                }
             }
-            if (keep) used += nrec;
+            cur = nxt;
             if (k1 != k) {
                 // event k is complete
                 const int e = e_first + w + kFilterWaves * k;
@@ -285,7 +345,7 @@ __global__ __launch_bounds__(kFilterThreads) void k_filter_count(const int64_t* 
                     counts[3 * (int64_t)e] = (int32_t)s0;
                     counts[3 * (int64_t)e + 1] = (int32_t)s1;
                     counts[3 * (int64_t)e + 2] = (int32_t)s2;
-                    ev_recs[e] = recs;
+                    ev_recs[e] = min(recs, kRecMax) | (entries ? kRecEntries : 0);
                 }
                 total += (int64_t)s0 + s1 + s2;
                 c[0] = c[1] = c[2] = 0u;
@@ -311,7 +371,7 @@ struct ScatterEvent {
     int64_t d[3];   // s[l] minus the layer-l hits of the wave's earlier events
     int64_t a;      // first hit of the event
     int32_t rec0;   // first record of the event in its wave's list
-    int32_t nrec;   // records of the event (0 for a malformed one)
+    int32_t nrec;   // records or entries of the event (0 for a malformed one)
     int32_t ok;     // the event range is well-formed
     int32_t pad;
 };
@@ -324,14 +384,42 @@ struct ScatterRec {
     uint32_t pad;
 };
 
-__global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_filter_scatter(
+// Sum of partials[0, n) by a whole wave, the loads of a batch in flight
+// together.
+__device__ __forceinline__ int64_t wave_prefix(const int64_t* __restrict__ partials, int n) {
+    const int lane = (int)trig::lane_id();
+    int64_t sum = 0;
+    for (int i0 = 0; i0 < n; i0 += 8 * trig::kWave) {
+        int64_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int i = i0 + u * trig::kWave + lane;
+            v[u] = i < n ? partials[i] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sum += v[u];
+    }
+#pragma unroll
+    for (int d = 1; d < trig::kWave; d <<= 1) sum += __shfl_xor(sum, d, trig::kWave);
+    return sum;
+}
+
+// Small batches (one event per wave, at most kSelfPrefix workgroups): each
+// wave sums the totals of the workgroups before its own (at most 32 KB from
+// L2) instead of a scan kernel between the two, which with its gap takes
+// longer than the sums (about 5 us against 1 us at 1,251 workgroups).
+constexpr int kSelfPrefix = 4096;
+
+template <int PER>
+__global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(PER == kMaxPer ? 8 : 6))) void k_filter_scatter(
     const int64_t* __restrict__ off, int n_events, int64_t n_hits, const uint8_t* __restrict__ st,
     const float* __restrict__ x, const float* __restrict__ y, uint32_t layers, int vec,
     const int32_t* __restrict__ counts, const int64_t* __restrict__ partials,
     const u32x4r* __restrict__ wave_recs, const int32_t* __restrict__ ev_recs, int n_blocks, int32_t capacity,
     int32_t* __restrict__ out_off, float* __restrict__ out_x, float* __restrict__ out_y, uint32_t* status) {
+    constexpr int kFilterEvents = PER * kFilterWaves;  // events of a workgroup
     static_assert(kFilterEvents <= trig::kWave, "one lane per event in the prologue");
-    constexpr int kPer = kFilterEvents / kFilterWaves;  // events of a wave
+    constexpr int kPer = PER;
     // Per wave, its own copies: no wave waits for another.
     __shared__ ScatterEvent ev_all[kFilterWaves][kPer];  // the wave's events w, w + 4, ...
     __shared__ int64_t cnt_all[kFilterWaves][kFilterEvents][3];
@@ -347,14 +435,18 @@ __global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(
     const int e_first = (int)blockIdx.x * kFilterEvents;
     const int64_t cap = capacity;
     ScatterEvent* ev = ev_all[w];
-    // The first 64 entries of the wave's list, loaded with the prologue's
-    // loads (one round trip for both; entries past the wave's records are
-    // not used, and the list holds kWaveRecords >= 64 entries).
-    static_assert(kWaveRecords >= trig::kWave, "first chunk inside the list");
-    const u32x4r* wrec = wave_recs + ((int64_t)blockIdx.x * kFilterWaves + w) * kWaveRecords;
-    const u32x4r first = wrec[lane];
+    // The first 64 records of the wave's list (or the last of a list of 32),
+    // loaded with the prologue's loads (one round trip for both; those past
+    // the wave's records are not used), and for small batches, where the chain
+    // of round trips is the kernel's time, the first 64 entries.
+    const u32x4r* wrec = wave_recs + ((int64_t)blockIdx.x * kFilterWaves + w) * wave_windows<PER>();
+    const uint32_t* went = reinterpret_cast<const uint32_t*>(wrec);
+    const u32x4r first = wrec[min(lane, wave_windows<PER>() - 1)];
+    const uint32_t first_entry = PER < kMaxPer ? went[lane] : 0u;
+    constexpr bool self = PER == 1;
+    const int64_t wg_base = self ? wave_prefix(partials, (int)blockIdx.x) : partials[blockIdx.x];
     if ((int)blockIdx.x == n_blocks - 1 && threadIdx.x == 0) {
-        const int64_t total = partials[n_blocks];
+        const int64_t total = self ? wg_base + partials[blockIdx.x] : partials[n_blocks];
         if (total > cap && status) atomicOr(status, TRIG_FILTER_CAPACITY);
         out_off[3 * (int64_t)n_events] = (int32_t)std::min<int64_t>(total, cap);
     }
@@ -362,9 +454,9 @@ __global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(
     // workgroup: its counts and record count; then, for the wave's own
     // events (j % 4 == w), the output positions, the first record in the
     // wave's list and the offsets out_off[3 e + l].
-    int32_t n_rec = 0;  // records of the wave's events
+    int32_t n_rec = 0;      // records of the wave's events
+    bool entries = false;   // they are hit entries
     {
-        const int64_t wg_base = partials[blockIdx.x];
         int64_t(*cnt)[3] = cnt_all[w];
         int32_t* nrec = nrec_all[w];
         const int j = lane;
@@ -399,7 +491,7 @@ __global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(
             int32_t rec_before = 0;
             for (int k = 0; k < j; ++k) before += cnt[k][0] + cnt[k][1] + cnt[k][2];
             for (int k = w; k < j; k += kFilterWaves) {
-                rec_before += nrec[k];
+                rec_before += nrec[k] & ~kRecEntries;
                 wave_before[0] += cnt[k][0];
                 wave_before[1] += cnt[k][1];
                 wave_before[2] += cnt[k][2];
@@ -412,7 +504,7 @@ __global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(
             for (int l = 0; l < 3; ++l) v.d[l] = v.s[l] - wave_before[l];
             v.a = r.a;
             v.rec0 = rec_before;
-            v.nrec = nr;
+            v.nrec = nr & ~kRecEntries;
             v.ok = r.ok ? 1 : 0;
             v.pad = 0;
             ev[j / kFilterWaves] = v;
@@ -421,11 +513,46 @@ __global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(
                 for (int l = 0; l < 3; ++l) out_off[3 * (int64_t)e + l] = (int32_t)std::min<int64_t>(v.s[l], cap);
             }
         }
-        for (int k = w; k < kFilterEvents; k += kFilterWaves) n_rec += nrec[k];  // wave-uniform LDS reads
+        int32_t kind = 0;
+        for (int k = w; k < kFilterEvents; k += kFilterWaves) {  // wave-uniform LDS reads
+            n_rec += nrec[k] & ~kRecEntries;
+            kind |= nrec[k];
+        }
         n_rec = trig::uniform_i(n_rec);
+        entries = trig::uniform_i(kind & kRecEntries) != 0;
         trig::wave_lds_sync();  // ev[] written
     }
-    if (n_rec <= kWaveRecords) {
+    if (entries && n_rec <= wave_entries<PER>()) {
+        // The wave's list holds every trigger hit: lane i takes entry i, whose
+        // rank in its layer is the number of that layer's entries before it.
+        int32_t carry[3] = {0, 0, 0};  // layer-l entries of the chunks before
+        for (int32_t cb = 0; cb < n_rec; cb += trig::kWave) {
+            const int32_t i = cb + lane;
+            const bool valid = i < n_rec;
+            const uint32_t R = !valid ? 0u : (PER < kMaxPer && cb == 0 ? first_entry : went[i]);
+            int j = 0;  // the wave's event (index among its kPer) that holds entry i
+            for (int k = 1; k < kPer; ++k)
+                if (ev[k].nrec > 0 && ev[k].rec0 <= i) j = k;
+            const int l = (int)(R >> kEntryLayer);
+            int32_t rank = 0;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const uint64_t lm = trig::lanes(valid && l == q);
+                const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(lm >> 32),
+                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)lm, 0u));
+                if (l == q) rank = carry[q] + below;
+                carry[q] += (int32_t)__builtin_popcountll(lm);
+            }
+            const int64_t p = ev[j].d[l < 3 ? l : 0] + rank;
+            const int64_t h = ev[j].a + (int64_t)(R & ((1u << kEntryLayer) - 1u));
+            if (valid && p >= 0 && p < cap) {  // positions past an int32 block prefix are never written
+                out_x[p] = x[h];
+                out_y[p] = y[h];
+            }
+        }
+        return;
+    }
+    if (!entries && n_rec <= wave_windows<PER>()) {
         // The wave's list is complete (the count kernel's condition): its
         // records, 64 at a time.  Lane i takes record i: its event (the
         // wave's event whose record range holds i), layer counts and, by a
@@ -463,7 +590,7 @@ __global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(
             constexpr int kRoundBatch = 8;
             for (int32_t q0 = 0; q0 < nc; q0 += 2 * kRoundBatch) {
                 float vx[kRoundBatch], vy[kRoundBatch];
-                int64_t pos[kRoundBatch];
+                int32_t pos[kRoundBatch];  // below the capacity where put
                 bool put[kRoundBatch];
 #pragma unroll
                 for (int r = 0; r < kRoundBatch; ++r) {
@@ -484,7 +611,7 @@ __global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(
                     const int64_t hh = ok ? h : 0;  // a record exists, so n_hits > 0
                     vx[r] = x[hh];
                     vy[r] = y[hh];
-                    pos[r] = p;
+                    pos[r] = (int32_t)p;
                     put[r] = ok;
                 }
 #pragma unroll
@@ -555,15 +682,64 @@ __global__ void k_filter_zero(int32_t* p) { *p = 0; }
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
+// Workspace: per-event layer counts, workgroup totals (and one more for the
+// scan), per-event record counts, the waves' records.
+struct FilterLayout {
+    int nb;  // workgroups
+    size_t partials, ev_recs, wave_recs, total;
+};
+FilterLayout filter_layout(int n_events, int per) {
+    FilterLayout L;
+    const int64_t events = (int64_t)per * kFilterWaves;
+    L.nb = (int)std::max<int64_t>(1, (n_events + events - 1) / events);
+    L.partials = align256(sizeof(int32_t) * 3 * (size_t)n_events);
+    L.ev_recs = L.partials + align256(sizeof(int64_t) * (size_t)(L.nb + 1));
+    L.wave_recs = L.ev_recs + align256(sizeof(int32_t) * (size_t)n_events);
+    L.total = L.wave_recs + align256((size_t)L.nb * (size_t)events * kEventRecBytes);
+    return L;
+}
+
+// Events per wave: the most that still gives every SIMD of a 256-CU GPU its
+// eight waves.  Fewer waves leave it short of loads in flight (5,003 events of
+// 5,000 hits, shuffled: 54 us at four events per wave); more workgroups than
+// fill it only add prologues and totals to scan.
+constexpr int kOneEvent = 16384;  // fewer events than this: one per wave
+int filter_per(int n_events) { return n_events < kOneEvent ? 1 : (n_events < 2 * kOneEvent ? 2 : kMaxPer); }
+
+template <int PER>
+int launch_filter(const trig_raw_events* ev, const trig_filter_params* p, hipStream_t s) {
+    const int n = ev->n_events;
+    const FilterLayout L = filter_layout(n, PER);
+    char* ws = static_cast<char*>(p->workspace);
+    auto* counts = reinterpret_cast<int32_t*>(ws);
+    auto* partials = reinterpret_cast<int64_t*>(ws + L.partials);
+    auto* ev_recs = reinterpret_cast<int32_t*>(ws + L.ev_recs);
+    auto* wave_recs = reinterpret_cast<u32x4r*>(ws + L.wave_recs);
+    const uint32_t layers = (uint32_t)p->layers[0] | ((uint32_t)p->layers[1] << 8) | ((uint32_t)p->layers[2] << 16);
+    const int vec = (reinterpret_cast<uintptr_t>(ev->station) & 15) == 0;
+    hipLaunchKernelGGL(k_filter_count<PER>, dim3(L.nb), dim3(kFilterThreads), 0, s, ev->offsets, n, ev->n_hits,
+                       ev->station, layers, vec, counts, partials, wave_recs, ev_recs, p->out_status);
+    if (hipGetLastError() != hipSuccess) return TRIG_EHIP;
+    static_assert(kOneEvent <= kSelfPrefix * kFilterWaves, "one event per wave: the waves sum the totals");
+    if (PER > 1) {
+        hipLaunchKernelGGL(k_scan_i64, dim3(1), dim3(kScanThreads), 0, s, partials, (int64_t)L.nb);
+        if (hipGetLastError() != hipSuccess) return TRIG_EHIP;
+    }
+    hipLaunchKernelGGL(k_filter_scatter<PER>, dim3(L.nb), dim3(kFilterThreads), 0, s, ev->offsets, n, ev->n_hits,
+                       ev->station, ev->x, ev->y, layers, vec, counts, partials, wave_recs, ev_recs, L.nb,
+                       p->out_capacity, p->out_layer_offsets, p->out_x, p->out_y, p->out_status);
+    return hipGetLastError() == hipSuccess ? TRIG_OK : TRIG_EHIP;
+}
+
 }  // namespace
 
 extern "C" {
 
 size_t trig_filter_workspace_bytes(int32_t n_events) {
     if (n_events < 0) return 0;
-    const int64_t nb = std::max<int64_t>(1, ((int64_t)n_events + kFilterEvents - 1) / kFilterEvents);
-    return align256(sizeof(int32_t) * 3 * (size_t)n_events) + align256(sizeof(int64_t) * (size_t)(nb + 1)) +
-           align256(sizeof(int32_t) * (size_t)n_events) + align256(16 * (size_t)nb * kFilterWaves * kWaveRecords);
+    // enough for any number of events per wave, and never less for more events
+    return std::max(filter_layout(n_events, 1).total,
+                    std::max(filter_layout(n_events, 2).total, filter_layout(n_events, kMaxPer).total));
 }
 
 int trig_filter_stations(const trig_raw_events* ev, const trig_filter_params* p, void* stream) {
@@ -580,29 +756,13 @@ int trig_filter_stations(const trig_raw_events* ev, const trig_filter_params* p,
         hipLaunchKernelGGL(k_filter_zero, dim3(1), dim3(1), 0, s, p->out_layer_offsets);
         return hipGetLastError() == hipSuccess ? TRIG_OK : TRIG_EHIP;
     }
-    const size_t need = trig_filter_workspace_bytes(n);
-    if (!p->workspace || p->workspace_bytes < need || (reinterpret_cast<uintptr_t>(p->workspace) & 255))
+    // (a workspace for four events per wave alone is accepted too)
+    if (!p->workspace || p->workspace_bytes < filter_layout(n, kMaxPer).total ||
+        (reinterpret_cast<uintptr_t>(p->workspace) & 255))
         return TRIG_EINVAL;
-    const int nb = (int)(((int64_t)n + kFilterEvents - 1) / kFilterEvents);
-    auto* counts = static_cast<int32_t*>(p->workspace);
-    char* ws = static_cast<char*>(p->workspace);
-    const size_t counts_bytes = align256(sizeof(int32_t) * 3 * (size_t)n);
-    auto* partials = reinterpret_cast<int64_t*>(ws + counts_bytes);
-    const size_t partial_bytes = align256(sizeof(int64_t) * (size_t)(nb + 1));
-    auto* ev_recs = reinterpret_cast<int32_t*>(ws + counts_bytes + partial_bytes);
-    auto* wave_recs = reinterpret_cast<u32x4r*>(ws + counts_bytes + partial_bytes +
-                                                align256(sizeof(int32_t) * (size_t)n));
-    const uint32_t layers = (uint32_t)p->layers[0] | ((uint32_t)p->layers[1] << 8) | ((uint32_t)p->layers[2] << 16);
-    const int vec = (reinterpret_cast<uintptr_t>(ev->station) & 15) == 0;
-    hipLaunchKernelGGL(k_filter_count, dim3(nb), dim3(kFilterThreads), 0, s, ev->offsets, n, ev->n_hits,
-                       ev->station, layers, vec, counts, partials, wave_recs, ev_recs, p->out_status);
-    if (hipGetLastError() != hipSuccess) return TRIG_EHIP;
-    hipLaunchKernelGGL(k_scan_i64, dim3(1), dim3(kScanThreads), 0, s, partials, (int64_t)nb);
-    if (hipGetLastError() != hipSuccess) return TRIG_EHIP;
-    hipLaunchKernelGGL(k_filter_scatter, dim3(nb), dim3(kFilterThreads), 0, s, ev->offsets, n, ev->n_hits,
-                       ev->station, ev->x, ev->y, layers, vec, counts, partials, wave_recs, ev_recs, nb, p->out_capacity,
-                       p->out_layer_offsets, p->out_x, p->out_y, p->out_status);
-    return hipGetLastError() == hipSuccess ? TRIG_OK : TRIG_EHIP;
+    int per = filter_per(n);
+    if (p->workspace_bytes < filter_layout(n, per).total) per = kMaxPer;
+    return per == 1 ? launch_filter<1>(ev, p, s) : per == 2 ? launch_filter<2>(ev, p, s) : launch_filter<4>(ev, p, s);
 }
 
 }  // extern "C"

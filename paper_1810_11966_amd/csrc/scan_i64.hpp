@@ -13,8 +13,10 @@ namespace {
 // One workgroup of kScanThreads: thread t sums its run of ceil(n / threads)
 // consecutive partials (loads issued kScanUnroll at a time); a wave scan of
 // those sums (shuffles) and one barrier to add the totals of the waves
-// before; then each thread rewrites its run from its prefix, again
-// kScanUnroll loads before their stores.
+// before; then each thread rewrites its run from its prefix, the first
+// kScanUnroll of it from registers (up to 8192 partials are read once: the
+// kernel is a chain of round trips), the rest again kScanUnroll loads before
+// their stores.
 constexpr int kScanThreads = 1024;
 constexpr int kScanWaves = kScanThreads / 64;
 constexpr int kScanUnroll = 8;
@@ -35,8 +37,13 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_i64(int64_t* partials, in
     const int t = (int)threadIdx.x, w = t / 64;
     const int64_t per = (n + kScanThreads - 1) / kScanThreads;
     const int64_t lo = min(n, (int64_t)t * per), hi = min(n, lo + per);
+    int64_t head[kScanUnroll];
+#pragma unroll
+    for (int u = 0; u < kScanUnroll; ++u) head[u] = lo + u < hi ? partials[lo + u] : 0;
     int64_t sum = 0;
-    for (int64_t i0 = lo; i0 < hi; i0 += kScanUnroll) {
+#pragma unroll
+    for (int u = 0; u < kScanUnroll; ++u) sum += head[u];
+    for (int64_t i0 = lo + kScanUnroll; i0 < hi; i0 += kScanUnroll) {
         int64_t v[kScanUnroll];
 #pragma unroll
         for (int u = 0; u < kScanUnroll; ++u) v[u] = i0 + u < hi ? partials[i0 + u] : 0;
@@ -49,7 +56,13 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_i64(int64_t* partials, in
     int64_t before = 0;
     for (int k = 0; k < w; ++k) before += wave_total[k];
     int64_t run = before + incl - sum;  // exclusive prefix of this run
-    for (int64_t i0 = lo; i0 < hi; i0 += kScanUnroll) {
+#pragma unroll
+    for (int u = 0; u < kScanUnroll; ++u)
+        if (lo + u < hi) {
+            partials[lo + u] = run;
+            run += head[u];
+        }
+    for (int64_t i0 = lo + kScanUnroll; i0 < hi; i0 += kScanUnroll) {
         // a batch's loads go out together, before its stores
         int64_t v[kScanUnroll];
 #pragma unroll

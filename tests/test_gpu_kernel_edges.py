@@ -69,3 +69,95 @@ def test_binned_pair_list_limit(gpu, test):  # noqa: F811
         want, accept, _, _ = oracle_result(s, R.OracleConfig(test=test, min_triplets=cap))
         assert np.array_equal(got["counts"], np.minimum(want, cap))
         assert np.array_equal(got["accept"], accept)
+
+
+# ------------------------------------------------------- station filter ---
+
+def filter_parity(torch, label, lens, station, layers=(13, 14, 15), workspace_bytes=None, capacity=None):
+    """The station filter on events of `lens` hits against the oracle, x and
+    y the hits' numbers (so that a wrong hit shows)."""
+    from oracle import reference as R
+    from paper_1810_11966_amd import filter as F
+    off = np.zeros(len(lens) + 1, np.int64)
+    np.cumsum(lens, out=off[1:])
+    station = np.asarray(station, np.uint8)
+    assert off[-1] == len(station)
+    x = np.arange(len(station), dtype=np.float32)
+    y = -x
+    print(f"[filter edges] {label} events={len(lens)} hits={len(station)} workspace={workspace_bytes}", flush=True)
+    cap = int(np.isin(station, layers).sum()) if capacity is None else capacity
+    d = [torch.from_numpy(a).cuda() for a in (off, station, x, y)]
+    ws = None if workspace_bytes is None else torch.empty(workspace_bytes, dtype=torch.uint8, device="cuda")
+    r = F.filter_stations(*d, layers, cap, workspace=ws)
+    torch.cuda.synchronize()
+    lo, fx, fy, status = R.filter_stations(off, station, x, y, layers)
+    assert np.array_equal(r.layer_offsets.cpu().numpy(), np.minimum(lo, cap)), label
+    assert np.array_equal(r.x.cpu().numpy()[:cap], fx[:cap]) and np.array_equal(r.y.cpu().numpy()[:cap], fy[:cap]), label
+    assert int(r.status.cpu()[0]) == status | (4 if lo[-1] > cap else 0), label
+
+
+def scattered(n_hits, n_trigger, rng):
+    """Station numbers of one event: trigger hits of all three layers at
+    random places."""
+    st = rng.integers(0, 13, n_hits)
+    st[rng.permutation(n_hits)[:n_trigger]] = rng.integers(13, 16, n_trigger)
+    return st
+
+
+def together(n_hits, windows, per_window):
+    """per_window trigger hits in each of `windows` runs of 64 hits."""
+    st = np.zeros(n_hits, np.int64)
+    for k in range(windows):
+        at = 64 * k + 3 * (k % 9)
+        st[at:at + per_window] = 13 + np.arange(per_window) % 3
+    return st
+
+
+def filter_workspace(n_events, per):
+    """Workspace bytes of a layout with `per` events per wave (four waves per
+    workgroup): layer counts, totals, record counts, 512 bytes of records per
+    event slot."""
+    a = lambda v: (v + 255) & ~255
+    nb = max(1, -(-n_events // (4 * per)))
+    return a(12 * n_events) + a(8 * (nb + 1)) + a(4 * n_events) + a(nb * 4 * per * 512)
+
+
+@pytest.mark.parametrize("per", (1, 4))
+def test_filter_record_lists(gpu, per):  # noqa: F811
+    """Both kinds of the waves' lists on both sides of their ends, and waves
+    whose events differ in kind, with one event per wave (small batches) and
+    with four (what a workspace of that layout alone gets)."""
+    rng = np.random.default_rng(51)
+    kinds = {
+        "entries": [scattered(3000, n, rng) for n in (127, 128, 129, 0, 300, 512, 513, 1, 128, 128, 128, 128, 128, 128,
+                                                      129, 128)],
+        "windows": [together(9000, w, p) for w, p in ((31, 9), (32, 9), (33, 9), (5, 30), (128, 5), (129, 5), (32, 4),
+                                                      (32, 12), (33, 4), (0, 0), (96, 8), (1, 40))],
+    }
+    kinds["mixed"] = [e for pair in zip(kinds["entries"], kinds["windows"]) for e in pair] + \
+        [scattered(4000, 90, rng) for _ in range(9)] + [together(4000, 4, 25) for _ in range(9)]
+    for name, evs in kinds.items():
+        for order in (0, 1, 5):
+            # 512 events: there a layout of one event per wave needs more
+            # than the layout of four that the smaller workspace has
+            e = ((evs[order:] + evs[:order]) * (512 // len(evs) + 1))[:512]
+            assert filter_workspace(512, 1) > filter_workspace(512, 4)
+            ws = filter_workspace(len(e), per)
+            filter_parity(gpu, f"{name} order {order}", [len(v) for v in e], np.concatenate(e), workspace_bytes=ws)
+    from paper_1810_11966_amd.trig import TrigError
+    with pytest.raises(TrigError):  # less than the smallest layout: refused
+        filter_parity(gpu, "short workspace", [len(v) for v in evs], np.concatenate(evs),
+                      workspace_bytes=filter_workspace(len(evs), 4) - 256)
+
+
+@pytest.mark.parametrize("n_events", (1, 3, 16383, 16384, 32767, 32768))
+def test_filter_event_split(gpu, n_events):  # noqa: F811
+    """Batches on both sides of the sizes where the events per wave change,
+    scattered and grouped, also with an output shorter than the hits."""
+    rng = np.random.default_rng(n_events)
+    lens = rng.integers(0, 40, n_events)
+    st = rng.integers(8, 16, int(lens.sum()))
+    filter_parity(gpu, "split scattered", lens, st)
+    ev = np.repeat(np.arange(n_events), lens)
+    filter_parity(gpu, "split grouped", lens, st[np.lexsort((st, ev))])
+    filter_parity(gpu, "split short output", lens, st, capacity=int(np.isin(st, (13, 14, 15)).sum()) // 2)
