@@ -61,7 +61,7 @@ __device__ __forceinline__ PreBound pre_bound(const Consts& c, const float* __re
                                               const EventRange& ev) {
     if constexpr (std::is_same<T, MsdFitTest>::value) {
         const float M = layer_mag(GlobalHits{x, y}, ev.o1, ev.n1);
-        return {__builtin_fmaxf(c.fit_b0x + c.fit_b1x * M, c.fit_b0y + c.fit_b1y * M), true};
+        return {(c.fit_b0x + c.fit_b1x * M) + (c.fit_b0y + c.fit_b1y * M), true};
     } else if constexpr (std::is_same<T, MsdZTest>::value) {
         // the slope bound of layers 0 and 2 (it holds for any two layers)
         const PairBounds b = MsdZPrune::event_bounds(c, SlopeHits{x, y, z}, ev.o0, ev.n0, ev.o2, ev.n2);
@@ -69,7 +69,7 @@ __device__ __forceinline__ PreBound pre_bound(const Consts& c, const float* __re
     } else if constexpr (std::is_same<T, MsdBasisTest>::value) {
         return {c.pre_msd, true};
     } else {
-        return {c.pre_win, true};
+        return {c.pre_win_sum, true};
     }
 }
 
@@ -573,7 +573,8 @@ Consts make_consts(const trig_params* p, int n_hits) {
     c.zs_a1x = sx.a1;
     c.zs_a0y = sy.a0;
     c.zs_a1y = sy.a1;
-    c.pre_msd = std::max(c.beta_x, c.beta_y);
+    c.pre_msd = c.beta_x + c.beta_y;
+    c.pre_win_sum = p->slope_window[0] + p->slope_window[1];
     c.pre_win = std::max(p->slope_window[0], p->slope_window[1]);
     c.win_x = p->slope_window[0];
     c.win_y = p->slope_window[1];

@@ -41,10 +41,10 @@ struct Consts {
     // |b| <= b0 + b1 M (device evaluation order, M >= |c1| the plane's
     // layer-1 coordinate), per plane
     float fit_a0x, fit_a1x, fit_a0y, fit_a1y, fit_b0x, fit_b1x, fit_b0y, fit_b1y;
-    // Pair prefilter of the batched form: (|u| <= bx and |v| <= by) implies
-    // max(|u|, |v|) <= max(bx, by).  MSD_BASIS: the larger beta; window: the
-    // larger window.
-    float pre_msd, pre_win;
+    // Prefilters: (|u| <= bx and |v| <= by) implies |u| + |v| <= bx + by and
+    // max(|u|, |v|) <= max(bx, by), in binary32 too.  MSD_BASIS: the sum of
+    // the betas; window: the sum of the windows and the larger window.
+    float pre_msd, pre_win_sum, pre_win;
     // TRIG_TEST_SLOPE_WINDOW
     float win_x, win_y;
     // Binned form, MSD_BASIS and window: half-width of the key interval
@@ -175,7 +175,7 @@ __device__ __forceinline__ uint64_t lanes(bool cmp) { return __builtin_amdgcn_ba
 //
 // Rejecting test of the every-triplet loops (wave_count): pre_pair(i, j) and
 // pre_k(k) give one value per plane, and a triplet that passes has
-// |pre_pair + pre_k| <= the loop's bound in both planes, one binary32 sum.
+// |pre_pair + pre_k| <= a bound in each plane, one binary32 sum each.
 //   MSD tests: the partial sum b = f32(p + w) of the basis form, p = f32(
 //     f32(V0 c_i) + f32(V1 c_j)), w = f32(V2 c_k).  Basis form: Q =
 //     f32(f32(a^2) + f32(b^2)) >= f32(b^2), so |b| <= beta.  Fit written out:
@@ -427,7 +427,7 @@ __device__ __forceinline__ uint32_t pair_tiles(const EventRange& ev) {
 }
 
 // Rejecting-test bound of an event (see the test policies): a triplet passes
-// only if both planes' sums are within `bound`; valid = false: no bound holds
+// only if the magnitudes of the two planes' sums add up to at most `bound`; valid = false: no bound holds
 // (per-hit z outside (0, inf) in layers 0 or 2) and every triplet takes the
 // full test.
 struct PreBound {
@@ -441,16 +441,18 @@ struct PreBound {
 // this wave's LDS slice (KCH hits per chunk).  Called by a whole wave with
 // uniform arguments; returns the same count on every lane.
 //
-// Every triplet gets the rejecting test of the policy (two sums, a max and
-// half a min3 on the vector unit: 3.5 instructions against 28 of the written-out
-// fit), folded over four layer-2 hits and the lane's NP pairs before one
-// vote; only a group in which some triplet is within the bound is
-// evaluated in full.  NP pairs per lane share one 16-byte LDS read per plane
+// Every triplet gets the rejecting test of the policy (three sums and half a
+// min3 on the vector unit: 8 SIMD cycles against 60 of the written-out fit),
+// on the sum of the two planes' magnitudes, folded over four layer-2 hits and
+// the lane's NP pairs before one vote; only a group in which some triplet is
+// within the bound is evaluated in full.  (A sum takes 2 SIMD cycles for 64
+// lanes, a max or min 4: the sum of the magnitudes instead of the larger one
+// saves 2 of 10 and lets twice as many of the few close triplets through.)  NP pairs per lane share one 16-byte LDS read per plane
 // and four layer-2 hits: with one pair per lane those reads (all lanes at one
 // address, still 1 KB each on a 128 B/clock LDS) take longer than the sums.
 // Bound by the vector unit.  100,000 events of 30 hits per layer, whole call:
-// 1.337 ms with the full test per triplet, 0.251 ms now (2.7e9 triplets; 0.15 ms
-// at 3.5 instructions each and the measured 63 T lane operations/s).
+// 1.335 ms with the full test per triplet, 0.246 ms now (2.7e9 triplets; 0.14 ms
+// at 8 SIMD cycles per 64 of them and 2.4 GHz).
 template <class T, int KCH>
 __device__ uint32_t wave_count(const float* __restrict__ x, const float* __restrict__ y,
                                const float* __restrict__ z, const EventRange& ev, uint32_t t_begin,
@@ -536,10 +538,10 @@ __device__ uint32_t wave_count(const float* __restrict__ x, const float* __restr
                 float m = nan;  // fmin drops NaN; all NaN stays NaN and fails
 #pragma unroll
                 for (int q = 0; q < NP; ++q) {
-                    const float s0 = __builtin_fmaxf(__builtin_fabsf(p[q].x + vx.x), __builtin_fabsf(p[q].y + vy.x));
-                    const float s1 = __builtin_fmaxf(__builtin_fabsf(p[q].x + vx.y), __builtin_fabsf(p[q].y + vy.y));
-                    const float s2 = __builtin_fmaxf(__builtin_fabsf(p[q].x + vx.z), __builtin_fabsf(p[q].y + vy.z));
-                    const float s3 = __builtin_fmaxf(__builtin_fabsf(p[q].x + vx.w), __builtin_fabsf(p[q].y + vy.w));
+                    const float s0 = __builtin_fabsf(p[q].x + vx.x) + __builtin_fabsf(p[q].y + vy.x);
+                    const float s1 = __builtin_fabsf(p[q].x + vx.y) + __builtin_fabsf(p[q].y + vy.y);
+                    const float s2 = __builtin_fabsf(p[q].x + vx.z) + __builtin_fabsf(p[q].y + vy.z);
+                    const float s3 = __builtin_fabsf(p[q].x + vx.w) + __builtin_fabsf(p[q].y + vy.w);
                     m = __builtin_fminf(__builtin_fminf(m, s0), s1);
                     m = __builtin_fminf(__builtin_fminf(m, s2), s3);
                 }
