@@ -105,10 +105,11 @@ typedef struct {
  *     Q = (r0*r0 + r1*r1) + r2*r2;
  *   TRIG_TEST_SLOPE_WINDOW: s_l = c_l / z_l with each hit's z;
  *   TRIG_TEST_MSD_BASIS: not provided (TRIG_EUNSUPPORTED).
- * With per-hit z the batched, binned and autotuned forms run one wave per
- * event from HBM, pruning pairs on their slopes c / z (a bound that every
- * passing triplet meets, for events whose layer-0 and layer-1 z lie in
- * (0, inf)); the plain and persistent forms test every triplet. */
+ * With per-hit z the batched, binned and autotuned forms prune pairs on their
+ * slopes c / z (a bound that every passing triplet meets, for events whose
+ * layer-0 and layer-1 z lie in (0, inf)), from blocks of events staged in LDS
+ * or, for large events, with one wave per event from HBM; the block_* fields
+ * are not used.  The plain and persistent forms test every triplet. */
 typedef struct {
     int32_t n_hits;
     const float *x;

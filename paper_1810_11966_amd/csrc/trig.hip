@@ -53,6 +53,9 @@ constexpr int kPersistBatch = 4;    // work units taken per atomic
 constexpr int kDefaultTileUnits = 8;  // pair tiles (of 64 pairs) per work unit
 constexpr int kClaimsPerGroup = 8;    // claims per workgroup (pipelined batched form) or per wave (binned)
 constexpr double kRuleFill = 0.85;    // built-in rule: hits per block over the LDS capacity
+constexpr int kZHits = 2048;          // per-hit z: hits and waves of a block,
+constexpr int kZWaves = 4;
+constexpr int kMinZEvents = 8;        // and the events it has to hold to be used
 
 // Bound of the rejecting test of wave_count over one event (whole wave).
 template <class T>
@@ -100,7 +103,8 @@ __global__ __launch_bounds__(WPB * kWave) void k_plain(const int32_t* __restrict
     if (cnt == 0) {
         const uint32_t tiles = pair_tiles(ev);
         if (tiles)
-            cnt = (int32_t)wave_count<T, kChunk>(x, y, z, ev, 0, tiles, c, pre_bound<T>(c, x, y, z, ev), lds_all[w]);
+            cnt = (int32_t)wave_count<T, kChunk>(x, y, z, ev, 0, tiles, c, pre_bound<T>(c, x, y, z, ev), lds_all[w],
+                                              lds_all[w] + kChunk);
     }
     if (lane_id() == 0) write_result(e, cnt, c, counts, accept, status);
 }
@@ -329,7 +333,8 @@ __global__ __launch_bounds__(WPB * kWave) void k_persistent(
                 const uint32_t tiles = pair_tiles(ev);
                 const uint32_t tb = (uint32_t)((u - ustart[e]) * tile_units);
                 const uint32_t te = min(tiles, tb + (uint32_t)tile_units);
-                const uint32_t cnt = wave_count<T, kChunk>(x, y, z, ev, tb, te, c, pre_bound<T>(c, x, y, z, ev), lds);
+                const uint32_t cnt =
+                    wave_count<T, kChunk>(x, y, z, ev, tb, te, c, pre_bound<T>(c, x, y, z, ev), lds, lds + kChunk);
                 if (lane_id() == 0 && cnt) atomicAdd(&counts[e], (int32_t)cnt);
             }
         }
@@ -444,9 +449,7 @@ __global__ __launch_bounds__(kTwoWaves * kWave) void k_two_particles(const int32
 // ------------------------------------------------------------ per-hit z ---
 
 // Per-hit z (trig_hits.z), batched, binned and autotuned forms: one wave per
-// event from HBM, pairs pruned on their slopes with the event's bound
-// (wave_event_pruned over SlopeHits), or every triplet (wave_count) when the
-// event has no valid bound.
+// event from HBM.
 template <class P, class T>
 __global__ __launch_bounds__(kBinWaves * kWave) void k_event_z(const int32_t* __restrict__ off, int n_events,
                                                                const float* __restrict__ x,
@@ -454,35 +457,15 @@ __global__ __launch_bounds__(kBinWaves * kWave) void k_event_z(const int32_t* __
                                                                const float* __restrict__ z, Consts c,
                                                                int32_t* __restrict__ counts,
                                                                uint8_t* __restrict__ accept, uint32_t* status) {
-    static_assert(kChunk >= kPBuf, "the pruned path's buffers fit in the staging slice");
-    __shared__ __align__(16) float lds_all[kBinWaves][2 * kChunk];
+    __shared__ __align__(16) float lds_all[kBinWaves][2 * kPBuf];
     const int w = uniform_i((int)(threadIdx.x / kWave));
     const int64_t e64 = (int64_t)blockIdx.x * kBinWaves + w;
     if (e64 >= n_events) return;
     const int e = (int)e64;
-    float* lds = lds_all[w];
     EventRange ev;
     int32_t cnt = load_event(off, e, c.n_hits, ev);
-    if (cnt == 0 && ev.n0 > 0 && ev.n1 > 0 && ev.n2 > 0) {
-        const SlopeHits sh{x, y, z};
-        const PairBounds pb = event_bounds<P>(c, sh, ev.o0, ev.n0, ev.o1, ev.n1);
-        if (pb.prune) {
-            // An event that fits one lane pass and one buffer fill takes the
-            // fast path (the prefilter folded over all pairs, one vote); the
-            // slope tests are symmetric in the two layers, as the batched
-            // form's are.
-            int R, TB, S;
-            event_layout(ev.n0, ev.n1, R, TB, S);
-            if (TB > 0)
-                cnt = (int32_t)wave_event_fast<P>(c, pb, sh, ev.o0, ev.n0, ev.o1, ev.n1, ev.o2, ev.n2, R, TB, S,
-                                                  recip16(S ? ev.n0 : ev.n1), lds, lds + kPBuf);
-            else
-                cnt = (int32_t)wave_event_pruned<P>(c, pb, sh, ev.o0, ev.n0, ev.o1, ev.n1, ev.o2, ev.n2, lds,
-                                                    lds + kPBuf);
-        } else {
-            cnt = (int32_t)wave_count<T, kChunk>(x, y, z, ev, 0, pair_tiles(ev), c, pre_bound<T>(c, x, y, z, ev), lds);
-        }
-    }
+    if (cnt == 0 && ev.n0 > 0 && ev.n1 > 0 && ev.n2 > 0)
+        cnt = (int32_t)wave_event_z<P, T>(c, x, y, z, ev, lds_all[w], lds_all[w] + kPBuf);
     if (lane_id() == 0) write_result(e, cnt, c, counts, accept, status);
 }
 
@@ -859,16 +842,30 @@ int launch_two_particles(const trig_events_csr* ev, const trig_hits* h, const Co
     return check_launch("k_two_particles");
 }
 
-// Per-hit z: brute force as asked, every other form one wave per event with
-// slope pruning (k_event_z).
+// Per-hit z: brute force as asked, every other form with slope pruning, from
+// blocks of events in LDS (k_block_z) or, where a block would hold fewer than
+// kMinZEvents events (two per wave) of the batch's mean size, one wave per
+// event from HBM (k_event_z).
 template <class T, class P>
 int run_form_z(const trig_events_csr* ev, const trig_hits* h, const trig_params* p, const Consts& c,
                const Layout& L, char* ws, int32_t* counts, uint8_t* accept, hipStream_t s) {
     int r = TRIG_OK;
     if (p->flags & (TRIG_EXEC_PRUNED | TRIG_EXEC_BINNED)) {
         if (mark_start(s)) return fail(TRIG_EHIP, "hipEventRecord(start)");
-        hipLaunchKernelGGL((k_event_z<P, T>), dim3((unsigned)cdiv(ev->n_events, kBinWaves)), dim3(kBinWaves * kWave),
-                           0, s, ev->layer_offsets, ev->n_events, h->x, h->y, h->z, c, counts, accept, p->out_status);
+        const int n = ev->n_events;
+        const double mean = std::max((double)h->n_hits / n, 1.0);
+        if (mean * kMinZEvents <= kRuleFill * kZHits) {
+            const int eb = events_for_fill(kRuleFill, kZHits, kZWaves, n, h->n_hits);
+            const int vec = ((reinterpret_cast<uintptr_t>(h->x) | reinterpret_cast<uintptr_t>(h->y) |
+                              reinterpret_cast<uintptr_t>(h->z)) & 15) == 0;
+            const auto kern = eb <= kSmallEB ? k_block_z<P, T, kZHits, kZWaves, kSmallEB>
+                                             : k_block_z<P, T, kZHits, kZWaves, kMaxEB>;
+            hipLaunchKernelGGL(kern, dim3((unsigned)cdiv(n, eb)), dim3(kZWaves * kWave), 0, s, ev->layer_offsets, n,
+                               h->x, h->y, h->z, c, eb, vec, counts, accept, p->out_status);
+        } else {
+            hipLaunchKernelGGL((k_event_z<P, T>), dim3((unsigned)cdiv(n, kBinWaves)), dim3(kBinWaves * kWave), 0, s,
+                               ev->layer_offsets, n, h->x, h->y, h->z, c, counts, accept, p->out_status);
+        }
         if ((r = check_launch("k_event_z"))) return r;
         if (mark_stop(s)) return fail(TRIG_EHIP, "hipEventRecord(stop)");
     } else if (p->flags & TRIG_EXEC_PERSISTENT) {

@@ -319,9 +319,9 @@ struct MsdZPrune {
     __device__ static __forceinline__ float2 layer0(const Consts&, float2 s) { return s; }
     __device__ static __forceinline__ float2 layer1(const Consts&, float2 s) { return s; }
     __device__ static __forceinline__ float2 layer(const Consts&, float2 s, int) { return s; }
-    // M, zmin and zmax over layers 0 and 1 (raw coordinates), by the wave.
+    // M and zmin over layers 0 and 1 (raw coordinates), by the wave.
     __device__ static PairBounds event_bounds(const Consts& c, const SlopeHits& h, int o0, int n0, int o1, int n1) {
-        float m = 0.0f, zlo = __builtin_inff(), zhi = 0.0f;
+        float m = 0.0f, zlo = __builtin_inff();
         bool bad = false;
         for (int t = (int)lane_id(); t < n0 + n1; t += kWave) {
             const int q = t < n0 ? o0 + t : o1 + (t - n0);
@@ -329,18 +329,21 @@ struct MsdZPrune {
             m = __builtin_fmaxf(m, __builtin_fmaxf(__builtin_fabsf(h.x[q]), __builtin_fabsf(h.y[q])));
             bad |= !(z > 0.0f && z < __builtin_inff());
             zlo = __builtin_fminf(zlo, z);
-            zhi = __builtin_fmaxf(zhi, z);
         }
-        PairBounds b;
         const float M = wave_max_f(m), zmin = wave_min_f(zlo);
         const float inv = 1.0f / zmin;
+        PairBounds b = slope_bounds(c, M, inv);
         // every z of layers 0 and 1 in (0, inf), and no slope that can
         // overflow (|c| / z <= M / zmin < 2^126): otherwise no pruning
         b.prune = !wave_any(bad) && M * inv < 0x1p126f;
+        return b;
+    }
+    // The bounds from M >= |x|, |y| and inv = 1 / zmin.
+    __device__ static __forceinline__ PairBounds slope_bounds(const Consts& c, float M, float inv) {
+        PairBounds b;
         b.bx = (c.zs_a0x + c.zs_a1x * M) * inv + 0x1p-126f;
         b.by = (c.zs_a0y + c.zs_a1y * M) * inv + 0x1p-126f;
         b.pre = b.bx + b.by;
-        (void)zhi;
         return b;
     }
     __device__ static __forceinline__ uint64_t pair_mask(const PairBounds& b, float2 p, float2 q) {
@@ -386,6 +389,7 @@ struct WindowZPrune {
     __device__ static __forceinline__ PairBounds bounds(const Consts& c, float) {
         return PairBounds{c.win_x, c.win_y, c.pre_win};
     }
+    __device__ static __forceinline__ PairBounds slope_bounds(const Consts& c, float, float) { return bounds(c, 0.0f); }
     __device__ static __forceinline__ float2 layer0(const Consts&, float2 s) { return s; }
     __device__ static __forceinline__ float2 layer1(const Consts&, float2 s) { return s; }
     __device__ static __forceinline__ float2 layer(const Consts&, float2 s, int) { return s; }
@@ -684,8 +688,18 @@ __device__ uint32_t fast_exact(const Consts& c, const PairBounds& pb, const H& h
 // Passing triplets of an event that fits one lane pass and one buffer fill
 // in the orientation S (S = 0: layer 1 in the lanes, as wave_event_pruned;
 // S = 1: layer 0): the computation of wave_event_pruned with its loops taken
-// once, and the prefilter minimum taken over the whole event before one
-// vote.  R, T and S come from the per-event descriptor (event_layout).
+// once, and the prefilter minimum (fast_score, per lane) taken over the whole
+// event before one vote.  R, T and S come from the per-event descriptor (event_layout).
+template <class P>
+__device__ __forceinline__ float fast_score(const float* px, const float* py, int T, int g, float2 q) {
+    const float4* ppx = reinterpret_cast<const float4*>(px + g * T);
+    const float4* ppy = reinterpret_cast<const float4*>(py + g * T);
+    float m = __builtin_nanf("");
+    int t = 0;
+    for (; t + 8 <= T; t += 8) m = fast_fold<P>(ppx, ppy, t + 4, q, fast_fold<P>(ppx, ppy, t, q, m));
+    if (t < T) m = fast_fold<P>(ppx, ppy, t, q, m);
+    return m;
+}
 template <class P, class H>
 __device__ uint32_t wave_event_fast(const Consts& c, const PairBounds& pb, const H& hits, int o0, int n0, int o1,
                                     int n1, int o2, int n2, int R, int T, int S, uint32_t r,
@@ -696,14 +710,8 @@ __device__ uint32_t wave_event_fast(const Consts& c, const PairBounds& pb, const
     float2 q;
     fast_setup<P>(c, hits, oB, nB, oL, nL, S, R, T, r, px, py, g, j, q);
     wave_lds_sync();
-    const float4* ppx = reinterpret_cast<const float4*>(px + g * T);
-    const float4* ppy = reinterpret_cast<const float4*>(py + g * T);
-    float m = __builtin_nanf("");
-    int t = 0;
-    for (; t + 8 <= T; t += 8) m = fast_fold<P>(ppx, ppy, t + 4, q, fast_fold<P>(ppx, ppy, t, q, m));
-    if (t < T) m = fast_fold<P>(ppx, ppy, t, q, m);
     uint32_t cnt = 0;
-    if (wave_any(m <= pb.pre)) cnt = fast_exact<P>(c, pb, hits, oB, oL, S, o2, n2, T, g, j, q, px, py);
+    if (wave_any(fast_score<P>(px, py, T, g, q) <= pb.pre)) cnt = fast_exact<P>(c, pb, hits, oB, oL, S, o2, n2, T, g, j, q, px, py);
     wave_lds_sync();
     return cnt;
 }
@@ -1218,6 +1226,201 @@ void k_block(const int32_t* __restrict__ off, int n_events,
         block_check_describe(L, c, e0, ne, base & ~3, counts, accept, status);
         __syncthreads();
         block_general<P>(L, c, x, y, e0, ne, uniform_i(L.s_bad) != 0, vec != 0, counts, accept, status);
+    }
+}
+
+// ---------------------------------------------------------- per-hit z ---
+
+// Passing triplets of one event with per-hit z (all layers non-empty), from
+// HBM: pairs pruned on their slopes with the event's bound (SlopeHits), or
+// every triplet (wave_count) when the event has no valid bound.  px, py: the
+// wave's kPBuf-entry LDS buffers.
+template <class P, class T>
+__device__ uint32_t wave_event_z(const Consts& c, const float* __restrict__ x, const float* __restrict__ y,
+                                 const float* __restrict__ z, const EventRange& ev, float* __restrict__ px,
+                                 float* __restrict__ py) {
+    const SlopeHits sh{x, y, z};
+    const PairBounds pb = event_bounds<P>(c, sh, ev.o0, ev.n0, ev.o1, ev.n1);
+    if (!pb.prune) {
+        // the slope bound of layers 0 and 2 (it holds for any two layers)
+        const PairBounds b = event_bounds<P>(c, sh, ev.o0, ev.n0, ev.o2, ev.n2);
+        return wave_count<T, kPBuf>(x, y, z, ev, 0, pair_tiles(ev), c, PreBound{b.pre, b.prune}, px, py);
+    }
+    // An event that fits one lane pass and one buffer fill takes the fast path
+    // (the prefilter folded over all pairs, one vote); the slope tests are
+    // symmetric in the two layers, as the batched form's are.
+    int R, TB, S;
+    event_layout(ev.n0, ev.n1, R, TB, S);
+    if (TB > 0)
+        return wave_event_fast<P>(c, pb, sh, ev.o0, ev.n0, ev.o1, ev.n1, ev.o2, ev.n2, R, TB, S,
+                                  recip16(S ? ev.n0 : ev.n1), px, py);
+    return wave_event_pruned<P>(c, pb, sh, ev.o0, ev.n0, ev.o1, ev.n1, ev.o2, ev.n2, px, py);
+}
+
+// Block kernel with per-hit z: blocks of events staged in LDS as k_block does
+// it, but as approximate slopes s' = c rcp(z) (one hardware reciprocal per hit,
+// where the pair test's binary32 divisions take some 40 vector cycles per
+// coordinate).  An event none of whose pairs is close in s' has no passing
+// triplet; the others (a few in a hundred) are counted by wave_event_z from
+// HBM.  With M the block's largest |x|, |y| and zmin its smallest z, s' is
+// within 2^-21 M / zmin of the slope c / z rounded to binary32 (reciprocal
+// within one step, one product), so |s'_j - s'_i| exceeds |f32(s_j - s_i)| by
+// less than 2^-19 M / zmin, which `pre` adds per plane.  Blocks whose z do not all
+// lie in [2^-100, 2^100], whose slopes could leave binary32's normal range,
+// that are malformed or do not fit in LDS go event by event to wave_event_z.
+// Bound by HBM latency and the pair scan together, as k_block.  1M staggered
+// events of 30 hits per layer, whole call: 0.511 ms with a wave per event from
+// HBM (nine loads of 4 bytes per lane and four divisions for each), 0.299 ms
+// now (3.7 TB/s of 17 bytes per event and 12 per hit).
+template <class P, class T, int HB, int NW, int EB>
+__global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(block_waves_per_simd<HB, NW, EB>())))
+void k_block_z(const int32_t* __restrict__ off, int n_events, const float* __restrict__ x,
+               const float* __restrict__ y, const float* __restrict__ z, Consts c, int eb, int vec,
+               int32_t* __restrict__ counts, uint8_t* __restrict__ accept, uint32_t* status) {
+    __shared__ __align__(16) BlockLds<HB, NW, EB> L;
+    __shared__ uint32_t wzlo[NW], wzhi[NW];  // per wave: ~(smallest z's bits), largest z's bits
+    constexpr int NT = NW * kWave;
+    const int t = (int)threadIdx.x;
+    const int w = uniform_i(t / kWave);
+    const int e0 = (int)blockIdx.x * eb;
+    const int ne = min(eb, n_events - e0);
+    float* px = L.pbuf_x[w];
+    float* py = L.pbuf_y[w];
+    constexpr int OQ = (3 * EB + 1 + NT - 1) / NT;
+    int ov[OQ];
+#pragma unroll
+    for (int k = 0; k < OQ; ++k) {
+        const int q = t + k * NT;
+        ov[k] = off[3 * (int64_t)e0 + min(q, 3 * ne)];  // clamped: every load in range, no branch
+    }
+    const int base = uniform_i(off[3 * (int64_t)e0]), end = uniform_i(off[3 * (int64_t)(e0 + ne)]);
+    constexpr int kCap = HB - 4;                   // (HitPrefetch's bounds)
+    constexpr int Q = (HB / 4 + NT - 1) / NT;      // float4 groups per thread
+    const int a0 = base & ~3;
+    const bool fits = vec && 0 <= base && base <= end && end <= c.n_hits && end - base <= kCap;
+    const int nq = fits ? min((end - a0 + 3) >> 2, (c.n_hits - a0) >> 2) : 0;  // groups entirely below n_hits
+    const bool whole = nq > 0;
+    bool good = false;  // staged, and the block's bounds hold
+    PairBounds pb{0.0f, 0.0f, 0.0f};
+    auto stage_offsets = [&] {
+#pragma unroll
+        for (int k = 0; k < OQ; ++k) {
+            const int q = t + k * NT;
+            if (q <= 3 * ne) L.soff[q] = ov[k];
+        }
+        if (t == 0) L.s_bad = 0;
+        __syncthreads();
+    };
+    if (whole) {
+        f32x4 vx[Q], vy[Q], vz[Q];
+#pragma unroll
+        for (int k = 0; k < Q; ++k) {
+            const int q = min(t + k * NT, nq - 1);
+            vx[k] = *reinterpret_cast<const f32x4*>(x + a0 + 4 * q);
+            vy[k] = *reinterpret_cast<const f32x4*>(y + a0 + 4 * q);
+            vz[k] = *reinterpret_cast<const f32x4*>(z + a0 + 4 * q);
+        }
+        stage_offsets();
+        block_check_describe(L, c, e0, ne, a0, counts, accept, status);
+        uint32_t mag = 0u, zlo = 0u, zhi = 0u;
+        auto hit = [&](float hx, float hy, float hz, float& sx, float& sy) {
+            const float r = __builtin_amdgcn_rcpf(hz);
+            sx = hx * r;
+            sy = hy * r;
+            const uint32_t zb = __builtin_bit_cast(uint32_t, hz);  // (0, inf): ordered as z; others above
+            mag = max(mag, max(abs_bits(hx), abs_bits(hy)));
+            zlo = max(zlo, ~zb);
+            zhi = max(zhi, zb);
+        };
+#pragma unroll
+        for (int k = 0; k < Q; ++k) {
+            const int q = t + k * NT;
+            f32x4 sx, sy;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                float ax, ay;
+                hit(vx[k][u], vy[k][u], vz[k][u], ax, ay);
+                sx[u] = ax;
+                sy[u] = ay;
+            }
+            if (q < nq) {
+                reinterpret_cast<f32x4*>(L.stage_x)[q] = sx;
+                reinterpret_cast<f32x4*>(L.stage_y)[q] = sy;
+            }
+        }
+        if (t == 0)
+            for (int h = a0 + 4 * nq; h < end; ++h) hit(x[h], y[h], z[h], L.stage_x[h - a0], L.stage_y[h - a0]);
+        publish_mag(L, mag);
+        zlo = wave_max_u(zlo);
+        zhi = wave_max_u(zhi);
+        if (lane_id() == 0) {
+            wzlo[w] = zlo;
+            wzhi[w] = zhi;
+        }
+        __syncthreads();
+        const float M = block_mag(L);
+        uint32_t lo = 0u, hi = 0u;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            lo = max(lo, wzlo[k]);
+            hi = max(hi, wzhi[k]);
+        }
+        const float inv = 1.0f / __builtin_bit_cast(float, ~lo);
+        good = uniform_i(L.s_bad) == 0 && ~lo >= __builtin_bit_cast(uint32_t, 0x1p-100f) &&
+               hi <= __builtin_bit_cast(uint32_t, 0x1p100f) && M * inv < 0x1p100f;
+        const float slack = M * inv * 0x1p-19f + 0x1p-100f;
+        pb = P::slope_bounds(c, M, inv);
+        pb.pre += 2.0f * slack;  // one per plane
+    } else {
+        stage_offsets();
+        block_check_describe(L, c, e0, ne, a0, counts, accept, status);
+        __syncthreads();
+    }
+    // Events round-robin over the waves; wave-uniform control flow.
+    const LdsHits lh{L.stage_x, L.stage_y};
+    for (int te = w; te < ne; te += NW) {
+        const int b0 = uniform_i(L.soff[3 * te]), b1 = uniform_i(L.soff[3 * te + 1]);
+        const int b2 = uniform_i(L.soff[3 * te + 2]), b3 = uniform_i(L.soff[3 * te + 3]);
+        if (!(0 <= b0 && b0 <= b1 && b1 <= b2 && b2 <= b3 && b3 <= c.n_hits)) {
+            L.sres[te] = -1;  // (already written and reported)
+            continue;
+        }
+        const EventRange ev{b0, b1, b2, b1 - b0, b2 - b1, b3 - b2};
+        const int64_t n01 = (int64_t)ev.n0 * ev.n1;
+        uint32_t cnt = 0;
+        if (ev.n2 > 0 && (n01 > (int64_t)INT32_MAX || n01 * ev.n2 > (int64_t)INT32_MAX)) {
+            L.sres[te] = -2;
+            continue;
+        }
+        if (ev.n0 > 0 && ev.n1 > 0 && ev.n2 > 0) {
+            bool close = true;
+            if (good) {
+                const uint32_t da = (uint32_t)uniform_i((int)L.da[te]), db = (uint32_t)uniform_i((int)L.db[te]);
+                const int R = (int)((da >> 26) & 31u), S = (int)(da >> 31), TB = (int)(db >> 26) * 4;
+                if (TB > 0) {
+                    int g, j;
+                    float2 q;
+                    fast_setup<P>(c, lh, (S ? b1 : b0) - a0, S ? ev.n1 : ev.n0, (S ? b0 : b1) - a0, S ? ev.n0 : ev.n1,
+                                  S, R, TB, (uint32_t)uniform_i((int)L.dr[te]), px, py, g, j, q);
+                    wave_lds_sync();
+                    close = wave_any(fast_score<P>(px, py, TB, g, q) <= pb.pre);
+                    wave_lds_sync();
+                }
+            }
+            if (close) {
+                cnt = wave_event_z<P, T>(c, x, y, z, ev, px, py);
+                wave_lds_sync();
+            }
+        }
+        L.sres[te] = (int32_t)cnt;  // uniform: every lane stores the same value
+    }
+    __syncthreads();
+    for (int te = t; te < ne; te += NT) {
+        const int32_t r = L.sres[te];
+        if (r == -1) continue;
+        counts[e0 + te] = capped(r, c);
+        accept[e0 + te] = (uint8_t)(r >= 0 && r >= c.min_triplets);
+        if (r < 0 && status) atomicOr(status, TRIG_STATUS_OVERFLOW);
     }
 }
 

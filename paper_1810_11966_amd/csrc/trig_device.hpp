@@ -140,6 +140,15 @@ __device__ __forceinline__ float wave_max_f(float v) {
     v = __builtin_fmaxf(v, dpp_f<kDppBcast31, 0xC>(v, v));
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
+__device__ __forceinline__ uint32_t wave_max_u(uint32_t v) {
+    v = max(v, (uint32_t)dpp_i<kDppQuadXor1>(0, (int)v));
+    v = max(v, (uint32_t)dpp_i<kDppQuadXor2>(0, (int)v));
+    v = max(v, (uint32_t)dpp_i<kDppHalfMirror>(0, (int)v));
+    v = max(v, (uint32_t)dpp_i<kDppRowMirror>(0, (int)v));
+    v = max(v, (uint32_t)dpp_i<kDppBcast15, 0xA>(0, (int)v));
+    v = max(v, (uint32_t)dpp_i<kDppBcast31, 0xC>(0, (int)v));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
 __device__ __forceinline__ uint32_t wave_sum_u(uint32_t v) {
     int x = (int)v;
     x += dpp_i<kDppQuadXor1>(0, x);
@@ -438,7 +447,7 @@ struct PreBound {
 // Passing triplets of one event over pair tiles [t_begin, t_end); each tile
 // is 64 consecutive (i, j) pairs in row-major order (pair p -> i = p / n1,
 // j = p % n1), one pair per lane, looping over every layer-2 hit staged in
-// this wave's LDS slice (KCH hits per chunk).  Called by a whole wave with
+// this wave's LDS slices wx and wy (KCH hits per chunk, 16-byte aligned).  Called by a whole wave with
 // uniform arguments; returns the same count on every lane.
 //
 // Every triplet gets the rejecting test of the policy (three sums and half a
@@ -456,15 +465,14 @@ struct PreBound {
 template <class T, int KCH>
 __device__ uint32_t wave_count(const float* __restrict__ x, const float* __restrict__ y,
                                const float* __restrict__ z, const EventRange& ev, uint32_t t_begin,
-                               uint32_t t_end, const Consts& c, const PreBound& pb, float* __restrict__ lds) {
+                               uint32_t t_end, const Consts& c, const PreBound& pb, float* __restrict__ wx,
+                               float* __restrict__ wy) {
     const uint32_t stop = (uint32_t)c.count_cap;  // enough: the result is capped there
     static_assert(KCH % 4 == 0, "chunk must hold whole float4 groups");
     const unsigned lane = lane_id();
     const uint32_t n0 = (uint32_t)ev.n0, n1 = (uint32_t)ev.n1;
     const uint32_t dq = kWave / n1, dr = kWave % n1;
     const float nan = __builtin_nanf("");
-    float* wx = lds;
-    float* wy = lds + KCH;
     uint32_t cnt = 0;
     for (int k0 = 0; k0 < ev.n2; k0 += KCH) {
         const int nk = min(KCH, ev.n2 - k0);

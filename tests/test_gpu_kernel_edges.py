@@ -161,3 +161,67 @@ def test_filter_event_split(gpu, n_events):  # noqa: F811
     ev = np.repeat(np.arange(n_events), lens)
     filter_parity(gpu, "split grouped", lens, st[np.lexsort((st, ev))])
     filter_parity(gpu, "split short output", lens, st, capacity=int(np.isin(st, (13, 14, 15)).sum()) // 2)
+
+
+# ------------------------------------------------------------ per-hit z ---
+
+@pytest.mark.parametrize("test", ("msd", "window"))
+def test_per_hit_z_blocks(gpu, test):  # noqa: F811
+    """Per-hit z from blocks of events in LDS: both event tables (blocks of up
+    to 52 and up to 128 events), hit counts that end inside a 16-byte group,
+    events of the general path (over 64 hits in both layers), blocks over the
+    hit capacity, blocks with one malformed event or one hit whose z no bound
+    covers, z scales at and past the range of the approximate slopes, and
+    batches on both sides of the size where a wave takes an event alone."""
+    rng = np.random.default_rng(61)
+    base = {
+        "small events": helpers.ragged_sizes_set([tuple(rng.integers(0, 9, 3)) for _ in range(700)], seed=62),
+        "medium events": helpers.ragged_sizes_set([tuple(rng.integers(20, 45, 3)) for _ in range(300)], seed=63),
+        "general path": helpers.ragged_sizes_set([(70, 66, 5), (3, 80, 4), (65, 65, 65)] * 8 + [(9, 9, 9)] * 60, seed=64),
+        "over capacity": helpers.ragged_sizes_set([(5, 5, 5)] * 90 + [(800, 9, 1300), (10, 900, 1200)] + [(6, 5, 4)] * 90,
+                                                  seed=65),
+        "wave per event": helpers.ragged_sizes_set([tuple(rng.integers(60, 90, 3)) for _ in range(40)], seed=66),
+    }
+    for tail in (1, 2, 3):
+        base[f"tail {tail}"] = helpers.ragged_sizes_set([(9, 8, 7)] * 40 + [(4, 4, 4 + (tail - 40 * 24 - 12) % 4)], seed=67)
+        assert base[f"tail {tail}"].n_hits % 4 == tail
+    for name, s0 in base.items():
+        s = synth.staggered(s0)
+        c = assert_parity(gpu, s, test, "pruned", f"z {name}")
+        assert c.sum() > 0, name
+        for k, bad_z in enumerate((0.0, -400.0, np.nan, np.inf)):
+            z = s.z.copy()
+            z[rng.integers(0, s.n_hits)] = bad_z
+            bad = synth.EventSet(s.offsets, s.x, s.y, s.n_tracks, z=z)
+            assert_parity(gpu, bad, test, "pruned", f"z {name} with a z of {bad_z}")
+        off = s.offsets.copy()
+        off[3 * (s.n_events // 2) + 1] = off[3 * (s.n_events // 2) + 2] + 1
+        assert_parity(gpu, synth.EventSet(off, s.x, s.y, s.n_tracks, z=s.z), test, "pruned", f"z {name} malformed")
+    s = synth.staggered(base["medium events"])
+    for e in (-101, -92, -60, 40, 91, 93):  # z times 2^e: at 2^+-92 around the range's ends
+        f = np.float32(2.0) ** np.float32(e)
+        scaled = synth.EventSet(s.offsets, s.x, s.y, s.n_tracks, z=s.z * f)
+        for w in (np.float32(0.005) / f, np.float32(1e30)):
+            assert_parity(gpu, scaled, test, "pruned", f"z scale 2^{e}", slope_window=(float(w), float(w)))
+        with np.errstate(over="ignore"):
+            both = synth.EventSet(s.offsets, s.x * f, s.y * f, s.n_tracks, z=s.z * f)
+        assert_parity(gpu, both, test, "pruned", f"all scales 2^{e}")
+
+
+def test_per_hit_z_misaligned(gpu):  # noqa: F811
+    """z (or x and y) starting 4 bytes past a 16-byte boundary."""
+    from paper_1810_11966_amd import trig
+    from tests.test_gpu_parity import oracle_result
+    from oracle import reference as R
+    s = synth.staggered(synth.make_event_set(synth.SMALL_10K, n_events=900))
+    want = oracle_result(s, R.OracleConfig())[0]
+    off = gpu.from_numpy(s.offsets).cuda()
+    for shift in ((1, 0, 0), (0, 1, 0), (0, 0, 1), (2, 2, 2)):
+        a = []
+        for v, k in zip((s.x, s.y, s.z), shift):
+            t = gpu.zeros(s.n_hits + 4, dtype=gpu.float32, device="cuda")
+            t[k:k + s.n_hits] = gpu.from_numpy(v).cuda()
+            a.append(t[k:k + s.n_hits])
+        print(f"[per-hit z misaligned] {shift}", flush=True)
+        r = trig.select(off, a[0], a[1], hit_z=a[2], form="pruned")
+        assert np.array_equal(r.counts.cpu().numpy(), want)
