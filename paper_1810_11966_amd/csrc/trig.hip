@@ -47,7 +47,6 @@ namespace {
 constexpr int kPlainWaves = 4;      // waves (events) per workgroup, plain form
 constexpr int kChunk = 512;         // layer-2 hits per LDS chunk of a wave (2 floats each)
 constexpr int kScanBlock = 256;     // threads of the scan/compaction kernels
-constexpr int kCompactItems = 4;    // events per thread in compaction
 constexpr int kPersistWaves = 4;    // waves per workgroup, persistent form
 constexpr int kPersistBatch = 4;    // work units taken per atomic
 constexpr int kDefaultTileUnits = 8;  // pair tiles (of 64 pairs) per work unit
@@ -156,72 +155,87 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_partials(V* partials, int n
 
 // ------------------------------------------------------------ compaction ---
 
-__global__ __launch_bounds__(kScanBlock) void k_compact_count(const uint8_t* __restrict__ accept,
-                                                              int n_events,
-                                                              int32_t* __restrict__ partials) {
-    const int64_t base = (int64_t)blockIdx.x * kScanBlock * kCompactItems +
-                         (int64_t)threadIdx.x * kCompactItems;
-    int32_t c = 0;
+// The flags of kCompactItems consecutive events, 0 past the last one (every
+// form writes exactly 0 or 1, so a word's set bits are its accepted events).
+// VEC: accept is 16-byte aligned.
+constexpr int kCompactItems = 16;  // events per thread: one 16-byte load
+constexpr int kCompactEvents = kScanBlock * kCompactItems;
+union Flags {
+    uint4 v;
+    uint32_t w[4];
+    __device__ __forceinline__ int count() const {
+        return (int)(__builtin_popcount(v.x) + __builtin_popcount(v.y) + __builtin_popcount(v.z) +
+                     __builtin_popcount(v.w));
+    }
+};
+template <bool VEC>
+__device__ __forceinline__ Flags load_flags(const uint8_t* __restrict__ accept, int64_t base, int64_t n) {
+    Flags f;
+    if (VEC && base + kCompactItems <= n) {
+        f.v = *reinterpret_cast<const uint4*>(accept + base);
+        return f;
+    }
 #pragma unroll
-    for (int k = 0; k < kCompactItems; ++k)
-        if (base + k < n_events) c += accept[base + k] != 0;
+    for (int q = 0; q < 4; ++q) {
+        f.w[q] = 0u;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (base + 4 * q + k < n) f.w[q] |= (uint32_t)(accept[base + 4 * q + k] != 0) << (8 * k);
+    }
+    return f;
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(kScanBlock) void k_compact_count(const uint8_t* __restrict__ accept, int n_events,
+                                                              int32_t* __restrict__ partials) {
+    const int64_t base = (int64_t)blockIdx.x * kCompactEvents + (int64_t)threadIdx.x * kCompactItems;
     int32_t total;
-    block_exclusive_scan<int32_t>(c, total);
+    block_exclusive_scan<int32_t>(load_flags<VEC>(accept, base, n_events).count(), total);
     if (threadIdx.x == 0) partials[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(kScanBlock) void k_compact_write(const uint8_t* __restrict__ accept,
-                                                              int n_events,
-                                                              const int32_t* __restrict__ partials,
-                                                              int n_blocks,
-                                                              int32_t* __restrict__ ids,
-                                                              int32_t* __restrict__ n_out) {
-    const int64_t base = (int64_t)blockIdx.x * kScanBlock * kCompactItems +
-                         (int64_t)threadIdx.x * kCompactItems;
-    uint8_t f[kCompactItems];
-    int32_t c = 0;
-#pragma unroll
-    for (int k = 0; k < kCompactItems; ++k) {
-        f[k] = (base + k < n_events) ? (accept[base + k] != 0) : 0;
-        c += f[k];
+// Where a write kernel's block takes the number of accepted events before it
+// from.
+enum CompactPrefix {
+    kPrefixScanned,  // partials, scanned
+    kPrefixSummed,   // it sums the counts of the blocks before it (from L2)
+    kPrefixFlags     // it counts the flags before it itself: no other kernel
+};
+// Up to this many blocks (4,194,304 events) a block sums the counts before it;
+// up to kFlagBlocks (65,536 events) it counts the flags, at most 60 KB of them,
+// 4 KB per step and eight steps in flight: one launch instead of two (1.8 +
+// 2.0 us and a gap at 1,000 events).
+constexpr int kPrefixBlocks = 1024;
+constexpr int kFlagBlocks = 16;
+
+template <CompactPrefix MODE, bool VEC>
+__global__ __launch_bounds__(kScanBlock) void k_compact_write(const uint8_t* __restrict__ accept, int n_events,
+                                                              const int32_t* __restrict__ partials, int n_blocks,
+                                                              int32_t* __restrict__ ids, int32_t* __restrict__ n_out) {
+    const int64_t base = (int64_t)blockIdx.x * kCompactEvents + (int64_t)threadIdx.x * kCompactItems;
+    const Flags f = load_flags<VEC>(accept, base, n_events);
+    int32_t prefix = 0;
+    if constexpr (MODE == kPrefixScanned) {
+        prefix = partials[blockIdx.x];
+    } else {
+        int32_t before = 0;
+        if constexpr (MODE == kPrefixSummed) {
+            for (int i = (int)threadIdx.x; i < (int)blockIdx.x; i += kScanBlock) before += partials[i];
+        } else {
+#pragma unroll 8
+            for (int i = 0; i < (int)blockIdx.x; ++i)
+                before += load_flags<VEC>(accept, (int64_t)i * kCompactEvents + (int64_t)threadIdx.x * kCompactItems,
+                                          n_events)
+                              .count();
+        }
+        block_exclusive_scan<int32_t>(before, prefix);
     }
     int32_t total;
-    int32_t pos = partials[blockIdx.x] + block_exclusive_scan<int32_t>(c, total);
+    int32_t pos = prefix + block_exclusive_scan<int32_t>(f.count(), total);
 #pragma unroll
-    for (int k = 0; k < kCompactItems; ++k)
-        if (f[k]) ids[pos++] = (int32_t)(base + k);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *n_out = partials[n_blocks];
-}
-
-// k_compact_write without the scan kernel before it: each block sums the
-// counts of the blocks before it (at most kPrefixBlocks of them, read from
-// L2), and the last block writes the total.
-constexpr int kPrefixBlocks = 4096;
-
-__global__ __launch_bounds__(kScanBlock) void k_compact_write_prefix(const uint8_t* __restrict__ accept,
-                                                                     int n_events,
-                                                                     const int32_t* __restrict__ partials,
-                                                                     int n_blocks,
-                                                                     int32_t* __restrict__ ids,
-                                                                     int32_t* __restrict__ n_out) {
-    int32_t before = 0;
-    for (int i = (int)threadIdx.x; i < (int)blockIdx.x; i += kScanBlock) before += partials[i];
-    int32_t prefix;
-    block_exclusive_scan<int32_t>(before, prefix);
-    const int64_t base = (int64_t)blockIdx.x * kScanBlock * kCompactItems +
-                         (int64_t)threadIdx.x * kCompactItems;
-    uint8_t f[kCompactItems];
-    int32_t c = 0;
-#pragma unroll
-    for (int k = 0; k < kCompactItems; ++k) {
-        f[k] = (base + k < n_events) ? (accept[base + k] != 0) : 0;
-        c += f[k];
-    }
-    int32_t total;
-    int32_t pos = prefix + block_exclusive_scan<int32_t>(c, total);
-#pragma unroll
-    for (int k = 0; k < kCompactItems; ++k)
-        if (f[k]) ids[pos++] = (int32_t)(base + k);
+    for (int q = 0; q < 4; ++q)
+        for (uint32_t m = f.w[q]; m; m &= m - 1u)
+            ids[pos++] = (int32_t)(base + 4 * q + (__builtin_ctz(m) >> 3));
     if ((int)blockIdx.x == n_blocks - 1 && threadIdx.x == 0) *n_out = prefix + total;
 }
 
@@ -625,7 +639,7 @@ Layout layout(int n_events, uint32_t flags) {
     Layout L;
     size_t at = 0;
     if (flags & TRIG_OUT_COMPACT) {
-        L.compact_blocks = (int)std::max<int64_t>(1, cdiv(n_events, (int64_t)kScanBlock * kCompactItems));
+        L.compact_blocks = (int)std::max<int64_t>(1, cdiv(n_events, kCompactEvents));
         L.compact_off = at;
         at += align256(sizeof(int32_t) * (size_t)(L.compact_blocks + 1));
     }
@@ -726,12 +740,18 @@ struct BlockShape {
     int hb, nw, eb;
 };
 // Events per block that fill `fill` of an hb-hit block at the batch's mean
-// event size.
+// event size, but in small batches no more than give every CU kSmallBlocks
+// blocks (and at least one event per wave): there the time is a block's own
+// (1,000 events of 15 hits per layer: 7.7 us at 18 events per block, 5.4 us at
+// one or two per wave).
+constexpr int kSmallBlocks = 4;
 int events_for_fill(double fill, int hb, int nw, int n_events, int n_hits) {
     const double mean = std::max(n_events > 0 ? (double)n_hits / n_events : 1.0, 1.0);
     int eb = (int)std::max(1.0, std::min((double)kMaxEB, std::floor(fill * hb / mean)));
     if (nw > 0 && eb >= nw) eb -= eb % nw;  // whole rounds of events over the waves
-    return eb;
+    const int64_t waves = std::max(nw, 1);
+    const int64_t spread = cdiv(cdiv(n_events, (int64_t)device_cus() * kSmallBlocks), waves) * waves;
+    return (int)std::min<int64_t>(eb, std::max(waves, spread));
 }
 
 BlockShape choose_block_shape(const trig_params* p, int n_events, int n_hits) {
@@ -840,6 +860,29 @@ int launch_two_particles(const trig_events_csr* ev, const trig_hits* h, const Co
     hipLaunchKernelGGL(k_two_particles<P>, dim3((unsigned)cdiv(waves, kTwoWaves)), dim3(kTwoWaves * kWave), 0, s,
                        ev->layer_offsets, ev->n_events, h->x, h->y, h->z, c, accept);
     return check_launch("k_two_particles");
+}
+
+// The ascending ids of accepted events.
+template <bool VEC>
+int launch_compact(const uint8_t* accept, int n, int32_t* part, int blocks, const trig_params* p, hipStream_t s) {
+    const dim3 grid((unsigned)blocks), block(kScanBlock);
+    int32_t* ids = p->out_accepted_ids;
+    int32_t* n_out = p->out_n_accepted;
+    if (blocks <= kFlagBlocks) {
+        hipLaunchKernelGGL((k_compact_write<kPrefixFlags, VEC>), grid, block, 0, s, accept, n, part, blocks, ids, n_out);
+        return check_launch("k_compact_write");
+    }
+    hipLaunchKernelGGL(k_compact_count<VEC>, grid, block, 0, s, accept, n, part);
+    if (int r = check_launch("k_compact_count")) return r;
+    if (blocks <= kPrefixBlocks) {
+        hipLaunchKernelGGL((k_compact_write<kPrefixSummed, VEC>), grid, block, 0, s, accept, n, part, blocks, ids,
+                           n_out);
+        return check_launch("k_compact_write");
+    }
+    hipLaunchKernelGGL(k_scan_partials<int32_t>, dim3(1), block, 0, s, part, blocks);
+    if (int r = check_launch("k_scan_partials")) return r;
+    hipLaunchKernelGGL((k_compact_write<kPrefixScanned, VEC>), grid, block, 0, s, accept, n, part, blocks, ids, n_out);
+    return check_launch("k_compact_write");
 }
 
 // Per-hit z: brute force as asked, every other form with slope pruning, from
@@ -1051,20 +1094,10 @@ int trig_select(const trig_events_csr* ev, const trig_hits* hits, const trig_par
             return check_launch("k_store_zero");
         }
         auto* part = reinterpret_cast<int32_t*>(ws + L.compact_off);
-        hipLaunchKernelGGL(k_compact_count, dim3(L.compact_blocks), dim3(kScanBlock), 0, s, out_accept, n, part);
-        if (int r = check_launch("k_compact_count")) return r;
-        if (L.compact_blocks <= kPrefixBlocks) {
-            // up to 4M events: no scan launch, each block sums the counts before it
-            hipLaunchKernelGGL(k_compact_write_prefix, dim3(L.compact_blocks), dim3(kScanBlock), 0, s, out_accept,
-                               n, part, L.compact_blocks, p->out_accepted_ids, p->out_n_accepted);
-            if (int r = check_launch("k_compact_write_prefix")) return r;
-        } else {
-            hipLaunchKernelGGL(k_scan_partials<int32_t>, dim3(1), dim3(kScanBlock), 0, s, part, L.compact_blocks);
-            if (int r = check_launch("k_scan_partials")) return r;
-            hipLaunchKernelGGL(k_compact_write, dim3(L.compact_blocks), dim3(kScanBlock), 0, s, out_accept, n,
-                               part, L.compact_blocks, p->out_accepted_ids, p->out_n_accepted);
-            if (int r = check_launch("k_compact_write")) return r;
-        }
+        const int r = (reinterpret_cast<uintptr_t>(out_accept) & 15) == 0
+                          ? launch_compact<true>(out_accept, n, part, L.compact_blocks, p, s)
+                          : launch_compact<false>(out_accept, n, part, L.compact_blocks, p, s);
+        if (r) return r;
     }
     g_detail.clear();
     return TRIG_OK;

@@ -225,3 +225,32 @@ def test_per_hit_z_misaligned(gpu):  # noqa: F811
         print(f"[per-hit z misaligned] {shift}", flush=True)
         r = trig.select(off, a[0], a[1], hit_z=a[2], form="pruned")
         assert np.array_equal(r.counts.cpu().numpy(), want)
+
+
+# ----------------------------------------------------------- compaction ---
+
+@pytest.mark.parametrize("n_events", (1, 15, 16, 17, 4095, 4096, 4097, 61440, 65535, 65536, 65537, 131077))
+def test_compaction_block_edges(gpu, n_events):  # noqa: F811
+    """Accepted ids at the edges of a thread's 16 events, a block's 4,096 and
+    the one-launch form's 65,536, few and many accepted, with the flags
+    16-byte aligned and not, whole and at the end of a longer buffer."""
+    from paper_1810_11966_amd import trig
+    rng = np.random.default_rng(n_events)
+    z = np.array([400.0, 410.0, 420.0])
+    for share in (0.0, 0.002, 0.5, 1.0):
+        hit = rng.random(n_events) < share
+        hit[-1] = share > 0
+        m = rng.uniform(-0.3, 0.3, n_events)
+        x = (m[:, None] * z + np.where(hit, 0.0, 30.0)[:, None] * np.array([0.0, 1.0, 0.0])).astype(np.float32).ravel()
+        d = [gpu.from_numpy(a).cuda() for a in (np.arange(3 * n_events + 1, dtype=np.int32), x, np.zeros_like(x))]
+        for shift in (0, 1, 16):
+            print(f"[compaction] events={n_events} share={share} shift={shift}", flush=True)
+            counts = gpu.full((n_events,), -9, dtype=gpu.int32, device="cuda")
+            flags = gpu.full((n_events + 40,), 7, dtype=gpu.uint8, device="cuda")
+            accept = flags[shift:shift + n_events]
+            r = trig.select(*d, form="pruned", compact=True, min_triplets=1, out=(counts, accept))
+            gpu.cuda.synchronize()
+            assert np.array_equal(accept.cpu().numpy() != 0, hit)
+            assert int(r.n_accepted.cpu()[0]) == int(hit.sum())
+            assert np.array_equal(r.ids.cpu().numpy()[: int(hit.sum())], np.flatnonzero(hit))
+            assert (flags[:shift].cpu().numpy() == 7).all() and (flags[shift + n_events:].cpu().numpy() == 7).all()
