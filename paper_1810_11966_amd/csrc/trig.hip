@@ -424,10 +424,16 @@ __global__ __launch_bounds__(kBinWaves * kWave) __attribute__((amdgpu_waves_per_
 // -------------------------------------------------- two-particle mode ---
 
 // TRIG_ACCEPT_TWO_PARTICLES, after the counting form has flagged the
-// candidates (count >= 2): each wave scans the flags of 64 consecutive
-// events and decides its candidates one by one (wave_two_particles), writing
-// the final flag.  Events without a candidate cost one coalesced read.
+// candidates (count >= 2): a workgroup reads the flags of kTwoEvents
+// consecutive events and its waves take the candidates in turn
+// (wave_two_particles), writing the final flag.  Events without a candidate
+// cost one coalesced read.  A candidate takes a wave some 5 us of dependent
+// round trips, so the kernel's time is the longest list of one wave: with 64
+// events per wave on its own 24 us (300,000 events, 1 % candidates), shared by
+// four waves per 128 events less than half of it (whole call with the window
+// test 117 -> 101 us, together with the batched form's approximate slopes).
 constexpr int kTwoWaves = 4;
+constexpr int kTwoEvents = 2 * kWave;
 constexpr int kTwoPartCap = 512;  // layer-0 and layer-1 partials a wave keeps in LDS
 
 template <class P>
@@ -437,10 +443,7 @@ __global__ __launch_bounds__(kTwoWaves * kWave) void k_two_particles(const int32
                                                                      const float* __restrict__ z, Consts c,
                                                                      uint8_t* __restrict__ accept) {
     const int w = uniform_i((int)(threadIdx.x / kWave));
-    const int64_t base = ((int64_t)blockIdx.x * kTwoWaves + w) * kWave;
-    if (base >= n_events) return;
-    const int64_t e = base + lane_id();
-    uint64_t m = lanes(e < n_events && accept[e] != 0);
+    const int64_t base = (int64_t)blockIdx.x * kTwoEvents;
     __shared__ float2 part_all[kTwoWaves][kTwoPartCap];
     using H = typename std::conditional<P::kZ, SlopeHits, GlobalHits>::type;
     H gh;
@@ -448,16 +451,26 @@ __global__ __launch_bounds__(kTwoWaves * kWave) void k_two_particles(const int32
         gh = SlopeHits{x, y, z};
     else
         gh = GlobalHits{x, y};
-    while (m) {
-        const int L = __builtin_ctzll(m);
-        m &= m - 1;
-        const int ev_i = (int)(base + L);
-        EventRange ev;
-        bool two = false;
-        if (load_event(off, ev_i, c.n_hits, ev) == 0 && ev.n0 > 0 && ev.n1 > 0 && ev.n2 > 0)
-            two = wave_two_particles<P>(c, gh, ev.o0, ev.n0, ev.o1, ev.n1, ev.o2, ev.n2, part_all[w], kTwoPartCap);
-        if (lane_id() == 0) accept[ev_i] = (uint8_t)two;
+    // Every wave reads all of the workgroup's flags, before any is rewritten.
+    uint64_t m[kTwoEvents / kWave];
+#pragma unroll
+    for (int q = 0; q < kTwoEvents / kWave; ++q) {
+        const int64_t e = base + q * kWave + lane_id();
+        m[q] = lanes(e < n_events && accept[e] != 0);
     }
+    __syncthreads();
+    int turn = 0;  // of the next candidate
+#pragma unroll 1
+    for (int q = 0; q < kTwoEvents / kWave; ++q)
+        for (uint64_t left = m[q]; left; left &= left - 1ull, turn = (turn + 1) % kTwoWaves) {
+            if (turn != w) continue;
+            const int ev_i = (int)(base + q * kWave + __builtin_ctzll(left));
+            EventRange ev;
+            bool two = false;
+            if (load_event(off, ev_i, c.n_hits, ev) == 0 && ev.n0 > 0 && ev.n1 > 0 && ev.n2 > 0)
+                two = wave_two_particles<P>(c, gh, ev.o0, ev.n0, ev.o1, ev.n1, ev.o2, ev.n2, part_all[w], kTwoPartCap);
+            if (lane_id() == 0) accept[ev_i] = (uint8_t)two;
+        }
 }
 
 // ------------------------------------------------------------ per-hit z ---
@@ -575,6 +588,12 @@ Consts make_consts(const trig_params* p, int n_hits) {
     c.pre_win = std::max(p->slope_window[0], p->slope_window[1]);
     c.win_x = p->slope_window[0];
     c.win_y = p->slope_window[1];
+    c.win_r0 = 1.0f / c.z0;
+    c.win_r1 = 1.0f / c.z1;
+    const bool normal = std::isnormal(c.win_r0) && std::isnormal(c.win_r1);
+    if (!normal) c.win_r0 = c.win_r1 = 0.0f;
+    c.win_slack0 = normal ? 0x1p-120f : INFINITY;
+    c.win_slack = normal ? std::max(c.win_r0, c.win_r1) * 0x1p-19f : 0.0f;
     c.bin_r = p->test == TRIG_TEST_SLOPE_WINDOW ? c.win_x : std::nextafter(c.beta_x, INFINITY);
     const bool two = (p->flags & TRIG_ACCEPT_TWO_PARTICLES) != 0;
     c.min_triplets = two ? 2 : p->min_triplets;  // two particles need two passing triplets
@@ -856,8 +875,7 @@ int launch_binned(const trig_events_csr* ev, const trig_hits* h, const trig_para
 template <class P>
 int launch_two_particles(const trig_events_csr* ev, const trig_hits* h, const Consts& c, uint8_t* accept,
                          hipStream_t s) {
-    const int64_t waves = cdiv(ev->n_events, kWave);
-    hipLaunchKernelGGL(k_two_particles<P>, dim3((unsigned)cdiv(waves, kTwoWaves)), dim3(kTwoWaves * kWave), 0, s,
+    hipLaunchKernelGGL(k_two_particles<P>, dim3((unsigned)cdiv(ev->n_events, kTwoEvents)), dim3(kTwoWaves * kWave), 0, s,
                        ev->layer_offsets, ev->n_events, h->x, h->y, h->z, c, accept);
     return check_launch("k_two_particles");
 }

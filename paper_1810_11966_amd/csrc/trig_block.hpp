@@ -114,6 +114,7 @@ struct SlopeHits {
 // TRIG_TEST_MSD_BASIS.
 struct MsdBasisPrune {
     static constexpr bool kMag = false;  // bounds do not depend on M
+    static constexpr bool kApprox = false;  // no cheaper approximation of the partials
     static constexpr bool kEventBounds = false;
     static constexpr bool kZ = false;
     __device__ static __forceinline__ PairBounds bounds(const Consts& c, float) {
@@ -201,6 +202,7 @@ struct MsdBasisPrune {
 // written out.
 struct MsdFitPrune {
     static constexpr bool kMag = true;  // bounds grow with M >= |c_j|
+    static constexpr bool kApprox = false;
     static constexpr bool kEventBounds = false;
     static constexpr bool kZ = false;
     __device__ static __forceinline__ PairBounds bounds(const Consts& c, float M) {
@@ -249,12 +251,22 @@ struct MsdFitPrune {
     }
 };
 
+// TRIG_TEST_SLOPE_WINDOW.  The fast path's prefilter compares approximate
+// slopes c fl(1 / z) (one product, where a binary32 division takes some 40
+// vector cycles): with M >= |c| they are within 3 2^-24 M / z of the rounded
+// quotients, so a pair's score rises by less than 2^-20 M max(1 / z0, 1 / z1),
+// which `pre` adds (win_slack0 = +inf where a 1 / z is no normal number).
 struct WindowPrune {
-    static constexpr bool kMag = false;
+    static constexpr bool kMag = true;  // of `pre` only
+    static constexpr bool kApprox = true;
     static constexpr bool kEventBounds = false;
     static constexpr bool kZ = false;
-    __device__ static __forceinline__ PairBounds bounds(const Consts& c, float) {
-        return PairBounds{c.win_x, c.win_y, c.pre_win};
+    __device__ static __forceinline__ PairBounds bounds(const Consts& c, float M) {
+        return PairBounds{c.win_x, c.win_y, (c.pre_win + c.win_slack0) + c.win_slack * M};
+    }
+    __device__ static __forceinline__ float2 layer_approx(const Consts& c, float2 h, int l) {
+        const float r = select_uniform(l, c.win_r1, c.win_r0);
+        return make_float2(h.x * r, h.y * r);
     }
     __device__ static __forceinline__ float2 layer0(const Consts& c, float2 h) {
         return make_float2(h.x / c.z0, h.y / c.z0);
@@ -314,6 +326,7 @@ struct WindowPrune {
 // layers 0 and 1; survivors completed with the per-hit-z fit.
 struct MsdZPrune {
     static constexpr bool kMag = false;
+    static constexpr bool kApprox = false;
     static constexpr bool kEventBounds = true;
     static constexpr bool kZ = true;  // reads hits through SlopeHits
     __device__ static __forceinline__ float2 layer0(const Consts&, float2 s) { return s; }
@@ -384,6 +397,7 @@ struct MsdZPrune {
 // layer-1 window is exact, as in WindowPrune.
 struct WindowZPrune {
     static constexpr bool kMag = false;
+    static constexpr bool kApprox = false;
     static constexpr bool kEventBounds = false;
     static constexpr bool kZ = true;  // reads hits through SlopeHits
     __device__ static __forceinline__ PairBounds bounds(const Consts& c, float) {
@@ -421,8 +435,9 @@ __device__ __forceinline__ PairBounds event_bounds(const Consts& c, const H& hit
     if constexpr (P::kEventBounds) {
         return P::event_bounds(c, hits, o0, n0, o1, n1);
     } else {
+        // (kApprox: the callers compare the exact partials)
         float M = 0.0f;
-        if constexpr (P::kMag) M = layer_mag(hits, o1, n1);
+        if constexpr (P::kMag && !P::kApprox) M = layer_mag(hits, o1, n1);
         return P::bounds(c, M);
     }
 }
@@ -508,11 +523,17 @@ __device__ bool wave_two_particles(const Consts& c, const H& hits, int o0, int n
             part[t] = t < n0 ? P::layer0(c, hits.at(o0 + t)) : P::layer1(c, hits.at(o1 + (t - n0)));
         wave_lds_sync();
     }
+    const uint32_t dq = kWave / un1, dr = kWave % un1;
+    uint32_t ni = lane / un1, nj = lane - ni * un1;  // the lane's next pair
     for (uint32_t p0 = 0; p0 < np; p0 += kWave) {
-        const uint32_t p = p0 + lane;
-        const bool v = p < np;
-        const uint32_t q = p / un1;
-        const int i = v ? (int)q : 0, j = v ? (int)(p - q * un1) : 0;
+        const bool v = p0 + lane < np;
+        const int i = v ? (int)ni : 0, j = v ? (int)nj : 0;
+        nj += dr;
+        ni += dq;
+        if (nj >= un1) {
+            nj -= un1;
+            ++ni;
+        }
         float2 u = nan2(), w = nan2();
         if (v) {
             u = staged ? part[i] : P::layer0(c, hits.at(o0 + i));
@@ -621,8 +642,8 @@ __device__ uint32_t wave_event_pruned(const Consts& c, const PairBounds& pb, con
 // layer's partials go to px/py (NaN past nB).  Both pair tests depend on the
 // two partials symmetrically (a sum, or the absolute value of a difference,
 // which binary32 gives the same either way round), so the orientation does
-// not change a count.
-template <class P, class H>
+// not change a count.  APPROX: the policy's approximate partials.
+template <class P, bool APPROX, class H>
 __device__ __forceinline__ void fast_setup(const Consts& c, const H& hits, int oB, int nB, int oL, int nL, int S,
                                            int R, int T, uint32_t r, float* __restrict__ px, float* __restrict__ py,
                                            int& g, int& j, float2& q) {
@@ -637,9 +658,15 @@ __device__ __forceinline__ void fast_setup(const Consts& c, const H& hits, int o
     // selects NaN where it has none; the whole kPBuf-entry buffer (>= T R
     // entries) is written.
     const float nan = __builtin_nanf("");
-    const float2 hq = P::layer(c, hits.at(oL + min(j, nL - 1)), S ? 0 : 1);
+    auto layer = [&](float2 h, int l) {
+        if constexpr (APPROX)
+            return P::layer_approx(c, h, l);
+        else
+            return P::layer(c, h, l);
+    };
+    const float2 hq = layer(hits.at(oL + min(j, nL - 1)), S ? 0 : 1);
     q = make_float2(jv ? hq.x : nan, jv ? hq.y : nan);
-    const float2 v = P::layer(c, hits.at(oB + min(lane, nB - 1)), S ? 1 : 0);
+    const float2 v = layer(hits.at(oB + min(lane, nB - 1)), S ? 1 : 0);
     px[lane] = lane < nB ? v.x : nan;
     py[lane] = lane < nB ? v.y : nan;
 }
@@ -708,10 +735,17 @@ __device__ uint32_t wave_event_fast(const Consts& c, const PairBounds& pb, const
     const int oL = S ? o0 : o1, nL = S ? n0 : n1;
     int g, j;
     float2 q;
-    fast_setup<P>(c, hits, oB, nB, oL, nL, S, R, T, r, px, py, g, j, q);
+    fast_setup<P, P::kApprox>(c, hits, oB, nB, oL, nL, S, R, T, r, px, py, g, j, q);
     wave_lds_sync();
     uint32_t cnt = 0;
-    if (wave_any(fast_score<P>(px, py, T, g, q) <= pb.pre)) cnt = fast_exact<P>(c, pb, hits, oB, oL, S, o2, n2, T, g, j, q, px, py);
+    if (wave_any(fast_score<P>(px, py, T, g, q) <= pb.pre)) {
+        if constexpr (P::kApprox) {
+            wave_lds_sync();
+            fast_setup<P, false>(c, hits, oB, nB, oL, nL, S, R, T, r, px, py, g, j, q);
+            wave_lds_sync();
+        }
+        cnt = fast_exact<P>(c, pb, hits, oB, oL, S, o2, n2, T, g, j, q, px, py);
+    }
     wave_lds_sync();
     return cnt;
 }
@@ -1400,7 +1434,7 @@ void k_block_z(const int32_t* __restrict__ off, int n_events, const float* __res
                 if (TB > 0) {
                     int g, j;
                     float2 q;
-                    fast_setup<P>(c, lh, (S ? b1 : b0) - a0, S ? ev.n1 : ev.n0, (S ? b0 : b1) - a0, S ? ev.n0 : ev.n1,
+                    fast_setup<P, false>(c, lh, (S ? b1 : b0) - a0, S ? ev.n1 : ev.n0, (S ? b0 : b1) - a0, S ? ev.n0 : ev.n1,
                                   S, R, TB, (uint32_t)uniform_i((int)L.dr[te]), px, py, g, j, q);
                     wave_lds_sync();
                     close = wave_any(fast_score<P>(px, py, TB, g, q) <= pb.pre);

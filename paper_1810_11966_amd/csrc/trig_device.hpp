@@ -47,6 +47,10 @@ struct Consts {
     float pre_msd, pre_win_sum, pre_win;
     // TRIG_TEST_SLOPE_WINDOW
     float win_x, win_y;
+    // Batched form's window prefilter: 1 / z0 and 1 / z1 rounded, and what the
+    // approximate slopes c fl(1 / z) can add to a pair's score (win_slack0 +
+    // win_slack M)
+    float win_r0, win_r1, win_slack0, win_slack;
     // Binned form, MSD_BASIS and window: half-width of the key interval
     // around a hit's centre (MSD_BASIS: the binary32 value above beta_x;
     // window: win_x).
@@ -426,7 +430,9 @@ __device__ __forceinline__ int load_event(const int32_t* __restrict__ off, int e
     if (!(0 <= a0 && a0 <= a1 && a1 <= a2 && a2 <= a3 && a3 <= n_hits)) return -1;
     ev.o0 = a0; ev.o1 = a1; ev.o2 = a2;
     ev.n0 = a1 - a0; ev.n1 = a2 - a1; ev.n2 = a3 - a2;
-    if (ev.n2 > 0 && (int64_t)ev.n0 * ev.n1 > (int64_t)INT32_MAX / ev.n2) return -2;
+    // (n0 n1 < 2^62, and with n0 n1 <= INT32_MAX the product with n2 too)
+    const int64_t n01 = (int64_t)ev.n0 * ev.n1;
+    if (ev.n2 > 0 && (n01 > (int64_t)INT32_MAX || n01 * ev.n2 > (int64_t)INT32_MAX)) return -2;
     return 0;
 }
 

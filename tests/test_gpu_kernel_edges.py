@@ -254,3 +254,24 @@ def test_compaction_block_edges(gpu, n_events):  # noqa: F811
             assert int(r.n_accepted.cpu()[0]) == int(hit.sum())
             assert np.array_equal(r.ids.cpu().numpy()[: int(hit.sum())], np.flatnonzero(hit))
             assert (flags[:shift].cpu().numpy() == 7).all() and (flags[shift + n_events:].cpu().numpy() == 7).all()
+
+
+# --------------------------------------------------- window prefilter ---
+
+@pytest.mark.parametrize("form", ("pruned", "persistent_pruned"))
+def test_window_prefilter_layer_positions(gpu, form):  # noqa: F811
+    """The batched window test's approximate slopes: pairs at the window's
+    edge far from the axis, and layer positions whose reciprocals are
+    subnormal, overflow, or sit at either end of the normal range."""
+    edge = synth.concat([helpers.window_boundary_events(100, 6, seed=71, rel=1e-6),
+                         helpers.window_boundary_events(100, 6, seed=72, rel=3e-8)])
+    c = assert_parity(gpu, edge, "window", form, "window edge")
+    assert c.sum() > 0
+    far = synth.EventSet(edge.offsets, edge.x * np.float32(512), edge.y * np.float32(512), edge.n_tracks)
+    for w in (2.56, 2.5600002, 1e-3, 300.0):
+        assert_parity(gpu, far, "window", form, f"far from the axis, window {w}", slope_window=(w, w))
+    s = helpers.ragged_sizes_set([(9, 8, 7), (20, 25, 22), (40, 3, 5)] * 20, seed=73)
+    for z in ((1e-42, 2e-42, 3e-42), (2e-38, 2.1e-38, 2.2e-38), (1e-3, 1e-38, 5.0), (3e38, 3.1e38, 3.2e38),
+              (8e37, 9e37, 1e38), (1e38, 1e-38, 1.0), (1e30, 1e30, 1e30)):
+        for w in (0.0, 1e-38, 1e-30, 1.0, 1e30, 3e38):
+            assert_parity(gpu, s, "window", form, f"z {z} window {w}", z=z, slope_window=(w, w))
