@@ -79,8 +79,16 @@ struct BinLds {
             float a2[kBinCap], b2[kBinCap];
         };
     };
-    uint32_t end1[kBinCap / 2];
-    uint32_t end2[kBinCap / 2];  // end2[0]: number of surviving pairs while `pairs` is used
+    // Layer-1 and layer-2 cell ends (kBinCap / 2 words each); or, while `pairs`
+    // is used, the layer-1 cells' starts (starts()), and the number of
+    // surviving pairs in the last word.
+    uint32_t ends[kBinCap];
+    __device__ __forceinline__ uint32_t* end1() { return ends; }
+    __device__ __forceinline__ uint32_t* end2() { return ends + kBinCap / 2; }
+    __device__ __forceinline__ const uint32_t* end1() const { return ends; }
+    __device__ __forceinline__ const uint32_t* end2() const { return ends + kBinCap / 2; }
+    __device__ __forceinline__ uint16_t* starts() { return reinterpret_cast<uint16_t*>(ends); }
+    __device__ __forceinline__ uint32_t* n_pairs() { return ends + kBinCap - 1; }
 };
 static_assert(kBinCap < 65536, "cell ends fit in 16 bits");
 
@@ -113,14 +121,17 @@ struct Bins {
 struct LayerRegs {
     float x[kBinRounds], y[kBinRounds];
     __device__ __forceinline__ void load(const float* __restrict__ xs, const float* __restrict__ ys, int o, int n) {
-        const int lane = (int)lane_id();
+        // (byte offsets from a scalar base: one vector instruction per round)
+        const char* bx = reinterpret_cast<const char*>(xs + o);
+        const char* by = reinterpret_cast<const char*>(ys + o);
+        const uint32_t lane4 = 4u * lane_id(), last = 4u * (uint32_t)(n - 1);
 #pragma unroll
         for (int r = 0; r < kBinRounds; ++r) {
             x[r] = y[r] = 0.0f;
             if (r * kWave < n) {  // wave-uniform: rounds past the layer are skipped
-                const int t = min(r * kWave + lane, n - 1);
-                x[r] = xs[o + t];
-                y[r] = ys[o + t];
+                const uint32_t t = min(lane4 + 4u * kWave * r, last);
+                x[r] = *reinterpret_cast<const float*>(bx + t);
+                y[r] = *reinterpret_cast<const float*>(by + t);
             }
         }
     }
@@ -226,9 +237,9 @@ __device__ __forceinline__ Bins build_bins(const Consts& c, const LayerRegs& h, 
 
 // A surviving pair (whole lanes of a divergent loop): the first kBinPairs of
 // the event are kept, all are counted.
-__device__ __forceinline__ void push_pair(BinLds& L, float xi, float yi, float xj, float yj) {
-    const uint32_t at = atomicAdd(&L.end2[0], 1u);
-    if (at < (uint32_t)kBinPairs) L.pairs[at] = make_float4(xi, yi, xj, yj);
+__device__ __forceinline__ void push_pair(BinLds& L, float4 p) {
+    const uint32_t at = atomicAdd(L.n_pairs(), 1u);
+    if (at < (uint32_t)kBinPairs) L.pairs[at] = p;
 }
 
 // Bounds of one event: pair test |a_x| <= bx, |a_y| <= by (window: strict,
@@ -259,21 +270,23 @@ struct MsdBasisBin {
             return make_float2(c.V2 * x, c.V2 * y);
         }
     };
-    // Pairs of layer-0 hit (xi, yi) that can pass, to the event's list.
-    __device__ static __forceinline__ void pairs_i(const Consts& c, const BinBounds& bb, float xi, float yi,
-                                                   const Bins& b1, BinLds& L) {
-        const float ux = c.U0 * xi;
-        if (!__builtin_isfinite(ux)) return;
-        const float lo = widen_down(-ux - bb.r1), hi = widen_up(-ux + bb.r1);
-        if (hi < b1.kmin || lo > b1.kmax) return;
-        int j0, j1;
-        b1.range(L.end1, lo, hi, j0, j1);
-        for (int j = j0; j < j1; ++j) {
-            const float xj = L.a1[j], yj = L.b1[j];
-            const float ax = c.U0 * xi + c.U1 * xj;
-            const float ay = c.U0 * yi + c.U1 * yj;
-            if (__builtin_fabsf(ax) <= bb.bx && __builtin_fabsf(ay) <= bb.by) push_pair(L, xi, yi, xj, yj);
-        }
+    // Largest layer-1 |key| for hits within |x| <= M.
+    __device__ static __forceinline__ float key_max(const Consts& c, float M) { return __builtin_fabsf(c.U1) * M; }
+    // A layer-0 hit's side of the pair test, the centre of its key interval,
+    // the test's score (at most bx + by for a pair that passes) and the test.
+    __device__ static __forceinline__ float2 side(const Consts& c, float x, float y) {
+        return make_float2(c.U0 * x, c.U0 * y);
+    }
+    __device__ static __forceinline__ float centre(float2 u) { return -u.x; }
+    __device__ static __forceinline__ float2 diff(const Consts& c, float2 u, float xj, float yj) {
+        return make_float2(u.x + c.U1 * xj, u.y + c.U1 * yj);
+    }
+    __device__ static __forceinline__ bool pair(const BinBounds& bb, float2 a) {
+        return __builtin_fabsf(a.x) <= bb.bx && __builtin_fabsf(a.y) <= bb.by;
+    }
+    // What the event's list holds of a pair that passed.
+    __device__ static __forceinline__ float4 entry(float xi, float yi, float2, float xj, float yj) {
+        return make_float4(xi, yi, xj, yj);
     }
     // Lanes whose layer-2 hit (x, y) makes a passing triplet with the pair.
     __device__ static __forceinline__ uint64_t complete(const Consts& c, float4 p, float x, float y) {
@@ -290,7 +303,7 @@ struct MsdBasisBin {
         const float lo = widen_down(-ux - r), hi = widen_up(-ux + r);
         if (hi < b1.kmin || lo > b1.kmax) return 0;
         int j0, j1;
-        b1.range(L.end1, lo, hi, j0, j1);
+        b1.range(L.end1(), lo, hi, j0, j1);
         uint32_t cnt = 0;
         for (int j = j0; j < j1; ++j) {
             const float xj = L.a1[j], yj = L.b1[j];
@@ -304,7 +317,7 @@ struct MsdBasisBin {
             const float lo2 = widen_down(-bx0 - bb.r2), hi2 = widen_up(-bx0 + bb.r2);
             if (hi2 < b2.kmin || lo2 > b2.kmax) continue;
             int k0, k1;
-            b2.range(L.end2, lo2, hi2, k0, k1);
+            b2.range(L.end2(), lo2, hi2, k0, k1);
             for (int k = k0; k < k1; ++k) {
                 const float bx = bx0 + L.a2[k];
                 const float qx = ax2 + bx * bx;
@@ -345,9 +358,17 @@ struct MsdFitBin {
             return make_float2(x, y);
         }
     };
-    __device__ static __forceinline__ void pairs_i(const Consts& c, const BinBounds& bb, float xi, float yi,
-                                                   const Bins& b1, BinLds& L) {
-        MsdBasisBin::pairs_i(c, bb, xi, yi, b1, L);
+    __device__ static __forceinline__ float key_max(const Consts& c, float M) { return MsdBasisBin::key_max(c, M); }
+    __device__ static __forceinline__ float2 side(const Consts& c, float x, float y) {
+        return MsdBasisBin::side(c, x, y);
+    }
+    __device__ static __forceinline__ float centre(float2 u) { return MsdBasisBin::centre(u); }
+    __device__ static __forceinline__ float2 diff(const Consts& c, float2 u, float xj, float yj) {
+        return MsdBasisBin::diff(c, u, xj, yj);
+    }
+    __device__ static __forceinline__ bool pair(const BinBounds& bb, float2 a) { return MsdBasisBin::pair(bb, a); }
+    __device__ static __forceinline__ float4 entry(float xi, float yi, float2, float xj, float yj) {
+        return make_float4(xi, yi, xj, yj);
     }
     __device__ static __forceinline__ uint64_t complete(const Consts& c, float4 p, float x, float y) {
         const MsdFitTest::Pair pr = MsdFitTest::pair(c, p.x, p.y, p.z, p.w);
@@ -361,7 +382,7 @@ struct MsdFitBin {
         const float lo = widen_down(-ux - bb.r1), hi = widen_up(-ux + bb.r1);
         if (hi < b1.kmin || lo > b1.kmax) return 0;
         int j0, j1;
-        b1.range(L.end1, lo, hi, j0, j1);
+        b1.range(L.end1(), lo, hi, j0, j1);
         const float pxi = xi * c.z0, pyi = yi * c.z0;
         uint32_t cnt = 0;
         for (int j = j0; j < j1; ++j) {
@@ -374,7 +395,7 @@ struct MsdFitBin {
             const float lo2 = widen_down(-bx0 - bb.r2), hi2 = widen_up(-bx0 + bb.r2);
             if (hi2 < b2.kmin || lo2 > b2.kmax) continue;
             int k0, k1;
-            b2.range(L.end2, lo2, hi2, k0, k1);
+            b2.range(L.end2(), lo2, hi2, k0, k1);
             const float sx01 = pxi + xj * c.z1;
             const float sy01 = pyi + yj * c.z1;
             for (int k = k0; k < k1; ++k) {
@@ -408,18 +429,20 @@ struct WindowBin {
             return make_float2(x / c.z2, y / c.z2);
         }
     };
-    // The pair's slopes; those of layer 1 are tested here and not needed again.
-    __device__ static __forceinline__ void pairs_i(const Consts& c, const BinBounds& bb, float xi, float yi,
-                                                   const Bins& b1, BinLds& L) {
-        const float sxi = xi / c.z0, syi = yi / c.z0;
-        if (!__builtin_isfinite(sxi)) return;
-        const float lo = widen_down(sxi - bb.r1), hi = widen_up(sxi + bb.r1);
-        if (hi < b1.kmin || lo > b1.kmax) return;
-        int j0, j1;
-        b1.range(L.end1, lo, hi, j0, j1);
-        for (int j = j0; j < j1; ++j)
-            if (__builtin_fabsf(L.a1[j] - sxi) < c.win_x && __builtin_fabsf(L.b1[j] - syi) < c.win_y)
-                push_pair(L, sxi, syi, 0.0f, 0.0f);
+    __device__ static __forceinline__ float key_max(const Consts& c, float M) { return M / c.z1; }
+    __device__ static __forceinline__ float2 side(const Consts& c, float x, float y) {
+        return make_float2(x / c.z0, y / c.z0);
+    }
+    __device__ static __forceinline__ float centre(float2 u) { return u.x; }
+    __device__ static __forceinline__ float2 diff(const Consts&, float2 u, float sxj, float syj) {
+        return make_float2(sxj - u.x, syj - u.y);
+    }
+    __device__ static __forceinline__ bool pair(const BinBounds& bb, float2 d) {
+        return __builtin_fabsf(d.x) < bb.bx && __builtin_fabsf(d.y) < bb.by;
+    }
+    // (the layer-1 window is tested by pair(); layer 2 needs s_i only)
+    __device__ static __forceinline__ float4 entry(float, float, float2 u, float, float) {
+        return make_float4(u.x, u.y, 0.0f, 0.0f);
     }
     __device__ static __forceinline__ uint64_t complete(const Consts& c, float4 p, float x, float y) {
         return lanes(__builtin_fabsf(x / c.z2 - p.x) < c.win_x) & lanes(__builtin_fabsf(y / c.z2 - p.y) < c.win_y);
@@ -432,14 +455,14 @@ struct WindowBin {
         uint32_t nj = 0, nk = 0;
         if (!(hi < b1.kmin || lo > b1.kmax)) {
             int j0, j1;
-            b1.range(L.end1, lo, hi, j0, j1);
+            b1.range(L.end1(), lo, hi, j0, j1);
             for (int j = j0; j < j1; ++j)
                 nj += (uint32_t)((__builtin_fabsf(L.a1[j] - sxi) < c.win_x) &
                                  (__builtin_fabsf(L.b1[j] - syi) < c.win_y));
         }
         if (nj == 0 || hi < b2.kmin || lo > b2.kmax) return 0;
         int k0, k1;
-        b2.range(L.end2, lo, hi, k0, k1);
+        b2.range(L.end2(), lo, hi, k0, k1);
         for (int k = k0; k < k1; ++k)
             nk += (uint32_t)((__builtin_fabsf(L.a2[k] - sxi) < c.win_x) &
                              (__builtin_fabsf(L.b2[k] - syi) < c.win_y));
@@ -457,44 +480,123 @@ struct WindowBin {
 // are completed one by one, lanes over layer 2 (at most four rounds each);
 // an event with more sorts layer 2 into cells too and looks each pair's
 // partners up there, so that its work stays in proportion to its hits.
-// Whole call with layer 2 sorted for every event and now: 100,000 events of
-// 200 hits per layer 0.156 -> 0.126 ms, 1M mixture events (mean 80 per layer)
-// 0.784 -> 0.580 ms; bound by the latency of an event's chain at eight waves
-// per SIMD.
+// 100,000 events of 200 hits per layer, whole call: 0.156 ms with layer 2
+// sorted for every event, 0.122 ms without (1M mixture events, mean 80 per
+// layer: 0.783 and 0.559 ms).
+//
+// The layer-1 cells are kBinCap = 256 equal intervals of [-K, K], K = key_max(M)
+// (rounding is monotone, so every key of a finite hit lies in it; others
+// land in some cell and fail the pair test): one wave-wide maximum gives
+// both the cells and the bounds.  A cell's count and its hits' ranks come
+// from one pass of LDS additions of 4 (bytes), on words that the sorted
+// hits overwrite later.  What bounds it is the vector unit: with three
+// wave-wide reductions, two passes of additions on packed counts and one
+// candidate per step the kernel issued 682 vector instructions per event of
+// 200 hits per layer, 89 of its 122 us; the same call takes 0.103 ms now (1M
+// mixture events 0.559 -> 0.483 ms).
+__device__ __forceinline__ uint32_t bin_cell(float key, float inv) {
+    // saturating and truncating: negative values and NaN give 0; non-decreasing in key
+    uint32_t t;
+    asm("v_cvt_u32_f32 %0, %1" : "=v"(t) : "v"(key * inv + 0.5f * (float)kBinCap));
+    return min(t, (uint32_t)(kBinCap - 1));
+}
+
 template <class B>
 __device__ uint32_t wave_event_binned(const Consts& c, const float* __restrict__ x, const float* __restrict__ y,
                                       int o0, int n0, int o1, int n1, int o2, int n2, BinLds& L) {
-    // The loads of layer 1 and of layer 0's first round in flight at once
-    // (one HBM latency); later layer-0 rounds are loaded one round ahead.
-    // Indices are clamped to the layers (n0, n1, n2 >= 1).
+    // The loads of layer 1 and of layer 0's first four rounds in flight at
+    // once (one HBM latency).  Indices are clamped to the layers (n0, n1, n2
+    // >= 1).
     const int lane = (int)lane_id();
-    LayerRegs h1;
+    LayerRegs h1, h0;
     h1.load(x, y, o1, n1);
-    float xi = x[o0 + min(lane, n0 - 1)], yi = y[o0 + min(lane, n0 - 1)];
-    float M = 0.0f;  // largest layer-1 |x|, |y| (rounds past the layer hold 0 or a layer-1 hit)
-    if constexpr (B::kMag) {
-        uint32_t m = 0u;
+    h0.load(x, y, o0, min(n0, kBinCap));
+    // M: the largest layer-1 |x|, |y| (rounds past the layer hold 0).  A hit
+    // with a coordinate that is not finite passes no test and does not count.
+    uint32_t m = 0u;
 #pragma unroll
-        for (int r = 0; r < kBinRounds; ++r)
-            if (r * kWave < n1) m = max(m, max(abs_bits(h1.x[r]), abs_bits(h1.y[r])));
-        M = wave_max_f(mag_of(m));
-    }
-    const BinBounds bb = B::bounds(c, M);
-    if (lane == 0) L.end2[0] = 0u;  // no pair yet (ordered by the cell build's syncs)
-    const Bins b1 = build_bins<typename B::Key1>(c, h1, n1, L.end1, L.a1, L.b1);
-    for (int i0 = 0; i0 < n0; i0 += kWave) {
-        float xn = 0.0f, yn = 0.0f;
-        if (i0 + kWave < n0) {  // wave-uniform
-            const int in = min(i0 + kWave + lane, n0 - 1);
-            xn = x[o0 + in];
-            yn = y[o0 + in];
+    for (int r = 0; r < kBinRounds; ++r) m = max(m, max(abs_bits(h1.x[r]), abs_bits(h1.y[r])));
+    m = wave_max_u(m);
+    if (m >= 0x7f800000u) {
+        m = 0u;
+#pragma unroll
+        for (int r = 0; r < kBinRounds; ++r) {
+            const uint32_t b = max(abs_bits(h1.x[r]), abs_bits(h1.y[r]));
+            m = max(m, b < 0x7f800000u ? b : 0u);
         }
-        if (i0 + lane < n0) B::pairs_i(c, bb, xi, yi, b1, L);
-        xi = xn;
-        yi = yn;
+        m = wave_max_u(m);
+    }
+    const float M = __builtin_bit_cast(float, m);
+    const BinBounds bb = B::bounds(c, M);
+    const float K = B::key_max(c, M);
+    // any scale >= 0 keeps the cells monotone; the hardware reciprocal is
+    // enough to spread the keys over them
+    const float inv = (K > 0.0f && K < __builtin_inff()) ? __builtin_amdgcn_rcpf(K) * (0.5f * (float)kBinCap) : 0.0f;
+    uint32_t* hist = reinterpret_cast<uint32_t*>(L.a1);
+    static_assert(kBinCap == 4 * kWave, "four cells per lane");
+    reinterpret_cast<uint4*>(hist)[lane] = make_uint4(0u, 0u, 0u, 0u);
+    if (lane == 0) *L.n_pairs() = 0u;
+    wave_lds_sync();
+    uint32_t cell[kBinRounds], rank[kBinRounds];  // rank: 4 bytes per hit of the cell before this one
+#pragma unroll
+    for (int r = 0; r < kBinRounds; ++r) {
+        cell[r] = rank[r] = 0u;
+        if (r * kWave < n1) {
+            cell[r] = bin_cell(B::Key1::key(c, h1.x[r], h1.y[r]), inv);
+            if (r * kWave + lane < n1) rank[r] = atomicAdd(&hist[cell[r]], 4u);
+        }
     }
     wave_lds_sync();
-    const int n_pairs = uniform_i((int)L.end2[0]);
+    {
+        // exclusive scan: starts()[t] the first byte of cell t's hits
+        const uint4 v = reinterpret_cast<const uint4*>(hist)[lane];
+        const uint32_t own = (v.x + v.y) + (v.z + v.w);
+        const uint32_t s0 = (uint32_t)wave_inclusive_sum((int)own) - own;
+        const uint32_t s1 = s0 + v.x, s2 = s1 + v.y, s3 = s2 + v.z;
+        reinterpret_cast<uint2*>(L.ends)[lane] = make_uint2(s0 | (s1 << 16), s2 | (s3 << 16));
+        if (lane == 0) L.starts()[kBinCap] = (uint16_t)(4 * n1);
+    }
+    wave_lds_sync();
+    char* pa = reinterpret_cast<char*>(L.a1);
+    char* pb = reinterpret_cast<char*>(L.b1);
+#pragma unroll
+    for (int r = 0; r < kBinRounds; ++r)
+        if (r * kWave + lane < n1) {
+            const uint32_t at = L.starts()[cell[r]] + rank[r];
+            const float2 p = B::Key1::payload(c, h1.x[r], h1.y[r]);
+            *reinterpret_cast<float*>(pa + at) = p.x;
+            *reinterpret_cast<float*>(pb + at) = p.y;
+        }
+    wave_lds_sync();
+    // Layer-0 hit (xi, yi): its cells' hits, two per step.  The interval's ends
+    // are moved outwards by |centre| 2^-21 and r1 2^-20 + 2^-126, more than the
+    // rounding of the two sums.
+    const float r1 = bb.r1 * 1.00000095367431640625f + 0x1p-126f, pre = bb.bx + bb.by;
+    auto scan = [&](float xi, float yi) {
+        const float2 u = B::side(c, xi, yi);
+        const float mid = B::centre(u), w = __builtin_fabsf(mid) * 0x1p-21f + r1;
+        uint32_t j = L.starts()[bin_cell(mid - w, inv)];
+        const uint32_t end = L.starts()[bin_cell(mid + w, inv) + 1];
+        for (; j < end; j += 8u) {
+            // (the second hit may lie past the cells: it fails the pair test, as
+            // every hit outside the interval does, or is not looked at)
+            const float x0 = *reinterpret_cast<const float*>(pa + j), x1 = *reinterpret_cast<const float*>(pa + j + 4);
+            const float y0 = *reinterpret_cast<const float*>(pb + j), y1 = *reinterpret_cast<const float*>(pb + j + 4);
+            const float2 a0 = B::diff(c, u, x0, y0), a1 = B::diff(c, u, x1, y1);
+            const float s0 = __builtin_fabsf(a0.x) + __builtin_fabsf(a0.y);
+            const float s1 = __builtin_fabsf(a1.x) + __builtin_fabsf(a1.y);
+            if (__builtin_fminf(s0, s1) <= pre) {
+                if (B::pair(bb, a0)) push_pair(L, B::entry(xi, yi, u, x0, y0));
+                if (j + 4u < end && B::pair(bb, a1)) push_pair(L, B::entry(xi, yi, u, x1, y1));
+            }
+        }
+    };
+#pragma unroll
+    for (int r = 0; r < kBinRounds; ++r)
+        if (r * kWave + lane < n0) scan(h0.x[r], h0.y[r]);
+    for (int i = kBinCap + lane; i < n0; i += kWave) scan(x[o0 + i], y[o0 + i]);
+    wave_lds_sync();
+    const int n_pairs = uniform_i((int)*L.n_pairs());
     uint32_t cnt = 0;
     if (n_pairs > 0) {
         LayerRegs h2;
@@ -511,7 +613,10 @@ __device__ uint32_t wave_event_binned(const Consts& c, const float* __restrict__
             }
         } else {
             wave_lds_sync();  // the cells overwrite the list
-            const Bins b2 = build_bins<typename B::Key2>(c, h2, n2, L.end2, L.a2, L.b2);
+            LayerRegs g1;
+            g1.load(x, y, o1, n1);
+            const Bins b1 = build_bins<typename B::Key1>(c, g1, n1, L.end1(), L.a1, L.b1);
+            const Bins b2 = build_bins<typename B::Key2>(c, h2, n2, L.end2(), L.a2, L.b2);
             for (int i0 = 0; i0 < n0; i0 += kWave) {
                 if (i0 + lane < n0) cnt += B::count_i(c, bb, x[o0 + i0 + lane], y[o0 + i0 + lane], b1, b2, L);
                 // decision only: stop once the (capped) result is known

@@ -275,3 +275,42 @@ def test_window_prefilter_layer_positions(gpu, form):  # noqa: F811
               (8e37, 9e37, 1e38), (1e38, 1e-38, 1.0), (1e30, 1e30, 1e30)):
         for w in (0.0, 1e-38, 1e-30, 1.0, 1e30, 3e38):
             assert_parity(gpu, s, "window", form, f"z {z} window {w}", z=z, slope_window=(w, w))
+
+
+# --------------------------------------------------------- binned cells ---
+
+@pytest.mark.parametrize("test", ("msd", "msd_basis", "window"))
+def test_binned_cell_edges(gpu, test):  # noqa: F811
+    """The binned form's cells: layer sizes at its rounds of 64 and its limit
+    of 256 (layer 0 beyond it), tracks through the outermost cells, |y| far
+    larger than |x| and the reverse, all x equal to 0, coordinate scales from
+    subnormal to huge, and one infinite or NaN hit per event."""
+    ns = (1, 2, 63, 64, 65, 128, 129, 192, 193, 255, 256)
+    s = helpers.ragged_sizes_set([(a, b, 9) for a in (1, 64, 65, 255, 256, 257, 600) for b in ns], seed=81)
+    c = assert_parity(gpu, s, test, "binned", "cell sizes")
+    assert (c > 0).all()
+    rng = np.random.default_rng(82)
+    t = helpers.ragged_sizes_set([(30, 40, 20), (100, 120, 70), (7, 250, 5)] * 6, seed=83, spread=150.0)
+    x, y = t.x.copy(), t.y.copy()
+    for e in range(t.n_events):  # a track whose layer-1 hit is the event's outermost in x
+        o = t.offsets[3 * e: 3 * e + 4]
+        sign = 1.0 if e % 2 else -1.0
+        for layer, z in enumerate((400.0, 410.0, 420.0)):
+            x[o[layer]] = np.float32(sign * 0.45 * z)
+            y[o[layer]] = np.float32(0.1 * z)
+    edge = synth.EventSet(t.offsets, x, y, t.n_tracks)
+    c = assert_parity(gpu, edge, test, "binned", "outermost cells")
+    assert (c > 0).all()
+    one = np.float32(1)
+    for fx, fy in ((one, np.float32(2e4)), (np.float32(2e4), one), (np.float32(0), one), (one, np.float32(0)),
+                   (np.float32(1e-43), np.float32(1e-43)), (np.float32(1e-30), one), (np.float32(1e30), np.float32(1e30)),
+                   (np.float32(1e36), np.float32(1e36))):
+        scaled = synth.EventSet(t.offsets, x * fx, y * fy, t.n_tracks)
+        w = (max(float(0.005 * fx), 1e-45), max(float(0.005 * fy), 1e-45))
+        assert_parity(gpu, scaled, test, "binned", f"scales {fx} {fy}", slope_window=w)
+    for bad in (np.inf, -np.inf, np.nan):
+        for plane in (0, 1):
+            v = [x.copy(), y.copy()]
+            for e in range(t.n_events):
+                v[plane][rng.integers(t.offsets[3 * e], t.offsets[3 * e + 3])] = bad
+            assert_parity(gpu, synth.EventSet(t.offsets, v[0], v[1], t.n_tracks), test, "binned", f"{bad} in plane {plane}")
