@@ -50,7 +50,7 @@ constexpr int kScanBlock = 256;     // threads of the scan/compaction kernels
 constexpr int kPersistWaves = 4;    // waves per workgroup, persistent form
 constexpr int kPersistBatch = 4;    // work units taken per atomic
 constexpr int kDefaultTileUnits = 8;  // pair tiles (of 64 pairs) per work unit
-constexpr int kClaimsPerGroup = 8;    // claims per workgroup (pipelined batched form) or per wave (binned)
+constexpr int kClaimsPerGroup = 8;    // claims per workgroup, pipelined batched form
 constexpr double kRuleFill = 0.85;    // built-in rule: hits per block over the LDS capacity
 constexpr int kZHits = 2048;          // per-hit z: hits and waves of a block,
 constexpr int kZWaves = 4;
@@ -370,12 +370,18 @@ __global__ __launch_bounds__(kScanBlock) void k_finalize(int n_events, Consts c,
 
 constexpr int kBinWaves = 4;     // waves (one event each) per workgroup
 constexpr int kBinResident = 8;  // binned workgroups per CU (LDS bound)
+constexpr int kBinSlices = 64;   // block stealing: slices of the events, each with its own counter,
+constexpr int kBinStride = 64;   // this many words apart
 
-// One wave per event.  Non-persistent when block_counter == nullptr:
-// workgroup b takes events [4 b, 4 b + 4), one per wave.  Otherwise every
-// wave on its own takes runs of `chunk` consecutive events from
-// *block_counter (zero at launch; one atomic per run) until none is left:
-// no barrier, and no LDS beyond the waves' cells (8 workgroups fit on a CU).
+// A wave counts runs of `chunk` consecutive events.  Non-persistent when
+// block_counter == nullptr: wave g takes run g.  Otherwise the events are cut
+// into kBinSlices slices, workgroup b working on slice b % kBinSlices: a wave
+// takes its first run by its own number and the others from the slice's
+// counter (zero at launch; one atomic per run), until none is left: no
+// barrier, and no LDS beyond the waves' cells (8 workgroups fit on a CU).
+// Atomics on one 256-byte line pass one by one, some 5 ns each (1M mixture
+// events with all claims on one word: 0.91 ms, of which they were most), so
+// each slice's counter has a line of its own.
 // Events with more than kBinCap hits in layer 1 or 2 take the pair-pruned
 // path from HBM.  The register budget is held to kBinResident waves per
 // SIMD, the occupancy its LDS allows (one wave per SIMD per workgroup).
@@ -405,19 +411,27 @@ __global__ __launch_bounds__(kBinWaves * kWave) __attribute__((amdgpu_waves_per_
         }
         if (lane_id() == 0) write_result(e, cnt, c, counts, accept, status);
     };
-    if (!block_counter) {
+    if (!block_counter && chunk == 1) {
+        // (its own copy: one event without the loop around it is 5 to 10 %
+        // faster than the loop taken once)
         const int64_t e = (int64_t)blockIdx.x * kBinWaves + w;
         if (e < n_events) one_event((int)e);
         return;
     }
+    // The workgroup's slice; every branch depends on wave-uniform values only.
+    const int slices = block_counter ? min(kBinSlices, (int)gridDim.x) : 1, slice = (int)(blockIdx.x % (unsigned)slices);
+    const int64_t begin = (int64_t)n_events * slice / slices, end = (int64_t)n_events * (slice + 1) / slices;
+    const unsigned groups = (gridDim.x - (unsigned)slice + (unsigned)slices - 1u) / (unsigned)slices;  // of the slice
+    int64_t turn = (int64_t)(blockIdx.x / (unsigned)slices) * kBinWaves + w;
     for (;;) {
-        // every branch below depends on wave-uniform values only
-        unsigned claim = 0u;
-        if (lane_id() == 0) claim = atomicAdd(block_counter, 1u);
-        const int64_t first = (int64_t)(unsigned)uniform_i((int)claim) * chunk;
-        if (first >= n_events) break;
-        const int last = (int)min(first + chunk, (int64_t)n_events);
+        const int64_t first = begin + turn * chunk;
+        if (first >= end) break;
+        const int last = (int)min(first + chunk, end);
         for (int e = (int)first; e < last; ++e) one_event(e);
+        if (!block_counter) break;
+        unsigned claim = 0u;
+        if (lane_id() == 0) claim = atomicAdd(&block_counter[slice * kBinStride], 1u);
+        turn = (int64_t)groups * kBinWaves + (int64_t)(unsigned)uniform_i((int)claim);
     }
 }
 
@@ -663,8 +677,8 @@ Layout layout(int n_events, uint32_t flags) {
         at += align256(sizeof(int32_t) * (size_t)(L.compact_blocks + 1));
     }
     if ((flags & TRIG_EXEC_PERSISTENT) && (flags & (TRIG_EXEC_PRUNED | TRIG_EXEC_BINNED))) {
-        L.counter_off = at;  // block counter only
-        at += 256;
+        L.counter_off = at;  // block counters only
+        at += 4 * kBinSlices * kBinStride;
     } else if (flags & TRIG_EXEC_PERSISTENT) {
         L.unit_blocks = (int)std::max<int64_t>(1, cdiv(n_events, kScanBlock));
         L.counter_off = at;
@@ -748,7 +762,7 @@ int launch_persistent(const trig_events_csr* ev, const trig_hits* h, const Const
     return check_launch("k_finalize");
 }
 
-__global__ void k_zero_u32(unsigned* p) { *p = 0u; }
+__global__ void k_zero_u32(unsigned* p, int stride) { p[threadIdx.x * stride] = 0u; }
 
 // Shape of the batched form: LDS hit capacity (hb), waves per workgroup (nw)
 // and events per block (eb).  Given values are used as they are; the
@@ -833,7 +847,7 @@ int launch_block(const trig_events_csr* ev, const trig_hits* h, const trig_param
     unsigned grid = (unsigned)n_blocks;
     if (pipelined) {
         counter = reinterpret_cast<unsigned*>(ws + L.counter_off);
-        hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s, counter);
+        hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s, counter, 1);
         if (int r = check_launch("k_zero_u32")) return r;
         grid = (unsigned)std::min<int64_t>(n_blocks, (int64_t)device_cus() * resident_per_cu(kern, bs.nw * kWave));
     }
@@ -852,18 +866,23 @@ template <class B>
 int launch_binned(const trig_events_csr* ev, const trig_hits* h, const trig_params* p, const Consts& c,
                   const Layout& L, char* ws, int32_t* counts, uint8_t* accept, hipStream_t s) {
     const int n = ev->n_events;
-    const int64_t n_blocks = cdiv(n, kBinWaves);
+    // Events per run: enough for kBinRuns runs per wave of a full GPU, at most
+    // kBinMaxRun.  A workgroup of one event per wave costs 0.45 us more than
+    // its events (1M mixture events: 0.478 ms with runs of one, 0.404 of eight);
+    // with few runs per wave the last ones leave waves idle (100,000 events of
+    // 200 hits per layer: 99.7, 97.6 and 107.6 us with runs of one, two and eight).
+    constexpr int kBinRuns = 6, kBinMaxRun = 8;
+    const int64_t waves = (int64_t)device_cus() * kBinResident * kBinWaves;
+    const int chunk = (int)std::min<int64_t>(kBinMaxRun, std::max<int64_t>(1, n / (waves * kBinRuns)));
+    const int64_t n_blocks = cdiv(cdiv(n, chunk), kBinWaves);
     unsigned* counter = nullptr;
     unsigned grid = (unsigned)n_blocks;
     if (p->flags & TRIG_EXEC_PERSISTENT) {
         counter = reinterpret_cast<unsigned*>(ws + L.counter_off);
-        hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s, counter);
+        hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(kBinSlices), 0, s, counter, kBinStride);
         if (int r = check_launch("k_zero_u32")) return r;
         grid = (unsigned)std::min<int64_t>(n_blocks, (int64_t)device_cus() * kBinResident);
     }
-    // Persistent: runs of events per claim, about kClaimsPerGroup claims per wave.
-    const int chunk =
-        counter ? (int)std::max<int64_t>(1, (int64_t)n / ((int64_t)grid * kBinWaves * kClaimsPerGroup)) : 1;
     if (mark_start(s)) return fail(TRIG_EHIP, "hipEventRecord(start)");
     hipLaunchKernelGGL(k_binned<B>, dim3(grid), dim3(kBinWaves * kWave), 0, s, ev->layer_offsets, n, h->x, h->y, c,
                        counter, chunk, counts, accept, p->out_status);

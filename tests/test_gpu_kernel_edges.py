@@ -314,3 +314,26 @@ def test_binned_cell_edges(gpu, test):  # noqa: F811
             for e in range(t.n_events):
                 v[plane][rng.integers(t.offsets[3 * e], t.offsets[3 * e + 3])] = bad
             assert_parity(gpu, synth.EventSet(t.offsets, v[0], v[1], t.n_tracks), test, "binned", f"{bad} in plane {plane}")
+
+
+@pytest.mark.parametrize("n_events", (1, 5, 255, 98303, 98304, 98311, 400003))
+def test_binned_runs_and_slices(gpu, n_events):  # noqa: F811
+    """The binned form's runs of one, two and eight events per wave with a
+    remainder, and its stealing form's 64 slices (fewer workgroups than
+    slices, slices of unequal size), with malformed events in between."""
+    rng = np.random.default_rng(n_events)
+    counts = rng.integers(0, 4, 3 * n_events)
+    off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    m = rng.uniform(-0.3, 0.3, (n_events, 2))
+    ev = np.repeat(np.arange(n_events), counts.reshape(-1, 3).sum(1))
+    z = np.repeat(np.tile([400.0, 410.0, 420.0], n_events), counts)
+    shift = np.where(rng.random(len(ev)) < 0.7, 0.0, 25.0)  # most hits on the event's track
+    x, y = ((m[ev, k] * z + shift).astype(np.float32) for k in range(2))
+    bad = off.copy()
+    for e in rng.integers(0, n_events, max(1, n_events // 500)):
+        bad[3 * e + 1] = -1
+    tracks = np.zeros(n_events, np.int8)
+    for form in ("binned", "persistent_binned"):
+        for o in (off, bad):
+            c = assert_parity(gpu, synth.EventSet(o, x, y, tracks), "msd", form, "runs")
+        assert n_events < 100 or c.max() > 8
