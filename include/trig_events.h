@@ -55,10 +55,12 @@ size_t trig_build_events_workspace_bytes(int64_t n_hits);
  *   out_n_events  int64[1]: E (device; read it after the stream reaches the call).
  *   out_status    optional uint32: sticky bits, OR-ed in (above).
  *   workspace     trig_build_events_workspace_bytes(n_hits) bytes, 256-byte aligned.
- * Kernels: per 64 hits one ballot of the event starts (time differences of
- * neighbouring lanes) into a bit mask in the workspace and per-wave counts,
- * an exclusive scan of the workgroup counts, then each wave ranks its masks'
- * set bits and writes their hit indices.  The stream's times are read once.
+ * Kernels: per 128 hits two ballots of the event starts (two hits per lane,
+ * their predecessors from the lane and the lane below) into bit masks in the
+ * workspace and per-wave counts, an exclusive scan of the workgroup counts
+ * (streams above 16,777,216 hits; below, each wave sums those it needs), then
+ * each wave ranks its masks' set bits and writes their hit indices.  The
+ * stream's times are read once.
  * Errors (returned before anything is enqueued): TRIG_EINVAL for a NULL
  * required pointer, n_hits outside [0, 2^40], gap < 0, out_capacity < 1, or a
  * workspace that is too small or not 256-byte aligned; TRIG_EHIP if a launch

@@ -384,26 +384,6 @@ struct ScatterRec {
     uint32_t pad;
 };
 
-// Sum of partials[0, n) by a whole wave, the loads of a batch in flight
-// together.
-__device__ __forceinline__ int64_t wave_prefix(const int64_t* __restrict__ partials, int n) {
-    const int lane = (int)trig::lane_id();
-    int64_t sum = 0;
-    for (int i0 = 0; i0 < n; i0 += 8 * trig::kWave) {
-        int64_t v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int i = i0 + u * trig::kWave + lane;
-            v[u] = i < n ? partials[i] : 0;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) sum += v[u];
-    }
-#pragma unroll
-    for (int d = 1; d < trig::kWave; d <<= 1) sum += __shfl_xor(sum, d, trig::kWave);
-    return sum;
-}
-
 // Small batches (one event per wave, at most kSelfPrefix workgroups): each
 // wave sums the totals of the workgroups before its own (at most 32 KB from
 // L2) instead of a scan kernel between the two, which with its gap takes
@@ -444,7 +424,7 @@ __global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(
     const u32x4r first = wrec[min(lane, wave_windows<PER>() - 1)];
     const uint32_t first_entry = PER < kMaxPer ? went[lane] : 0u;
     constexpr bool self = PER == 1;
-    const int64_t wg_base = self ? wave_prefix(partials, (int)blockIdx.x) : partials[blockIdx.x];
+    const int64_t wg_base = self ? wave_prefix_i64(partials, (int)blockIdx.x) : partials[blockIdx.x];
     if ((int)blockIdx.x == n_blocks - 1 && threadIdx.x == 0) {
         const int64_t total = self ? wg_base + partials[blockIdx.x] : partials[n_blocks];
         if (total > cap && status) atomicOr(status, TRIG_FILTER_CAPACITY);

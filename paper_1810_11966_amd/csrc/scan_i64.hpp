@@ -32,6 +32,23 @@ __device__ __forceinline__ int64_t scan_wave_incl(int64_t v) {
     return v;
 }
 
+// Sum of partials[0, n) by a whole wave, the loads of a batch in flight
+// together (the same value on every lane).
+__device__ __forceinline__ int64_t wave_prefix_i64(const int64_t* __restrict__ partials, int n) {
+    const int lane = (int)(threadIdx.x & 63);
+    int64_t sum = 0;
+    for (int i0 = 0; i0 < n; i0 += kScanUnroll * 64) {
+        int64_t v[kScanUnroll];
+#pragma unroll
+        for (int u = 0; u < kScanUnroll; ++u) v[u] = i0 + u * 64 + lane < n ? partials[i0 + u * 64 + lane] : 0;
+#pragma unroll
+        for (int u = 0; u < kScanUnroll; ++u) sum += v[u];
+    }
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) sum += __shfl_xor(sum, d, 64);
+    return sum;
+}
+
 __global__ __launch_bounds__(kScanThreads) void k_scan_i64(int64_t* partials, int64_t n) {
     __shared__ int64_t wave_total[kScanWaves];
     const int t = (int)threadIdx.x, w = t / 64;

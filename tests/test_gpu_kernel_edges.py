@@ -4,6 +4,7 @@ touches the GPU."""
 import numpy as np
 import pytest
 
+from oracle import reference as R
 from paper_1810_11966_amd import synth
 from tests import helpers
 from tests.test_gpu_parity import assert_parity, gpu  # noqa: F401 (fixture)
@@ -337,3 +338,49 @@ def test_binned_runs_and_slices(gpu, n_events):  # noqa: F811
         for o in (off, bad):
             c = assert_parity(gpu, synth.EventSet(o, x, y, tracks), "msd", form, "runs")
         assert n_events < 100 or c.max() > 8
+
+
+# -------------------------------------------------------- event building ---
+
+@pytest.mark.parametrize("off", (0, 1))
+def test_event_building_edges(gpu, off):  # noqa: F811
+    """Stream sizes around a lane's two hits, the rounds of 128, the batches
+    of 256, the wave's 4,096 and the workgroup's 16,384, on 16-byte aligned
+    times and on times 8 bytes further; every hit an event, none, a start or a
+    time reversal on each side of those edges; capacities up to all offsets."""
+    from paper_1810_11966_amd import events as EB
+    for n in (1, 2, 3, 63, 64, 127, 128, 129, 255, 256, 257, 4095, 4096, 4097, 16383, 16384, 16385, 50001):
+        edges = [e for e in (1, 2, 3, 127, 128, 129, 255, 256, 257, 4095, 4096, 4097, 16383, 16384, 16385) if e < n]
+        steps = [np.full(n, 6), np.zeros(n, np.int64), np.where(np.arange(n) % 3 == 2, 6, 5)]
+        for sign in (6, -1):
+            step = np.zeros(n, np.int64)
+            step[edges] = sign
+            steps.append(step)
+        for k, step in enumerate(steps):
+            t = -(2 ** 40) + np.cumsum(step).astype(np.int64)
+            want, st = R.build_events_numpy(t, 5)
+            d = gpu.from_numpy(np.concatenate([np.zeros(off, np.int64), t])).cuda()[off:]
+            for cap in sorted({len(want), max(1, len(want) - 1), 1}):
+                print(f"[events] hits={n} offset={off} stream {k} capacity {cap}", flush=True)
+                r = EB.build_events(d, 5, capacity=cap)
+                gpu.cuda.synchronize()
+                assert int(r.n_events.cpu()[0]) == len(want) - 1
+                assert np.array_equal(r.offsets.cpu().numpy(), want[:cap])
+                assert int(r.status.cpu()[0]) == (st | (4 if cap < len(want) else 0))
+
+
+@pytest.mark.parametrize("off", (0, 1))
+@pytest.mark.parametrize("n", (1024 * 16384, 1024 * 16384 + 1, 48 << 20, (48 << 20) + 1))
+def test_event_building_long_streams(gpu, n, off):  # noqa: F811
+    """Both sides of the largest stream whose waves sum the totals themselves
+    (1,024 workgroups) and of the largest one read with cached loads."""
+    from paper_1810_11966_amd import events as EB
+    rng = np.random.default_rng(5)
+    t = np.cumsum(rng.choice(np.array([0, 1, 2, 9], np.int64), n))
+    print(f"[events] hits={n}", flush=True)
+    want, st = R.build_events_numpy(t, 3)
+    d = gpu.from_numpy(np.concatenate([np.zeros(off, np.int64), t])).cuda()[off:]
+    r = EB.build_events(d, 3)
+    gpu.cuda.synchronize()
+    assert int(r.n_events.cpu()[0]) == len(want) - 1 and int(r.status.cpu()[0]) == st
+    assert np.array_equal(r.offsets.cpu().numpy()[:len(want)], want)
