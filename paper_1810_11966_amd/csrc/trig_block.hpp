@@ -24,13 +24,16 @@
 // from the line through the vertex and hit i, in cm) are completed against
 // every layer-2 hit with the full binary32 test, lanes over k.
 //
-// Lane layout of the pair scan: lane L holds layer-1 hit j and its constant
+// Staged events first go through the direct scan (below): a prefilter over
+// all pairs straight from the staged coordinates, two lane-layer hits per
+// lane and one vote per event.  The events it sends on, events too large for
+// it and events read from HBM are scanned with the exact partials.
+//
+// Lane layout of that exact scan: lane L holds layer-1 hit j and its constant
 // part of a; for n1 <= 32 the 64 lanes hold R = floor(64/n1) copies of the
 // layer-1 hits, copy g scanning layer-0 hits i = g, g+R, g+2R, ... so that
 // few lanes idle.  The layer-0 part of a (or the layer-0 slope) is computed
-// once per hit into a per-wave LDS buffer and read with a broadcast.  An
-// event that fits one pass takes layer 0 into the lanes instead when that
-// needs fewer buffer steps (the pair tests are symmetric in the two layers).
+// once per hit into a per-wave LDS buffer and read with a broadcast.
 #pragma once
 
 #include "trig_device.hpp"
@@ -61,12 +64,11 @@ __device__ __forceinline__ int div_small(int a, int n) {
 __device__ __forceinline__ uint32_t recip16(int n) { return (65536u + (uint32_t)n - 1u) / (uint32_t)n; }
 __device__ __forceinline__ int div_lane(int lane, uint32_t r) { return (int)(__umul24((unsigned)lane, r) >> 16); }
 
-// Hits of the current sub-block in LDS (structure of arrays), indexed
-// relative to the staged range's 4-aligned start.
+// Hits of the current sub-block in LDS as (x, y) pairs (one read and one
+// address for both), indexed relative to the staged range's 4-aligned start.
 struct LdsHits {
-    const float* xs;
-    const float* ys;
-    __device__ __forceinline__ float2 at(int h) const { return make_float2(xs[h], ys[h]); }
+    const float2* h;
+    __device__ __forceinline__ float2 at(int i) const { return h[i]; }
 };
 // Hits read straight from HBM (events too large for LDS, irregular blocks).
 struct GlobalHits {
@@ -114,7 +116,6 @@ struct SlopeHits {
 // TRIG_TEST_MSD_BASIS.
 struct MsdBasisPrune {
     static constexpr bool kMag = false;  // bounds do not depend on M
-    static constexpr bool kApprox = false;  // no cheaper approximation of the partials
     static constexpr bool kEventBounds = false;
     static constexpr bool kZ = false;
     __device__ static __forceinline__ PairBounds bounds(const Consts& c, float) {
@@ -144,8 +145,10 @@ struct MsdBasisPrune {
     // against 4) and lets about twice as many pairs through, 0.7 % of the
     // events at 30 hits per layer.
     __device__ static __forceinline__ float score(float2 p, float2 q) {
-        const float ax = p.x + q.x;
-        const float ay = p.y + q.y;
+        return fold(p.x + q.x, p.y + q.y);
+    }
+    // The score of a pair's combined coordinates (ax, ay).
+    __device__ static __forceinline__ float fold(float ax, float ay) {
         return __builtin_fabsf(ax) + __builtin_fabsf(ay);
     }
     // Passing triplets of the surviving pair (hi, hj) over layer-2 hits
@@ -202,7 +205,6 @@ struct MsdBasisPrune {
 // written out.
 struct MsdFitPrune {
     static constexpr bool kMag = true;  // bounds grow with M >= |c_j|
-    static constexpr bool kApprox = false;
     static constexpr bool kEventBounds = false;
     static constexpr bool kZ = false;
     __device__ static __forceinline__ PairBounds bounds(const Consts& c, float M) {
@@ -223,6 +225,7 @@ struct MsdFitPrune {
         return MsdBasisPrune::pair_mask(b, p, q);
     }
     __device__ static __forceinline__ float score(float2 p, float2 q) { return MsdBasisPrune::score(p, q); }
+    __device__ static __forceinline__ float fold(float ax, float ay) { return MsdBasisPrune::fold(ax, ay); }
     template <class H>
     __device__ static uint32_t complete(const Consts& c, const H& hits, int hi, int hj, int o2, int n2) {
         const float2 ci = hits.at(hi), cj = hits.at(hj);
@@ -251,22 +254,13 @@ struct MsdFitPrune {
     }
 };
 
-// TRIG_TEST_SLOPE_WINDOW.  The fast path's prefilter compares approximate
-// slopes c fl(1 / z) (one product, where a binary32 division takes some 40
-// vector cycles): with M >= |c| they are within 3 2^-24 M / z of the rounded
-// quotients, so a pair's score rises by less than 2^-20 M max(1 / z0, 1 / z1),
-// which `pre` adds (win_slack0 = +inf where a 1 / z is no normal number).
+// TRIG_TEST_SLOPE_WINDOW.
 struct WindowPrune {
-    static constexpr bool kMag = true;  // of `pre` only
-    static constexpr bool kApprox = true;
+    static constexpr bool kMag = false;
     static constexpr bool kEventBounds = false;
     static constexpr bool kZ = false;
-    __device__ static __forceinline__ PairBounds bounds(const Consts& c, float M) {
-        return PairBounds{c.win_x, c.win_y, (c.pre_win + c.win_slack0) + c.win_slack * M};
-    }
-    __device__ static __forceinline__ float2 layer_approx(const Consts& c, float2 h, int l) {
-        const float r = select_uniform(l, c.win_r1, c.win_r0);
-        return make_float2(h.x * r, h.y * r);
+    __device__ static __forceinline__ PairBounds bounds(const Consts& c, float) {
+        return PairBounds{c.win_x, c.win_y, c.pre_win};
     }
     __device__ static __forceinline__ float2 layer0(const Consts& c, float2 h) {
         return make_float2(h.x / c.z0, h.y / c.z0);
@@ -285,7 +279,10 @@ struct WindowPrune {
     // (the windows are wide enough that the sum's extra candidates, one event
     // in ten more at 30 hits per layer, would cost more than it saves).
     __device__ static __forceinline__ float score(float2 p, float2 q) {
-        return __builtin_fmaxf(__builtin_fabsf(q.x - p.x), __builtin_fabsf(q.y - p.y));
+        return fold(q.x - p.x, q.y - p.y);
+    }
+    __device__ static __forceinline__ float fold(float dx, float dy) {
+        return __builtin_fmaxf(__builtin_fabsf(dx), __builtin_fabsf(dy));
     }
     template <class H>
     __device__ static uint32_t complete(const Consts& c, const H& hits, int hi, int /*hj*/, int o2, int n2) {
@@ -326,7 +323,6 @@ struct WindowPrune {
 // layers 0 and 1; survivors completed with the per-hit-z fit.
 struct MsdZPrune {
     static constexpr bool kMag = false;
-    static constexpr bool kApprox = false;
     static constexpr bool kEventBounds = true;
     static constexpr bool kZ = true;  // reads hits through SlopeHits
     __device__ static __forceinline__ float2 layer0(const Consts&, float2 s) { return s; }
@@ -363,7 +359,10 @@ struct MsdZPrune {
         return lanes(__builtin_fabsf(q.x - p.x) <= b.bx) & lanes(__builtin_fabsf(q.y - p.y) <= b.by);
     }
     __device__ static __forceinline__ float score(float2 p, float2 q) {
-        return __builtin_fabsf(q.x - p.x) + __builtin_fabsf(q.y - p.y);
+        return fold(q.x - p.x, q.y - p.y);
+    }
+    __device__ static __forceinline__ float fold(float dx, float dy) {
+        return __builtin_fabsf(dx) + __builtin_fabsf(dy);
     }
     __device__ static __forceinline__ uint64_t triplet_mask(const Consts& c, const SlopeHits& h, int hi, int hj,
                                                           int hk, bool valid) {
@@ -397,7 +396,6 @@ struct MsdZPrune {
 // layer-1 window is exact, as in WindowPrune.
 struct WindowZPrune {
     static constexpr bool kMag = false;
-    static constexpr bool kApprox = false;
     static constexpr bool kEventBounds = false;
     static constexpr bool kZ = true;  // reads hits through SlopeHits
     __device__ static __forceinline__ PairBounds bounds(const Consts& c, float) {
@@ -411,6 +409,7 @@ struct WindowZPrune {
         return WindowPrune::pair_mask(b, p, q);
     }
     __device__ static __forceinline__ float score(float2 p, float2 q) { return WindowPrune::score(p, q); }
+    __device__ static __forceinline__ float fold(float dx, float dy) { return WindowPrune::fold(dx, dy); }
     template <class H>
     __device__ static uint64_t complete_mask(const Consts& c, const H& hits, int hi, int /*hj*/, int o2, int n2,
                                              int k0) {
@@ -435,9 +434,8 @@ __device__ __forceinline__ PairBounds event_bounds(const Consts& c, const H& hit
     if constexpr (P::kEventBounds) {
         return P::event_bounds(c, hits, o0, n0, o1, n1);
     } else {
-        // (kApprox: the callers compare the exact partials)
         float M = 0.0f;
-        if constexpr (P::kMag && !P::kApprox) M = layer_mag(hits, o1, n1);
+        if constexpr (P::kMag) M = layer_mag(hits, o1, n1);
         return P::bounds(c, M);
     }
 }
@@ -634,7 +632,7 @@ __device__ uint32_t wave_event_pruned(const Consts& c, const PairBounds& pb, con
     return cnt;
 }
 
-// Fast path (one lane pass, one buffer fill of at most kPBuf = kWave
+// Fast path of events read from HBM (one lane pass, one buffer fill of at most kPBuf = kWave
 // entries; R, T and the orientation from event_layout).  One of layers 0
 // and 1 goes to the lanes (layer l = S ? 0 : 1, offset oL, nL hits), the
 // other to the LDS buffer (offset oB, nB hits):
@@ -642,8 +640,8 @@ __device__ uint32_t wave_event_pruned(const Consts& c, const PairBounds& pb, con
 // layer's partials go to px/py (NaN past nB).  Both pair tests depend on the
 // two partials symmetrically (a sum, or the absolute value of a difference,
 // which binary32 gives the same either way round), so the orientation does
-// not change a count.  APPROX: the policy's approximate partials.
-template <class P, bool APPROX, class H>
+// not change a count.
+template <class P, class H>
 __device__ __forceinline__ void fast_setup(const Consts& c, const H& hits, int oB, int nB, int oL, int nL, int S,
                                            int R, int T, uint32_t r, float* __restrict__ px, float* __restrict__ py,
                                            int& g, int& j, float2& q) {
@@ -658,15 +656,9 @@ __device__ __forceinline__ void fast_setup(const Consts& c, const H& hits, int o
     // selects NaN where it has none; the whole kPBuf-entry buffer (>= T R
     // entries) is written.
     const float nan = __builtin_nanf("");
-    auto layer = [&](float2 h, int l) {
-        if constexpr (APPROX)
-            return P::layer_approx(c, h, l);
-        else
-            return P::layer(c, h, l);
-    };
-    const float2 hq = layer(hits.at(oL + min(j, nL - 1)), S ? 0 : 1);
+    const float2 hq = P::layer(c, hits.at(oL + min(j, nL - 1)), S ? 0 : 1);
     q = make_float2(jv ? hq.x : nan, jv ? hq.y : nan);
-    const float2 v = layer(hits.at(oB + min(lane, nB - 1)), S ? 1 : 0);
+    const float2 v = P::layer(c, hits.at(oB + min(lane, nB - 1)), S ? 1 : 0);
     px[lane] = lane < nB ? v.x : nan;
     py[lane] = lane < nB ? v.y : nan;
 }
@@ -735,17 +727,11 @@ __device__ uint32_t wave_event_fast(const Consts& c, const PairBounds& pb, const
     const int oL = S ? o0 : o1, nL = S ? n0 : n1;
     int g, j;
     float2 q;
-    fast_setup<P, P::kApprox>(c, hits, oB, nB, oL, nL, S, R, T, r, px, py, g, j, q);
+    fast_setup<P>(c, hits, oB, nB, oL, nL, S, R, T, r, px, py, g, j, q);
     wave_lds_sync();
     uint32_t cnt = 0;
-    if (wave_any(fast_score<P>(px, py, T, g, q) <= pb.pre)) {
-        if constexpr (P::kApprox) {
-            wave_lds_sync();
-            fast_setup<P, false>(c, hits, oB, nB, oL, nL, S, R, T, r, px, py, g, j, q);
-            wave_lds_sync();
-        }
+    if (wave_any(fast_score<P>(px, py, T, g, q) <= pb.pre))
         cnt = fast_exact<P>(c, pb, hits, oB, oL, S, o2, n2, T, g, j, q, px, py);
-    }
     wave_lds_sync();
     return cnt;
 }
@@ -773,6 +759,156 @@ __device__ __forceinline__ void event_layout(int n0, int n1, int& R, int& T, int
         T = T1;
         S = 1;
     }
+}
+
+// Pair prefilter of an event staged in LDS ("direct scan"): the pairs' scores
+// from the staged coordinates themselves, with no buffer of partials.  Scaled
+// so that one layer needs no product: layer l = S ? 0 : 1 goes to the lanes,
+// times k, the other is read as it is, and
+//     s = fl(c_B + fl(k c_L)),   k = U_L / U_B (MSD) or -z_B / z_L (window).
+// Lane L holds copy g = L / w of two lane-layer hits, j and j + w with w =
+// ceil(nL / 2): each LDS read of the other layer serves two pairs (the reads
+// of one hit per lane took 75 of the 127 cycles per event the LDS has at 30
+// hits per layer).  Copy g scans the T = ceil(nB / R) hits from g T on, the
+// last copies the last T: pairs may be scored twice, but only the event's own
+// (a neighbouring layer's hits are no substitute past the end: a lane-layer
+// hit scored against itself is always close).  A score that reaches the
+// bound sends the event to the exact pass, which takes each pair once.
+//
+// Bound by vector instructions, the LDS and the staging's latency together.
+// Against one hit per lane, partials in a buffer and masked lanes, with the
+// staged block's bound on |x|, |y| cheaper by 80 cycles per wave (mag2), the
+// whole call takes 198 for 211 us on a million events of 30 hits per layer,
+// 264 for 288 with per-hit z and 10.2 for 11.5 on 1000 events of 15; two hits
+// per lane without the rest gave 2 %.
+//
+// pre: with M >= every staged |x|, |y| and u = 2^-24, a pair that passes the
+// exact pair test has, in the MSD tests' units,
+//     |U0 c0 + U1 c1| <= b (1 + 2u) + 1.01 u (|U0| + |U1|) M + 2^-148
+// in a plane with bound b, and s lies within (3.1 u |k| + 1.1 u) M + 2^-148 of
+// (U0 c0 + U1 c1) / U_B; the window's rounded quotients give the same form
+// with U_l = 1 / z_l.  So s <= (b / |U_B|) (1 + 2u) + 4.3 u (1 + |k|) M + 2^-80
+// while 2^-60 <= z0, z1 and |k| in [2^-60, 2^60]; the constants hold two
+// planes' sum with 4 times that slack, and +inf outside those ranges.
+// A block's factors and bounds for both orientations, lane 2 b + S of one
+// register (b: the bound), read by v_readlane: as scalars they would be
+// spilled over the event loop, eight at a time.
+__device__ __forceinline__ float direct_consts(const Consts& c, const PairBounds& pb, float M) {
+    const int lane = (int)lane_id();
+    const float p0 = (pb.pre * c.dir_scale[0] + c.dir_slack[0] * M) + c.dir_slack0;
+    const float p1 = (pb.pre * c.dir_scale[1] + c.dir_slack[1] * M) + c.dir_slack0;
+    return lane < 2 ? (lane ? c.dir_k[1] : c.dir_k[0]) : (lane & 1 ? p1 : p0);
+}
+__device__ __forceinline__ float direct_const(float d, int lane) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, d), lane));
+}
+
+constexpr int kDirectCopies = 16;   // R at most
+constexpr int kDirectSteps = 1023;  // T at most (dr holds it above direct_recip's 17 bits)
+
+// R copies of the lane layer (nL hits, w = (nL + 1) / 2 lanes each) and T
+// steps over the other layer's nB hits; T = 0: too large for one lane pass.
+__device__ __forceinline__ void direct_side(int nB, int nL, int& R, int& T) {
+    const int w = (nL + 1) >> 1;
+    R = w <= kWave / 2 ? min(div_small(kWave, w), kDirectCopies) : 1;
+    T = (w <= kWave && nB <= kDirectSteps) ? div_small(nB + R - 1, R) : 0;
+}
+// The orientation with fewer steps (S = 0: layer 1 in the lanes).
+__device__ __forceinline__ void direct_layout(int n0, int n1, int& R, int& T, int& S) {
+    int R1, T1;
+    direct_side(n0, n1, R, T);
+    direct_side(n1, n0, R1, T1);
+    S = 0;
+    if (T1 > 0 && (T == 0 || T1 < T)) {
+        R = R1;
+        T = T1;
+        S = 1;
+    }
+}
+// For floor(lane / w), 1 <= w <= 64, as (lane r) >> 16: any r with r w = 2^16 +
+// d, 0 <= d < 1040 gives it (lane d < 2^16, see recip16); here w - 1 < d < 2 w + 1.
+__device__ __forceinline__ uint32_t direct_recip(int w) {
+    return (uint32_t)(65536.0f * __builtin_amdgcn_rcpf((float)w)) + 2u;
+}
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));  // a native vector (float4 copies are memcpys)
+typedef float f32x4_8 __attribute__((ext_vector_type(4), aligned(8)));  // two hits, anywhere in a layer
+
+// Per lane, the smallest score over the lane's pairs.  st: the staged hits;
+// oB, oL: local indices; the other arguments wave-uniform.
+template <class P>
+__device__ __forceinline__ float direct_score(const float2* st, int oB, int nB, int oL, int nL, int T, uint32_t r,
+                                              float k) {
+    const int lane = (int)lane_id();
+    const int w = (nL + 1) >> 1;
+    const int g = div_lane(lane, r);
+    const int j = lane - g * w, j2 = min(j + w, nL - 1);
+    const float2 h = st[oL + j], h2 = st[oL + j2];
+    const float qx = k * h.x, qy = k * h.y, rx = k * h2.x, ry = k * h2.y;
+    const float2* b = st + oB + min((int)__umul24((unsigned)g, (unsigned)T), nB - T);
+    float m = __builtin_nanf("");  // fmin drops NaN scores; all NaN leaves NaN, which fails every bound
+    auto pair = [&](float vx, float vy) {
+        m = __builtin_fminf(__builtin_fminf(m, P::fold(vx + qx, vy + qy)), P::fold(vx + rx, vy + ry));
+    };
+    int t = 0;
+    for (; t + 4 <= T; t += 4) {
+        const f32x4 u = *reinterpret_cast<const f32x4_8*>(b + t), v = *reinterpret_cast<const f32x4_8*>(b + t + 2);
+        pair(u.x, u.y);
+        pair(u.z, u.w);
+        pair(v.x, v.y);
+        pair(v.z, v.w);
+    }
+    if (T & 2) {
+        const f32x4 u = *reinterpret_cast<const f32x4_8*>(b + t);
+        pair(u.x, u.y);
+        pair(u.z, u.w);
+        t += 2;
+    }
+    if (T & 1) pair(b[t].x, b[t].y);
+    return m;
+}
+
+// Passing triplets of a staged event some of whose scores reached the bound:
+// the same lanes and steps with the exact partials (NaN where there is no
+// hit), the surviving pairs completed against layer 2 (layer-0 hit first).
+// Needs R T <= kPBuf.
+template <class P, class H>
+__device__ uint32_t direct_exact(const Consts& c, const PairBounds& pb, const H& hits, int oB, int nB, int oL, int nL,
+                                 int S, int o2, int n2, int R, int T, uint32_t r, float* __restrict__ px,
+                                 float* __restrict__ py) {
+    const int lane = (int)lane_id();
+    const int w = (nL + 1) >> 1;
+    const int gl = div_lane(lane, r);
+    const int j = lane - gl * w, j2 = j + w;
+    const int g = min(gl, R - 1);
+    const float nan = __builtin_nanf("");
+    const bool jv = gl < R, jv2 = gl < R && j2 < nL;
+    float2 q = P::layer(c, hits.at(oL + j), S ? 0 : 1);
+    float2 q2 = P::layer(c, hits.at(oL + min(j2, nL - 1)), S ? 0 : 1);
+    q = make_float2(jv ? q.x : nan, jv ? q.y : nan);
+    q2 = make_float2(jv2 ? q2.x : nan, jv2 ? q2.y : nan);
+    const float2 v = P::layer(c, hits.at(oB + min(lane, nB - 1)), S ? 1 : 0);
+    px[lane] = lane < nB ? v.x : nan;
+    py[lane] = lane < nB ? v.y : nan;
+    wave_lds_sync();
+    uint32_t cnt = 0;
+    auto finish = [&](uint64_t m, int t, int jl) {
+        while (m) {
+            const int L = __builtin_ctzll(m);
+            m &= m - 1;
+            const int hB = oB + __builtin_amdgcn_readlane(g, L) * T + t;
+            const int hL = oL + __builtin_amdgcn_readlane(jl, L);
+            cnt += S ? P::complete(c, hits, hL, hB, o2, n2) : P::complete(c, hits, hB, hL, o2, n2);
+            if (cnt >= (uint32_t)c.count_cap) return;  // the result is capped there
+        }
+    };
+    for (int t = 0; t < T; ++t) {
+        const float2 p = make_float2(px[g * T + t], py[g * T + t]);
+        finish(P::pair_mask(pb, p, q), t, j);
+        finish(P::pair_mask(pb, p, q2), t, j2);
+    }
+    wave_lds_sync();
+    return cnt;
 }
 
 // Count of event e (absolute index) whose CSR range was checked by the
@@ -803,13 +939,21 @@ __device__ void wave_event(const Consts& c, const H& hits, int h_base, int o0, i
 // The one float4 group that would cross n_hits is copied element by element
 // by thread 0.  Needs x and y 16-byte aligned (checked by the host; `vec`
 // false otherwise: plain 4-byte loads).
-// Largest |x|, |y| of staged values as binary32 bit patterns without the
-// sign: for non-negative floats the integer order is the float order, so an
-// integer max (no NaN canonicalisation) finds it; a NaN pattern lies above
-// +inf and is clamped to +inf (an infinite bound: no pruning), see mag_of.
+// Magnitudes as binary32 bit patterns: for non-negative floats the integer
+// order is the float order, NaN above +inf.
 __device__ __forceinline__ uint32_t abs_bits(float v) { return __builtin_bit_cast(uint32_t, v) & 0x7fffffffu; }
+// A bound on the |x|, |y| of staged values, at most twice the largest: the
+// larger of the sums |a| + |b| as bit patterns (an integer max: no NaN
+// canonicalisation; a NaN pattern is clamped to +inf, an infinite bound and
+// so no pruning, see mag_of).  The bounds
+// hold for any M from the largest up and grow by far less than a percent; an
+// add with |operands| takes 2 SIMD cycles, where masking the signs and taking
+// the larger of the two takes 8.
+__device__ __forceinline__ uint32_t mag2(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_fabsf(a) + __builtin_fabsf(b));
+}
 __device__ __forceinline__ uint32_t mag4(uint32_t m, float a, float b, float c, float d) {
-    return max(max(m, max(abs_bits(a), abs_bits(b))), max(abs_bits(c), abs_bits(d)));
+    return max(max(m, mag2(a, b)), mag2(c, d));
 }
 __device__ __forceinline__ float mag_of(uint32_t m) { return __builtin_bit_cast(float, min(m, 0x7f800000u)); }
 
@@ -817,7 +961,7 @@ __device__ __forceinline__ float mag_of(uint32_t m) { return __builtin_bit_cast(
 // neighbours of the range: only an upper bound is needed).
 template <int HB, int NT>
 __device__ __forceinline__ uint32_t stage_hits(const float* __restrict__ x, const float* __restrict__ y,
-                                               int base, int nh, int n_hits, bool vec, float* xs, float* ys) {
+                                               int base, int nh, int n_hits, bool vec, float2* st) {
     constexpr int Q = (HB + 6) / 4 / NT + 1;  // float4 groups per thread, upper bound
     const int a0 = base & ~3;
     const int nq = (base + nh - a0 + 3) >> 2;             // float4 groups to copy
@@ -846,24 +990,22 @@ __device__ __forceinline__ uint32_t stage_hits(const float* __restrict__ x, cons
             for (int k = 0; k < Q; ++k) {
                 const int q = t + k * NT;
                 if (q < nq_full) {
-                    reinterpret_cast<float4*>(xs)[q] = vx[k];
-                    reinterpret_cast<float4*>(ys)[q] = vy[k];
+                    reinterpret_cast<float4*>(st)[2 * q] = make_float4(vx[k].x, vy[k].x, vx[k].y, vy[k].y);
+                    reinterpret_cast<float4*>(st)[2 * q + 1] = make_float4(vx[k].z, vy[k].z, vx[k].w, vy[k].w);
                 }
                 mag = mag4(mag4(mag, vx[k].x, vx[k].y, vx[k].z, vx[k].w), vy[k].x, vy[k].y, vy[k].z, vy[k].w);
             }
         }
         if (t == 0 && nq_full < nq) {
             for (int g = a0 + 4 * nq_full; g < base + nh; ++g) {
-                xs[g - a0] = x[g];
-                ys[g - a0] = y[g];
+                st[g - a0] = make_float2(x[g], y[g]);
                 mag = mag4(mag, x[g], y[g], 0.0f, 0.0f);
             }
         }
     } else {
         for (int h = t; h < nh; h += NT) {
             const float hx = x[base + h], hy = y[base + h];
-            xs[base - a0 + h] = hx;
-            ys[base - a0 + h] = hy;
+            st[base - a0 + h] = make_float2(hx, hy);
             mag = mag4(mag, hx, hy, 0.0f, 0.0f);
         }
     }
@@ -875,14 +1017,13 @@ __device__ __forceinline__ uint32_t stage_hits(const float* __restrict__ x, cons
 template <int HB, int NW, int EB>
 struct BlockLds {
     // HB hits plus up to 3 before the first and 3 after the last (4-aligned copy)
-    float stage_x[HB + 8];
-    float stage_y[HB + 8];
+    float2 stage[HB + 8];
     float pbuf_x[NW][kPBuf];
     float pbuf_y[NW][kPBuf];
     // Event descriptors, 13-bit fields (local hit indices < HB + 8 <= 4104,
     // layer sizes <= HB <= 4096): da = o0 | n0 << 13 | R << 26 (R <= 16) |
-    // S << 31, db = o1 | n1 << 13 | (T / 4) << 26 (T <= 64), dc = o2 | n2 << 13.
-    // dr = recip16 of the lane layer's size (fast-path events only).
+    // S << 31, db = o1 | n1 << 13, dc = o2 | n2 << 13, dr = direct_recip of the
+    // lanes per copy | T << 20.
     uint32_t da[EB], db[EB], dc[EB], dr[EB];
     int32_t soff[3 * EB + 1];
     int32_t sres[EB];
@@ -909,8 +1050,8 @@ static_assert(block_waves_per_simd<2048, 4, kSmallEB>() == 8, "eight 2048-hit wo
 // the next barrier by block_mag).  m: mag4 bits.
 template <int HB, int NW, int EB>
 __device__ __forceinline__ void publish_mag(BlockLds<HB, NW, EB>& L, uint32_t m) {
-    const float wm = wave_max_f(mag_of(m));
-    if (lane_id() == 0) L.wmag[threadIdx.x / kWave] = wm;
+    const uint32_t wm = wave_max_u(m);
+    if (lane_id() == 0) L.wmag[threadIdx.x / kWave] = mag_of(wm);
 }
 template <int HB, int NW, int EB>
 __device__ __forceinline__ float block_mag(const BlockLds<HB, NW, EB>& L) {
@@ -958,13 +1099,13 @@ __device__ void block_descriptors(BlockLds<HB, NW, EB>& L, int cur, int nsub, in
             res = -2;
         } else if (n0 > 0 && n1 > 0 && n2 > 0) {
             work = 1;
-            event_layout(n0, n1, R, T, S);
+            direct_layout(n0, n1, R, T, S);
         }
         L.da[te] = (uint32_t)(b0 - a0) | ((uint32_t)n0 << 13) | ((uint32_t)(work ? R : 0) << 26) |
                    ((uint32_t)S << 31);
-        L.db[te] = (uint32_t)(b1 - a0) | ((uint32_t)n1 << 13) | ((uint32_t)(T >> 2) << 26);
+        L.db[te] = (uint32_t)(b1 - a0) | ((uint32_t)n1 << 13);
         L.dc[te] = (uint32_t)(b2 - a0) | ((uint32_t)n2 << 13);
-        L.dr[te] = T > 0 ? recip16(S ? n0 : n1) : 0u;
+        L.dr[te] = direct_recip(((S ? n0 : n1) + 1) >> 1) | ((uint32_t)T << 20);
         L.sres[te] = res;
     }
     __syncthreads();
@@ -994,13 +1135,13 @@ __device__ __forceinline__ void block_check_describe(BlockLds<HB, NW, EB>& L, co
             res = -2;
         } else if (n0 > 0 && n1 > 0 && n2 > 0) {
             work = 1;
-            event_layout(n0, n1, R, T, S);
+            direct_layout(n0, n1, R, T, S);
         }
         L.da[te] = (uint32_t)(b0 - a0) | ((uint32_t)n0 << 13) | ((uint32_t)(work ? R : 0) << 26) |
                    ((uint32_t)S << 31);
-        L.db[te] = (uint32_t)(b1 - a0) | ((uint32_t)n1 << 13) | ((uint32_t)(T >> 2) << 26);
+        L.db[te] = (uint32_t)(b1 - a0) | ((uint32_t)n1 << 13);
         L.dc[te] = (uint32_t)(b2 - a0) | ((uint32_t)n2 << 13);
-        L.dr[te] = T > 0 ? recip16(S ? n0 : n1) : 0u;
+        L.dr[te] = direct_recip(((S ? n0 : n1) + 1) >> 1) | ((uint32_t)T << 20);
         L.sres[te] = res;
     }
 }
@@ -1015,38 +1156,43 @@ __device__ void block_count(BlockLds<HB, NW, EB>& L, const Consts& c, int e_firs
     const int w = uniform_i(threadIdx.x / kWave);
     float* px = L.pbuf_x[w];
     float* py = L.pbuf_y[w];
-    const LdsHits lh{L.stage_x, L.stage_y};
-    float M = 0.0f;
-    if constexpr (P::kMag) M = block_mag(L);
+    const LdsHits lh{L.stage};
+    const float M = block_mag(L);
     const PairBounds pb = P::bounds(c, M);
+    const float dc = direct_consts(c, pb, M);
     // The wave's next descriptor is read while the current event is
     // counted (its LDS round trip off the per-event chain).
-    uint32_t nda = 0u, ndb = 0u, ndc = 0u, ndr = 0u;
+    uint32_t nda = 0u, ndb = 0u, ndr = 0u;
     if (w < nsub) {
         nda = L.da[w];
         ndb = L.db[w];
-        ndc = L.dc[w];
         ndr = L.dr[w];
     }
     for (int te = w; te < nsub; te += NW) {
         const uint32_t da = (uint32_t)uniform_i((int)nda);
         const uint32_t db = (uint32_t)uniform_i((int)ndb);
-        const uint32_t dc = (uint32_t)uniform_i((int)ndc);
         const uint32_t dr = (uint32_t)uniform_i((int)ndr);
         if (te + NW < nsub) {
             nda = L.da[te + NW];
             ndb = L.db[te + NW];
-            ndc = L.dc[te + NW];
             ndr = L.dr[te + NW];
         }
         constexpr uint32_t kF = (1u << 13) - 1;
         const int o0 = (int)(da & kF), n0 = (int)((da >> 13) & kF), R = (int)((da >> 26) & 31u);
         const int S = (int)(da >> 31);
-        const int o1 = (int)(db & kF), n1 = (int)((db >> 13) & kF), T = (int)(db >> 26) * 4;
-        const int o2 = (int)(dc & kF), n2 = (int)((dc >> 13) & kF);
+        const int o1 = (int)(db & kF), n1 = (int)(db >> 13), T = (int)(dr >> 20);
         if (R == 0) continue;  // decided in the descriptor pass
-        const uint32_t cnt = T > 0 ? wave_event_fast<P>(c, pb, lh, o0, n0, o1, n1, o2, n2, R, T, S, dr, px, py)
-                                   : wave_event_pruned<P>(c, pb, lh, o0, n0, o1, n1, o2, n2, px, py);
+        const int oB = S ? o1 : o0, nB = S ? n1 : n0;
+        const int oL = S ? o0 : o1, nL = S ? n0 : n1;
+        const uint32_t r = dr & ((1u << 17) - 1);
+        if (T > 0 && !wave_any(direct_score<P>(L.stage, oB, nB, oL, nL, T, r, direct_const(dc, S)) <=
+                               direct_const(dc, 2 + S)))
+            continue;  // no pair can pass: the descriptor pass wrote 0
+        const uint32_t d2 = (uint32_t)uniform_i((int)L.dc[te]);
+        const int o2 = (int)(d2 & kF), n2 = (int)(d2 >> 13);
+        const uint32_t cnt = T > 0 && R * T <= kPBuf
+                                 ? direct_exact<P>(c, pb, lh, oB, nB, oL, nL, S, o2, n2, R, T, r, px, py)
+                                 : wave_event_pruned<P>(c, pb, lh, o0, n0, o1, n1, o2, n2, px, py);
         L.sres[te] = (int32_t)cnt;  // uniform: every lane stores the same value
     }
     __syncthreads();
@@ -1106,8 +1252,8 @@ __device__ void block_general(BlockLds<HB, NW, EB>& L, const Consts& c, const fl
         }
         const int end = cur + nfit;
         const int nh = L.soff[3 * end] - base;
-        const uint32_t mag = stage_hits<HB, NT>(x, y, base, nh, c.n_hits, vec, L.stage_x, L.stage_y);
-        if constexpr (P::kMag) publish_mag(L, mag);
+        const uint32_t mag = stage_hits<HB, NT>(x, y, base, nh, c.n_hits, vec, L.stage);
+        publish_mag(L, mag);
         block_descriptors(L, cur, nfit, base & ~3);
         block_count<P>(L, c, e0 + cur, nfit, counts, accept, status);
         cur = end;
@@ -1121,8 +1267,6 @@ __device__ void block_general(BlockLds<HB, NW, EB>& L, const Consts& c, const fl
 // three hits below n_hits) is copied by thread 0 at the store.  The groups
 // are named members (G<k> holds group k of this thread), not an array, so
 // that they stay in registers across the pipeline loop.
-typedef float f32x4 __attribute__((ext_vector_type(4)));  // a native vector (float4 copies are memcpys)
-
 template <int K, int NT>
 struct HitGroups {
     f32x4 vx, vy;
@@ -1135,20 +1279,20 @@ struct HitGroups {
         rest.load(x, y, a0, nq_full);
     }
     // Returns the largest |x|, |y| of the groups (and m), as mag4 bits.
-    __device__ __forceinline__ uint32_t store(int nq_full, float* xs, float* ys, uint32_t m) const {
+    __device__ __forceinline__ uint32_t store(int nq_full, float2* st, uint32_t m) const {
         const int q = (int)threadIdx.x + (K - 1) * NT;
         if (q < nq_full) {
-            reinterpret_cast<f32x4*>(xs)[q] = vx;
-            reinterpret_cast<f32x4*>(ys)[q] = vy;
+            reinterpret_cast<f32x4*>(st)[2 * q] = f32x4{vx.x, vy.x, vx.y, vy.y};
+            reinterpret_cast<f32x4*>(st)[2 * q + 1] = f32x4{vx.z, vy.z, vx.w, vy.w};
         }
         m = mag4(mag4(m, vx.x, vx.y, vx.z, vx.w), vy.x, vy.y, vy.z, vy.w);
-        return rest.store(nq_full, xs, ys, m);
+        return rest.store(nq_full, st, m);
     }
 };
 template <int NT>
 struct HitGroups<0, NT> {
     __device__ __forceinline__ void load(const float*, const float*, int, int) {}
-    __device__ __forceinline__ uint32_t store(int, float*, float*, uint32_t m) const { return m; }
+    __device__ __forceinline__ uint32_t store(int, float2*, uint32_t m) const { return m; }
 };
 
 template <int HB, int NT>
@@ -1180,13 +1324,12 @@ struct HitPrefetch {
     // Stores the block's hits; returns the largest |x|, |y| this thread
     // stored (the groups of a block with nq_full <= 0 are not loaded: 0).
     __device__ __forceinline__ uint32_t store(const float* __restrict__ x, const float* __restrict__ y, int base,
-                                              int nh, float* xs, float* ys) const {
+                                              int nh, float2* st) const {
         const int a0 = base & ~3;
-        uint32_t m = nq_full > 0 ? g.store(nq_full, xs, ys, 0u) : 0u;
+        uint32_t m = nq_full > 0 ? g.store(nq_full, st, 0u) : 0u;
         if (threadIdx.x == 0)
             for (int h = a0 + 4 * max(nq_full, 0); h < base + nh; ++h) {
-                xs[h - a0] = x[h];
-                ys[h - a0] = y[h];
+                st[h - a0] = make_float2(x[h], y[h]);
                 m = mag4(m, x[h], y[h], 0.0f, 0.0f);
             }
         return m;
@@ -1247,8 +1390,8 @@ void k_block(const int32_t* __restrict__ off, int n_events,
         pf.issue_full(x, y, base, Prefetch::full_groups(base, end - base, c.n_hits));
         stage_offsets();
         block_check_describe(L, c, e0, ne, base & ~3, counts, accept, status);
-        const uint32_t mag = pf.store(x, y, base, end - base, L.stage_x, L.stage_y);
-        if constexpr (P::kMag) publish_mag(L, mag);
+        const uint32_t mag = pf.store(x, y, base, end - base, L.stage);
+        publish_mag(L, mag);
         __syncthreads();
         const bool bad = uniform_i(L.s_bad) != 0;
         if (!bad)
@@ -1304,8 +1447,8 @@ __device__ uint32_t wave_event_z(const Consts& c, const float* __restrict__ x, c
 // that are malformed or do not fit in LDS go event by event to wave_event_z.
 // Bound by HBM latency and the pair scan together, as k_block.  1M staggered
 // events of 30 hits per layer, whole call: 0.511 ms with a wave per event from
-// HBM (nine loads of 4 bytes per lane and four divisions for each), 0.299 ms
-// now (3.7 TB/s of 17 bytes per event and 12 per hit).
+// HBM (nine loads of 4 bytes per lane and four divisions for each), 0.264 ms
+// now (4.2 TB/s of 17 bytes per event and 12 per hit).
 template <class P, class T, int HB, int NW, int EB>
 __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(block_waves_per_simd<HB, NW, EB>())))
 void k_block_z(const int32_t* __restrict__ off, int n_events, const float* __restrict__ x,
@@ -1362,28 +1505,28 @@ void k_block_z(const int32_t* __restrict__ off, int n_events, const float* __res
             sx = hx * r;
             sy = hy * r;
             const uint32_t zb = __builtin_bit_cast(uint32_t, hz);  // (0, inf): ordered as z; others above
-            mag = max(mag, max(abs_bits(hx), abs_bits(hy)));
+            mag = max(mag, mag2(hx, hy));
             zlo = max(zlo, ~zb);
             zhi = max(zhi, zb);
         };
 #pragma unroll
         for (int k = 0; k < Q; ++k) {
             const int q = t + k * NT;
-            f32x4 sx, sy;
+            f32x4 s0, s1;  // hits 4 q, 4 q + 1 and 4 q + 2, 4 q + 3
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 float ax, ay;
                 hit(vx[k][u], vy[k][u], vz[k][u], ax, ay);
-                sx[u] = ax;
-                sy[u] = ay;
+                (u < 2 ? s0 : s1)[2 * (u & 1)] = ax;
+                (u < 2 ? s0 : s1)[2 * (u & 1) + 1] = ay;
             }
             if (q < nq) {
-                reinterpret_cast<f32x4*>(L.stage_x)[q] = sx;
-                reinterpret_cast<f32x4*>(L.stage_y)[q] = sy;
+                reinterpret_cast<f32x4*>(L.stage)[2 * q] = s0;
+                reinterpret_cast<f32x4*>(L.stage)[2 * q + 1] = s1;
             }
         }
         if (t == 0)
-            for (int h = a0 + 4 * nq; h < end; ++h) hit(x[h], y[h], z[h], L.stage_x[h - a0], L.stage_y[h - a0]);
+            for (int h = a0 + 4 * nq; h < end; ++h) hit(x[h], y[h], z[h], L.stage[h - a0].x, L.stage[h - a0].y);
         publish_mag(L, mag);
         zlo = wave_max_u(zlo);
         zhi = wave_max_u(zhi);
@@ -1411,7 +1554,7 @@ void k_block_z(const int32_t* __restrict__ off, int n_events, const float* __res
         __syncthreads();
     }
     // Events round-robin over the waves; wave-uniform control flow.
-    const LdsHits lh{L.stage_x, L.stage_y};
+    const LdsHits lh{L.stage};
     for (int te = w; te < ne; te += NW) {
         const int b0 = uniform_i(L.soff[3 * te]), b1 = uniform_i(L.soff[3 * te + 1]);
         const int b2 = uniform_i(L.soff[3 * te + 2]), b3 = uniform_i(L.soff[3 * te + 3]);
@@ -1429,17 +1572,13 @@ void k_block_z(const int32_t* __restrict__ off, int n_events, const float* __res
         if (ev.n0 > 0 && ev.n1 > 0 && ev.n2 > 0) {
             bool close = true;
             if (good) {
-                const uint32_t da = (uint32_t)uniform_i((int)L.da[te]), db = (uint32_t)uniform_i((int)L.db[te]);
-                const int R = (int)((da >> 26) & 31u), S = (int)(da >> 31), TB = (int)(db >> 26) * 4;
-                if (TB > 0) {
-                    int g, j;
-                    float2 q;
-                    fast_setup<P, false>(c, lh, (S ? b1 : b0) - a0, S ? ev.n1 : ev.n0, (S ? b0 : b1) - a0, S ? ev.n0 : ev.n1,
-                                  S, R, TB, (uint32_t)uniform_i((int)L.dr[te]), px, py, g, j, q);
-                    wave_lds_sync();
-                    close = wave_any(fast_score<P>(px, py, TB, g, q) <= pb.pre);
-                    wave_lds_sync();
-                }
+                const int S = uniform_i((int)L.da[te]) < 0 ? 1 : 0;
+                const uint32_t dr = (uint32_t)uniform_i((int)L.dr[te]);
+                const int TB = (int)(dr >> 20);
+                if (TB > 0)  // slopes: the layers differ by a sign
+                    close = wave_any(direct_score<P>(L.stage, (S ? b1 : b0) - a0, S ? ev.n1 : ev.n0,
+                                                     (S ? b0 : b1) - a0, S ? ev.n0 : ev.n1, TB, dr & ((1u << 17) - 1),
+                                                     -1.0f) <= pb.pre);
             }
             if (close) {
                 cnt = wave_event_z<P, T>(c, x, y, z, ev, px, py);
@@ -1526,8 +1665,8 @@ __global__ __launch_bounds__(NW * kWave) void k_block_pipe(const int32_t* __rest
         if (regular) {
             const int base = L.soff[0];
             const int nh = L.soff[3 * ne] - base;
-            const uint32_t mag = pf.store(x, y, base, nh, L.stage_x, L.stage_y);
-            if constexpr (P::kMag) publish_mag(L, mag);
+            const uint32_t mag = pf.store(x, y, base, nh, L.stage);
+            publish_mag(L, mag);
             block_descriptors(L, 0, ne, base & ~3);
         } else {
             block_general<P>(L, c, x, y, e0, ne, bad, true, counts, accept, status);

@@ -47,10 +47,10 @@ struct Consts {
     float pre_msd, pre_win_sum, pre_win;
     // TRIG_TEST_SLOPE_WINDOW
     float win_x, win_y;
-    // Batched form's window prefilter: 1 / z0 and 1 / z1 rounded, and what the
-    // approximate slopes c fl(1 / z) can add to a pair's score (win_slack0 +
-    // win_slack M)
-    float win_r0, win_r1, win_slack0, win_slack;
+    // Batched form's prefilter on staged coordinates, by the layer in the
+    // lanes (index 0: layer 1, index 1: layer 0): the factor on that layer,
+    // and a passing pair's score is at most (pre scale + slack M) + slack0
+    float dir_k[2], dir_scale[2], dir_slack[2], dir_slack0;
     // Binned form, MSD_BASIS and window: half-width of the key interval
     // around a hit's centre (MSD_BASIS: the binary32 value above beta_x;
     // window: win_x).
@@ -69,6 +69,9 @@ struct Consts {
 __device__ __forceinline__ int32_t capped(int32_t cnt, const Consts& c) { return cnt < c.count_cap ? cnt : c.count_cap; }
 
 __device__ __forceinline__ int uniform_i(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ float uniform_f(float v) {
+    return __builtin_bit_cast(float, uniform_i(__builtin_bit_cast(int, v)));
+}
 // cond ? a : b for wave-uniform operands, on the scalar unit (a compare
 // and a scalar select; the compiler would otherwise select per lane).
 __device__ __forceinline__ float select_uniform(int cond, float a, float b) {

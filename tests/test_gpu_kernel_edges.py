@@ -278,6 +278,38 @@ def test_window_prefilter_layer_positions(gpu, form):  # noqa: F811
             assert_parity(gpu, s, "window", form, f"z {z} window {w}", z=z, slope_window=(w, w))
 
 
+# ----------------------------------------------------- direct pair scan ---
+
+@pytest.mark.parametrize("test", ("msd", "msd_basis", "window", "msd_z", "window_z"))
+def test_direct_scan_edges(gpu, test):  # noqa: F811
+    """The batched form's scan of staged pairs, two hits per lane: layer sizes
+    around the copies' counts (1 to 64 lanes per copy, 16 copies to one), its
+    limit of 128 hits in the lanes, 1,023 steps over the other layer and 64
+    entries of the exact pass; overlapping last copies; every pair of an event
+    close; layers at the ends of the scan's range of z ratios and beyond."""
+    ns = (1, 2, 3, 4, 7, 8, 9, 15, 16, 17, 21, 22, 31, 32, 33, 42, 43, 63, 64, 65, 127, 128, 129)
+    sizes = [(a, b, 5) for a in ns for b in ns]
+    sizes += [p for n in (1022, 1023, 1024) for m in (65, 127, 129) for p in ((n, m, 3), (m, n, 3))]
+    s = helpers.ragged_sizes_set(sizes, seed=91)
+    dup = duplicated_track_events([(a, b, 3) for a in (1, 2, 9, 30, 70) for b in (1, 2, 9, 30, 70)], 4, seed=92)
+    near = synth.concat([helpers.near_threshold_events(40, n, seed=95, rel=1e-6) for n in (5, 16, 33)]
+                        + [helpers.pair_boundary_events(40, 12, seed=96), helpers.window_boundary_events(40, 12, seed=97)])
+    if test.endswith("_z"):
+        s, dup, near = (synth.staggered(v) for v in (s, dup, near))
+    t = test.replace("_z", "")
+    for label, v in (("sizes", s), ("close pairs", dup), ("near the bounds", near)):
+        for form in ("pruned",) if test.endswith("_z") else ("pruned", "persistent_pruned"):
+            c = assert_parity(gpu, v, t, form, f"direct scan, {label}, {test}")
+            assert c.sum() > 0
+    if not test.endswith("_z"):
+        few = helpers.ragged_sizes_set([(30, 33, 31), (5, 40, 9), (64, 17, 20)] * 10, seed=98)
+        for z in ((1.0, 1e18, 2e18), (1e18, 1.0, 2e18), (1.0, 2e18, 3e18), (1e-18, 1.0, 2.0), (4e-19, 4.1e-19, 1.0),
+                  (1e30, 1.0, 1e30), (1e-20, 1e20, 1e20)):
+            for cut in (0.0, 1e-3, 1e20):
+                assert_parity(gpu, few, t, "pruned", f"direct scan, z {z} cut {cut}", z=z, msd_max=(cut, cut),
+                              slope_window=(cut, cut))
+
+
 # --------------------------------------------------------- binned cells ---
 
 @pytest.mark.parametrize("test", ("msd", "msd_basis", "window"))
