@@ -777,10 +777,10 @@ __device__ __forceinline__ void event_layout(int n0, int n1, int& R, int& T, int
 //
 // Bound by vector instructions, the LDS and the staging's latency together.
 // Against one hit per lane, partials in a buffer and masked lanes, with the
-// staged block's bound on |x|, |y| cheaper by 80 cycles per wave (mag2), the
-// whole call takes 198 for 211 us on a million events of 30 hits per layer,
-// 264 for 288 with per-hit z and 10.2 for 11.5 on 1000 events of 15; two hits
-// per lane without the rest gave 2 %.
+// staged block's bound on |x|, |y| cheaper by 80 cycles per wave (mag2) and
+// descriptors in lanes, the whole call takes 195 for 211 us on a million
+// events of 30 hits per layer and 239 for 288 with per-hit z; two hits per
+// lane without the rest gave 2 %.
 //
 // pre: with M >= every staged |x|, |y| and u = 2^-24, a pair that passes the
 // exact pair test has, in the MSD tests' units,
@@ -806,29 +806,32 @@ __device__ __forceinline__ float direct_const(float d, int lane) {
 constexpr int kDirectCopies = 16;   // R at most
 constexpr int kDirectSteps = 1023;  // T at most (dr holds it above direct_recip's 17 bits)
 
-// R copies of the lane layer (nL hits, w = (nL + 1) / 2 lanes each) and T
-// steps over the other layer's nB hits; T = 0: too large for one lane pass.
-__device__ __forceinline__ void direct_side(int nB, int nL, int& R, int& T) {
+// For floor(v / w), 0 <= v <= 64 and 1 <= w <= 64, as (v r) >> 16: any r with
+// r w = 2^16 + d, 0 <= d < 1024 gives it (v d < 2^16, see recip16); here
+// w - 1 < d < 2 w + 1.
+__device__ __forceinline__ uint32_t direct_recip(int w) {
+    return (uint32_t)(65536.0f * __builtin_amdgcn_rcpf((float)w)) + 2u;
+}
+// R copies of the lane layer (nL hits, w = (nL + 1) / 2 lanes each), T steps
+// over the other layer's nB hits and r = direct_recip(w); T = 0: too large
+// for one lane pass.
+__device__ __forceinline__ void direct_side(int nB, int nL, int& R, int& T, uint32_t& r) {
     const int w = (nL + 1) >> 1;
-    R = w <= kWave / 2 ? min(div_small(kWave, w), kDirectCopies) : 1;
+    r = direct_recip(w);
+    R = min(max((int)(r >> 10), 1), kDirectCopies);  // floor(64 / w)
     T = (w <= kWave && nB <= kDirectSteps) ? div_small(nB + R - 1, R) : 0;
 }
 // The orientation with fewer steps (S = 0: layer 1 in the lanes).
-__device__ __forceinline__ void direct_layout(int n0, int n1, int& R, int& T, int& S) {
+__device__ __forceinline__ void direct_layout(int n0, int n1, int& R, int& T, int& S, uint32_t& r) {
     int R1, T1;
-    direct_side(n0, n1, R, T);
-    direct_side(n1, n0, R1, T1);
-    S = 0;
-    if (T1 > 0 && (T == 0 || T1 < T)) {
-        R = R1;
-        T = T1;
-        S = 1;
-    }
-}
-// For floor(lane / w), 1 <= w <= 64, as (lane r) >> 16: any r with r w = 2^16 +
-// d, 0 <= d < 1040 gives it (lane d < 2^16, see recip16); here w - 1 < d < 2 w + 1.
-__device__ __forceinline__ uint32_t direct_recip(int w) {
-    return (uint32_t)(65536.0f * __builtin_amdgcn_rcpf((float)w)) + 2u;
+    uint32_t r1;
+    direct_side(n0, n1, R, T, r);
+    direct_side(n1, n0, R1, T1, r1);
+    const bool swap = T1 > 0 && (T == 0 || T1 < T);
+    S = swap ? 1 : 0;
+    R = swap ? R1 : R;
+    T = swap ? T1 : T;
+    r = swap ? r1 : r;
 }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));  // a native vector (float4 copies are memcpys)
@@ -1082,31 +1085,40 @@ __device__ bool block_validate(BlockLds<HB, NW, EB>& L, const Consts& c, int e0,
     return uniform_i(L.s_bad) != 0;
 }
 
-// Descriptors of events [cur, cur + nsub) of a staged sub-block (local hit
-// index = global index - a0), one lane per event; events decided without
-// pairs get their result here (0 for an empty layer, -2 for a count beyond
-// int32).  Ends with a barrier.
+// Descriptor of event te of a staged block from its offsets b0 <= b1 <= b2 <=
+// b3 (local hit index = global index - a0); an event decided without pairs
+// gets its result here (0 for an empty layer, -2 for a count beyond int32).
+template <int HB, int NW, int EB>
+__device__ __forceinline__ void describe_event(BlockLds<HB, NW, EB>& L, int te, int b0, int b1, int b2, int b3,
+                                               int a0) {
+    const int n0 = b1 - b0, n1 = b2 - b1, n2 = b3 - b2;
+    int R, T, S, res = 0;
+    uint32_t r;
+    direct_layout(n0, n1, R, T, S, r);
+    bool work = min(min(n0, n1), n2) > 0;
+    // (three layers of HB hits together: at most (HB / 3)^3 triplets)
+    if constexpr ((int64_t)HB * HB * HB / 27 > (int64_t)INT32_MAX) {
+        const int64_t n01 = (int64_t)n0 * n1;
+        if (n2 > 0 && (n01 > (int64_t)INT32_MAX || n01 * n2 > (int64_t)INT32_MAX)) {
+            res = -2;
+            work = false;
+        }
+    }
+    L.da[te] = (uint32_t)(b0 - a0) | ((uint32_t)n0 << 13) | ((uint32_t)(work ? R : 0) << 26) | ((uint32_t)S << 31);
+    L.db[te] = (uint32_t)(b1 - a0) | ((uint32_t)n1 << 13);
+    L.dc[te] = (uint32_t)(b2 - a0) | ((uint32_t)n2 << 13);
+    L.dr[te] = r | ((uint32_t)T << 20);
+    L.sres[te] = res;
+}
+
+// Descriptors of events [cur, cur + nsub) of a staged sub-block, one lane per
+// event.  Ends with a barrier.
 template <int HB, int NW, int EB>
 __device__ void block_descriptors(BlockLds<HB, NW, EB>& L, int cur, int nsub, int a0) {
     constexpr int NT = NW * kWave;
     for (int te = threadIdx.x; te < nsub; te += NT) {
         const int ev = cur + te;
-        const int b0 = L.soff[3 * ev], b1 = L.soff[3 * ev + 1], b2 = L.soff[3 * ev + 2], b3 = L.soff[3 * ev + 3];
-        const int n0 = b1 - b0, n1 = b2 - b1, n2 = b3 - b2;
-        const int64_t n01 = (int64_t)n0 * n1;
-        int R = 0, T = 0, S = 0, res = 0, work = 0;
-        if (n2 > 0 && (n01 > (int64_t)INT32_MAX || n01 * n2 > (int64_t)INT32_MAX)) {
-            res = -2;
-        } else if (n0 > 0 && n1 > 0 && n2 > 0) {
-            work = 1;
-            direct_layout(n0, n1, R, T, S);
-        }
-        L.da[te] = (uint32_t)(b0 - a0) | ((uint32_t)n0 << 13) | ((uint32_t)(work ? R : 0) << 26) |
-                   ((uint32_t)S << 31);
-        L.db[te] = (uint32_t)(b1 - a0) | ((uint32_t)n1 << 13);
-        L.dc[te] = (uint32_t)(b2 - a0) | ((uint32_t)n2 << 13);
-        L.dr[te] = direct_recip(((S ? n0 : n1) + 1) >> 1) | ((uint32_t)T << 20);
-        L.sres[te] = res;
+        describe_event(L, te, L.soff[3 * ev], L.soff[3 * ev + 1], L.soff[3 * ev + 2], L.soff[3 * ev + 3], a0);
     }
     __syncthreads();
 }
@@ -1121,28 +1133,19 @@ __device__ __forceinline__ void block_check_describe(BlockLds<HB, NW, EB>& L, co
     constexpr int NT = NW * kWave;
     for (int te = threadIdx.x; te < ne; te += NT) {
         const int b0 = L.soff[3 * te], b1 = L.soff[3 * te + 1], b2 = L.soff[3 * te + 2], b3 = L.soff[3 * te + 3];
-        if (!(0 <= b0 && b0 <= b1 && b1 <= b2 && b2 <= b3 && b3 <= c.n_hits)) {
+        // 0 <= b0 <= b1 <= b2 <= b3 <= n_hits as one sign: none of the five is
+        // negative (then no difference overflows) and neither is a difference
+        // (as unsigned arithmetic, which wraps where an offset is negative)
+        const uint32_t u0 = (uint32_t)b0, u1 = (uint32_t)b1, u2 = (uint32_t)b2, u3 = (uint32_t)b3;
+        const uint32_t neg = (u0 | u1 | u2 | u3) | (u1 - u0) | (u2 - u1) | (u3 - u2) | ((uint32_t)c.n_hits - u3);
+        if ((int32_t)neg < 0) {
             counts[e0 + te] = -1;
             accept[e0 + te] = 0;
             if (status) atomicOr(status, TRIG_STATUS_MALFORMED);
             atomicOr(&L.s_bad, 1);
             continue;
         }
-        const int n0 = b1 - b0, n1 = b2 - b1, n2 = b3 - b2;
-        const int64_t n01 = (int64_t)n0 * n1;
-        int R = 0, T = 0, S = 0, res = 0, work = 0;
-        if (n2 > 0 && (n01 > (int64_t)INT32_MAX || n01 * n2 > (int64_t)INT32_MAX)) {
-            res = -2;
-        } else if (n0 > 0 && n1 > 0 && n2 > 0) {
-            work = 1;
-            direct_layout(n0, n1, R, T, S);
-        }
-        L.da[te] = (uint32_t)(b0 - a0) | ((uint32_t)n0 << 13) | ((uint32_t)(work ? R : 0) << 26) |
-                   ((uint32_t)S << 31);
-        L.db[te] = (uint32_t)(b1 - a0) | ((uint32_t)n1 << 13);
-        L.dc[te] = (uint32_t)(b2 - a0) | ((uint32_t)n2 << 13);
-        L.dr[te] = direct_recip(((S ? n0 : n1) + 1) >> 1) | ((uint32_t)T << 20);
-        L.sres[te] = res;
+        describe_event(L, te, b0, b1, b2, b3, a0);
     }
 }
 
@@ -1160,40 +1163,33 @@ __device__ void block_count(BlockLds<HB, NW, EB>& L, const Consts& c, int e_firs
     const float M = block_mag(L);
     const PairBounds pb = P::bounds(c, M);
     const float dc = direct_consts(c, pb, M);
-    // The wave's next descriptor is read while the current event is
-    // counted (its LDS round trip off the per-event chain).
-    uint32_t nda = 0u, ndb = 0u, ndr = 0u;
-    if (w < nsub) {
-        nda = L.da[w];
-        ndb = L.db[w];
-        ndr = L.dr[w];
-    }
-    for (int te = w; te < nsub; te += NW) {
-        const uint32_t da = (uint32_t)uniform_i((int)nda);
-        const uint32_t db = (uint32_t)uniform_i((int)ndb);
-        const uint32_t dr = (uint32_t)uniform_i((int)ndr);
-        if (te + NW < nsub) {
-            nda = L.da[te + NW];
-            ndb = L.db[te + NW];
-            ndr = L.dr[te + NW];
+    // Lane i reads the descriptor of the wave's event i (64 at a time).
+    for (int tb = w; tb < nsub; tb += NW * kWave) {
+        const int mine = min(tb + (int)lane_id() * NW, nsub - 1);
+        const int vda = (int)L.da[mine], vdb = (int)L.db[mine], vdr = (int)L.dr[mine];
+        for (int i = 0; i < kWave && tb + i * NW < nsub; ++i) {
+            const int te = tb + i * NW;
+            const uint32_t da = (uint32_t)__builtin_amdgcn_readlane(vda, i);
+            const uint32_t db = (uint32_t)__builtin_amdgcn_readlane(vdb, i);
+            const uint32_t dr = (uint32_t)__builtin_amdgcn_readlane(vdr, i);
+            constexpr uint32_t kF = (1u << 13) - 1;
+            const int o0 = (int)(da & kF), n0 = (int)((da >> 13) & kF), R = (int)((da >> 26) & 31u);
+            const int S = (int)(da >> 31);
+            const int o1 = (int)(db & kF), n1 = (int)(db >> 13), T = (int)(dr >> 20);
+            if (R == 0) continue;  // decided in the descriptor pass
+            const int oB = S ? o1 : o0, nB = S ? n1 : n0;
+            const int oL = S ? o0 : o1, nL = S ? n0 : n1;
+            const uint32_t r = dr & ((1u << 17) - 1);
+            if (T > 0 && !wave_any(direct_score<P>(L.stage, oB, nB, oL, nL, T, r, direct_const(dc, S)) <=
+                                   direct_const(dc, 2 + S)))
+                continue;  // no pair can pass: the descriptor pass wrote 0
+            const uint32_t d2 = (uint32_t)uniform_i((int)L.dc[te]);
+            const int o2 = (int)(d2 & kF), n2 = (int)(d2 >> 13);
+            const uint32_t cnt = T > 0 && R * T <= kPBuf
+                                     ? direct_exact<P>(c, pb, lh, oB, nB, oL, nL, S, o2, n2, R, T, r, px, py)
+                                     : wave_event_pruned<P>(c, pb, lh, o0, n0, o1, n1, o2, n2, px, py);
+            L.sres[te] = (int32_t)cnt;  // uniform: every lane stores the same value
         }
-        constexpr uint32_t kF = (1u << 13) - 1;
-        const int o0 = (int)(da & kF), n0 = (int)((da >> 13) & kF), R = (int)((da >> 26) & 31u);
-        const int S = (int)(da >> 31);
-        const int o1 = (int)(db & kF), n1 = (int)(db >> 13), T = (int)(dr >> 20);
-        if (R == 0) continue;  // decided in the descriptor pass
-        const int oB = S ? o1 : o0, nB = S ? n1 : n0;
-        const int oL = S ? o0 : o1, nL = S ? n0 : n1;
-        const uint32_t r = dr & ((1u << 17) - 1);
-        if (T > 0 && !wave_any(direct_score<P>(L.stage, oB, nB, oL, nL, T, r, direct_const(dc, S)) <=
-                               direct_const(dc, 2 + S)))
-            continue;  // no pair can pass: the descriptor pass wrote 0
-        const uint32_t d2 = (uint32_t)uniform_i((int)L.dc[te]);
-        const int o2 = (int)(d2 & kF), n2 = (int)(d2 >> 13);
-        const uint32_t cnt = T > 0 && R * T <= kPBuf
-                                 ? direct_exact<P>(c, pb, lh, oB, nB, oL, nL, S, o2, n2, R, T, r, px, py)
-                                 : wave_event_pruned<P>(c, pb, lh, o0, n0, o1, n1, o2, n2, px, py);
-        L.sres[te] = (int32_t)cnt;  // uniform: every lane stores the same value
     }
     __syncthreads();
     for (int te = threadIdx.x; te < nsub; te += NT) {
@@ -1447,8 +1443,8 @@ __device__ uint32_t wave_event_z(const Consts& c, const float* __restrict__ x, c
 // that are malformed or do not fit in LDS go event by event to wave_event_z.
 // Bound by HBM latency and the pair scan together, as k_block.  1M staggered
 // events of 30 hits per layer, whole call: 0.511 ms with a wave per event from
-// HBM (nine loads of 4 bytes per lane and four divisions for each), 0.264 ms
-// now (4.2 TB/s of 17 bytes per event and 12 per hit).
+// HBM (nine loads of 4 bytes per lane and four divisions for each), 0.239 ms
+// now (4.6 TB/s of 17 bytes per event and 12 per hit).
 template <class P, class T, int HB, int NW, int EB>
 __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(block_waves_per_simd<HB, NW, EB>())))
 void k_block_z(const int32_t* __restrict__ off, int n_events, const float* __restrict__ x,
@@ -1554,38 +1550,50 @@ void k_block_z(const int32_t* __restrict__ off, int n_events, const float* __res
         __syncthreads();
     }
     // Events round-robin over the waves; wave-uniform control flow.
-    const LdsHits lh{L.stage};
-    for (int te = w; te < ne; te += NW) {
-        const int b0 = uniform_i(L.soff[3 * te]), b1 = uniform_i(L.soff[3 * te + 1]);
-        const int b2 = uniform_i(L.soff[3 * te + 2]), b3 = uniform_i(L.soff[3 * te + 3]);
-        if (!(0 <= b0 && b0 <= b1 && b1 <= b2 && b2 <= b3 && b3 <= c.n_hits)) {
-            L.sres[te] = -1;  // (already written and reported)
-            continue;
-        }
+    auto count = [&](int te, int b0, int b1, int b2, int b3) {
         const EventRange ev{b0, b1, b2, b1 - b0, b2 - b1, b3 - b2};
-        const int64_t n01 = (int64_t)ev.n0 * ev.n1;
-        uint32_t cnt = 0;
-        if (ev.n2 > 0 && (n01 > (int64_t)INT32_MAX || n01 * ev.n2 > (int64_t)INT32_MAX)) {
-            L.sres[te] = -2;
-            continue;
-        }
-        if (ev.n0 > 0 && ev.n1 > 0 && ev.n2 > 0) {
-            bool close = true;
-            if (good) {
-                const int S = uniform_i((int)L.da[te]) < 0 ? 1 : 0;
-                const uint32_t dr = (uint32_t)uniform_i((int)L.dr[te]);
-                const int TB = (int)(dr >> 20);
-                if (TB > 0)  // slopes: the layers differ by a sign
-                    close = wave_any(direct_score<P>(L.stage, (S ? b1 : b0) - a0, S ? ev.n1 : ev.n0,
-                                                     (S ? b0 : b1) - a0, S ? ev.n0 : ev.n1, TB, dr & ((1u << 17) - 1),
-                                                     -1.0f) <= pb.pre);
+        L.sres[te] = (int32_t)wave_event_z<P, T>(c, x, y, z, ev, px, py);  // uniform
+        wave_lds_sync();
+    };
+    if (good) {
+        // Lane i reads the descriptor of the wave's event i (64 at a time).
+        for (int tb = w; tb < ne; tb += NW * kWave) {
+            const int mine = min(tb + (int)lane_id() * NW, ne - 1);
+            const int vda = (int)L.da[mine], vdb = (int)L.db[mine], vdr = (int)L.dr[mine];
+            for (int i = 0; i < kWave && tb + i * NW < ne; ++i) {
+                const int te = tb + i * NW;
+                const uint32_t da = (uint32_t)__builtin_amdgcn_readlane(vda, i);
+                const uint32_t db = (uint32_t)__builtin_amdgcn_readlane(vdb, i);
+                const uint32_t dr = (uint32_t)__builtin_amdgcn_readlane(vdr, i);
+                constexpr uint32_t kF = (1u << 13) - 1;
+                if (((da >> 26) & 31u) == 0u) continue;  // decided in the descriptor pass
+                const int o0 = (int)(da & kF), n0 = (int)((da >> 13) & kF), o1 = (int)(db & kF), n1 = (int)(db >> 13);
+                const int S = (int)(da >> 31), TB = (int)(dr >> 20);
+                // slopes: the layers differ by a sign
+                if (TB > 0 && !wave_any(direct_score<P>(L.stage, S ? o1 : o0, S ? n1 : n0, S ? o0 : o1, S ? n0 : n1, TB,
+                                                        dr & ((1u << 17) - 1), -1.0f) <= pb.pre))
+                    continue;  // no pair can pass: the descriptor pass wrote 0
+                count(te, uniform_i(L.soff[3 * te]), uniform_i(L.soff[3 * te + 1]), uniform_i(L.soff[3 * te + 2]),
+                      uniform_i(L.soff[3 * te + 3]));
             }
-            if (close) {
-                cnt = wave_event_z<P, T>(c, x, y, z, ev, px, py);
-                wave_lds_sync();
-            }
         }
-        L.sres[te] = (int32_t)cnt;  // uniform: every lane stores the same value
+    } else {
+        for (int te = w; te < ne; te += NW) {
+            const int b0 = uniform_i(L.soff[3 * te]), b1 = uniform_i(L.soff[3 * te + 1]);
+            const int b2 = uniform_i(L.soff[3 * te + 2]), b3 = uniform_i(L.soff[3 * te + 3]);
+            if (!(0 <= b0 && b0 <= b1 && b1 <= b2 && b2 <= b3 && b3 <= c.n_hits)) {
+                L.sres[te] = -1;  // (already written and reported)
+                continue;
+            }
+            const int64_t n01 = (int64_t)(b1 - b0) * (b2 - b1);
+            const int n2 = b3 - b2;
+            if (n2 > 0 && (n01 > (int64_t)INT32_MAX || n01 * n2 > (int64_t)INT32_MAX))
+                L.sres[te] = -2;
+            else if (n01 > 0 && n2 > 0)
+                count(te, b0, b1, b2, b3);
+            else
+                L.sres[te] = 0;
+        }
     }
     __syncthreads();
     for (int te = t; te < ne; te += NT) {

@@ -310,6 +310,29 @@ def test_direct_scan_edges(gpu, test):  # noqa: F811
                               slope_window=(cut, cut))
 
 
+@pytest.mark.parametrize("hit_z", (False, True))
+def test_block_offset_checks(gpu, hit_z):  # noqa: F811
+    """Blocks with one malformed offset at each place of an event: below 0,
+    the ends of int32 (whose differences wrap) and one beyond its neighbour or
+    the hits; and one to 130 events per block, among them empty layers."""
+    base = helpers.ragged_sizes_set([(3, 4, 5), (0, 2, 1), (6, 0, 2), (7, 7, 0), (9, 8, 11)] * 26, seed=99)
+    n = int(base.offsets[-1])
+    lo, hi = -2 ** 31, 2 ** 31 - 1
+    for n_events in (1, 2, 63, 65, 130):
+        off = base.offsets[: 3 * n_events + 1].copy()
+        whole = synth.EventSet(off, base.x[: off[-1]], base.y[: off[-1]], base.n_tracks[:n_events])
+        whole = synth.staggered(whole) if hit_z else whole
+        assert_parity(gpu, whole, "msd", "pruned", f"block of {n_events}")
+        for at in sorted({0, 1, 2, 3 * (n_events // 2) + 1, 3 * n_events - 1, 3 * n_events}):
+            for bad in (lo, lo + 1, -1, hi, hi - 1, n + 1, int(off[min(at + 1, 3 * n_events)]) + 1):
+                o = off.copy()
+                o[at] = bad
+                s = synth.EventSet(o, whole.x, whole.y, whole.n_tracks)
+                if hit_z:
+                    s.z = whole.z
+                assert_parity(gpu, s, "msd", "pruned", f"block of {n_events}, offset {at} = {bad}")
+
+
 # --------------------------------------------------------- binned cells ---
 
 @pytest.mark.parametrize("test", ("msd", "msd_basis", "window"))
