@@ -36,8 +36,8 @@ sys.path.insert(0, ROOT)
 # non-fused, non-packed fp32 operation per lane per clock.
 HBM_PEAK_GBS = 8000.0
 VALU_F32_PEAK_TOPS = 256 * 128 * 2.4e9 / 1e12  # 78.64
-# The every-triplet loops' rejecting test per triplet: two sums, one max and
-# half a min3 (the few triplets it does not reject are evaluated in full).
+# The every-triplet loops' rejecting test per triplet: three sums and half a
+# min3 (the few triplets it does not reject are evaluated in full).
 OPS_PER_TRIPLET = {"msd": 3.5, "msd_basis": 3.5, "window": 3.5}
 
 WORKLOAD_TEXT = {

@@ -132,12 +132,14 @@ enum {
                                    (event, pair-range) work units of the
                                    every-triplet loop from a global counter;
                                    with TRIG_EXEC_PRUNED: workgroups steal event
-                                   blocks; with TRIG_EXEC_BINNED: workgroups
-                                   steal event groups.  Needs workspace */
+                                   blocks; with TRIG_EXEC_BINNED: waves steal
+                                   runs of events from 64 slices of the batch.
+                                   Needs workspace */
     TRIG_EXEC_BINNED = 2u,      /* binned form for high-multiplicity events:
-                                   one wave per event sorts layers 1 and 2
-                                   into cells of a slope-proportional key in
-                                   LDS and tests only hits in the cells whose
+                                   one wave per event sorts layer 1 (and layer
+                                   2 of events with more than 64 surviving
+                                   pairs) into cells of a slope-proportional key
+                                   in LDS and tests only hits in the cells whose
                                    key interval can pass (MSD tests: bounds on
                                    the partial sums a and b that every passing
                                    triplet meets; window: the slope windows),

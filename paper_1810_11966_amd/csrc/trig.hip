@@ -372,11 +372,12 @@ constexpr int kBinWaves = 4;     // waves (one event each) per workgroup
 constexpr int kBinResident = 8;  // binned workgroups per CU (LDS bound)
 constexpr int kBinSlices = 64;   // block stealing: slices of the events, each with its own counter,
 constexpr int kBinStride = 64;   // this many words apart
+static_assert(kBinSlices == 64, "k_binned shifts by 6");
 
 // A wave counts runs of `chunk` consecutive events.  Non-persistent when
 // block_counter == nullptr: wave g takes run g.  Otherwise the events are cut
-// into kBinSlices slices, workgroup b working on slice b % kBinSlices: a wave
-// takes its first run by its own number and the others from the slice's
+// into kBinSlices slices of slice_events (fewer workgroups: a slice each),
+// workgroup b working on slice b % kBinSlices: a wave takes its first run by its own number and the others from the slice's
 // counter (zero at launch; one atomic per run), until none is left: no
 // barrier, and no LDS beyond the waves' cells (8 workgroups fit on a CU).
 // Atomics on one 256-byte line pass one by one, some 5 ns each (1M mixture
@@ -388,8 +389,8 @@ constexpr int kBinStride = 64;   // this many words apart
 template <class B>
 __global__ __launch_bounds__(kBinWaves * kWave) __attribute__((amdgpu_waves_per_eu(kBinResident))) void k_binned(
     const int32_t* __restrict__ off, int n_events, const float* __restrict__ x, const float* __restrict__ y,
-    Consts c, unsigned* block_counter, int chunk, int32_t* __restrict__ counts, uint8_t* __restrict__ accept,
-    uint32_t* status) {
+    Consts c, unsigned* block_counter, int chunk, int slice_events, int32_t* __restrict__ counts,
+    uint8_t* __restrict__ accept, uint32_t* status) {
     __shared__ __align__(16) BinLds lds_all[kBinWaves];
     const int w = uniform_i((int)(threadIdx.x / kWave));
     BinLds& L = lds_all[w];
@@ -419,10 +420,12 @@ __global__ __launch_bounds__(kBinWaves * kWave) __attribute__((amdgpu_waves_per_
         return;
     }
     // The workgroup's slice; every branch depends on wave-uniform values only.
-    const int slices = block_counter ? min(kBinSlices, (int)gridDim.x) : 1, slice = (int)(blockIdx.x % (unsigned)slices);
-    const int64_t begin = (int64_t)n_events * slice / slices, end = (int64_t)n_events * (slice + 1) / slices;
-    const unsigned groups = (gridDim.x - (unsigned)slice + (unsigned)slices - 1u) / (unsigned)slices;  // of the slice
-    int64_t turn = (int64_t)(blockIdx.x / (unsigned)slices) * kBinWaves + w;
+    const bool wide = block_counter && gridDim.x >= (unsigned)kBinSlices;
+    const unsigned slice = wide ? blockIdx.x & (kBinSlices - 1u) : (block_counter ? blockIdx.x : 0u);
+    const unsigned turn_wg = wide ? blockIdx.x >> 6 : (block_counter ? 0u : blockIdx.x);
+    const unsigned groups = wide ? (gridDim.x - slice + kBinSlices - 1u) >> 6 : 1u;  // of the slice
+    const int64_t begin = (int64_t)slice * slice_events, end = min(begin + slice_events, (int64_t)n_events);
+    int64_t turn = (int64_t)turn_wg * kBinWaves + w;
     for (;;) {
         const int64_t first = begin + turn * chunk;
         if (first >= end) break;
@@ -445,7 +448,7 @@ __global__ __launch_bounds__(kBinWaves * kWave) __attribute__((amdgpu_waves_per_
 // round trips, so the kernel's time is the longest list of one wave: with 64
 // events per wave on its own 24 us (300,000 events, 1 % candidates), shared by
 // four waves per 128 events less than half of it (whole call with the window
-// test 117 -> 101 us, together with the batched form's approximate slopes).
+// test 117 -> 101 us, together with a batched prefilter without divisions).
 constexpr int kTwoWaves = 4;
 constexpr int kTwoEvents = 2 * kWave;
 constexpr int kTwoPartCap = 512;  // layer-0 and layer-1 partials a wave keeps in LDS
@@ -887,15 +890,17 @@ int launch_binned(const trig_events_csr* ev, const trig_hits* h, const trig_para
     const int64_t n_blocks = cdiv(cdiv(n, chunk), kBinWaves);
     unsigned* counter = nullptr;
     unsigned grid = (unsigned)n_blocks;
+    int slice_events = n;
     if (p->flags & TRIG_EXEC_PERSISTENT) {
         counter = reinterpret_cast<unsigned*>(ws + L.counter_off);
         hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(kBinSlices), 0, s, counter, kBinStride);
         if (int r = check_launch("k_zero_u32")) return r;
         grid = (unsigned)std::min<int64_t>(n_blocks, (int64_t)device_cus() * kBinResident);
+        slice_events = (int)cdiv(n, std::min<int64_t>(grid, kBinSlices));
     }
     if (mark_start(s)) return fail(TRIG_EHIP, "hipEventRecord(start)");
     hipLaunchKernelGGL(k_binned<B>, dim3(grid), dim3(kBinWaves * kWave), 0, s, ev->layer_offsets, n, h->x, h->y, c,
-                       counter, chunk, counts, accept, p->out_status);
+                       counter, chunk, slice_events, counts, accept, p->out_status);
     if (int r = check_launch("k_binned")) return r;
     if (mark_stop(s)) return fail(TRIG_EHIP, "hipEventRecord(stop)");
     return TRIG_OK;
