@@ -51,7 +51,10 @@ constexpr int kPersistWaves = 4;    // waves per workgroup, persistent form
 constexpr int kPersistBatch = 4;    // work units taken per atomic
 constexpr int kDefaultTileUnits = 8;  // pair tiles (of 64 pairs) per work unit
 constexpr int kClaimsPerGroup = 8;    // claims per workgroup, pipelined batched form
-constexpr double kRuleFill = 0.85;    // built-in rule: hits per block over the LDS capacity
+constexpr int kRuleHits = 2048;       // built-in rule: hit capacity of a block, its waves
+constexpr int kRuleWaves = 4;
+constexpr double kRuleFill = 0.92;    // and hits per block over the capacity
+constexpr double kLargeMean = 109.0;  // block stealing: hits per event from which blocks hold 4096
 constexpr int kZHits = 2048;          // per-hit z: hits and waves of a block,
 constexpr int kZWaves = 4;
 constexpr int kMinZEvents = 8;        // and the events it has to hold to be used
@@ -778,10 +781,19 @@ int launch_persistent(const trig_events_csr* ev, const trig_hits* h, const Const
 __global__ void k_zero_u32(unsigned* p, int stride) { p[threadIdx.x * stride] = 0u; }
 
 // Shape of the batched form: LDS hit capacity (hb), waves per workgroup (nw)
-// and events per block (eb).  Given values are used as they are; the
-// defaults take the largest capacity whose block holds at least 8 events of
-// the batch's mean multiplicity at 60 % fill (fluctuations fit; blocks that
-// overflow are split into sub-blocks by the kernel), one wave per 1024 hits.
+// and events per block (eb).  Given values are used as they are; the default
+// is kRuleHits hits and kRuleWaves waves, eight workgroups on a CU, at every
+// multiplicity, filled to kRuleFill of the capacity by events of the batch's
+// mean size (a block that overflows is split into sub-blocks by the kernel).
+// Whole calls, MSD, this shape against 1024 hits and 2 waves and 4096 and 4:
+// a million events of 15 hits per layer 120, 140, - us; 60,000 of 100 hits 84,
+// 90, 104; 30,000 of 200 hits 156, 257, 207; 5,000 of 450 hits 290, 221, 301
+// (the binned form's field); only at 300 hits with the window test was 4096
+// faster (364 against 354).  300,000 events of 30 hits take 63.6 us at a fill of
+// 0.92 and 67.3 at 0.85 (20 and 16 events per block).  Block stealing, whose
+// registers leave fewer workgroups on a CU, keeps 4096 hits for events of more
+// than kLargeMean: 300,000 events of 15 hits per layer 132 us with 2048 (251 with
+// 1024), 60,000 of 100 hits 223 (147 with 4096).
 struct BlockShape {
     int hb, nw, eb;
 };
@@ -801,11 +813,11 @@ int events_for_fill(double fill, int hb, int nw, int n_events, int n_hits) {
 }
 
 BlockShape choose_block_shape(const trig_params* p, int n_events, int n_hits) {
-    const double mean = std::max(n_events > 0 ? (double)n_hits / n_events : 1.0, 1.0);
+    const double mean = n_events > 0 ? (double)n_hits / n_events : 1.0;
     int hb = p->block_hits;
-    if (hb <= 0) hb = kRuleFill * 1024 / mean >= 16.0 ? 1024 : kRuleFill * 2048 / mean >= 16.0 ? 2048 : 4096;
+    if (hb <= 0) hb = (p->flags & TRIG_EXEC_PERSISTENT) && mean > kLargeMean ? 4096 : kRuleHits;
     int nw = p->block_waves;
-    if (nw <= 0) nw = std::min(4, hb / 512);
+    if (nw <= 0) nw = std::min(kRuleWaves, hb / 512);
     int eb = p->block_events;
     if (eb <= 0) eb = events_for_fill(kRuleFill, hb, nw, n_events, n_hits);
     return {hb, nw, eb};

@@ -779,7 +779,8 @@ __device__ __forceinline__ void event_layout(int n0, int n1, int& R, int& T, int
 // Against one hit per lane, partials in a buffer and masked lanes, with the
 // staged block's bound on |x|, |y| cheaper by 80 cycles per wave (mag2) and
 // descriptors in lanes, the whole call takes 195 for 211 us on a million
-// events of 30 hits per layer and 239 for 288 with per-hit z; two hits per
+// events of 30 hits per layer and 239 for 288 with per-hit z (16 events per
+// block; 229 with 20); two hits per
 // lane without the rest gave 2 %.
 //
 // pre: with M >= every staged |x|, |y| and u = 2^-24, a pair that passes the
@@ -1443,8 +1444,8 @@ __device__ uint32_t wave_event_z(const Consts& c, const float* __restrict__ x, c
 // that are malformed or do not fit in LDS go event by event to wave_event_z.
 // Bound by HBM latency and the pair scan together, as k_block.  1M staggered
 // events of 30 hits per layer, whole call: 0.511 ms with a wave per event from
-// HBM (nine loads of 4 bytes per lane and four divisions for each), 0.239 ms
-// now (4.6 TB/s of 17 bytes per event and 12 per hit).
+// HBM (nine loads of 4 bytes per lane and four divisions for each), 0.229 ms
+// now (4.8 TB/s of 17 bytes per event and 12 per hit).
 template <class P, class T, int HB, int NW, int EB>
 __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(block_waves_per_simd<HB, NW, EB>())))
 void k_block_z(const int32_t* __restrict__ off, int n_events, const float* __restrict__ x,
