@@ -608,22 +608,14 @@ Consts make_consts(const trig_params* p, int n_hits) {
     c.pre_win = std::max(p->slope_window[0], p->slope_window[1]);
     c.win_x = p->slope_window[0];
     c.win_y = p->slope_window[1];
-    {
-        // Scaled combination of two layers (trig_block.hpp, direct scan)
-        const bool win = p->test == TRIG_TEST_SLOPE_WINDOW;
-        const double u0 = win ? 1.0 / (double)c.z0 : (double)c.U0, u1 = win ? -1.0 / (double)c.z1 : (double)c.U1;
-        const double k = u1 / u0;
-        const auto within = [](double v) { return std::fabs(v) >= 0x1p-60 && std::fabs(v) <= 0x1p60; };
-        const bool ok = within(k) && within(u0) && within(u1);
-        c.dir_k[0] = ok ? (float)k : 1.0f;
-        c.dir_k[1] = ok ? (float)(1.0 / k) : 1.0f;
-        const double u[2] = {u0, u1};
-        for (int s = 0; s < 2; ++s) {
-            c.dir_scale[s] = ok ? (float)((1.0 + 0x1p-18) / std::fabs(u[s])) : 1.0f;
-            c.dir_slack[s] = ok ? (1.0f + std::fabs(c.dir_k[s])) * 0x1p-19f : 1.0f;
-        }
-        c.dir_slack0 = ok ? 0x1p-80f : INFINITY;
+    const bool win = p->test == TRIG_TEST_SLOPE_WINDOW;
+    const DirectBounds d = direct_bounds(win ? 1.0 / (double)c.z0 : (double)c.U0, win ? -1.0 / (double)c.z1 : (double)c.U1);
+    for (int l = 0; l < 2; ++l) {
+        c.dir_k[l] = d.k[l];
+        c.dir_scale[l] = d.scale[l];
+        c.dir_slack[l] = d.slack[l];
     }
+    c.dir_limit = d.limit;
     c.bin_r = p->test == TRIG_TEST_SLOPE_WINDOW ? c.win_x : std::nextafter(c.beta_x, INFINITY);
     const bool two = (p->flags & TRIG_ACCEPT_TWO_PARTICLES) != 0;
     c.min_triplets = two ? 2 : p->min_triplets;  // two particles need two passing triplets

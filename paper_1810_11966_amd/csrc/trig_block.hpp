@@ -36,6 +36,7 @@
 // once per hit into a per-wave LDS buffer and read with a broadcast.
 #pragma once
 
+#include "trig_bounds.hpp"
 #include "trig_device.hpp"
 
 namespace trig {
@@ -783,21 +784,16 @@ __device__ __forceinline__ void event_layout(int n0, int n1, int& R, int& T, int
 // block; 229 with 20); two hits per
 // lane without the rest gave 2 %.
 //
-// pre: with M >= every staged |x|, |y| and u = 2^-24, a pair that passes the
-// exact pair test has, in the MSD tests' units,
-//     |U0 c0 + U1 c1| <= b (1 + 2u) + 1.01 u (|U0| + |U1|) M + 2^-148
-// in a plane with bound b, and s lies within (3.1 u |k| + 1.1 u) M + 2^-148 of
-// (U0 c0 + U1 c1) / U_B; the window's rounded quotients give the same form
-// with U_l = 1 / z_l.  So s <= (b / |U_B|) (1 + 2u) + 4.3 u (1 + |k|) M + 2^-80
-// while 2^-60 <= z0, z1 and |k| in [2^-60, 2^60]; the constants hold two
-// planes' sum with 4 times that slack, and +inf outside those ranges.
+// The bound on a passing pair's score and its derivation: direct_bounds and
+// direct_pre (trig_bounds.hpp).
+//
 // A block's factors and bounds for both orientations, lane 2 b + S of one
 // register (b: the bound), read by v_readlane: as scalars they would be
 // spilled over the event loop, eight at a time.
 __device__ __forceinline__ float direct_consts(const Consts& c, const PairBounds& pb, float M) {
     const int lane = (int)lane_id();
-    const float p0 = (pb.pre * c.dir_scale[0] + c.dir_slack[0] * M) + c.dir_slack0;
-    const float p1 = (pb.pre * c.dir_scale[1] + c.dir_slack[1] * M) + c.dir_slack0;
+    const float p0 = trig_host::direct_pre(pb.pre, c.dir_scale[0], c.dir_slack[0], c.dir_limit, M);
+    const float p1 = trig_host::direct_pre(pb.pre, c.dir_scale[1], c.dir_slack[1], c.dir_limit, M);
     return lane < 2 ? (lane ? c.dir_k[1] : c.dir_k[0]) : (lane & 1 ? p1 : p0);
 }
 __device__ __forceinline__ float direct_const(float d, int lane) {

@@ -3,8 +3,8 @@
 // necessary conditions on partial sums that the pruned and binned forms use
 // to skip pairs and cells without changing a count.
 //
-// Plain C++ (no HIP): the library's host code and a CPU test (g++) compile
-// the same file.  Every function is deterministic and exact in the sense its
+// Plain C++: the library's host code and CPU tests (g++) compile the same
+// file; the functions marked TRIG_HD also run in the kernels.  Every function is deterministic and exact in the sense its
 // comment states; the fit bounds are rigorous upper bounds derived below.
 //
 // Notation (paper Sec. 3.2, step 2: a line through the vertex, c = m z, per
@@ -48,6 +48,12 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+
+#ifdef __HIPCC__
+#define TRIG_HD __host__ __device__
+#else
+#define TRIG_HD
+#endif
 
 namespace trig_host {
 
@@ -205,6 +211,47 @@ inline SlopeBounds slope_bounds(float qmax) {
     const LD A1 = (1 + u) * (r2 * r2 * u / (1 - u) + 2 * u);
     const LD up = 1 / ((1 - u) * (1 - u) * (1 - u) * (1 - u) * (1 - u));
     return SlopeBounds{round_up_f32(A0 * up * (1 + slack)), round_up_f32(A1 * up * (1 + slack))};
+}
+
+// Batched form's prefilter on staged coordinates (trig_block.hpp, direct
+// scan).  A pair's score in a plane is |s|, s = fl(c_B + fl(k c_L)) with k =
+// u_L / u_B, where the pair test looks at u_0 c_0 + u_1 c_1 (MSD: the basis
+// coefficients; window: 1 / z_0 and -1 / z_1); index 0: layer 1 is layer L,
+// index 1: layer 0.  direct_pre() is the bound on the two planes' scores of a
+// pair that passes, given the pair test's bound `pre` on its own quantity and
+// M >= every |c|.  With u = 2^-24, a passing pair has in a plane with bound b
+//     |u_0 c_0 + u_1 c_1| <= b (1 + 2u) + 1.01 u (|u_0| + |u_1|) M + 2^-148
+// (MSD: the rounded products and sum; window: the rounded quotients), and s
+// lies within (3.1 u |k| + 1.1 u) M + 2^-148 of (u_0 c_0 + u_1 c_1) / u_B as
+// long as neither the product nor the sum overflows, so
+//     |s| <= (b / |u_B|) (1 + 2u) + 4.3 u (1 + |k|) M + 2^-80
+// while |u_0|, |u_1| and |k| lie in [2^-60, 2^60]; the constants hold two
+// planes' sum with 4 times that slack.  From M max(1, |k|) = 2^126 on (where
+// product and sum could overflow) and outside those ranges no bound holds:
+// +inf, every event goes to the exact pass.
+struct DirectBounds {
+    float k[2], scale[2], slack[2];
+    float limit;  // of M
+};
+
+inline DirectBounds direct_bounds(double u0, double u1) {
+    const auto within = [](double v) { return std::fabs(v) >= 0x1p-60 && std::fabs(v) <= 0x1p60; };
+    const double k = u1 / u0;
+    DirectBounds d{{1.0f, 1.0f}, {1.0f, 1.0f}, {1.0f, 1.0f}, 0.0f};
+    if (!(within(k) && within(u0) && within(u1))) return d;
+    const double u[2] = {u0, u1};
+    d.k[0] = (float)k;
+    d.k[1] = (float)(1.0 / k);
+    for (int s = 0; s < 2; ++s) {
+        d.scale[s] = (float)((1.0 + 0x1p-18) / std::fabs(u[s]));
+        d.slack[s] = (1.0f + std::fabs(d.k[s])) * 0x1p-19f;
+    }
+    d.limit = 0x1p126f / std::fmax(1.0f, std::fmax(std::fabs(d.k[0]), std::fabs(d.k[1])));
+    return d;
+}
+
+TRIG_HD inline float direct_pre(float pre, float scale, float slack, float limit, float M) {
+    return M < limit ? (pre * scale + slack * M) + 0x1p-80f : __builtin_inff();
 }
 
 }  // namespace trig_host

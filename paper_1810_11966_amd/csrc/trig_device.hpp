@@ -48,9 +48,8 @@ struct Consts {
     // TRIG_TEST_SLOPE_WINDOW
     float win_x, win_y;
     // Batched form's prefilter on staged coordinates, by the layer in the
-    // lanes (index 0: layer 1, index 1: layer 0): the factor on that layer,
-    // and a passing pair's score is at most (pre scale + slack M) + slack0
-    float dir_k[2], dir_scale[2], dir_slack[2], dir_slack0;
+    // lanes (index 0: layer 1, index 1: layer 0): trig_host::DirectBounds
+    float dir_k[2], dir_scale[2], dir_slack[2], dir_limit;
     // Binned form, MSD_BASIS and window: half-width of the key interval
     // around a hit's centre (MSD_BASIS: the binary32 value above beta_x;
     // window: win_x).
