@@ -495,7 +495,8 @@ struct WindowBin {
 // 200 hits per layer, 89 of its 122 us; the same call takes 0.103 ms now (1M
 // mixture events 0.559 -> 0.483 ms).
 __device__ __forceinline__ uint32_t bin_cell(float key, float inv) {
-    // saturating and truncating: negative values and NaN give 0; non-decreasing in key
+    // saturating and truncating: negative values and NaN give 0; non-decreasing
+    // in key for the scales that cell_scale gives
     uint32_t t;
     asm("v_cvt_u32_f32 %0, %1" : "=v"(t) : "v"(key * inv + 0.5f * (float)kBinCap));
     return min(t, (uint32_t)(kBinCap - 1));
@@ -529,9 +530,8 @@ __device__ uint32_t wave_event_binned(const Consts& c, const float* __restrict__
     const float M = __builtin_bit_cast(float, m);
     const BinBounds bb = B::bounds(c, M);
     const float K = B::key_max(c, M);
-    // any scale >= 0 keeps the cells monotone; the hardware reciprocal is
-    // enough to spread the keys over them
-    const float inv = (K > 0.0f && K < __builtin_inff()) ? __builtin_amdgcn_rcpf(K) * (0.5f * (float)kBinCap) : 0.0f;
+    // (the hardware reciprocal is enough to spread the keys over the cells)
+    const float inv = trig_host::cell_scale(K, __builtin_amdgcn_rcpf(K), (float)kBinCap);
     uint32_t* hist = reinterpret_cast<uint32_t*>(L.a1);
     static_assert(kBinCap == 4 * kWave, "four cells per lane");
     reinterpret_cast<uint4*>(hist)[lane] = make_uint4(0u, 0u, 0u, 0u);

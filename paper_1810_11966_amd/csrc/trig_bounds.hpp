@@ -254,4 +254,15 @@ TRIG_HD inline float direct_pre(float pre, float scale, float slack, float limit
     return M < limit ? (pre * scale + slack * M) + 0x1p-80f : __builtin_inff();
 }
 
+// Binned form: the scale of a layer's cells, cell(v) = min(trunc(v scale +
+// n / 2), n - 1) with values below 0 and NaN in cell 0, for keys within [-K, K]
+// and rcp an approximation of 1 / K (0 or +inf where it leaves the normal
+// range).  A finite scale above 0 keeps cell() non-decreasing over all
+// binary32 arguments, infinite ones included; a scale of 0 would put the end
+// +inf of an interval (0 inf = NaN) below its hits.  At 2^-126 every finite
+// key lies within 4 cells of the middle.
+TRIG_HD inline float cell_scale(float K, float rcp, float n) {
+    return K > 0.0f ? __builtin_fminf(__builtin_fmaxf(rcp * (0.5f * n), 0x1p-126f), 0x1.fffffep127f) : 0x1p-126f;
+}
+
 }  // namespace trig_host

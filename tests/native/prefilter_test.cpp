@@ -1,6 +1,6 @@
-// Host checks of the batched form's prefilter bound
-// (paper_1810_11966_amd/csrc/trig_bounds.hpp, direct_bounds and direct_pre).
-// Built with g++ -ffp-contract=off by tests/test_prefilter.py and run on the
+// Host checks of the batched form's prefilter bound and of the binned form's
+// cells (paper_1810_11966_amd/csrc/trig_bounds.hpp: direct_bounds, direct_pre,
+// cell_scale).  Built with g++ -ffp-contract=off by tests/test_prefilter.py and run on the
 // CPU (x86-64 SSE binary32 arithmetic, round to nearest even, subnormals
 // kept).
 //
@@ -9,6 +9,9 @@
 // positions whose ratio spans the bound's range and more: every pair that
 // passes has a score within direct_pre for M = max(|c0|, |c1|), in both
 // orientations.
+//
+// Keys and intervals up to the ends of binary32: the cells of the interval's
+// ends enclose the cell of every key inside it.
 #include <algorithm>
 #include <cfloat>
 #include <cmath>
@@ -92,8 +95,50 @@ static void test_direct_bounds() {
     CHECK(2 * passes - infinite > 1000000);
 }
 
+// The kernel's cell of a value (its conversion truncates and saturates, NaN
+// and negative values give 0).
+static uint32_t cell(float v, float scale) {
+    volatile float p = v * scale;
+    volatile float t = p + 128.0f;
+    if (!((float)t > 0.0f)) return 0;
+    return (float)t >= 256.0f ? 255u : (uint32_t)(float)t;
+}
+
+static void test_cells() {
+    std::mt19937_64 rng(99);
+    std::uniform_real_distribution<double> U(-1.0, 1.0);
+    const double Ks[] = {0.0, 1e-45, 1e-40, 1.2e-38, 1e-20, 0.45, 300.0, 1e20, 8e37, 9e37, 1.7e38, 3.4e38, INFINITY};
+    const float big = FLT_MAX, inf = INFINITY;
+    long checked = 0;
+    for (double Kd : Ks) {
+        const float K = (float)Kd;
+        // the reciprocal as it is, and flushed to 0 or overflowing
+        for (float rcp : {1.0f / K, 0.0f, inf}) {
+            const float scale = cell_scale(K, rcp, 256.0f);
+            CHECK(std::isfinite(scale) && scale > 0.0f);
+            for (int it = 0; it < 3000; ++it) {
+                const float key = it % 9 ? (float)std::max(-(double)big, std::min((double)big, Kd * U(rng))) : 0.0f;
+                const float radius[] = {0.0f, 1e-45f, 1e-38f, (float)(std::min(Kd, 1e37) * std::fabs(U(rng))), 3e38f, big, inf};
+                for (float r : radius)
+                    for (float mid : {key, (float)(key * (1.0 + 1e-3 * U(rng))), 0.0f, big, -big, (float)(3e38 * U(rng))}) {
+                        volatile float lo = mid - r, hi = mid + r;
+                        if (!(std::isfinite(key) && (float)lo <= key && key <= (float)hi)) continue;
+                        ++checked;
+                        CHECK(cell((float)lo, scale) <= cell(key, scale) && cell(key, scale) <= cell((float)hi, scale));
+                    }
+            }
+        }
+    }
+    // keys spread over the cells
+    const float s = cell_scale(200.0f, 1.0f / 200.0f, 256.0f);
+    CHECK(cell(-200.0f, s) == 0 && cell(-100.0f, s) == 64 && cell(0.0f, s) == 128 && cell(199.0f, s) == 255);
+    std::printf("cells: %ld keys in intervals\n", checked);
+    CHECK(checked > 100000);
+}
+
 int main() {
     test_direct_bounds();
+    test_cells();
     if (failures) {
         std::printf("%ld checks failed\n", failures);
         return 1;

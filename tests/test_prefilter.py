@@ -1,6 +1,7 @@
 """Host constants of the prefilters (csrc/trig_bounds.hpp), built with g++ and
 run on the CPU: the bound of the batched form's scan on pairs that pass the
-pair test, up to the largest binary32 (paper Sec. 3.2, step 2)."""
+pair test and the binned form's cells, up to the largest binary32 (paper Sec.
+3.2, step 2)."""
 import os
 import subprocess
 
