@@ -615,7 +615,6 @@ Consts make_consts(const trig_params* p, int n_hits) {
         c.dir_scale[l] = d.scale[l];
         c.dir_slack[l] = d.slack[l];
     }
-    c.dir_limit = d.limit;
     c.bin_r = p->test == TRIG_TEST_SLOPE_WINDOW ? c.win_x : std::nextafter(c.beta_x, INFINITY);
     const bool two = (p->flags & TRIG_ACCEPT_TWO_PARTICLES) != 0;
     c.min_triplets = two ? 2 : p->min_triplets;  // two particles need two passing triplets

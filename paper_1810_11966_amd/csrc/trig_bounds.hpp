@@ -226,18 +226,17 @@ inline SlopeBounds slope_bounds(float qmax) {
 // long as neither the product nor the sum overflows, so
 //     |s| <= (b / |u_B|) (1 + 2u) + 4.3 u (1 + |k|) M + 2^-80
 // while |u_0|, |u_1| and |k| lie in [2^-60, 2^60]; the constants hold two
-// planes' sum with 4 times that slack.  From M max(1, |k|) = 2^126 on (where
-// product and sum could overflow) and outside those ranges no bound holds:
-// +inf, every event goes to the exact pass.
+// planes' sum with 4 times that slack.  From M (1 + |k|) = 2^126 on, where
+// product or sum could overflow, and outside those ranges (slack +inf) no
+// bound holds: +inf, every event goes to the exact pass.
 struct DirectBounds {
     float k[2], scale[2], slack[2];
-    float limit;  // of M
 };
 
 inline DirectBounds direct_bounds(double u0, double u1) {
     const auto within = [](double v) { return std::fabs(v) >= 0x1p-60 && std::fabs(v) <= 0x1p60; };
     const double k = u1 / u0;
-    DirectBounds d{{1.0f, 1.0f}, {1.0f, 1.0f}, {1.0f, 1.0f}, 0.0f};
+    DirectBounds d{{1.0f, 1.0f}, {1.0f, 1.0f}, {INFINITY, INFINITY}};
     if (!(within(k) && within(u0) && within(u1))) return d;
     const double u[2] = {u0, u1};
     d.k[0] = (float)k;
@@ -246,12 +245,12 @@ inline DirectBounds direct_bounds(double u0, double u1) {
         d.scale[s] = (float)((1.0 + 0x1p-18) / std::fabs(u[s]));
         d.slack[s] = (1.0f + std::fabs(d.k[s])) * 0x1p-19f;
     }
-    d.limit = 0x1p126f / std::fmax(1.0f, std::fmax(std::fabs(d.k[0]), std::fabs(d.k[1])));
     return d;
 }
 
-TRIG_HD inline float direct_pre(float pre, float scale, float slack, float limit, float M) {
-    return M < limit ? (pre * scale + slack * M) + 0x1p-80f : __builtin_inff();
+TRIG_HD inline float direct_pre(float pre, float scale, float slack, float M) {
+    const float t = slack * M;
+    return t < 0x1p107f ? (pre * scale + t) + 0x1p-80f : __builtin_inff();
 }
 
 // Binned form: the scale of a layer's cells, cell(v) = min(trunc(v scale +

@@ -49,7 +49,7 @@ struct Consts {
     float win_x, win_y;
     // Batched form's prefilter on staged coordinates, by the layer in the
     // lanes (index 0: layer 1, index 1: layer 0): trig_host::DirectBounds
-    float dir_k[2], dir_scale[2], dir_slack[2], dir_limit;
+    float dir_k[2], dir_scale[2], dir_slack[2];
     // Binned form, MSD_BASIS and window: half-width of the key interval
     // around a hit's centre (MSD_BASIS: the binary32 value above beta_x;
     // window: win_x).

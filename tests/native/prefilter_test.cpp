@@ -45,7 +45,7 @@ static void check_pair(const DirectBounds& d, float pre, float c0, float c1) {
     const float M = std::max(std::fabs(c0), std::fabs(c1));
     ++passes;
     for (int o = 0; o < 2; ++o) {
-        const float s = score(d, o, c0, c1), bound = direct_pre(pre, d.scale[o], d.slack[o], d.limit, M);
+        const float s = score(d, o, c0, c1), bound = direct_pre(pre, d.scale[o], d.slack[o], M);
         infinite += std::isinf(bound);
         // the kernel takes the event on unless every score is above the bound
         CHECK(s <= bound);
@@ -90,7 +90,7 @@ static void test_direct_bounds() {
     // The bound prunes at ordinary coordinates: close to the pair test's own.
     const DirectBounds n = direct_bounds(1.0 / 400.0, -1.0 / 410.0);
     for (int o = 0; o < 2; ++o)
-        CHECK(direct_pre(0.005f, n.scale[o], n.slack[o], n.limit, 400.0f) < 1.001f * 0.005f * (o ? 410.0f : 400.0f));
+        CHECK(direct_pre(0.005f, n.scale[o], n.slack[o], 400.0f) < 1.001f * 0.005f * (o ? 410.0f : 400.0f));
     std::printf("direct bounds: %ld passing pairs, %ld infinite bounds\n", passes, infinite);
     CHECK(2 * passes - infinite > 1000000);
 }
