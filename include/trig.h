@@ -234,7 +234,9 @@ int trig_params_init(trig_params *p);
 int trig_params_check(const trig_params *p);
 
 /* Bytes of device workspace trig_select needs for this batch and these
- * parameters (0 for the plain form without compaction).  Host-only call: it
+ * parameters (0 for the plain form without compaction).  TRIG_EXEC_PERSISTENT
+ * with pruning or binning, and TRIG_EXEC_AUTOTUNE, also run with 16,128 bytes
+ * less (their counters side by side: slower with binning).  Host-only call: it
  * reads ev->n_events and p->flags, never device memory.  Returns 0 for invalid
  * arguments as well; trig_select then reports the error. */
 size_t trig_workspace_bytes(const trig_events_csr *ev, const trig_params *p);

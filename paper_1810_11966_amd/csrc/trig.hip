@@ -374,7 +374,7 @@ __global__ __launch_bounds__(kScanBlock) void k_finalize(int n_events, Consts c,
 constexpr int kBinWaves = 4;     // waves (one event each) per workgroup
 constexpr int kBinResident = 8;  // binned workgroups per CU (LDS bound)
 constexpr int kBinSlices = 64;   // block stealing: slices of the events, each with its own counter,
-constexpr int kBinStride = 64;   // this many words apart
+constexpr int kBinStride = 64;   // this many words apart (a workspace with room for 256 bytes of them: one)
 static_assert(kBinSlices == 64, "k_binned shifts by 6");
 
 // A wave counts runs of `chunk` consecutive events.  Non-persistent when
@@ -392,7 +392,7 @@ static_assert(kBinSlices == 64, "k_binned shifts by 6");
 template <class B>
 __global__ __launch_bounds__(kBinWaves * kWave) __attribute__((amdgpu_waves_per_eu(kBinResident))) void k_binned(
     const int32_t* __restrict__ off, int n_events, const float* __restrict__ x, const float* __restrict__ y,
-    Consts c, unsigned* block_counter, int chunk, int slice_events, int32_t* __restrict__ counts,
+    Consts c, unsigned* block_counter, int counter_stride, int chunk, int slice_events, int32_t* __restrict__ counts,
     uint8_t* __restrict__ accept, uint32_t* status) {
     __shared__ __align__(16) BinLds lds_all[kBinWaves];
     const int w = uniform_i((int)(threadIdx.x / kWave));
@@ -436,7 +436,7 @@ __global__ __launch_bounds__(kBinWaves * kWave) __attribute__((amdgpu_waves_per_
         for (int e = (int)first; e < last; ++e) one_event(e);
         if (!block_counter) break;
         unsigned claim = 0u;
-        if (lane_id() == 0) claim = atomicAdd(&block_counter[slice * kBinStride], 1u);
+        if (lane_id() == 0) claim = atomicAdd(&block_counter[slice * counter_stride], 1u);
         turn = (int64_t)groups * kBinWaves + (int64_t)(unsigned)uniform_i((int)claim);
     }
 }
@@ -672,10 +672,13 @@ int validate_params(const trig_params* p, bool need_outputs) {
 
 struct Layout {
     size_t compact_off = 0, units_off = 0, upart_off = 0, counter_off = 0, total = 0;
-    int compact_blocks = 0, unit_blocks = 0;
+    int compact_blocks = 0, unit_blocks = 0, counter_stride = 1;
 };
 
-Layout layout(int n_events, uint32_t flags) {
+// `bytes`: the workspace there is.  One without room for the stealing
+// counters' own lines, but for 256 bytes of counters, keeps them side by side
+// (the binned form's claims are then slower, see k_binned).
+Layout layout(int n_events, uint32_t flags, size_t bytes) {
     Layout L;
     size_t at = 0;
     if (flags & TRIG_OUT_COMPACT) {
@@ -685,7 +688,11 @@ Layout layout(int n_events, uint32_t flags) {
     }
     if ((flags & TRIG_EXEC_PERSISTENT) && (flags & (TRIG_EXEC_PRUNED | TRIG_EXEC_BINNED))) {
         L.counter_off = at;  // block counters only
-        at += 4 * kBinSlices * kBinStride;
+        constexpr size_t kSmall = 4 * kBinSlices, kLines = kSmall * kBinStride;
+        static_assert(kSmall == 256, "aligned to 256 bytes");
+        const bool lines = bytes >= at + kLines || bytes < at + kSmall;
+        L.counter_stride = lines ? kBinStride : 1;
+        at += lines ? kLines : kSmall;
     } else if (flags & TRIG_EXEC_PERSISTENT) {
         L.unit_blocks = (int)std::max<int64_t>(1, cdiv(n_events, kScanBlock));
         L.counter_off = at;
@@ -896,14 +903,14 @@ int launch_binned(const trig_events_csr* ev, const trig_hits* h, const trig_para
     int slice_events = n;
     if (p->flags & TRIG_EXEC_PERSISTENT) {
         counter = reinterpret_cast<unsigned*>(ws + L.counter_off);
-        hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(kBinSlices), 0, s, counter, kBinStride);
+        hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(kBinSlices), 0, s, counter, L.counter_stride);
         if (int r = check_launch("k_zero_u32")) return r;
         grid = (unsigned)std::min<int64_t>(n_blocks, (int64_t)device_cus() * kBinResident);
         slice_events = (int)cdiv(n, std::min<int64_t>(grid, kBinSlices));
     }
     if (mark_start(s)) return fail(TRIG_EHIP, "hipEventRecord(start)");
     hipLaunchKernelGGL(k_binned<B>, dim3(grid), dim3(kBinWaves * kWave), 0, s, ev->layer_offsets, n, h->x, h->y, c,
-                       counter, chunk, slice_events, counts, accept, p->out_status);
+                       counter, L.counter_stride, chunk, slice_events, counts, accept, p->out_status);
     if (int r = check_launch("k_binned")) return r;
     if (mark_stop(s)) return fail(TRIG_EHIP, "hipEventRecord(stop)");
     return TRIG_OK;
@@ -1094,7 +1101,7 @@ int trig_params_check(const trig_params* p) {
 
 size_t trig_workspace_bytes(const trig_events_csr* ev, const trig_params* p) {
     if (!ev || !p || ev->n_events < 0) return 0;
-    return layout(ev->n_events, layout_flags(p)).total;
+    return layout(ev->n_events, layout_flags(p), SIZE_MAX).total;
 }
 
 int trig_select(const trig_events_csr* ev, const trig_hits* hits, const trig_params* p_in,
@@ -1112,7 +1119,7 @@ int trig_select(const trig_events_csr* ev, const trig_hits* hits, const trig_par
     }
     const int n = ev->n_events;
     if (n > 0 && (!out_counts || !out_accept)) return fail(TRIG_EINVAL, "out_counts or out_accept is NULL");
-    const Layout L = layout(n, layout_flags(p_in));
+    const Layout L = layout(n, layout_flags(p_in), p->workspace_bytes);
     if (L.total && (!p->workspace || p->workspace_bytes < L.total))
         return fail(TRIG_EWORKSPACE, "workspace smaller than trig_workspace_bytes()");
     if (L.total && (reinterpret_cast<uintptr_t>(p->workspace) & 255))
