@@ -17,8 +17,9 @@
 //   k_block        batched form: blocks of events staged in LDS, exact pair
 //                  pruning (trig_block.hpp); optionally persistent
 //   k_binned       binned form: one wave per event, slope-cell binning of
-//                  layers 1 and 2 in LDS (trig_binned.hpp); optionally
-//                  persistent
+//                  layer 1, and of layer 2 where many pairs survive, in LDS
+//                  (trig_binned.hpp); k_bin_runs: a wave per run of events;
+//                  k_bin_steal: persistent
 //   k_compact_*    ordered list of accepted event ids
 #include <hip/hip_runtime.h>
 
@@ -377,24 +378,30 @@ constexpr int kBinSlices = 64;   // block stealing: slices of the events, each w
 constexpr int kBinStride = 64;   // this many words apart (a workspace with room for 256 bytes of them: one)
 static_assert(kBinSlices == 64, "k_binned shifts by 6");
 
-// A wave counts runs of `chunk` consecutive events.  Non-persistent when
-// block_counter == nullptr: wave g takes run g.  Otherwise the events are cut
-// into kBinSlices slices of slice_events (fewer workgroups: a slice each),
-// workgroup b working on slice b % kBinSlices: a wave takes its first run by its own number and the others from the slice's
-// counter (zero at launch; one atomic per run), until none is left: no
-// barrier, and no LDS beyond the waves' cells (8 workgroups fit on a CU).
+// A wave counts runs of `chunk` consecutive events.  kBinSingle, kBinRun: wave
+// g takes run g (a run of one event without the loop around it is 5 to 10 %
+// faster than the loop taken once).  kBinSteal: the runs are dealt out to kBinSlices slices (fewer workgroups: a slice each), one of every
+// kBinSlices neighbours to each slice (turn t of slice s: run 64 t +
+// (s + t) % 64), workgroup b working on slice b % kBinSlices: a wave takes its
+// first run by its own number and the others from the slice's counter (zero at
+// launch; one atomic per run), until none is left: no barrier, and no LDS
+// beyond the waves' cells (8 workgroups fit on a CU).  Dealt out, a cluster of
+// large events is shared by all slices: 300,000 events, the first 6,000 of 240
+// hits per layer and the others of 10, take 185 us, with slices of consecutive
+// runs 630 (and 136 or 135 with the large events spread out).
 // Atomics on one 256-byte line pass one by one, some 5 ns each (1M mixture
 // events with all claims on one word: 0.91 ms, of which they were most), so
 // each slice's counter has a line of its own.
 // Events with more than kBinCap hits in layer 1 or 2 take the pair-pruned
 // path from HBM.  The register budget is held to kBinResident waves per
 // SIMD, the occupancy its LDS allows (one wave per SIMD per workgroup).
-template <class B>
-__global__ __launch_bounds__(kBinWaves * kWave) __attribute__((amdgpu_waves_per_eu(kBinResident))) void k_binned(
-    const int32_t* __restrict__ off, int n_events, const float* __restrict__ x, const float* __restrict__ y,
-    Consts c, unsigned* block_counter, int counter_stride, int chunk, int slice_events, int32_t* __restrict__ counts,
-    uint8_t* __restrict__ accept, uint32_t* status) {
-    __shared__ __align__(16) BinLds lds_all[kBinWaves];
+enum BinMode { kBinSingle, kBinRun, kBinSteal };
+template <class B, BinMode MODE>
+__device__ __forceinline__ void binned_waves(BinLds* lds_all, const int32_t* __restrict__ off, int n_events,
+                                             const float* __restrict__ x, const float* __restrict__ y, const Consts& c,
+                                             unsigned* block_counter, int counter_stride, int chunk,
+                                             int32_t* __restrict__ counts, uint8_t* __restrict__ accept,
+                                             uint32_t* status) {
     const int w = uniform_i((int)(threadIdx.x / kWave));
     BinLds& L = lds_all[w];
     auto one_event = [&](int e) {
@@ -415,31 +422,51 @@ __global__ __launch_bounds__(kBinWaves * kWave) __attribute__((amdgpu_waves_per_
         }
         if (lane_id() == 0) write_result(e, cnt, c, counts, accept, status);
     };
-    if (!block_counter && chunk == 1) {
-        // (its own copy: one event without the loop around it is 5 to 10 %
-        // faster than the loop taken once)
-        const int64_t e = (int64_t)blockIdx.x * kBinWaves + w;
-        if (e < n_events) one_event((int)e);
-        return;
-    }
-    // The workgroup's slice; every branch depends on wave-uniform values only.
-    const bool wide = block_counter && gridDim.x >= (unsigned)kBinSlices;
-    const unsigned slice = wide ? blockIdx.x & (kBinSlices - 1u) : (block_counter ? blockIdx.x : 0u);
-    const unsigned turn_wg = wide ? blockIdx.x >> 6 : (block_counter ? 0u : blockIdx.x);
-    const unsigned groups = wide ? (gridDim.x - slice + kBinSlices - 1u) >> 6 : 1u;  // of the slice
-    const int64_t begin = (int64_t)slice * slice_events, end = min(begin + slice_events, (int64_t)n_events);
-    int64_t turn = (int64_t)turn_wg * kBinWaves + w;
-    for (;;) {
-        const int64_t first = begin + turn * chunk;
-        if (first >= end) break;
-        const int last = (int)min(first + chunk, end);
-        for (int e = (int)first; e < last; ++e) one_event(e);
-        if (!block_counter) break;
-        unsigned claim = 0u;
-        if (lane_id() == 0) claim = atomicAdd(&block_counter[slice * counter_stride], 1u);
-        turn = (int64_t)groups * kBinWaves + (int64_t)(unsigned)uniform_i((int)claim);
+    // Every branch below depends on wave-uniform values only.
+    if constexpr (MODE != kBinSteal) {
+        const int64_t first = ((int64_t)blockIdx.x * kBinWaves + w) * (MODE == kBinSingle ? 1 : chunk);
+        if constexpr (MODE == kBinSingle) {
+            if (first < n_events) one_event((int)first);
+        } else {
+            if (first >= n_events) return;
+            const int last = (int)min(first + chunk, (int64_t)n_events);
+            for (int e = (int)first; e < last; ++e) one_event(e);
+        }
+    } else {
+        const bool wide = gridDim.x >= (unsigned)kBinSlices;
+        const unsigned n_slices = wide ? (unsigned)kBinSlices : gridDim.x;
+        const unsigned slice = wide ? blockIdx.x & (kBinSlices - 1u) : blockIdx.x;  // the workgroup's
+        const unsigned groups = wide ? (gridDim.x - slice + kBinSlices - 1u) >> 6 : 1u;  // of the slice
+        unsigned turn = (wide ? blockIdx.x >> 6 : 0u) * kBinWaves + (unsigned)w;
+        for (;;) {
+            const unsigned place = wide ? (slice + turn) & (kBinSlices - 1u) : (slice + turn) % n_slices;
+            const int64_t first = ((int64_t)turn * n_slices + place) * chunk;
+            if (first >= n_events) break;  // (the slice's later runs lie beyond too)
+            const int last = (int)min(first + chunk, (int64_t)n_events);
+            for (int e = (int)first; e < last; ++e) one_event(e);
+            unsigned claim = 0u;
+            if (lane_id() == 0) claim = atomicAdd(&block_counter[slice * counter_stride], 1u);
+            turn = groups * kBinWaves + (unsigned)uniform_i((int)claim);
+        }
     }
 }
+
+// One kernel per mode: with all in one, the others' copies cost registers (3 to
+// 5 % of the time).
+#define TRIG_BINNED_KERNEL(NAME, MODE)                                                                               \
+    template <class B>                                                                                               \
+    __global__ __launch_bounds__(kBinWaves * kWave) __attribute__((amdgpu_waves_per_eu(kBinResident))) void NAME(    \
+        const int32_t* __restrict__ off, int n_events, const float* __restrict__ x, const float* __restrict__ y,     \
+        Consts c, unsigned* block_counter, int counter_stride, int chunk, int32_t* __restrict__ counts,              \
+        uint8_t* __restrict__ accept, uint32_t* status) {                                                            \
+        __shared__ __align__(16) BinLds lds_all[kBinWaves];                                                          \
+        binned_waves<B, MODE>(lds_all, off, n_events, x, y, c, block_counter, counter_stride, chunk, counts, accept, \
+                              status);                                                                               \
+    }
+TRIG_BINNED_KERNEL(k_binned, kBinSingle)
+TRIG_BINNED_KERNEL(k_bin_runs, kBinRun)
+TRIG_BINNED_KERNEL(k_bin_steal, kBinSteal)
+#undef TRIG_BINNED_KERNEL
 
 // -------------------------------------------------- two-particle mode ---
 
@@ -900,17 +927,16 @@ int launch_binned(const trig_events_csr* ev, const trig_hits* h, const trig_para
     const int64_t n_blocks = cdiv(cdiv(n, chunk), kBinWaves);
     unsigned* counter = nullptr;
     unsigned grid = (unsigned)n_blocks;
-    int slice_events = n;
     if (p->flags & TRIG_EXEC_PERSISTENT) {
         counter = reinterpret_cast<unsigned*>(ws + L.counter_off);
         hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(kBinSlices), 0, s, counter, L.counter_stride);
         if (int r = check_launch("k_zero_u32")) return r;
         grid = (unsigned)std::min<int64_t>(n_blocks, (int64_t)device_cus() * kBinResident);
-        slice_events = (int)cdiv(n, std::min<int64_t>(grid, kBinSlices));
     }
     if (mark_start(s)) return fail(TRIG_EHIP, "hipEventRecord(start)");
-    hipLaunchKernelGGL(k_binned<B>, dim3(grid), dim3(kBinWaves * kWave), 0, s, ev->layer_offsets, n, h->x, h->y, c,
-                       counter, L.counter_stride, chunk, slice_events, counts, accept, p->out_status);
+    const auto kern = counter ? k_bin_steal<B> : chunk > 1 ? k_bin_runs<B> : k_binned<B>;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBinWaves * kWave), 0, s, ev->layer_offsets, n, h->x, h->y, c, counter,
+                       L.counter_stride, chunk, counts, accept, p->out_status);
     if (int r = check_launch("k_binned")) return r;
     if (mark_stop(s)) return fail(TRIG_EHIP, "hipEventRecord(stop)");
     return TRIG_OK;

@@ -1,0 +1,55 @@
+"""GPU: a form's time must not hang on the order of the batch's events or on
+how close the cuts are.  Each case times two batches or two cuts in the same
+process, in turn, and compares the best times with a wide margin."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_parity import gpu  # noqa: F401 (fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def batch(torch, per_layer, seed, spread=200.0):
+    """Noise events with per_layer[e] hits in each layer, on the GPU."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    per = torch.as_tensor(per_layer, dtype=torch.int64, device="cuda")
+    off = torch.zeros(3 * per.numel() + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(per.repeat_interleave(3), 0, out=off[1:])
+    x, y = ((torch.rand(int(off[-1]), generator=g, device="cuda") * 2 - 1) * spread for _ in range(2))
+    return off.int(), x, y
+
+
+def best_ms(torch, calls, rounds=7, reps=4):
+    """The best time of each call, ms, taken in turn."""
+    best = [float("inf")] * len(calls)
+    for r in range(rounds + 1):
+        for k, call in enumerate(calls):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            call()
+            a.record()
+            for _ in range(reps):
+                call()
+            b.record()
+            b.synchronize()
+            if r:  # the first round warms up
+                best[k] = min(best[k], a.elapsed_time(b) / reps)
+    return best
+
+
+def test_binned_stealing_clustered_events(gpu):  # noqa: F811
+    """2 % of the events 24 times as large as the others, at the front or
+    spread out: the stealing binned form shares a cluster among all slices
+    (slices of consecutive events took 4.7 times as long, dealt out ones
+    1.4)."""
+    from paper_1810_11966_amd import trig
+    n = 300_000
+    e = np.arange(n)
+    calls = []
+    for large in (e < n // 50, e % 50 == 0):
+        b = batch(gpu, np.where(large, 240, 10), seed=3)
+        calls.append(lambda b=b: trig.select(*b, form="persistent_binned"))
+    print("[balance] persistent_binned, 300,000 events", flush=True)
+    front, spread = best_ms(gpu, calls)
+    print(f"front {front:.3f} ms, spread {spread:.3f} ms", flush=True)
+    assert front < 2.5 * spread
