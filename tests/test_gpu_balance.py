@@ -38,18 +38,36 @@ def best_ms(torch, calls, rounds=7, reps=4):
 
 
 def test_binned_stealing_clustered_events(gpu):  # noqa: F811
-    """2 % of the events 24 times as large as the others, at the front or
-    spread out: the stealing binned form shares a cluster among all slices
-    (slices of consecutive events took 4.7 times as long, dealt out ones
-    1.4)."""
+    """2 % of the events 30 times as large as the others, at the front or
+    spread out: the stealing binned form shares a cluster among all slices."""
     from paper_1810_11966_amd import trig
     n = 300_000
     e = np.arange(n)
     calls = []
     for large in (e < n // 50, e % 50 == 0):
-        b = batch(gpu, np.where(large, 240, 10), seed=3)
+        b = batch(gpu, np.where(large, 300, 10), seed=3)
         calls.append(lambda b=b: trig.select(*b, form="persistent_binned"))
     print("[balance] persistent_binned, 300,000 events", flush=True)
     front, spread = best_ms(gpu, calls)
     print(f"front {front:.3f} ms, spread {spread:.3f} ms", flush=True)
     assert front < 2.5 * spread
+
+
+def test_stolen_units_of_wide_events(gpu):  # noqa: F811
+    """The stealing every-triplet form's units cost their own pairs: events of
+    3 x 200,000 pairs against as many pairs of 775 x 775 (50 times as long
+    where each unit read the whole layer for its bound)."""
+    from paper_1810_11966_amd import trig
+    calls = []
+    for n0, n1 in ((3, 200_000), (775, 775)):
+        g = gpu.Generator(device="cuda")
+        g.manual_seed(5)
+        per = gpu.tensor([n0, n1, 3], device="cuda").repeat(20)
+        off = gpu.zeros(61, dtype=gpu.int64, device="cuda")
+        gpu.cumsum(per, 0, out=off[1:])
+        x, y = ((gpu.rand(int(off[-1]), generator=g, device="cuda") * 2 - 1) * 200 for _ in range(2))
+        calls.append(lambda b=(off.int(), x, y): trig.select(*b, form="persistent"))
+    print("[balance] wide events, persistent", flush=True)
+    wide, square = best_ms(gpu, calls)
+    print(f"wide {wide:.3f} ms, square {square:.3f} ms", flush=True)
+    assert wide < 4 * square
