@@ -73,8 +73,9 @@ __device__ __forceinline__ PreBound pre_bound(const Consts& c, const float* __re
             const int h = ev.o1 + j0 + t - (j0 + t < ev.n1 ? 0 : ev.n1);
             m = __builtin_fmaxf(m, __builtin_fmaxf(__builtin_fabsf(x[h]), __builtin_fabsf(y[h])));
         }
-        const float M = wave_max_f(m);
-        return {(c.fit_b0x + c.fit_b1x * M) + (c.fit_b0y + c.fit_b1y * M), true};
+        const float M = wave_max_f(m), bound = (c.fit_b0x + c.fit_b1x * M) + (c.fit_b0y + c.fit_b1y * M);
+        // (a bound this loose is not worth staging for: most |pre_k| are about |V2| M)
+        return {bound, bound * T::kLoose < __builtin_fabsf(c.V2) * M};
     } else if constexpr (std::is_same<T, MsdZTest>::value) {
         // the slope bound of layers 0 and 2 (it holds for any two layers)
         const PairBounds b = MsdZPrune::event_bounds(c, SlopeHits{x, y, z}, ev.o0 + i0, ni, ev.o2, ev.n2);
@@ -113,9 +114,8 @@ __global__ __launch_bounds__(WPB * kWave) void k_plain(const int32_t* __restrict
     if (cnt == 0) {
         const uint32_t tiles = pair_tiles(ev);
         if (tiles)
-            cnt = (int32_t)wave_count<T, kChunk>(x, y, z, ev, 0, tiles, c,
-                                                 pre_bound<T>(c, x, y, z, ev, 0, ev.n0, 0, ev.n1), lds_all[w],
-                                                 lds_all[w] + kChunk);
+            cnt = (int32_t)wave_count<T, 2 * kChunk>(x, y, z, ev, 0, tiles, c,
+                                                     pre_bound<T>(c, x, y, z, ev, 0, ev.n0, 0, ev.n1), lds_all[w]);
     }
     if (lane_id() == 0) write_result(e, cnt, c, counts, accept, status);
 }
@@ -367,7 +367,7 @@ __global__ __launch_bounds__(WPB * kWave) void k_persistent(
                 const uint32_t ia = pa / n1, ie = (pe - 1u) / n1;
                 const PreBound pb = pre_bound<T>(c, x, y, z, ev, (int)ia, (int)(ie - ia) + 1, (int)(pa - ia * n1),
                                                  (int)min(pe - pa, n1));
-                const uint32_t cnt = wave_count<T, kChunk>(x, y, z, ev, tb, te, c, pb, lds, lds + kChunk);
+                const uint32_t cnt = wave_count<T, 2 * kChunk>(x, y, z, ev, tb, te, c, pb, lds);
                 if (lane_id() == 0 && cnt) atomicAdd(&counts[e], (int32_t)cnt);
             }
         }
@@ -546,7 +546,8 @@ __global__ __launch_bounds__(kBinWaves * kWave) void k_event_z(const int32_t* __
                                                                const float* __restrict__ z, Consts c,
                                                                int32_t* __restrict__ counts,
                                                                uint8_t* __restrict__ accept, uint32_t* status) {
-    __shared__ __align__(16) float lds_all[kBinWaves][2 * kPBuf];
+    constexpr int kLds = 960;  // floats of a wave: 160 hits of the staged full test
+    __shared__ __align__(16) float lds_all[kBinWaves][kLds];
     const int w = uniform_i((int)(threadIdx.x / kWave));
     const int64_t e64 = (int64_t)blockIdx.x * kBinWaves + w;
     if (e64 >= n_events) return;
@@ -554,7 +555,7 @@ __global__ __launch_bounds__(kBinWaves * kWave) void k_event_z(const int32_t* __
     EventRange ev;
     int32_t cnt = load_event(off, e, c.n_hits, ev);
     if (cnt == 0 && ev.n0 > 0 && ev.n1 > 0 && ev.n2 > 0)
-        cnt = (int32_t)wave_event_z<P, T>(c, x, y, z, ev, lds_all[w], lds_all[w] + kPBuf);
+        cnt = (int32_t)wave_event_z<P, T, kLds>(c, x, y, z, ev, lds_all[w]);
     if (lane_id() == 0) write_result(e, cnt, c, counts, accept, status);
 }
 

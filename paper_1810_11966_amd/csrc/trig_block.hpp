@@ -1018,8 +1018,7 @@ template <int HB, int NW, int EB>
 struct BlockLds {
     // HB hits plus up to 3 before the first and 3 after the last (4-aligned copy)
     float2 stage[HB + 8];
-    float pbuf_x[NW][kPBuf];
-    float pbuf_y[NW][kPBuf];
+    float pbuf[NW][2 * kPBuf];  // per wave: x and y buffers of kPBuf
     // Event descriptors, 13-bit fields (local hit indices < HB + 8 <= 4104,
     // layer sizes <= HB <= 4096): da = o0 | n0 << 13 | R << 26 (R <= 16) |
     // S << 31, db = o1 | n1 << 13, dc = o2 | n2 << 13, dr = direct_recip of the
@@ -1154,8 +1153,8 @@ __device__ void block_count(BlockLds<HB, NW, EB>& L, const Consts& c, int e_firs
                             uint8_t* accept, uint32_t* status) {
     constexpr int NT = NW * kWave;
     const int w = uniform_i(threadIdx.x / kWave);
-    float* px = L.pbuf_x[w];
-    float* py = L.pbuf_y[w];
+    float* px = L.pbuf[w];
+    float* py = L.pbuf[w] + kPBuf;
     const LdsHits lh{L.stage};
     const float M = block_mag(L);
     const PairBounds pb = P::bounds(c, M);
@@ -1208,8 +1207,8 @@ __device__ void block_general(BlockLds<HB, NW, EB>& L, const Consts& c, const fl
                               uint8_t* accept, uint32_t* status) {
     constexpr int NT = NW * kWave;
     const int w = uniform_i(threadIdx.x / kWave);
-    float* px = L.pbuf_x[w];
-    float* py = L.pbuf_y[w];
+    float* px = L.pbuf[w];
+    float* py = L.pbuf[w] + kPBuf;
     const GlobalHits ghits{x, y};
     if (bad) {
         for (int t = w; t < ne; t += NW) {
@@ -1403,18 +1402,20 @@ void k_block(const int32_t* __restrict__ off, int n_events,
 
 // Passing triplets of one event with per-hit z (all layers non-empty), from
 // HBM: pairs pruned on their slopes with the event's bound (SlopeHits), or
-// every triplet (wave_count) when the event has no valid bound.  px, py: the
-// wave's kPBuf-entry LDS buffers.
-template <class P, class T>
+// every triplet (wave_count) when the event has no valid bound.  lds: the
+// wave's LF floats (at least 2 kPBuf).
+template <class P, class T, int LF>
 __device__ uint32_t wave_event_z(const Consts& c, const float* __restrict__ x, const float* __restrict__ y,
-                                 const float* __restrict__ z, const EventRange& ev, float* __restrict__ px,
-                                 float* __restrict__ py) {
+                                 const float* __restrict__ z, const EventRange& ev, float* __restrict__ lds) {
+    static_assert(LF >= 2 * kPBuf, "two buffers of kPBuf");
+    float* px = lds;
+    float* py = lds + kPBuf;
     const SlopeHits sh{x, y, z};
     const PairBounds pb = event_bounds<P>(c, sh, ev.o0, ev.n0, ev.o1, ev.n1);
     if (!pb.prune) {
         // the slope bound of layers 0 and 2 (it holds for any two layers)
         const PairBounds b = event_bounds<P>(c, sh, ev.o0, ev.n0, ev.o2, ev.n2);
-        return wave_count<T, kPBuf>(x, y, z, ev, 0, pair_tiles(ev), c, PreBound{b.pre, b.prune}, px, py);
+        return wave_count<T, LF>(x, y, z, ev, 0, pair_tiles(ev), c, PreBound{b.pre, b.prune}, lds);
     }
     // An event that fits one lane pass and one buffer fill takes the fast path
     // (the prefilter folded over all pairs, one vote); the slope tests are
@@ -1454,8 +1455,6 @@ void k_block_z(const int32_t* __restrict__ off, int n_events, const float* __res
     const int w = uniform_i(t / kWave);
     const int e0 = (int)blockIdx.x * eb;
     const int ne = min(eb, n_events - e0);
-    float* px = L.pbuf_x[w];
-    float* py = L.pbuf_y[w];
     constexpr int OQ = (3 * EB + 1 + NT - 1) / NT;
     int ov[OQ];
 #pragma unroll
@@ -1549,7 +1548,7 @@ void k_block_z(const int32_t* __restrict__ off, int n_events, const float* __res
     // Events round-robin over the waves; wave-uniform control flow.
     auto count = [&](int te, int b0, int b1, int b2, int b3) {
         const EventRange ev{b0, b1, b2, b1 - b0, b2 - b1, b3 - b2};
-        L.sres[te] = (int32_t)wave_event_z<P, T>(c, x, y, z, ev, px, py);  // uniform
+        L.sres[te] = (int32_t)wave_event_z<P, T, 2 * kPBuf>(c, x, y, z, ev, L.pbuf[w]);  // uniform
         wave_lds_sync();
     };
     if (good) {

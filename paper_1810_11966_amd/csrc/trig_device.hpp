@@ -198,12 +198,18 @@ __device__ __forceinline__ uint64_t lanes(bool cmp) { return __builtin_amdgcn_ba
 //   window: s_k - s_i (as s_k + (-s_i), the same binary32 value) is the
 //     test's own quantity; a pair outside the layer-1 window gives NaN.
 //   per-hit z, MSD: s_k - s_i, |.| <= (a0 + a1 M) / zmin.
+// kLoose, kNear, kShare: where the rejecting test does not pay, see wave_count;
+// kMinHits: layer-2 hits from which on it does.  kPreTests: pre_pair and pre_k
+// are all that the test itself needs (pre_pass).
 // Invalid pairs and padding are NaN, which fails every comparison.
 // ----------------------------------------------------------------------------
 
 // TRIG_TEST_MSD_BASIS: Q = a^2 + b^2 in the basis (u, v).
 struct MsdBasisTest {
     static constexpr int HF = 2;
+    static constexpr float kLoose = 12.0f;
+    static constexpr int kNear = 8, kShare = 3, kMinHits = 1;
+    static constexpr bool kPreTests = false;
     static constexpr bool kZ = false;  // layer positions from the parameters
     struct Pair {
         float ax2, bx0, ay2, by0;
@@ -246,6 +252,9 @@ struct MsdBasisTest {
 // their sum of squares), the paper's definition of the test.
 struct MsdFitTest {
     static constexpr int HF = 4;
+    static constexpr float kLoose = 12.0f;
+    static constexpr int kNear = 8, kShare = 3, kMinHits = 1;
+    static constexpr bool kPreTests = false;
     static constexpr bool kZ = false;  // layer positions from the parameters
     struct Pair {
         float xi, xj, sx01, yi, yj, sy01;
@@ -291,6 +300,9 @@ struct MsdFitTest {
 
 struct WindowTest {
     static constexpr int HF = 2;
+    static constexpr float kLoose = 3.0f;
+    static constexpr int kNear = 16, kShare = 3, kMinHits = 5;
+    static constexpr bool kPreTests = true;
     static constexpr bool kZ = false;  // layer positions from the parameters
     struct Pair {
         float sxi, syi;  // NaN when the layer-1 window already fails
@@ -298,6 +310,9 @@ struct WindowTest {
     __device__ static __forceinline__ void stage(const Consts& c, float x, float y, float* h) {
         h[0] = x / c.z2;
         h[1] = y / c.z2;
+    }
+    __device__ static __forceinline__ uint64_t pre_pass(const Consts& c, float2 p, float wx, float wy) {
+        return lanes(__builtin_fabsf(p.x + wx) < c.win_x) & lanes(__builtin_fabsf(p.y + wy) < c.win_y);
     }
     __device__ static __forceinline__ float2 pre_k(const Consts& c, float x, float y) {
         return make_float2(x / c.z2, y / c.z2);
@@ -329,6 +344,9 @@ struct WindowTest {
 // m = ((ci*zi + cj*zj) + ck*zk) * w,  r_l = c_l - m*z_l.
 struct MsdZTest {
     static constexpr int HF = 6;
+    static constexpr float kLoose = 6.0f;
+    static constexpr int kNear = 8, kShare = 3, kMinHits = 1;
+    static constexpr bool kPreTests = false;
     static constexpr bool kZ = true;
     struct Pair {
         float xi, xj, sx01, yi, yj, sy01, zi, zj, szz01;
@@ -380,6 +398,9 @@ struct MsdZTest {
 // Per-hit z, window test: slopes c / z with each hit's own z.
 struct WindowZTest {
     static constexpr int HF = 2;
+    static constexpr float kLoose = 3.0f;
+    static constexpr int kNear = 16, kShare = 3, kMinHits = 5;
+    static constexpr bool kPreTests = true;
     static constexpr bool kZ = true;
     struct Pair {
         float sxi, syi;  // NaN when the layer-1 window already fails
@@ -387,6 +408,9 @@ struct WindowZTest {
     __device__ static __forceinline__ void stage(const Consts&, float x, float y, float z, float* h) {
         h[0] = x / z;
         h[1] = y / z;
+    }
+    __device__ static __forceinline__ uint64_t pre_pass(const Consts& c, float2 p, float wx, float wy) {
+        return lanes(__builtin_fabsf(p.x + wx) < c.win_x) & lanes(__builtin_fabsf(p.y + wy) < c.win_y);
     }
     __device__ static __forceinline__ float2 pre_k(const Consts&, float x, float y, float z) {
         return make_float2(x / z, y / z);
@@ -443,89 +467,163 @@ __device__ __forceinline__ uint32_t pair_tiles(const EventRange& ev) {
     return (ev.n2 == 0) ? 0u : (uint32_t)((np + kWave - 1) / kWave);
 }
 
-// Rejecting-test bound of an event (see the test policies): a triplet passes
-// only if the magnitudes of the two planes' sums add up to at most `bound`; valid = false: no bound holds
-// (per-hit z outside (0, inf) in layers 0 or 2) and every triplet takes the
-// full test.
+// Rejecting-test bound (see the test policies): a triplet passes only if the
+// magnitudes of the two planes' sums add up to at most `bound`; valid = false:
+// no bound holds (per-hit z outside (0, inf) in layers 0 or 2) and every
+// triplet takes the full test.
 struct PreBound {
     float bound;
     bool valid;
 };
 
-// Passing triplets of one event over pair tiles [t_begin, t_end); each tile
-// is 64 consecutive (i, j) pairs in row-major order (pair p -> i = p / n1,
-// j = p % n1), one pair per lane, looping over every layer-2 hit staged in
-// this wave's LDS slices wx and wy (KCH hits per chunk, 16-byte aligned).  Called by a whole wave with
-// uniform arguments; returns the same count on every lane.
-//
-// Every triplet gets the rejecting test of the policy (three sums and half a
-// min3 on the vector unit: 8 SIMD cycles against 60 of the written-out fit),
-// on the sum of the two planes' magnitudes, folded over four layer-2 hits and
-// the lane's NP pairs before one vote; only a group in which some triplet is
-// within the bound is evaluated in full.  (A sum takes 2 SIMD cycles for 64
-// lanes, a max or min 4: the sum of the magnitudes instead of the larger one
-// saves 2 of 10 and lets twice as many of the few close triplets through.)  NP pairs per lane share one 16-byte LDS read per plane
-// and four layer-2 hits: with one pair per lane those reads (all lanes at one
-// address, still 1 KB each on a 128 B/clock LDS) take longer than the sums.
-// Bound by the vector unit.  100,000 events of 30 hits per layer, whole call:
-// 1.335 ms with the full test per triplet, 0.246 ms now (2.7e9 triplets; 0.14 ms
-// at 8 SIMD cycles per 64 of them and 2.4 GHz).
-template <class T, int KCH>
-__device__ uint32_t wave_count(const float* __restrict__ x, const float* __restrict__ y,
-                               const float* __restrict__ z, const EventRange& ev, uint32_t t_begin,
-                               uint32_t t_end, const Consts& c, const PreBound& pb, float* __restrict__ wx,
-                               float* __restrict__ wy) {
-    const uint32_t stop = (uint32_t)c.count_cap;  // enough: the result is capped there
-    static_assert(KCH % 4 == 0, "chunk must hold whole float4 groups");
-    const unsigned lane = lane_id();
-    const uint32_t n0 = (uint32_t)ev.n0, n1 = (uint32_t)ev.n1;
-    const uint32_t dq = kWave / n1, dr = kWave % n1;
+// One step of 64 pairs for a lane's pair (i, j).
+struct PairStep {
+    uint32_t n1, dq, dr;
+    __device__ __forceinline__ explicit PairStep(uint32_t n) : n1(n), dq(kWave / n), dr(kWave % n) {}
+    __device__ __forceinline__ void operator()(uint32_t& i, uint32_t& j) const {
+        j += dr;
+        i += dq;
+        if (j >= n1) {
+            j -= n1;
+            ++i;
+        }
+    }
+};
+
+// The pair part of the full test for the lane's pair (i, j).
+template <class T>
+__device__ __forceinline__ typename T::Pair pair_of(const float* __restrict__ x, const float* __restrict__ y,
+                                                    const float* __restrict__ z, const EventRange& ev, const Consts& c,
+                                                    uint32_t i, uint32_t j) {
+    typename T::Pair pr = T::invalid();
+    if (i < (uint32_t)ev.n0) {
+        if constexpr (T::kZ)
+            pr = T::pair(c, x[ev.o0 + i], y[ev.o0 + i], z[ev.o0 + i], x[ev.o1 + j], y[ev.o1 + j], z[ev.o1 + j]);
+        else
+            pr = T::pair(c, x[ev.o0 + i], y[ev.o0 + i], x[ev.o1 + j], y[ev.o1 + j]);
+    }
+    return pr;
+}
+
+// pre_k of the layer-2 hits [k0, k0 + nk) into wx and wy, NaN up to a whole
+// group of four.  Returns |pre_k| (both planes' sum) of the lane's first hit.
+template <class T>
+__device__ __forceinline__ float stage_pre(const float* __restrict__ x, const float* __restrict__ y,
+                                           const float* __restrict__ z, const EventRange& ev, const Consts& c, int k0,
+                                           int nk, float* __restrict__ wx, float* __restrict__ wy) {
+    const int lane = (int)lane_id(), nk_pad = (nk + 3) & ~3;
     const float nan = __builtin_nanf("");
+    float own = __builtin_inff();
+    for (int t = lane; t < nk_pad; t += kWave) {
+        const int k = ev.o2 + k0 + min(t, nk - 1);
+        float2 w;
+        if constexpr (T::kZ)
+            w = T::pre_k(c, x[k], y[k], z[k]);
+        else
+            w = T::pre_k(c, x[k], y[k]);
+        wx[t] = t < nk ? w.x : nan;
+        wy[t] = t < nk ? w.y : nan;
+        if (t < kWave) own = __builtin_fabsf(w.x) + __builtin_fabsf(w.y);
+    }
+    return own;
+}
+
+// The full test of every triplet of pair tiles [t_begin, t_end) (see
+// wave_count), the hits' part of it staged in the wave's LF floats of LDS;
+// staged: the first chunk's pre_k is there (tests of two values per hit only).
+template <class T, int LF>
+__device__ __forceinline__ uint32_t wave_count_full(const float* __restrict__ x, const float* __restrict__ y,
+                                                    const float* __restrict__ z, const EventRange& ev,
+                                                    uint32_t t_begin, uint32_t t_end, const Consts& c,
+                                                    float* __restrict__ lds, bool staged) {
+    constexpr bool kPlanes = T::HF == 2;  // the values are pre_k, kept as wave_count_pre does
+    constexpr int KCH = LF / T::HF & ~3;  // hits per chunk
+    static_assert(KCH > 0, "room for one group of four hits");
+    const uint32_t stop = (uint32_t)c.count_cap;  // enough: the result is capped there
+    const unsigned lane = lane_id();
+    const PairStep step((uint32_t)ev.n1);
     uint32_t cnt = 0;
     for (int k0 = 0; k0 < ev.n2; k0 += KCH) {
         const int nk = min(KCH, ev.n2 - k0);
         const int nk_pad = (nk + 3) & ~3;
-        for (int t = (int)lane; t < nk_pad; t += kWave) {
-            const int k = ev.o2 + k0 + min(t, nk - 1);
-            float2 w;
-            if constexpr (T::kZ)
-                w = T::pre_k(c, x[k], y[k], z[k]);
-            else
-                w = T::pre_k(c, x[k], y[k]);
-            wx[t] = t < nk ? w.x : nan;
-            wy[t] = t < nk ? w.y : nan;
+        if constexpr (kPlanes) {
+            if (!(staged && k0 == 0)) stage_pre<T>(x, y, z, ev, c, k0, nk, lds, lds + KCH);
+        } else {
+            for (int t = (int)lane; t < nk_pad; t += kWave) {
+                float* h = lds + t * T::HF;
+                if (t < nk) {
+                    if constexpr (T::kZ)
+                        T::stage(c, x[ev.o2 + k0 + t], y[ev.o2 + k0 + t], z[ev.o2 + k0 + t], h);
+                    else
+                        T::stage(c, x[ev.o2 + k0 + t], y[ev.o2 + k0 + t], h);
+                } else {
+#pragma unroll
+                    for (int f = 0; f < T::HF; ++f) h[f] = __builtin_nanf("");
+                }
+            }
         }
         wave_lds_sync();
         const uint32_t p0 = t_begin * (uint32_t)kWave + lane;
-        uint32_t i = p0 / n1, j = p0 - (p0 / n1) * n1;  // the lane's pair of tile t
-        uint32_t t = t_begin;
-        // The full test of NP tiles from t on and layer-2 hits [k, k + 4).
-        auto exact = [&](int np, int k) {
-#pragma unroll 1
-            for (int q = 0; q < np; ++q) {
-                const uint32_t p = (t + (uint32_t)q) * (uint32_t)kWave + lane;
-                const uint32_t pi = p / n1, pj = p - (p / n1) * n1;
-                typename T::Pair pr = T::invalid();
-                if (pi < n0) {
-                    if constexpr (T::kZ)
-                        pr = T::pair(c, x[ev.o0 + pi], y[ev.o0 + pi], z[ev.o0 + pi], x[ev.o1 + pj], y[ev.o1 + pj],
-                                     z[ev.o1 + pj]);
-                    else
-                        pr = T::pair(c, x[ev.o0 + pi], y[ev.o0 + pi], x[ev.o1 + pj], y[ev.o1 + pj]);
+        uint32_t i = p0 / step.n1, j = p0 - (p0 / step.n1) * step.n1;
+        for (uint32_t t = t_begin; t < t_end; ++t) {
+            const typename T::Pair pr = pair_of<T>(x, y, z, ev, c, i, j);
+            // nk_pad is a multiple of 4: four layer-2 hits per iteration
+            for (int k = 0; k < nk_pad; k += 4) {
+                uint64_t m[4];
+                if constexpr (kPlanes) {
+                    const float4 vx = *reinterpret_cast<const float4*>(lds + k);
+                    const float4 vy = *reinterpret_cast<const float4*>(lds + KCH + k);
+                    const float h[8] = {vx.x, vy.x, vx.y, vy.y, vx.z, vy.z, vx.w, vy.w};
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) m[u] = T::pass(c, pr, h + 2 * u);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) m[u] = T::pass(c, pr, lds + (k + u) * T::HF);
                 }
-                const int ke = min(k + 4, nk);
-#pragma unroll 1
-                for (int kk = k; kk < ke; ++kk) {
-                    const int h2 = ev.o2 + k0 + kk;
-                    float h[T::HF];
-                    if constexpr (T::kZ)
-                        T::stage(c, x[h2], y[h2], z[h2], h);
-                    else
-                        T::stage(c, x[h2], y[h2], h);
-                    cnt += (uint32_t)__builtin_popcountll(T::pass(c, pr, h));
-                }
+                cnt += (uint32_t)(__builtin_popcountll(m[0]) + __builtin_popcountll(m[1]) +
+                                  __builtin_popcountll(m[2]) + __builtin_popcountll(m[3]));
             }
-        };
+            step(i, j);
+            if (cnt >= stop) break;  // wave-uniform
+        }
+        wave_lds_sync();
+        if (cnt >= stop) break;
+    }
+    return cnt;
+}
+
+// The same with the rejecting test before the full one (see wave_count); false
+// where it does not pay (cnt is then not the count; the first chunk is staged
+// if the event has one only).
+template <class T, int LF>
+__device__ __forceinline__ bool wave_count_pre(const float* __restrict__ x, const float* __restrict__ y,
+                                               const float* __restrict__ z, const EventRange& ev, uint32_t t_begin,
+                                               uint32_t t_end, const Consts& c, float bound, float* __restrict__ lds,
+                                               uint32_t& cnt) {
+    constexpr int KCH = LF / 2;  // hits per chunk
+    static_assert(KCH % 4 == 0, "chunk must hold whole float4 groups");
+    const uint32_t stop = (uint32_t)c.count_cap;  // enough: the result is capped there
+    float* wx = lds;
+    float* wy = lds + KCH;
+    const unsigned lane = lane_id();
+    const uint32_t n0 = (uint32_t)ev.n0;
+    const PairStep step((uint32_t)ev.n1);
+    const float nan = __builtin_nanf("");
+    cnt = 0;
+    int32_t budget = T::kNear;  // of groups (a tile and four hits) taken on
+    for (int k0 = 0; k0 < ev.n2; k0 += KCH) {
+        const int nk = min(KCH, ev.n2 - k0);
+        const int nk_pad = (nk + 3) & ~3;
+        const float own = stage_pre<T>(x, y, z, ev, c, k0, nk, wx, wy);
+        wave_lds_sync();
+        // (MsdFitTest: by its bound and M, before anything is staged)
+        const bool check = T::HF == 2 || (T::kZ && t_end - t_begin > 4u);
+        if (check && k0 == 0 &&
+            2 * __builtin_popcountll(lanes((int)lane < nk && own <= bound * T::kLoose)) >= min(nk, kWave))
+            return false;
+        const uint32_t p0 = t_begin * (uint32_t)kWave + lane;
+        uint32_t i = p0 / step.n1, j = p0 - (p0 / step.n1) * step.n1;  // the lane's pair of tile t
+        uint32_t t = t_begin;
         auto tiles = [&](auto np) {
             constexpr int NP = decltype(np)::value;
             float2 p[NP];
@@ -540,41 +638,121 @@ __device__ uint32_t wave_count(const float* __restrict__ x, const float* __restr
                     p[q] = T::pre_pair(c, x[hi], y[hi], x[hj], y[hj]);
                 p[q].x = v ? p[q].x : nan;
                 p[q].y = v ? p[q].y : nan;
-                jn += dr;
-                in += dq;
-                if (jn >= n1) {
-                    jn -= n1;
-                    ++in;
-                }
+                step(in, jn);
             }
             // nk_pad is a multiple of 4: four layer-2 hits per iteration
             for (int k = 0; k < nk_pad; k += 4) {
                 const float4 vx = *reinterpret_cast<const float4*>(wx + k);
                 const float4 vy = *reinterpret_cast<const float4*>(wy + k);
-                float m = nan;  // fmin drops NaN; all NaN stays NaN and fails
-#pragma unroll
-                for (int q = 0; q < NP; ++q) {
+                // the smallest sum over q's four triplets and `from`
+                auto fold = [&](int q, float from) {
                     const float s0 = __builtin_fabsf(p[q].x + vx.x) + __builtin_fabsf(p[q].y + vy.x);
                     const float s1 = __builtin_fabsf(p[q].x + vx.y) + __builtin_fabsf(p[q].y + vy.y);
                     const float s2 = __builtin_fabsf(p[q].x + vx.z) + __builtin_fabsf(p[q].y + vy.z);
                     const float s3 = __builtin_fabsf(p[q].x + vx.w) + __builtin_fabsf(p[q].y + vy.w);
-                    m = __builtin_fminf(__builtin_fminf(m, s0), s1);
-                    m = __builtin_fminf(__builtin_fminf(m, s2), s3);
+                    const float m = __builtin_fminf(__builtin_fminf(from, s0), s1);
+                    return __builtin_fminf(__builtin_fminf(m, s2), s3);
+                };
+                float m = nan;  // fmin drops NaN; all NaN stays NaN and fails
+#pragma unroll
+                for (int q = 0; q < NP; ++q) m = fold(q, m);
+                if (!wave_any(m <= bound)) continue;
+                if constexpr (T::kPreTests) {
+#pragma unroll
+                    for (int q = 0; q < NP; ++q)
+                        cnt += (uint32_t)(__builtin_popcountll(T::pre_pass(c, p[q], vx.x, vy.x)) +
+                                          __builtin_popcountll(T::pre_pass(c, p[q], vx.y, vy.y)) +
+                                          __builtin_popcountll(T::pre_pass(c, p[q], vx.z, vy.z)) +
+                                          __builtin_popcountll(T::pre_pass(c, p[q], vx.w, vy.w)));
+                    budget -= NP;
+                } else {
+                    uint32_t near = 1u;  // the tiles to take on
+                    if constexpr (NP > 1) {
+                        near = 0u;
+#pragma unroll
+                        for (int q = 0; q < NP; ++q) near |= wave_any(fold(q, nan) <= bound) ? 1u << q : 0u;
+                    }
+                    budget -= __builtin_popcount(near);
+                    uint32_t pi = i, pj = j;
+#pragma unroll 1
+                    for (; near; near >>= 1, step(pi, pj)) {
+                        if (!(near & 1u)) continue;
+                        const typename T::Pair pr = pair_of<T>(x, y, z, ev, c, pi, pj);
+#pragma unroll 1
+                        for (int kk = k; kk < min(k + 4, nk); ++kk) {
+                            float h[T::HF];
+                            const int h2 = ev.o2 + k0 + kk;
+                            if constexpr (T::HF == 2) {
+                                h[0] = wx[kk];
+                                h[1] = wy[kk];
+                            } else if constexpr (T::kZ) {
+                                T::stage(c, x[h2], y[h2], z[h2], h);
+                            } else {
+                                T::stage(c, x[h2], y[h2], h);
+                            }
+                            cnt += (uint32_t)__builtin_popcountll(T::pass(c, pr, h));
+                        }
+                    }
                 }
-                if (!pb.valid || wave_any(m <= pb.bound)) exact(NP, k);
             }
+            budget += (int32_t)(NP * nk_pad) >> T::kShare;  // its share of the tiles' groups
             i = in;
             j = jn;
             t += NP;
         };
         // wave-uniform control flow
-        while (t + 4 <= t_end && cnt < stop) tiles(std::integral_constant<int, 4>{});
-        if (t + 2 <= t_end && cnt < stop) tiles(std::integral_constant<int, 2>{});
-        if (t < t_end && cnt < stop) tiles(std::integral_constant<int, 1>{});
+        while (t + 4 <= t_end && cnt < stop && budget >= 0) tiles(std::integral_constant<int, 4>{});
+        if (t + 2 <= t_end && cnt < stop && budget >= 0) tiles(std::integral_constant<int, 2>{});
+        if (t < t_end && cnt < stop && budget >= 0) tiles(std::integral_constant<int, 1>{});
         wave_lds_sync();
-        if (cnt >= stop) break;
+        if (cnt >= stop) return true;
+        if (t < t_end) return false;  // out of budget
     }
-    return cnt;
+    return true;
+}
+
+// Passing triplets of one event over pair tiles [t_begin, t_end); each tile
+// is 64 consecutive (i, j) pairs in row-major order (pair p -> i = p / n1,
+// j = p % n1), one pair per lane, looping over every layer-2 hit staged in
+// this wave's LF floats of LDS (16-byte aligned).  Called by a whole wave with
+// uniform arguments; returns the same count on every lane.
+//
+// Every triplet gets the rejecting test of the policy (three sums and half a
+// min3 on the vector unit: 8 SIMD cycles against 60 of the written-out fit),
+// on the sum of the two planes' magnitudes, folded over four layer-2 hits and
+// the lane's NP pairs before one vote; only a tile and group of four hits in
+// which some triplet is within the bound is evaluated in full.  (A sum takes 2
+// SIMD cycles for 64 lanes, a max or min 4: the sum of the magnitudes instead
+// of the larger one saves 2 of 10 and lets twice as many of the few close
+// triplets through.)  NP pairs per lane share one 16-byte LDS read per plane
+// and four layer-2 hits: with one pair per lane those reads (all lanes at one
+// address, still 1 KB each on a 128 B/clock LDS) take longer than the sums.
+// Bound by the vector unit.  100,000 events of 30 hits per layer, whole call:
+// 1.335 ms with the full test per triplet, 0.246 ms now (2.7e9 triplets; 0.14 ms
+// at 8 SIMD cycles per 64 of them and 2.4 GHz).
+//
+// The rejecting test pays while few groups are taken on.  So an event goes to
+// the staged full test (wave_count_full) at once if no bound holds or if kLoose
+// times the bound reaches at least half of its layer-2 hits' |pre_k| (of the
+// first 64; MsdFitTest: about |V2| M): with sums spread evenly over +-S, median
+// 3/4 S, the share of groups (256 triplets) with one within B is 128 (B / S)^2
+// (MSD; 0.5 at 1/16), 12 / 2 (B / S)^2 per-hit z at 30 hits per layer, and for
+// the window tests, whose pairs have passed the layer-1 window, 512 (B / 2
+// S)^4.  Events of another kind (many tracks) go there, from the start again,
+// once more than kNear groups and a share of 2^(2 - kShare) of them were taken
+// on.  20,000 events of 30 hits per layer, cuts 1, 10 and 100 times the default
+// in cm, us: MSD 58, 129, 329 (always the full test: 326), basis form 56, 101,
+// 126 (124), window 81, 87, 116 (115); each hit on a track: MSD 130 (280),
+// window 81 (94).  Small events gain less: 200,000 of 3 hits per layer 63, 60
+// and 60 us (68, 57, 60).
+template <class T, int LF>
+__device__ uint32_t wave_count(const float* __restrict__ x, const float* __restrict__ y,
+                               const float* __restrict__ z, const EventRange& ev, uint32_t t_begin,
+                               uint32_t t_end, const Consts& c, const PreBound& pb, float* __restrict__ lds) {
+    uint32_t cnt;
+    const bool pre = pb.valid && (T::kMinHits <= 1 || ev.n2 >= T::kMinHits);  // (n2 > 0)
+    if (pre && wave_count_pre<T, LF>(x, y, z, ev, t_begin, t_end, c, pb.bound, lds, cnt)) return cnt;
+    return wave_count_full<T, LF>(x, y, z, ev, t_begin, t_end, c, lds, pre && ev.n2 <= LF / 2);
 }
 
 }  // namespace trig

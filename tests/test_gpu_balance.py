@@ -53,6 +53,21 @@ def test_binned_stealing_clustered_events(gpu):  # noqa: F811
     assert front < 2.5 * spread
 
 
+@pytest.mark.parametrize("form", ("plain", "persistent"))
+def test_every_triplet_loops_at_loose_cuts(gpu, form):  # noqa: F811
+    """Cuts that reject next to nothing cost the every-triplet loops the full
+    test of each triplet and no more (window test, 20,000 events of 30 hits per
+    layer: 7 to 9 times the default cuts' time where each group of triplets went
+    through the rejecting test and was then tested hit by hit)."""
+    from paper_1810_11966_amd import trig
+    b = batch(gpu, np.full(20_000, 30), seed=4)
+    calls = [lambda w=w: trig.select(*b, test="window", form=form, slope_window=(w, w)) for w in (0.15, 0.005)]
+    print(f"[balance] loose cuts, {form}", flush=True)
+    loose, tight = best_ms(gpu, calls)
+    print(f"loose {loose:.3f} ms, tight {tight:.3f} ms", flush=True)
+    assert loose < 5 * tight
+
+
 def test_stolen_units_of_wide_events(gpu):  # noqa: F811
     """The stealing every-triplet form's units cost their own pairs: events of
     3 x 200,000 pairs against as many pairs of 775 x 775 (50 times as long
