@@ -395,15 +395,16 @@ static_assert(kBinSlices == 64, "k_binned shifts by 6");
 
 // A wave counts runs of `chunk` consecutive events.  kBinSingle, kBinRun: wave
 // g takes run g (a run of one event without the loop around it is 5 to 10 %
-// faster than the loop taken once).  kBinSteal: the runs are dealt out to kBinSlices slices (fewer workgroups: a slice each), one of every
+// faster than the loop taken once).  kBinSteal (at least kBinSlices
+// workgroups): the runs are dealt out to kBinSlices slices, one of every
 // kBinSlices neighbours to each slice (turn t of slice s: run 64 t +
 // (s + t) % 64), workgroup b working on slice b % kBinSlices: a wave takes its
 // first run by its own number and the others from the slice's counter (zero at
 // launch; one atomic per run), until none is left: no barrier, and no LDS
 // beyond the waves' cells (8 workgroups fit on a CU).  Dealt out, a cluster of
 // large events is shared by all slices: 300,000 events, the first 6,000 of 240
-// hits per layer and the others of 10, take 185 us, with slices of consecutive
-// runs 630 (and 136 or 135 with the large events spread out).
+// hits per layer and the others of 10, take 180 us, with slices of consecutive
+// runs 627 (and 136 with the large events spread out).
 // Atomics on one 256-byte line pass one by one, some 5 ns each (1M mixture
 // events with all claims on one word: 0.91 ms, of which they were most), so
 // each slice's counter has a line of its own.
@@ -448,16 +449,15 @@ __device__ __forceinline__ void binned_waves(BinLds* lds_all, const int32_t* __r
             for (int e = (int)first; e < last; ++e) one_event(e);
         }
     } else {
-        const bool wide = gridDim.x >= (unsigned)kBinSlices;
-        const unsigned n_slices = wide ? (unsigned)kBinSlices : gridDim.x;
-        const unsigned slice = wide ? blockIdx.x & (kBinSlices - 1u) : blockIdx.x;  // the workgroup's
-        const unsigned groups = wide ? (gridDim.x - slice + kBinSlices - 1u) >> 6 : 1u;  // of the slice
-        unsigned turn = (wide ? blockIdx.x >> 6 : 0u) * kBinWaves + (unsigned)w;
+        const unsigned slice = blockIdx.x & (kBinSlices - 1u);  // the workgroup's
+        const unsigned groups = (gridDim.x - slice + kBinSlices - 1u) >> 6;  // of the slice
+        unsigned turn = (blockIdx.x >> 6) * kBinWaves + (unsigned)w;
         for (;;) {
-            const unsigned place = wide ? (slice + turn) & (kBinSlices - 1u) : (slice + turn) % n_slices;
-            const int64_t first = ((int64_t)turn * n_slices + place) * chunk;
-            if (first >= n_events) break;  // (the slice's later runs lie beyond too)
-            const int last = (int)min(first + chunk, (int64_t)n_events);
+            // (below 2^31 + 2^17: a wave stops at its first run past the end)
+            const unsigned first =
+                (turn * kBinSlices + ((slice + turn) & (kBinSlices - 1u))) * (unsigned)chunk;
+            if (first >= (unsigned)n_events) break;  // (the slice's later runs lie beyond too)
+            const int last = (int)min(first + (unsigned)chunk, (unsigned)n_events);
             for (int e = (int)first; e < last; ++e) one_event(e);
             unsigned claim = 0u;
             if (lane_id() == 0) claim = atomicAdd(&block_counter[slice * counter_stride], 1u);
@@ -943,7 +943,8 @@ int launch_binned(const trig_events_csr* ev, const trig_hits* h, const trig_para
     const int64_t n_blocks = cdiv(cdiv(n, chunk), kBinWaves);
     unsigned* counter = nullptr;
     unsigned grid = (unsigned)n_blocks;
-    if (p->flags & TRIG_EXEC_PERSISTENT) {
+    // (fewer workgroups than slices all run at once: nothing to steal)
+    if ((p->flags & TRIG_EXEC_PERSISTENT) && n_blocks >= kBinSlices) {
         counter = reinterpret_cast<unsigned*>(ws + L.counter_off);
         hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(kBinSlices), 0, s, counter, L.counter_stride);
         if (int r = check_launch("k_zero_u32")) return r;

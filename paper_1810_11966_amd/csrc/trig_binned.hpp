@@ -30,7 +30,9 @@
 //
 // The pairs that pass their test are listed, and only an event with such a
 // pair reads its layer 2 (wave_event_binned): a few pairs are completed
-// against all of it, many look their partners up in layer-2 cells.
+// against all of it, more look their partners up in layer-2 cells.  Events
+// whose bounds let too many pairs through for the list have both layers in
+// cells and list none.
 //
 // One wave per event.  Cells are built in LDS with a counting sort (histogram
 // of the cell indices, exclusive scan, scatter); events with more than
@@ -61,16 +63,17 @@ __device__ __forceinline__ float widen_up(float f) {
 }
 
 
-// Surviving pairs an event may have before its layer 2 is put into cells as
-// well (wave_event_binned).
-constexpr int kBinPairs = 64;
+// Surviving pairs of an event that its list holds (wave_event_binned).
+constexpr int kBinPairs = 128;
 
 // LDS of one wave: cell ends and the two payload floats per hit, in cell
-// order, for layer 1, and either the surviving pairs (x_i, y_i, x_j, y_j) or
-// the same cells for layer 2.  Float arrays first (16-byte aligned: the
-// fallback path reuses a1/b1 as its layer-0 buffers).  A cell end is at most
-// kBinCap = 256, so the ends are 16-bit, two cells per 32-bit word (cell t in
-// the half t & 1 of word t >> 1): 5 KB per wave, eight workgroups per CU.
+// order: first the layer-1 cells in a1/b1 and the surviving pairs (x_i, y_i,
+// x_j, y_j), then the layer-2 cells in a1/b1 with the pairs or, where both
+// layers are needed in cells, layer 1 in a2/b2.  Float arrays first (16-byte
+// aligned: the fallback path reuses a1/b1 as its layer-0 buffers).  A cell end
+// is at most kBinCap = 256, so the ends are 16-bit, two cells per 32-bit word
+// (cell t in the half t & 1 of word t >> 1): 5 KB per wave, eight workgroups
+// per CU.
 struct BinLds {
     float a1[kBinCap], b1[kBinCap];
     union {
@@ -79,8 +82,8 @@ struct BinLds {
             float a2[kBinCap], b2[kBinCap];
         };
     };
-    // Layer-1 and layer-2 cell ends (kBinCap / 2 words each); or, while `pairs`
-    // is used, the layer-1 cells' starts (starts()), and the number of
+    // Cell ends of a1/b1 and of a2/b2 (kBinCap / 2 words each); or, while pairs
+    // are listed, the layer-1 cells' starts (starts()), and the number of
     // surviving pairs in the last word.
     uint32_t ends[kBinCap];
     __device__ __forceinline__ uint32_t* end1() { return ends; }
@@ -254,6 +257,7 @@ struct BinBounds {
 // TRIG_TEST_MSD_BASIS.
 struct MsdBasisBin {
     using Prune = MsdBasisPrune;
+    static constexpr int kFewPairs = 4;
     static constexpr bool kMag = false;
     __device__ static __forceinline__ BinBounds bounds(const Consts& c, float) {
         return BinBounds{c.beta_x, c.beta_y, c.bin_r, c.bin_r};
@@ -294,7 +298,35 @@ struct MsdBasisBin {
         const float h[2] = {c.V2 * x, c.V2 * y};
         return MsdBasisTest::pass(c, pr, h);
     }
-    // Passing triplets with layer-0 hit (xi, yi), from the cells of both layers.
+    // Passing triplets of a pair, from the layer-2 cells (in a1/b1).
+    __device__ static uint32_t count_cells(const Consts& c, const BinBounds& bb, float xi, float yi, float xj, float yj,
+                                           const Bins& b2, const BinLds& L) {
+        const float ax = c.U0 * xi + c.U1 * xj;
+        const float ay = c.U0 * yi + c.U1 * yj;
+        const float ax2 = ax * ax, ay2 = ay * ay;
+        const float bx0 = c.V0 * xi + c.V1 * xj;
+        const float by0 = c.V0 * yi + c.V1 * yj;
+        if (!__builtin_isfinite(bx0)) return 0;
+        const float lo2 = widen_down(-bx0 - bb.r2), hi2 = widen_up(-bx0 + bb.r2);
+        if (hi2 < b2.kmin || lo2 > b2.kmax) return 0;
+        int k0, k1;
+        b2.range(L.end1(), lo2, hi2, k0, k1);
+        uint32_t cnt = 0;
+        for (int k = k0; k < k1; ++k) {
+            const float bx = bx0 + L.a1[k];
+            const float qx = ax2 + bx * bx;
+            const float by = by0 + L.b1[k];
+            const float qy = ay2 + by * by;
+            cnt += (uint32_t)((qx <= c.qmax_x) & (qy <= c.qmax_y));
+        }
+        return cnt;
+    }
+    __device__ static uint32_t count_pair(const Consts& c, const BinBounds& bb, float4 p, const Bins& b2,
+                                          const BinLds& L) {
+        return count_cells(c, bb, p.x, p.y, p.z, p.w, b2, L);
+    }
+    // Passing triplets with layer-0 hit (xi, yi), from the cells of both layers
+    // (layer 1 in a2/b2).
     __device__ static uint32_t count_i(const Consts& c, const BinBounds& bb, float xi, float yi, const Bins& b1,
                                        const Bins& b2, const BinLds& L) {
         const float ux = c.U0 * xi;
@@ -303,28 +335,14 @@ struct MsdBasisBin {
         const float lo = widen_down(-ux - r), hi = widen_up(-ux + r);
         if (hi < b1.kmin || lo > b1.kmax) return 0;
         int j0, j1;
-        b1.range(L.end1(), lo, hi, j0, j1);
+        b1.range(L.end2(), lo, hi, j0, j1);
         uint32_t cnt = 0;
         for (int j = j0; j < j1; ++j) {
-            const float xj = L.a1[j], yj = L.b1[j];
+            const float xj = L.a2[j], yj = L.b2[j];
             const float ax = c.U0 * xi + c.U1 * xj;
             const float ay = c.U0 * yi + c.U1 * yj;
             if (!(__builtin_fabsf(ax) <= bb.bx && __builtin_fabsf(ay) <= bb.by)) continue;
-            const float ax2 = ax * ax, ay2 = ay * ay;
-            const float bx0 = c.V0 * xi + c.V1 * xj;
-            const float by0 = c.V0 * yi + c.V1 * yj;
-            if (!__builtin_isfinite(bx0)) continue;
-            const float lo2 = widen_down(-bx0 - bb.r2), hi2 = widen_up(-bx0 + bb.r2);
-            if (hi2 < b2.kmin || lo2 > b2.kmax) continue;
-            int k0, k1;
-            b2.range(L.end2(), lo2, hi2, k0, k1);
-            for (int k = k0; k < k1; ++k) {
-                const float bx = bx0 + L.a2[k];
-                const float qx = ax2 + bx * bx;
-                const float by = by0 + L.b2[k];
-                const float qy = ay2 + by * by;
-                cnt += (uint32_t)((qx <= c.qmax_x) & (qy <= c.qmax_y));
-            }
+            cnt += count_cells(c, bb, xi, yi, xj, yj, b2, L);
         }
         return cnt;
     }
@@ -336,6 +354,7 @@ struct MsdBasisBin {
 // M = |x_j| (finite for a hit in a cell) the bound on |b| is finite.
 struct MsdFitBin {
     using Prune = MsdFitPrune;
+    static constexpr int kFewPairs = 4;
     static constexpr bool kMag = true;
     __device__ static __forceinline__ BinBounds bounds(const Consts& c, float M) {
         // 1 + 2^-20: fl(A (1 + 2^-20)) >= A (1 + 2^-23), above the next
@@ -375,6 +394,29 @@ struct MsdFitBin {
         const float h[4] = {x, y, x * c.z2, y * c.z2};
         return MsdFitTest::pass(c, pr, h);
     }
+    __device__ static uint32_t count_cells(const Consts& c, const BinBounds& bb, float xi, float yi, float xj, float yj,
+                                           const Bins& b2, const BinLds& L) {
+        const float bx0 = c.V0 * xi + c.V1 * xj;
+        if (!__builtin_isfinite(bx0)) return 0;
+        const float lo2 = widen_down(-bx0 - bb.r2), hi2 = widen_up(-bx0 + bb.r2);
+        if (hi2 < b2.kmin || lo2 > b2.kmax) return 0;
+        int k0, k1;
+        b2.range(L.end1(), lo2, hi2, k0, k1);
+        const float sx01 = xi * c.z0 + xj * c.z1;
+        const float sy01 = yi * c.z0 + yj * c.z1;
+        uint32_t cnt = 0;
+        for (int k = k0; k < k1; ++k) {
+            const float xk = L.a1[k], yk = L.b1[k];
+            const float qx = MsdFitTest::plane_q(c, xi, xj, sx01, xk, xk * c.z2);
+            const float qy = MsdFitTest::plane_q(c, yi, yj, sy01, yk, yk * c.z2);
+            cnt += (uint32_t)((qx <= c.qmax_x) & (qy <= c.qmax_y));
+        }
+        return cnt;
+    }
+    __device__ static uint32_t count_pair(const Consts& c, const BinBounds& bb, float4 p, const Bins& b2,
+                                          const BinLds& L) {
+        return count_cells(c, bb, p.x, p.y, p.z, p.w, b2, L);
+    }
     __device__ static uint32_t count_i(const Consts& c, const BinBounds& bb, float xi, float yi, const Bins& b1,
                                        const Bins& b2, const BinLds& L) {
         const float ux = c.U0 * xi;
@@ -382,28 +424,14 @@ struct MsdFitBin {
         const float lo = widen_down(-ux - bb.r1), hi = widen_up(-ux + bb.r1);
         if (hi < b1.kmin || lo > b1.kmax) return 0;
         int j0, j1;
-        b1.range(L.end1(), lo, hi, j0, j1);
-        const float pxi = xi * c.z0, pyi = yi * c.z0;
+        b1.range(L.end2(), lo, hi, j0, j1);
         uint32_t cnt = 0;
         for (int j = j0; j < j1; ++j) {
-            const float xj = L.a1[j], yj = L.b1[j];
+            const float xj = L.a2[j], yj = L.b2[j];
             const float ax = c.U0 * xi + c.U1 * xj;
             const float ay = c.U0 * yi + c.U1 * yj;
             if (!(__builtin_fabsf(ax) <= bb.bx && __builtin_fabsf(ay) <= bb.by)) continue;
-            const float bx0 = c.V0 * xi + c.V1 * xj;
-            if (!__builtin_isfinite(bx0)) continue;
-            const float lo2 = widen_down(-bx0 - bb.r2), hi2 = widen_up(-bx0 + bb.r2);
-            if (hi2 < b2.kmin || lo2 > b2.kmax) continue;
-            int k0, k1;
-            b2.range(L.end2(), lo2, hi2, k0, k1);
-            const float sx01 = pxi + xj * c.z1;
-            const float sy01 = pyi + yj * c.z1;
-            for (int k = k0; k < k1; ++k) {
-                const float xk = L.a2[k], yk = L.b2[k];
-                const float qx = MsdFitTest::plane_q(c, xi, xj, sx01, xk, xk * c.z2);
-                const float qy = MsdFitTest::plane_q(c, yi, yj, sy01, yk, yk * c.z2);
-                cnt += (uint32_t)((qx <= c.qmax_x) & (qy <= c.qmax_y));
-            }
+            cnt += count_cells(c, bb, xi, yi, xj, yj, b2, L);
         }
         return cnt;
     }
@@ -413,6 +441,7 @@ struct MsdFitBin {
 
 struct WindowBin {
     using Prune = WindowPrune;
+    static constexpr int kFewPairs = 6;
     static constexpr bool kMag = false;
     __device__ static __forceinline__ BinBounds bounds(const Consts& c, float) {
         return BinBounds{c.win_x, c.win_y, c.bin_r, c.bin_r};
@@ -447,26 +476,37 @@ struct WindowBin {
     __device__ static __forceinline__ uint64_t complete(const Consts& c, float4 p, float x, float y) {
         return lanes(__builtin_fabsf(x / c.z2 - p.x) < c.win_x) & lanes(__builtin_fabsf(y / c.z2 - p.y) < c.win_y);
     }
+    // Layer-2 partners of a layer-0 hit with slopes (sxi, syi).
+    __device__ static uint32_t count_cells(const Consts& c, const BinBounds& bb, float sxi, float syi, const Bins& b2,
+                                           const BinLds& L) {
+        if (!__builtin_isfinite(sxi)) return 0;
+        const float lo = widen_down(sxi - bb.r2), hi = widen_up(sxi + bb.r2);
+        if (hi < b2.kmin || lo > b2.kmax) return 0;
+        int k0, k1;
+        b2.range(L.end1(), lo, hi, k0, k1);
+        uint32_t nk = 0;
+        for (int k = k0; k < k1; ++k)
+            nk += (uint32_t)((__builtin_fabsf(L.a1[k] - sxi) < c.win_x) & (__builtin_fabsf(L.b1[k] - syi) < c.win_y));
+        return nk;
+    }
+    __device__ static uint32_t count_pair(const Consts& c, const BinBounds& bb, float4 p, const Bins& b2,
+                                          const BinLds& L) {
+        return count_cells(c, bb, p.x, p.y, b2, L);
+    }
     __device__ static uint32_t count_i(const Consts& c, const BinBounds& bb, float xi, float yi, const Bins& b1,
                                        const Bins& b2, const BinLds& L) {
         const float sxi = xi / c.z0, syi = yi / c.z0;
         if (!__builtin_isfinite(sxi)) return 0;
         const float lo = widen_down(sxi - bb.r1), hi = widen_up(sxi + bb.r1);
-        uint32_t nj = 0, nk = 0;
+        uint32_t nj = 0;
         if (!(hi < b1.kmin || lo > b1.kmax)) {
             int j0, j1;
-            b1.range(L.end1(), lo, hi, j0, j1);
+            b1.range(L.end2(), lo, hi, j0, j1);
             for (int j = j0; j < j1; ++j)
-                nj += (uint32_t)((__builtin_fabsf(L.a1[j] - sxi) < c.win_x) &
-                                 (__builtin_fabsf(L.b1[j] - syi) < c.win_y));
+                nj += (uint32_t)((__builtin_fabsf(L.a2[j] - sxi) < c.win_x) &
+                                 (__builtin_fabsf(L.b2[j] - syi) < c.win_y));
         }
-        if (nj == 0 || hi < b2.kmin || lo > b2.kmax) return 0;
-        int k0, k1;
-        b2.range(L.end2(), lo, hi, k0, k1);
-        for (int k = k0; k < k1; ++k)
-            nk += (uint32_t)((__builtin_fabsf(L.a2[k] - sxi) < c.win_x) &
-                             (__builtin_fabsf(L.b2[k] - syi) < c.win_y));
-        return nj * nk;
+        return nj == 0 ? 0u : nj * count_cells(c, bb, sxi, syi, b2, L);
     }
 };
 
@@ -476,10 +516,17 @@ struct WindowBin {
 //
 // Layer 2 is read only for events with a pair that can pass: an event of 200
 // hits per layer in the default cuts has 0.16 such pairs on average, so most
-// events neither read nor sort a third of their hits.  Up to kBinPairs pairs
-// are completed one by one, lanes over layer 2 (at most four rounds each);
-// an event with more sorts layer 2 into cells too and looks each pair's
-// partners up there, so that its work stays in proportion to its hits.
+// events neither read nor sort a third of their hits.  A few pairs are
+// completed one by one, lanes over layer 2 (at most kFewPairs, which cost about
+// what putting layer 2 into cells does); with more, up to kBinPairs, layer 2 goes into cells and each
+// lane looks a pair's partners up there.  An event whose list overflows, or
+// whose bounds let half of that through (P = bx by / K^2 of its pairs, for
+// hits spread over +-M), has both layers in cells and each lane follows a
+// layer-0 hit through both, so that its work stays in proportion to its hits.
+// Whole calls, us, with every layer in cells / the pairs of a longer list one by
+// one / so: 20,000 events of 30 hits per layer each on a track, MSD 24.5, 35.4,
+// 15.3, window 15.0, 25.2, 15.5; 100,000 of 200 with windows 3 and 10 times the
+// default 325, 419, 309 and 1035, 1396, 1050.
 // 100,000 events of 200 hits per layer, whole call: 0.156 ms with layer 2
 // sorted for every event, 0.122 ms without (1M mixture events, mean 80 per
 // layer: 0.783 and 0.559 ms).
@@ -532,76 +579,80 @@ __device__ uint32_t wave_event_binned(const Consts& c, const float* __restrict__
     const float K = B::key_max(c, M);
     // (the hardware reciprocal is enough to spread the keys over the cells)
     const float inv = trig_host::cell_scale(K, __builtin_amdgcn_rcpf(K), (float)kBinCap);
-    uint32_t* hist = reinterpret_cast<uint32_t*>(L.a1);
-    static_assert(kBinCap == 4 * kWave, "four cells per lane");
-    reinterpret_cast<uint4*>(hist)[lane] = make_uint4(0u, 0u, 0u, 0u);
-    if (lane == 0) *L.n_pairs() = 0u;
-    wave_lds_sync();
-    uint32_t cell[kBinRounds], rank[kBinRounds];  // rank: 4 bytes per hit of the cell before this one
+    const float share = __builtin_amdgcn_rcpf(K);
+    int n_pairs = kBinPairs + 1;
+    if (!((float)n0 * (float)n1 * (bb.bx * share) * (bb.by * share) > 0.5f * (float)kBinPairs)) {
+        uint32_t* hist = reinterpret_cast<uint32_t*>(L.a1);
+        static_assert(kBinCap == 4 * kWave, "four cells per lane");
+        reinterpret_cast<uint4*>(hist)[lane] = make_uint4(0u, 0u, 0u, 0u);
+        if (lane == 0) *L.n_pairs() = 0u;
+        wave_lds_sync();
+        uint32_t cell[kBinRounds], rank[kBinRounds];  // rank: 4 bytes per hit of the cell before this one
 #pragma unroll
-    for (int r = 0; r < kBinRounds; ++r) {
-        cell[r] = rank[r] = 0u;
-        if (r * kWave < n1) {
-            cell[r] = bin_cell(B::Key1::key(c, h1.x[r], h1.y[r]), inv);
-            if (r * kWave + lane < n1) rank[r] = atomicAdd(&hist[cell[r]], 4u);
-        }
-    }
-    wave_lds_sync();
-    {
-        // exclusive scan: starts()[t] the first byte of cell t's hits
-        const uint4 v = reinterpret_cast<const uint4*>(hist)[lane];
-        const uint32_t own = (v.x + v.y) + (v.z + v.w);
-        const uint32_t s0 = (uint32_t)wave_inclusive_sum((int)own) - own;
-        const uint32_t s1 = s0 + v.x, s2 = s1 + v.y, s3 = s2 + v.z;
-        reinterpret_cast<uint2*>(L.ends)[lane] = make_uint2(s0 | (s1 << 16), s2 | (s3 << 16));
-        if (lane == 0) L.starts()[kBinCap] = (uint16_t)(4 * n1);
-    }
-    wave_lds_sync();
-    char* pa = reinterpret_cast<char*>(L.a1);
-    char* pb = reinterpret_cast<char*>(L.b1);
-#pragma unroll
-    for (int r = 0; r < kBinRounds; ++r)
-        if (r * kWave + lane < n1) {
-            const uint32_t at = L.starts()[cell[r]] + rank[r];
-            const float2 p = B::Key1::payload(c, h1.x[r], h1.y[r]);
-            *reinterpret_cast<float*>(pa + at) = p.x;
-            *reinterpret_cast<float*>(pb + at) = p.y;
-        }
-    wave_lds_sync();
-    // Layer-0 hit (xi, yi): its cells' hits, two per step.  The interval's ends
-    // are moved outwards by |centre| 2^-21 and r1 2^-20 + 2^-126, more than the
-    // rounding of the two sums.
-    const float r1 = bb.r1 * 1.00000095367431640625f + 0x1p-126f, pre = bb.bx + bb.by;
-    auto scan = [&](float xi, float yi) {
-        const float2 u = B::side(c, xi, yi);
-        const float mid = B::centre(u), w = __builtin_fabsf(mid) * 0x1p-21f + r1;
-        uint32_t j = L.starts()[bin_cell(mid - w, inv)];
-        const uint32_t end = L.starts()[bin_cell(mid + w, inv) + 1];
-        for (; j < end; j += 8u) {
-            // (the second hit may lie past the cells: it fails the pair test, as
-            // every hit outside the interval does, or is not looked at)
-            const float x0 = *reinterpret_cast<const float*>(pa + j), x1 = *reinterpret_cast<const float*>(pa + j + 4);
-            const float y0 = *reinterpret_cast<const float*>(pb + j), y1 = *reinterpret_cast<const float*>(pb + j + 4);
-            const float2 a0 = B::diff(c, u, x0, y0), a1 = B::diff(c, u, x1, y1);
-            const float s0 = __builtin_fabsf(a0.x) + __builtin_fabsf(a0.y);
-            const float s1 = __builtin_fabsf(a1.x) + __builtin_fabsf(a1.y);
-            if (__builtin_fminf(s0, s1) <= pre) {
-                if (B::pair(bb, a0)) push_pair(L, B::entry(xi, yi, u, x0, y0));
-                if (j + 4u < end && B::pair(bb, a1)) push_pair(L, B::entry(xi, yi, u, x1, y1));
+        for (int r = 0; r < kBinRounds; ++r) {
+            cell[r] = rank[r] = 0u;
+            if (r * kWave < n1) {
+                cell[r] = bin_cell(B::Key1::key(c, h1.x[r], h1.y[r]), inv);
+                if (r * kWave + lane < n1) rank[r] = atomicAdd(&hist[cell[r]], 4u);
             }
         }
-    };
+        wave_lds_sync();
+        {
+            // exclusive scan: starts()[t] the first byte of cell t's hits
+            const uint4 v = reinterpret_cast<const uint4*>(hist)[lane];
+            const uint32_t own = (v.x + v.y) + (v.z + v.w);
+            const uint32_t s0 = (uint32_t)wave_inclusive_sum((int)own) - own;
+            const uint32_t s1 = s0 + v.x, s2 = s1 + v.y, s3 = s2 + v.z;
+            reinterpret_cast<uint2*>(L.ends)[lane] = make_uint2(s0 | (s1 << 16), s2 | (s3 << 16));
+            if (lane == 0) L.starts()[kBinCap] = (uint16_t)(4 * n1);
+        }
+        wave_lds_sync();
+        char* pa = reinterpret_cast<char*>(L.a1);
+        char* pb = reinterpret_cast<char*>(L.b1);
 #pragma unroll
-    for (int r = 0; r < kBinRounds; ++r)
-        if (r * kWave + lane < n0) scan(h0.x[r], h0.y[r]);
-    for (int i = kBinCap + lane; i < n0; i += kWave) scan(x[o0 + i], y[o0 + i]);
-    wave_lds_sync();
-    const int n_pairs = uniform_i((int)*L.n_pairs());
+        for (int r = 0; r < kBinRounds; ++r)
+            if (r * kWave + lane < n1) {
+                const uint32_t at = L.starts()[cell[r]] + rank[r];
+                const float2 p = B::Key1::payload(c, h1.x[r], h1.y[r]);
+                *reinterpret_cast<float*>(pa + at) = p.x;
+                *reinterpret_cast<float*>(pb + at) = p.y;
+            }
+        wave_lds_sync();
+        // Layer-0 hit (xi, yi): its cells' hits, two per step.  The interval's ends
+        // are moved outwards by |centre| 2^-21 and r1 2^-20 + 2^-126, more than the
+        // rounding of the two sums.
+        const float r1 = bb.r1 * 1.00000095367431640625f + 0x1p-126f, pre = bb.bx + bb.by;
+        auto scan = [&](float xi, float yi) {
+            const float2 u = B::side(c, xi, yi);
+            const float mid = B::centre(u), w = __builtin_fabsf(mid) * 0x1p-21f + r1;
+            uint32_t j = L.starts()[bin_cell(mid - w, inv)];
+            const uint32_t end = L.starts()[bin_cell(mid + w, inv) + 1];
+            for (; j < end; j += 8u) {
+                // (the second hit may lie past the cells: it fails the pair test, as
+                // every hit outside the interval does, or is not looked at)
+                const float x0 = *reinterpret_cast<const float*>(pa + j), x1 = *reinterpret_cast<const float*>(pa + j + 4);
+                const float y0 = *reinterpret_cast<const float*>(pb + j), y1 = *reinterpret_cast<const float*>(pb + j + 4);
+                const float2 a0 = B::diff(c, u, x0, y0), a1 = B::diff(c, u, x1, y1);
+                const float s0 = __builtin_fabsf(a0.x) + __builtin_fabsf(a0.y);
+                const float s1 = __builtin_fabsf(a1.x) + __builtin_fabsf(a1.y);
+                if (__builtin_fminf(s0, s1) <= pre) {
+                    if (B::pair(bb, a0)) push_pair(L, B::entry(xi, yi, u, x0, y0));
+                    if (j + 4u < end && B::pair(bb, a1)) push_pair(L, B::entry(xi, yi, u, x1, y1));
+                }
+            }
+        };
+#pragma unroll
+        for (int r = 0; r < kBinRounds; ++r)
+            if (r * kWave + lane < n0) scan(h0.x[r], h0.y[r]);
+        for (int i = kBinCap + lane; i < n0; i += kWave) scan(x[o0 + i], y[o0 + i]);
+        wave_lds_sync();
+        n_pairs = uniform_i((int)*L.n_pairs());
+    }
     uint32_t cnt = 0;
     if (n_pairs > 0) {
         LayerRegs h2;
         h2.load(x, y, o2, n2);
-        if (n_pairs <= kBinPairs) {
+        if (n_pairs <= B::kFewPairs) {
             for (int p = 0; p < n_pairs; ++p) {
                 const float4 pr = L.pairs[p];
 #pragma unroll
@@ -612,15 +663,19 @@ __device__ uint32_t wave_event_binned(const Consts& c, const float* __restrict__
                 if (cnt >= (uint32_t)c.count_cap) break;  // the result is capped there
             }
         } else {
-            wave_lds_sync();  // the cells overwrite the list
-            LayerRegs g1;
-            g1.load(x, y, o1, n1);
-            const Bins b1 = build_bins<typename B::Key1>(c, g1, n1, L.end1(), L.a1, L.b1);
-            const Bins b2 = build_bins<typename B::Key2>(c, h2, n2, L.end2(), L.a2, L.b2);
-            for (int i0 = 0; i0 < n0; i0 += kWave) {
-                if (i0 + lane < n0) cnt += B::count_i(c, bb, x[o0 + i0 + lane], y[o0 + i0 + lane], b1, b2, L);
-                // decision only: stop once the (capped) result is known
-                if (c.count_cap != INT32_MAX && i0 + kWave < n0 && wave_sum_u(cnt) >= (uint32_t)c.count_cap) break;
+            wave_lds_sync();  // the layer-2 cells overwrite layer 1's
+            const Bins b2 = build_bins<typename B::Key2>(c, h2, n2, L.end1(), L.a1, L.b1);
+            if (n_pairs <= kBinPairs) {
+                for (int p = lane; p < n_pairs; p += kWave) cnt += B::count_pair(c, bb, L.pairs[p], b2, L);
+            } else {
+                LayerRegs g1;
+                g1.load(x, y, o1, n1);
+                const Bins b1 = build_bins<typename B::Key1>(c, g1, n1, L.end2(), L.a2, L.b2);
+                for (int i0 = 0; i0 < n0; i0 += kWave) {
+                    if (i0 + lane < n0) cnt += B::count_i(c, bb, x[o0 + i0 + lane], y[o0 + i0 + lane], b1, b2, L);
+                    // decision only: stop once the (capped) result is known
+                    if (c.count_cap != INT32_MAX && i0 + kWave < n0 && wave_sum_u(cnt) >= (uint32_t)c.count_cap) break;
+                }
             }
             cnt = wave_sum_u(cnt);
         }

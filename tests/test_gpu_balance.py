@@ -86,3 +86,18 @@ def test_stolen_units_of_wide_events(gpu):  # noqa: F811
     wide, square = best_ms(gpu, calls)
     print(f"wide {wide:.3f} ms, square {square:.3f} ms", flush=True)
     assert wide < 4 * square
+
+
+def test_binned_cells_at_loose_cuts(gpu):  # noqa: F811
+    """The binned form where many pairs pass (window test, decisions only,
+    20,000 events of 150 hits per layer, windows 10 times the default): layer 2
+    in cells at once, without listing pairs first (3.7 times the default
+    windows' time where every event first listed its pairs)."""
+    from paper_1810_11966_amd import trig
+    b = batch(gpu, np.full(20_000, 150), seed=6)
+    calls = [lambda w=w: trig.select(*b, test="window", form="binned", slope_window=(w, w),
+                                     extra_flags=trig.TRIG_DECISION_ONLY) for w in (0.05, 0.005)]
+    print("[balance] loose cuts, binned", flush=True)
+    loose, tight = best_ms(gpu, calls)
+    print(f"loose {loose:.4f} ms, tight {tight:.4f} ms", flush=True)
+    assert loose < 2.5 * tight
