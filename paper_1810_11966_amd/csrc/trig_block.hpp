@@ -116,6 +116,7 @@ struct SlopeHits {
 
 // TRIG_TEST_MSD_BASIS.
 struct MsdBasisPrune {
+    static constexpr float kClose = 2.4f;  // see direct_scanned
     static constexpr bool kMag = false;  // bounds do not depend on M
     static constexpr bool kEventBounds = false;
     static constexpr bool kZ = false;
@@ -205,6 +206,7 @@ struct MsdBasisPrune {
 // the written-out fit (a0 + a1 M), and survivors are completed with the fit
 // written out.
 struct MsdFitPrune {
+    static constexpr float kClose = 2.4f;  // see direct_scanned
     static constexpr bool kMag = true;  // bounds grow with M >= |c_j|
     static constexpr bool kEventBounds = false;
     static constexpr bool kZ = false;
@@ -257,6 +259,7 @@ struct MsdFitPrune {
 
 // TRIG_TEST_SLOPE_WINDOW.
 struct WindowPrune {
+    static constexpr float kClose = 4.8f;  // see direct_scanned
     static constexpr bool kMag = false;
     static constexpr bool kEventBounds = false;
     static constexpr bool kZ = false;
@@ -799,6 +802,26 @@ __device__ __forceinline__ float direct_consts(const Consts& c, const PairBounds
 __device__ __forceinline__ float direct_const(float d, int lane) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, d), lane));
 }
+// Descriptor word dr of a lane's event with kScan set if the event is worth
+// scanning: it fits, and few enough of its pairs are expected to be close.  For
+// hits spread evenly over a disc of radius S a pair is close with probability
+// kClose (pre / 2 S)^2, and M, the largest sum of two magnitudes, is about 2 S;
+// an event with a close pair pays for the scan and for the exact pass, which
+// takes some five times as long where R T <= kPBuf (1.6 close pairs expected:
+// 80 % of such events have one) and little longer beyond (0.6: 45 %).  Scanning
+// every event / so, us: 20,000 events of 100 hits per layer, default windows
+// 56.1, 45.1, MSD at 10 times the default cuts 63.2, 47.8; 40,000 of 90 with
+// stealing, default windows 159, 130; 100,000 of 30 at 30 times the default
+// cuts 68.3, 60.7; nothing at the default MSD cuts.
+constexpr uint32_t kScan = 1u << 19;
+template <class P>
+__device__ __forceinline__ uint32_t direct_scanned(uint32_t da, uint32_t db, uint32_t dr, float pre, float M) {
+    const uint32_t T = dr >> 20, R = (da >> 26) & 31u;
+    const float q = M * __builtin_amdgcn_rcpf(pre);  // NaN (no bound) scans
+    const float close = (float)__umul24((da >> 13) & 8191u, db >> 13) * P::kClose;
+    const bool many = close > q * q * (R * T > (uint32_t)kPBuf ? 0.6f : 1.6f);
+    return T > 0u && !many ? dr | kScan : dr;
+}
 
 constexpr int kDirectCopies = 16;   // R at most
 constexpr int kDirectSteps = 1023;  // T at most (dr holds it above direct_recip's 17 bits)
@@ -1162,7 +1185,8 @@ __device__ void block_count(BlockLds<HB, NW, EB>& L, const Consts& c, int e_firs
     // Lane i reads the descriptor of the wave's event i (64 at a time).
     for (int tb = w; tb < nsub; tb += NW * kWave) {
         const int mine = min(tb + (int)lane_id() * NW, nsub - 1);
-        const int vda = (int)L.da[mine], vdb = (int)L.db[mine], vdr = (int)L.dr[mine];
+        const int vda = (int)L.da[mine], vdb = (int)L.db[mine];
+        const int vdr = (int)direct_scanned<P>((uint32_t)vda, (uint32_t)vdb, L.dr[mine], direct_const(dc, 2), M);
         for (int i = 0; i < kWave && tb + i * NW < nsub; ++i) {
             const int te = tb + i * NW;
             const uint32_t da = (uint32_t)__builtin_amdgcn_readlane(vda, i);
@@ -1176,8 +1200,9 @@ __device__ void block_count(BlockLds<HB, NW, EB>& L, const Consts& c, int e_firs
             const int oB = S ? o1 : o0, nB = S ? n1 : n0;
             const int oL = S ? o0 : o1, nL = S ? n0 : n1;
             const uint32_t r = dr & ((1u << 17) - 1);
-            if (T > 0 && !wave_any(direct_score<P>(L.stage, oB, nB, oL, nL, T, r, direct_const(dc, S)) <=
-                                   direct_const(dc, 2 + S)))
+            if ((dr & kScan) != 0u &&
+                !wave_any(direct_score<P>(L.stage, oB, nB, oL, nL, T, r, direct_const(dc, S)) <=
+                          direct_const(dc, 2 + S)))
                 continue;  // no pair can pass: the descriptor pass wrote 0
             const uint32_t d2 = (uint32_t)uniform_i((int)L.dc[te]);
             const int o2 = (int)(d2 & kF), n2 = (int)(d2 >> 13);
