@@ -28,7 +28,7 @@ HEADERS = [os.path.join(CSRC, "trig_device.hpp"), os.path.join(CSRC, "trig_block
            os.path.join(CSRC, "serve_core.hpp"), os.path.join(INCLUDE, "trig.h"),
            os.path.join(INCLUDE, "trig_probe.h"), os.path.join(INCLUDE, "trig_serve.h"),
            os.path.join(INCLUDE, "trig_filter.h"), os.path.join(INCLUDE, "trig_events.h"),
-           os.path.join(CSRC, "scan_i64.hpp")]
+           os.path.join(CSRC, "scan_i64.hpp"), os.path.join(CSRC, "trig_rules.hpp")]
 ARCH = "gfx950"
 
 COMMON = ["-std=c++17", "-O3", f"--offload-arch={ARCH}", "-ffp-contract=off",

@@ -40,8 +40,10 @@
 #include "trig_block.hpp"
 #include "trig_bounds.hpp"
 #include "trig_device.hpp"
+#include "trig_rules.hpp"
 
 using namespace trig;
+using namespace trig_rules;
 
 namespace {
 
@@ -52,10 +54,6 @@ constexpr int kPersistWaves = 4;    // waves per workgroup, persistent form
 constexpr int kPersistBatch = 4;    // work units taken per atomic
 constexpr int kDefaultTileUnits = 8;  // pair tiles (of 64 pairs) per work unit
 constexpr int kClaimsPerGroup = 8;    // claims per workgroup, pipelined batched form
-constexpr int kRuleHits = 2048;       // built-in rule: hit capacity of a block, its waves
-constexpr int kRuleWaves = 4;
-constexpr double kRuleFill = 0.92;    // and hits per block over the capacity
-constexpr double kLargeMean = 109.0;  // block stealing: hits per event from which blocks hold 4096
 constexpr int kZHits = 2048;          // per-hit z: hits and waves of a block,
 constexpr int kZWaves = 4;
 constexpr int kMinZEvents = 8;        // and the events it has to hold to be used
@@ -821,47 +819,11 @@ int launch_persistent(const trig_events_csr* ev, const trig_hits* h, const Const
 
 __global__ void k_zero_u32(unsigned* p, int stride) { p[threadIdx.x * stride] = 0u; }
 
-// Shape of the batched form: LDS hit capacity (hb), waves per workgroup (nw)
-// and events per block (eb).  Given values are used as they are; the default
-// is kRuleHits hits and kRuleWaves waves, eight workgroups on a CU, at every
-// multiplicity, filled to kRuleFill of the capacity by events of the batch's
-// mean size (a block that overflows is split into sub-blocks by the kernel).
-// Whole calls, MSD, this shape against 1024 hits and 2 waves and 4096 and 4:
-// a million events of 15 hits per layer 120, 140, - us; 60,000 of 100 hits 84,
-// 90, 104; 30,000 of 200 hits 156, 257, 207; 5,000 of 450 hits 290, 221, 301
-// (the binned form's field); only at 300 hits with the window test was 4096
-// faster (364 against 354).  300,000 events of 30 hits take 63.6 us at a fill of
-// 0.92 and 67.3 at 0.85 (20 and 16 events per block).  Block stealing, whose
-// registers leave fewer workgroups on a CU, keeps 4096 hits for events of more
-// than kLargeMean: 300,000 events of 15 hits per layer 132 us with 2048 (251 with
-// 1024), 60,000 of 100 hits 223 (147 with 4096).
-struct BlockShape {
-    int hb, nw, eb;
-};
-// Events per block that fill `fill` of an hb-hit block at the batch's mean
-// event size, but in small batches no more than give every CU kSmallBlocks
-// blocks (and at least one event per wave): there the time is a block's own
-// (1,000 events of 15 hits per layer: 7.7 us at 18 events per block, 5.4 us at
-// one or two per wave).
-constexpr int kSmallBlocks = 4;
-int events_for_fill(double fill, int hb, int nw, int n_events, int n_hits) {
-    const double mean = std::max(n_events > 0 ? (double)n_hits / n_events : 1.0, 1.0);
-    int eb = (int)std::max(1.0, std::min((double)kMaxEB, std::floor(fill * hb / mean)));
-    if (nw > 0 && eb >= nw) eb -= eb % nw;  // whole rounds of events over the waves
-    const int64_t waves = std::max(nw, 1);
-    const int64_t spread = cdiv(cdiv(n_events, (int64_t)device_cus() * kSmallBlocks), waves) * waves;
-    return (int)std::min<int64_t>(eb, std::max(waves, spread));
-}
+static_assert(kMaxEvents == kMaxEB, "the rules' largest block");
 
 BlockShape choose_block_shape(const trig_params* p, int n_events, int n_hits) {
-    const double mean = n_events > 0 ? (double)n_hits / n_events : 1.0;
-    int hb = p->block_hits;
-    if (hb <= 0) hb = (p->flags & TRIG_EXEC_PERSISTENT) && mean > kLargeMean ? 4096 : kRuleHits;
-    int nw = p->block_waves;
-    if (nw <= 0) nw = std::min(kRuleWaves, hb / 512);
-    int eb = p->block_events;
-    if (eb <= 0) eb = events_for_fill(kRuleFill, hb, nw, n_events, n_hits);
-    return {hb, nw, eb};
+    return trig_rules::choose_block_shape(p->block_hits, p->block_waves, p->block_events,
+                                          (p->flags & TRIG_EXEC_PERSISTENT) != 0, n_events, n_hits, device_cus());
 }
 
 using BlockKernel = void (*)(const int32_t*, int, const float*, const float*, Consts, int, int, unsigned*, int,
@@ -1003,7 +965,8 @@ int run_form_z(const trig_events_csr* ev, const trig_hits* h, const trig_params*
         const int n = ev->n_events;
         const double mean = std::max((double)h->n_hits / n, 1.0);
         if (mean * kMinZEvents <= kRuleFill * kZHits) {
-            const int eb = events_for_fill(kRuleFill, kZHits, kZWaves, n, h->n_hits);
+            const int eb = spread_events(events_for_fill(kRuleFill, kZHits, kZWaves, n, h->n_hits), kZWaves, n,
+                                         device_cus(), kSmallBlocks);
             const int vec = ((reinterpret_cast<uintptr_t>(h->x) | reinterpret_cast<uintptr_t>(h->y) |
                               reinterpret_cast<uintptr_t>(h->z)) & 15) == 0;
             const auto kern = eb <= kSmallEB ? k_block_z<P, T, kZHits, kZWaves, kSmallEB>
@@ -1108,7 +1071,9 @@ trig_params resolve_autotune(const trig_params* p, int n_events, int n_hits) {
         if (t.binned) return q;
         if (!q.block_hits) q.block_hits = t.hb;
         if (!q.block_waves) q.block_waves = t.nw;
-        if (!q.block_events) q.block_events = events_for_fill(t.fill, q.block_hits, q.block_waves, n_events, n_hits);
+        if (!q.block_events)
+            q.block_events = spread_events(events_for_fill(t.fill, q.block_hits, q.block_waves, n_events, n_hits),
+                                           q.block_waves, n_events, device_cus(), kSmallBlocks);
         if (t.persistent) q.flags |= TRIG_EXEC_PERSISTENT;
     }
     return q;
@@ -1347,7 +1312,9 @@ int trig_autotune(const trig_events_csr* ev, const trig_hits* hits, const trig_p
             q.flags = (t.binned ? TRIG_EXEC_BINNED : TRIG_EXEC_PRUNED) | (t.persistent ? TRIG_EXEC_PERSISTENT : 0u);
             q.block_hits = t.hb;
             q.block_waves = t.nw;
-            q.block_events = t.binned ? 0 : events_for_fill(t.fill, t.hb, t.nw, n, n_hits);
+            q.block_events = t.binned ? 0
+                                      : spread_events(events_for_fill(t.fill, t.hb, t.nw, n, n_hits), t.nw, n,
+                                                      device_cus(), kSmallBlocks);
             q.out_accepted_ids = nullptr;
             q.out_n_accepted = nullptr;
             double total = 0.0;

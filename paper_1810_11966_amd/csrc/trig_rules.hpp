@@ -1,0 +1,90 @@
+// Rules that choose a launch shape or a kernel from the sizes of a batch.
+// Plain C++ (no HIP): the library's host code and a CPU test (g++) compile the
+// same file.  `cus`: compute units of the device.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+
+namespace trig_rules {
+
+constexpr int kMaxEvents = 128;       // events per block, at most
+constexpr int kRuleHits = 2048;       // batched form: hit capacity of a block, its waves
+constexpr int kRuleWaves = 4;
+constexpr double kRuleFill = 0.92;    // and hits per block over the capacity
+constexpr int kLargeHits = 4096;      // the larger capacity
+
+// Hits per event of a batch, at least one.
+inline double mean_hits(int n_events, int n_hits) {
+    return std::max(n_events > 0 ? (double)n_hits / n_events : 1.0, 1.0);
+}
+
+// Events per block that fill `fill` of an hb-hit block at the batch's mean
+// event size, in whole rounds over nw waves.
+inline int events_for_fill(double fill, int hb, int nw, int n_events, int n_hits) {
+    int eb = (int)std::max(1.0, std::min((double)kMaxEvents, std::floor(fill * hb / mean_hits(n_events, n_hits))));
+    if (nw > 0 && eb >= nw) eb -= eb % nw;
+    return eb;
+}
+
+// The same, but no more than spread the batch over `blocks` blocks per compute
+// unit, and at least one event per wave.
+inline int spread_events(int eb, int nw, int n_events, int cus, int blocks) {
+    const int64_t waves = std::max(nw, 1), per = (int64_t)cus * blocks;
+    const int64_t spread = ((n_events + per - 1) / per + waves - 1) / waves * waves;
+    return (int)std::min<int64_t>(eb, std::max(waves, spread));
+}
+
+// Shape of the batched form: LDS hit capacity (hb), waves per workgroup (nw)
+// and events per block (eb).  Given values (> 0) are used as they are.
+//
+// Default without stealing: kRuleHits hits and kRuleWaves waves, eight
+// workgroups on a CU (seven with more than 52 events in a block), at every
+// multiplicity, filled to kRuleFill of the capacity by events of the batch's
+// mean size (a block that overflows is split into sub-blocks by the kernel).
+// Whole calls, MSD, this shape against 1024 hits and 2 waves and 4096 and 4:
+// a million events of 15 hits per layer 120, 140, - us; 60,000 of 100 hits 84,
+// 90, 104; 30,000 of 200 hits 156, 257, 207; 5,000 of 450 hits 290, 221, 301
+// (the binned form's field); only at 300 hits with the window test was 4096
+// faster (364 against 354).  300,000 events of 30 hits take 63.6 us at a fill of
+// 0.92 and 67.3 at 0.85 (20 and 16 events per block).
+// Batches whose blocks run all at once take smaller ones, kSmallBlocks per CU:
+// the time is a block's own (1,000 events of 15 hits per layer: 7.7 us at 18
+// events per block, 5.4 us at one or two per wave; 25,000 uneven events of 54
+// hits, window test, 14.0 us at four blocks per CU, 10.7 at eight).  If all run
+// at once with kLargeHits too (four per CU) and four events would as often as
+// not overflow kRuleHits, they take that (600 uneven events of 450 hits: 56.6 us
+// with 2048, 35.3 with 4096).
+//
+// Default with stealing: its claims pass one counter and its registers leave
+// five workgroups on a CU (three with kLargeHits), so fewer, larger blocks are
+// better: one per CU in small batches (4,000 events of 15 hits per layer: 16.5 us,
+// at four per CU 40.8), and kLargeHits where they still give every CU one
+// (100,000 events of 25 hits per layer: 62 against 90 us; 8,000: 24.5 against
+// 23.3) and hold more than ten events (40,000 of 140 hits, window test: 236
+// against 224).
+struct BlockShape {
+    int hb, nw, eb;
+};
+constexpr int kSmallBlocks = 8, kStealBlocks = 1;
+
+inline BlockShape choose_block_shape(int hb, int nw, int eb, bool stealing, int n_events, int n_hits, int cus) {
+    const double mean = mean_hits(n_events, n_hits);
+    if (hb <= 0) {
+        hb = kRuleHits;
+        if (stealing) {
+            if (n_hits >= (double)cus * kRuleFill * kLargeHits && mean * 10.0 <= kRuleFill * kLargeHits) hb = kLargeHits;
+        } else if (nw <= 0 && eb <= 0 && mean * kRuleWaves > 0.6 * kRuleHits && n_events <= 4 * kRuleWaves * cus) {
+            hb = kLargeHits;
+            eb = kRuleWaves;
+        }
+    }
+    if (nw <= 0) nw = std::min(kRuleWaves, hb / 512);
+    if (eb <= 0)
+        eb = spread_events(events_for_fill(kRuleFill, hb, nw, n_events, n_hits), nw, n_events, cus,
+                           stealing ? kStealBlocks : kSmallBlocks);
+    return {hb, nw, eb};
+}
+
+}  // namespace trig_rules
