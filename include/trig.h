@@ -300,8 +300,9 @@ typedef struct {
  * rule's shape; block_hits 1024/2048/4096 x block_waves 2/4 x block fill
  * 0.5/0.7/0.85/1.0 of the LDS capacity (in mean event sizes) x block
  * stealing off/on; the binned form with and without stealing.  Each is timed `reps`
- * times (1..100) after one warm-up; every candidate computes the same
- * counts.  Arguments are those
+ * times (1..100) after one warm-up (the rule's shape, the first, twice); every
+ * candidate computes the same counts.  If the rule's shape wins, later batches
+ * of the class get the rule's shape for their own size.  Arguments are those
  * of trig_select, with TRIG_EXEC_AUTOTUNE set in p->flags; block_* fields of
  * p are ignored while timing.  On return (the call synchronises `stream`)
  * out_counts, out_accept (and the compact outputs, if requested) hold the
