@@ -54,9 +54,6 @@ constexpr int kPersistWaves = 4;    // waves per workgroup, persistent form
 constexpr int kPersistBatch = 4;    // work units taken per atomic
 constexpr int kDefaultTileUnits = 8;  // pair tiles (of 64 pairs) per work unit
 constexpr int kClaimsPerGroup = 8;    // claims per workgroup, pipelined batched form
-constexpr int kZHits = 2048;          // per-hit z: hits and waves of a block,
-constexpr int kZWaves = 4;
-constexpr int kMinZEvents = 8;        // and the events it has to hold to be used
 
 // Bound of the rejecting test of wave_count over pairs of the layer-0 hits [i0,
 // i0 + ni) and of nj <= n1 layer-1 hits from j0 on, round the layer's end, of
@@ -953,9 +950,8 @@ int launch_compact(const uint8_t* accept, int n, int32_t* part, int blocks, cons
 }
 
 // Per-hit z: brute force as asked, every other form with slope pruning, from
-// blocks of events in LDS (k_block_z) or, where a block would hold fewer than
-// kMinZEvents events (two per wave) of the batch's mean size, one wave per
-// event from HBM (k_event_z).
+// blocks of events in LDS (k_block_z) or one wave per event from HBM
+// (k_event_z), see trig_rules::blocks_z.
 template <class T, class P>
 int run_form_z(const trig_events_csr* ev, const trig_hits* h, const trig_params* p, const Consts& c,
                const Layout& L, char* ws, int32_t* counts, uint8_t* accept, hipStream_t s) {
@@ -963,21 +959,21 @@ int run_form_z(const trig_events_csr* ev, const trig_hits* h, const trig_params*
     if (p->flags & (TRIG_EXEC_PRUNED | TRIG_EXEC_BINNED)) {
         if (mark_start(s)) return fail(TRIG_EHIP, "hipEventRecord(start)");
         const int n = ev->n_events;
-        const double mean = std::max((double)h->n_hits / n, 1.0);
-        if (mean * kMinZEvents <= kRuleFill * kZHits) {
+        const bool aligned = ((reinterpret_cast<uintptr_t>(h->x) | reinterpret_cast<uintptr_t>(h->y) |
+                               reinterpret_cast<uintptr_t>(h->z)) & 15) == 0;
+        if (blocks_z(aligned, p->test == TRIG_TEST_SLOPE_WINDOW, n, h->n_hits)) {
             const int eb = spread_events(events_for_fill(kRuleFill, kZHits, kZWaves, n, h->n_hits), kZWaves, n,
                                          device_cus(), kSmallBlocks);
-            const int vec = ((reinterpret_cast<uintptr_t>(h->x) | reinterpret_cast<uintptr_t>(h->y) |
-                              reinterpret_cast<uintptr_t>(h->z)) & 15) == 0;
             const auto kern = eb <= kSmallEB ? k_block_z<P, T, kZHits, kZWaves, kSmallEB>
                                              : k_block_z<P, T, kZHits, kZWaves, kMaxEB>;
             hipLaunchKernelGGL(kern, dim3((unsigned)cdiv(n, eb)), dim3(kZWaves * kWave), 0, s, ev->layer_offsets, n,
-                               h->x, h->y, h->z, c, eb, vec, counts, accept, p->out_status);
+                               h->x, h->y, h->z, c, eb, counts, accept, p->out_status);
+            if ((r = check_launch("k_block_z"))) return r;
         } else {
             hipLaunchKernelGGL((k_event_z<P, T>), dim3((unsigned)cdiv(n, kBinWaves)), dim3(kBinWaves * kWave), 0, s,
                                ev->layer_offsets, n, h->x, h->y, h->z, c, counts, accept, p->out_status);
+            if ((r = check_launch("k_event_z"))) return r;
         }
-        if ((r = check_launch("k_event_z"))) return r;
         if (mark_stop(s)) return fail(TRIG_EHIP, "hipEventRecord(stop)");
     } else if (p->flags & TRIG_EXEC_PERSISTENT) {
         const int tile_units = p->tile_pairs ? p->tile_pairs / kWave : kDefaultTileUnits;

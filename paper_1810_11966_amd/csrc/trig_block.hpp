@@ -326,6 +326,8 @@ struct WindowPrune {
 // (a0 + a1 M) / zmin (csrc/trig_bounds.hpp), M and zmin over the event's
 // layers 0 and 1; survivors completed with the per-hit-z fit.
 struct MsdZPrune {
+    static constexpr float kClose = 2.4f;  // see direct_scanned
+    static constexpr bool kSignedZ = true;  // its bounds need z > 0
     static constexpr bool kMag = false;
     static constexpr bool kEventBounds = true;
     static constexpr bool kZ = true;  // reads hits through SlopeHits
@@ -399,6 +401,8 @@ struct MsdZPrune {
 // Per-hit z, window test: the slopes are the test's own quantities, so the
 // layer-1 window is exact, as in WindowPrune.
 struct WindowZPrune {
+    static constexpr float kClose = 4.8f;
+    static constexpr bool kSignedZ = false;
     static constexpr bool kMag = false;
     static constexpr bool kEventBounds = false;
     static constexpr bool kZ = true;  // reads hits through SlopeHits
@@ -1453,17 +1457,72 @@ __device__ uint32_t wave_event_z(const Consts& c, const float* __restrict__ x, c
     return wave_event_pruned<P>(c, pb, sh, ev.o0, ev.n0, ev.o1, ev.n1, ev.o2, ev.n2, px, py);
 }
 
+// Passing triplets of an event staged as approximate slopes (k_block_z) with a
+// close pair: direct_score's lanes and steps again, four steps per vote, each
+// pair once.  Pairs whose approximate slopes differ by at most the exact
+// bounds and the approximation's slack meet layer 2 from HBM; the window test's
+// completion takes the pair test for granted, so there a pair within the slack
+// of the window's edge takes the exact one first (a0: index of st[0];
+// direct_layout's R, T, S and r).
+template <class P>
+__device__ __forceinline__ uint32_t direct_pairs_z(const Consts& c, const PairBounds& pb, float slack,
+                                                   const float2* st, const SlopeHits& sh, int a0, int oB, int nB,
+                                                   int oL, int nL, int S, int o2, int n2, int R, int T, uint32_t r) {
+    const int lane = (int)lane_id();
+    const int w = (nL + 1) >> 1;
+    const int g = div_lane(lane, r);
+    const int j = lane - g * w, j2 = j + w;
+    const bool jv = g < R, jv2 = g < R && j2 < nL;
+    const float2 q = st[oL + j], q2 = st[oL + min(j2, nL - 1)];
+    const int own = (int)__umul24((unsigned)g, (unsigned)T);  // the copy's first hit, read from `from` on
+    const int from = min(own, nB - T);
+    const float2* b = st + oB + from;
+    const float bx = pb.bx + slack, by = pb.by + slack;
+    uint32_t cnt = 0;
+    for (int t0 = 0; t0 < T; t0 += 4) {
+        float m = __builtin_nanf("");
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float2 v = b[min(t0 + u, T - 1)];
+            m = __builtin_fminf(__builtin_fminf(m, P::fold(v.x - q.x, v.y - q.y)), P::fold(v.x - q2.x, v.y - q2.y));
+        }
+        if (!wave_any(m <= pb.pre)) continue;
+#pragma unroll 1
+        for (int k = 0; k < 8 && t0 + (k >> 1) < T; ++k) {  // lane hits j and j2 of each step
+            const int t = t0 + (k >> 1);
+            const float2 v = b[t];
+            const float dx = __builtin_fabsf(v.x - (k & 1 ? q2.x : q.x)), dy = __builtin_fabsf(v.y - (k & 1 ? q2.y : q.y));
+            const bool in = (k & 1 ? jv2 : jv) && from + t >= own && dx <= bx && dy <= by;
+            const uint64_t sure = lanes(in && (P::kMag || (dx < pb.bx - slack && dy < pb.by - slack)));
+            for (uint64_t left = lanes(in); left; left &= left - 1u) {
+                const int L = __builtin_ctzll(left);
+                const int hB = a0 + oB + __builtin_amdgcn_readlane(from, L) + t;
+                const int hL = a0 + oL + __builtin_amdgcn_readlane(j, L) + (k & 1 ? w : 0);
+                const int hi = S ? hL : hB, hj = S ? hB : hL;
+                if (!((sure >> L) & 1u) && !P::pair_mask(pb, sh.at(hi), sh.at(hj))) continue;
+                cnt += P::complete(c, sh, hi, hj, o2, n2);
+                if (cnt >= (uint32_t)c.count_cap) return cnt;  // the result is capped there
+            }
+        }
+    }
+    return cnt;
+}
+
 // Block kernel with per-hit z: blocks of events staged in LDS as k_block does
 // it, but as approximate slopes s' = c rcp(z) (one hardware reciprocal per hit,
 // where the pair test's binary32 divisions take some 40 vector cycles per
 // coordinate).  An event none of whose pairs is close in s' has no passing
-// triplet; the others (a few in a hundred) are counted by wave_event_z from
-// HBM.  With M the block's largest |x|, |y| and zmin its smallest z, s' is
+// triplet; the close pairs of the others (a few events in a hundred at the
+// default MSD cuts) are completed from HBM (direct_pairs_z), events too large
+// for one lane pass or expected to have many are counted there
+// (wave_event_z).  With M the block's largest |x|, |y| and zmin its smallest z, s' is
 // within 2^-21 M / zmin of the slope c / z rounded to binary32 (reciprocal
 // within one step, one product), so |s'_j - s'_i| exceeds |f32(s_j - s_i)| by
-// less than 2^-19 M / zmin, which `pre` adds per plane.  Blocks whose z do not all
-// lie in [2^-100, 2^100], whose slopes could leave binary32's normal range,
-// that are malformed or do not fit in LDS go event by event to wave_event_z.
+// less than 2^-19 M / zmin, which `pre` adds per plane.  Blocks whose z (window:
+// |z|) do not all lie in [2^-100, 2^100], whose slopes could leave binary32's
+// normal range, that are malformed or do not fit in LDS go event by event to
+// wave_event_z, each wave taking the next one that is left.  Needs x, y and z
+// 16-byte aligned.
 // Bound by HBM latency and the pair scan together, as k_block.  1M staggered
 // events of 30 hits per layer, whole call: 0.511 ms with a wave per event from
 // HBM (nine loads of 4 bytes per lane and four divisions for each), 0.229 ms
@@ -1471,10 +1530,11 @@ __device__ uint32_t wave_event_z(const Consts& c, const float* __restrict__ x, c
 template <class P, class T, int HB, int NW, int EB>
 __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(block_waves_per_simd<HB, NW, EB>())))
 void k_block_z(const int32_t* __restrict__ off, int n_events, const float* __restrict__ x,
-               const float* __restrict__ y, const float* __restrict__ z, Consts c, int eb, int vec,
+               const float* __restrict__ y, const float* __restrict__ z, Consts c, int eb,
                int32_t* __restrict__ counts, uint8_t* __restrict__ accept, uint32_t* status) {
     __shared__ __align__(16) BlockLds<HB, NW, EB> L;
     __shared__ uint32_t wzlo[NW], wzhi[NW];  // per wave: ~(smallest z's bits), largest z's bits
+    __shared__ int next_event;               // of a block counted from HBM
     constexpr int NT = NW * kWave;
     const int t = (int)threadIdx.x;
     const int w = uniform_i(t / kWave);
@@ -1491,18 +1551,19 @@ void k_block_z(const int32_t* __restrict__ off, int n_events, const float* __res
     constexpr int kCap = HB - 4;                   // (HitPrefetch's bounds)
     constexpr int Q = (HB / 4 + NT - 1) / NT;      // float4 groups per thread
     const int a0 = base & ~3;
-    const bool fits = vec && 0 <= base && base <= end && end <= c.n_hits && end - base <= kCap;
+    const bool fits = 0 <= base && base <= end && end <= c.n_hits && end - base <= kCap;
     const int nq = fits ? min((end - a0 + 3) >> 2, (c.n_hits - a0) >> 2) : 0;  // groups entirely below n_hits
     const bool whole = nq > 0;
     bool good = false;  // staged, and the block's bounds hold
     PairBounds pb{0.0f, 0.0f, 0.0f};
+    float reach = 0.0f, slack = 0.0f;  // at least every |slope| of a good block; see below
     auto stage_offsets = [&] {
 #pragma unroll
         for (int k = 0; k < OQ; ++k) {
             const int q = t + k * NT;
             if (q <= 3 * ne) L.soff[q] = ov[k];
         }
-        if (t == 0) L.s_bad = 0;
+        if (t == 0) L.s_bad = next_event = 0;
         __syncthreads();
     };
     if (whole) {
@@ -1521,7 +1582,8 @@ void k_block_z(const int32_t* __restrict__ off, int n_events, const float* __res
             const float r = __builtin_amdgcn_rcpf(hz);
             sx = hx * r;
             sy = hy * r;
-            const uint32_t zb = __builtin_bit_cast(uint32_t, hz);  // (0, inf): ordered as z; others above
+            // (0, inf): ordered as z; others above
+            const uint32_t zb = P::kSignedZ ? __builtin_bit_cast(uint32_t, hz) : abs_bits(hz);
             mag = max(mag, mag2(hx, hy));
             zlo = max(zlo, ~zb);
             zhi = max(zhi, zb);
@@ -1562,44 +1624,59 @@ void k_block_z(const int32_t* __restrict__ off, int n_events, const float* __res
         const float inv = 1.0f / __builtin_bit_cast(float, ~lo);
         good = uniform_i(L.s_bad) == 0 && ~lo >= __builtin_bit_cast(uint32_t, 0x1p-100f) &&
                hi <= __builtin_bit_cast(uint32_t, 0x1p100f) && M * inv < 0x1p100f;
-        const float slack = M * inv * 0x1p-19f + 0x1p-100f;
+        slack = M * inv * 0x1p-19f + 0x1p-100f;
         pb = P::slope_bounds(c, M, inv);
         pb.pre += 2.0f * slack;  // one per plane
+        reach = M * inv;
     } else {
         stage_offsets();
         block_check_describe(L, c, e0, ne, a0, counts, accept, status);
         __syncthreads();
     }
-    // Events round-robin over the waves; wave-uniform control flow.
+    // Wave-uniform control flow.
     auto count = [&](int te, int b0, int b1, int b2, int b3) {
         const EventRange ev{b0, b1, b2, b1 - b0, b2 - b1, b3 - b2};
         L.sres[te] = (int32_t)wave_event_z<P, T, 2 * kPBuf>(c, x, y, z, ev, L.pbuf[w]);  // uniform
         wave_lds_sync();
     };
     if (good) {
+        const SlopeHits sh{x, y, z};
         // Lane i reads the descriptor of the wave's event i (64 at a time).
         for (int tb = w; tb < ne; tb += NW * kWave) {
             const int mine = min(tb + (int)lane_id() * NW, ne - 1);
-            const int vda = (int)L.da[mine], vdb = (int)L.db[mine], vdr = (int)L.dr[mine];
+            const int vda = (int)L.da[mine], vdb = (int)L.db[mine];
+            const int vdr = (int)direct_scanned<P>((uint32_t)vda, (uint32_t)vdb, L.dr[mine], pb.pre, reach);
             for (int i = 0; i < kWave && tb + i * NW < ne; ++i) {
                 const int te = tb + i * NW;
                 const uint32_t da = (uint32_t)__builtin_amdgcn_readlane(vda, i);
                 const uint32_t db = (uint32_t)__builtin_amdgcn_readlane(vdb, i);
                 const uint32_t dr = (uint32_t)__builtin_amdgcn_readlane(vdr, i);
                 constexpr uint32_t kF = (1u << 13) - 1;
-                if (((da >> 26) & 31u) == 0u) continue;  // decided in the descriptor pass
+                const int R = (int)((da >> 26) & 31u);
+                if (R == 0) continue;  // decided in the descriptor pass
                 const int o0 = (int)(da & kF), n0 = (int)((da >> 13) & kF), o1 = (int)(db & kF), n1 = (int)(db >> 13);
                 const int S = (int)(da >> 31), TB = (int)(dr >> 20);
+                const int oB = S ? o1 : o0, nB = S ? n1 : n0, oL = S ? o0 : o1, nL = S ? n0 : n1;
+                const uint32_t r = dr & ((1u << 17) - 1);
                 // slopes: the layers differ by a sign
-                if (TB > 0 && !wave_any(direct_score<P>(L.stage, S ? o1 : o0, S ? n1 : n0, S ? o0 : o1, S ? n0 : n1, TB,
-                                                        dr & ((1u << 17) - 1), -1.0f) <= pb.pre))
-                    continue;  // no pair can pass: the descriptor pass wrote 0
-                count(te, uniform_i(L.soff[3 * te]), uniform_i(L.soff[3 * te + 1]), uniform_i(L.soff[3 * te + 2]),
-                      uniform_i(L.soff[3 * te + 3]));
+                if ((dr & kScan) != 0u) {
+                    if (!wave_any(direct_score<P>(L.stage, oB, nB, oL, nL, TB, r, -1.0f) <= pb.pre))
+                        continue;  // no pair can pass: the descriptor pass wrote 0
+                    const uint32_t d2 = (uint32_t)uniform_i((int)L.dc[te]);
+                    L.sres[te] = (int32_t)direct_pairs_z<P>(c, pb, slack, L.stage, sh, a0, oB, nB, oL, nL, S,
+                                                            a0 + (int)(d2 & kF), (int)((d2 >> 13) & kF), R, TB, r);
+                } else {
+                    count(te, uniform_i(L.soff[3 * te]), uniform_i(L.soff[3 * te + 1]), uniform_i(L.soff[3 * te + 2]),
+                          uniform_i(L.soff[3 * te + 3]));
+                }
             }
         }
     } else {
-        for (int te = w; te < ne; te += NW) {
+        for (;;) {
+            int claim = 0;
+            if (lane_id() == 0) claim = atomicAdd(&next_event, 1);
+            const int te = uniform_i(claim);
+            if (te >= ne) break;
             const int b0 = uniform_i(L.soff[3 * te]), b1 = uniform_i(L.soff[3 * te + 1]);
             const int b2 = uniform_i(L.soff[3 * te + 2]), b3 = uniform_i(L.soff[3 * te + 3]);
             if (!(0 <= b0 && b0 <= b1 && b1 <= b2 && b2 <= b3 && b3 <= c.n_hits)) {

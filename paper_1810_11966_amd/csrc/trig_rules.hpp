@@ -87,4 +87,25 @@ inline BlockShape choose_block_shape(int hb, int nw, int eb, bool stealing, int 
     return {hb, nw, eb};
 }
 
+// Per-hit z: whether blocks of events staged in LDS (k_block_z: kZHits hits,
+// kZWaves waves) are faster than a wave per event from HBM (k_event_z).  They
+// need 16-byte aligned arrays (without, nothing is staged: 100,000 events of 70
+// hits per layer 127 us for 122) and at least kMinZEvents events of the mean
+// size, two per wave.  A block's barrier and its longest wave show while the
+// events' own waves would run all at once (8,192 events): in whole calls, blocks
+// against waves, 10,000 events of 8 hits per layer take 6.4 and 7.1 us (MSD), of
+// 60 hits 16.8 and 14.9, 20,000 20.5 and 23.5.  With the window test more events
+// have close pairs, and their completion from HBM is spread less evenly: 20,000
+// of 8 hits 8.0 and 9.0, of 30 hits 17.7 and 13.0, 80,000 33.9 and 37.3, of 60
+// hits 83.9 and 75.4.
+constexpr int kZHits = 2048, kZWaves = 4;
+constexpr int kMinZEvents = 8;
+
+inline bool blocks_z(bool aligned, bool window, int n_events, int n_hits) {
+    const double mean = mean_hits(n_events, n_hits);
+    if (!aligned || mean * kMinZEvents > kRuleFill * kZHits) return false;
+    if (window) return mean <= 120.0 && n_events >= std::max(8192.0, 720.0 * mean);
+    return n_events >= std::max(8192.0, 90.0 * mean);
+}
+
 }  // namespace trig_rules

@@ -65,8 +65,23 @@ static void test_small_batches() {
     CHECK(choose_block_shape(0, 0, 0, true, 40000, 40000 * 420, kCus).hb == 2048);
 }
 
+// Per-hit z: a wave per event for arrays off a 16-byte boundary, small batches
+// and large events.
+static void test_blocks_z() {
+    for (bool window : {false, true}) {
+        CHECK(!blocks_z(false, window, 1000000, 1000000 * 24));
+        CHECK(blocks_z(true, window, 1000000, 1000000 * 24));
+        CHECK(blocks_z(true, window, 1000000, 1000000 * 90));
+        CHECK(!blocks_z(true, window, 3000, 3000 * 90));
+        CHECK(!blocks_z(true, window, 100000, 100000 * 300));
+    }
+    CHECK(blocks_z(true, false, 20000, 20000 * 180) && !blocks_z(true, false, 10000, 10000 * 180));
+    CHECK(blocks_z(true, true, 80000, 80000 * 90) && !blocks_z(true, true, 40000, 40000 * 90));
+}
+
 int main() {
     test_shapes();
+    test_blocks_z();
     test_small_batches();
     if (failures) {
         std::printf("%ld checks failed\n", failures);
