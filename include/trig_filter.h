@@ -60,8 +60,8 @@ typedef struct {
  * call; 0 for n_events < 0; never less for more events): per event 16 bytes
  * of layer and record counts and 512 bytes of records, plus 8 bytes per 4
  * events, each part rounded up.  A workspace with room for 8 bytes per 16
- * events there (and the events rounded up to 16) is accepted too; batches of
- * fewer than 32,768 events then run on fewer waves. */
+ * events there (and the events rounded up to 16) is accepted too; small
+ * batches then run on fewer waves. */
 size_t trig_filter_workspace_bytes(int32_t n_events);
 
 /* Keep the hits of the trigger layers, event by event.
@@ -71,9 +71,9 @@ size_t trig_filter_workspace_bytes(int32_t n_events);
  * the index in out_x/out_y of the first hit of event e in trigger layer l,
  * out_layer_offsets[3*n_events] the total, and the hits of each (event,
  * layer) keep their input order.  Kernels: per-event counts of the three
- * layers and, per wave (four consecutive events of every 16, or two or one
- * in batches of fewer than 32,768 or 16,384), a list of its trigger hits, as
- * 16-byte records of the 32-hit windows that hold some (their start and
+ * layers and, per wave (four events of a workgroup's 16: the wave's number
+ * and every fourth from there, or two of 8 or one of 4 in smaller batches), a
+ * list of its trigger hits, as 16-byte records of the 32-hit windows that hold some (their start and
  * per-layer bit masks) or as 4-byte entries per hit, whichever is shorter at
  * the wave's first trigger hits (one pass over the station numbers); an
  * exclusive scan of the workgroup totals (in small batches each wave sums

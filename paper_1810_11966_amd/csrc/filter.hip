@@ -32,14 +32,16 @@
 #include "trig_device.hpp"
 #include "trig_filter.h"
 #include "scan_i64.hpp"
+#include "trig_rules.hpp"
 
 namespace {
 
 constexpr int kFilterThreads = 256;
 constexpr int kFilterWaves = kFilterThreads / trig::kWave;
 // Events of a wave (PER): 4 where there are enough of them to fill the GPU
-// with waves, else 2 or 1 (filter_per).
-constexpr int kMaxPer = 4;
+// with waves, else 2 or 1 (trig_rules::filter_shape).
+constexpr int kMaxPer = trig_rules::kFilterMaxPer;
+static_assert(kFilterWaves == trig_rules::kFilterWaves, "the rule's workgroups");
 constexpr int kEventRecBytes = 512;  // record bytes per event in the workspace
 
 struct Range {
@@ -384,19 +386,15 @@ struct ScatterRec {
     uint32_t pad;
 };
 
-// Small batches (one event per wave, at most kSelfPrefix workgroups): each
-// wave sums the totals of the workgroups before its own (at most 32 KB from
-// L2) instead of a scan kernel between the two, which with its gap takes
-// longer than the sums (about 5 us against 1 us at 1,251 workgroups).
-constexpr int kSelfPrefix = 4096;
-
+// self: each wave sums the totals of the workgroups before its own (at most
+// 16 KB from L2) instead of a scan kernel between the two (filter_shape).
 template <int PER>
 __global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(PER == kMaxPer ? 8 : 6))) void k_filter_scatter(
     const int64_t* __restrict__ off, int n_events, int64_t n_hits, const uint8_t* __restrict__ st,
     const float* __restrict__ x, const float* __restrict__ y, uint32_t layers, int vec,
     const int32_t* __restrict__ counts, const int64_t* __restrict__ partials,
-    const u32x4r* __restrict__ wave_recs, const int32_t* __restrict__ ev_recs, int n_blocks, int32_t capacity,
-    int32_t* __restrict__ out_off, float* __restrict__ out_x, float* __restrict__ out_y, uint32_t* status) {
+    const u32x4r* __restrict__ wave_recs, const int32_t* __restrict__ ev_recs, int n_blocks, int self,
+    int32_t capacity, int32_t* __restrict__ out_off, float* __restrict__ out_x, float* __restrict__ out_y, uint32_t* status) {
     constexpr int kFilterEvents = PER * kFilterWaves;  // events of a workgroup
     static_assert(kFilterEvents <= trig::kWave, "one lane per event in the prologue");
     constexpr int kPer = PER;
@@ -423,7 +421,6 @@ __global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(
     const uint32_t* went = reinterpret_cast<const uint32_t*>(wrec);
     const u32x4r first = wrec[min(lane, wave_windows<PER>() - 1)];
     const uint32_t first_entry = PER < kMaxPer ? went[lane] : 0u;
-    constexpr bool self = PER == 1;
     const int64_t wg_base = self ? wave_prefix_i64(partials, (int)blockIdx.x) : partials[blockIdx.x];
     if ((int)blockIdx.x == n_blocks - 1 && threadIdx.x == 0) {
         const int64_t total = self ? wg_base + partials[blockIdx.x] : partials[n_blocks];
@@ -679,15 +676,8 @@ FilterLayout filter_layout(int n_events, int per) {
     return L;
 }
 
-// Events per wave: the most that still gives every SIMD of a 256-CU GPU its
-// eight waves.  Fewer waves leave it short of loads in flight (5,003 events of
-// 5,000 hits, shuffled: 54 us at four events per wave); more workgroups than
-// fill it only add prologues and totals to scan.
-constexpr int kOneEvent = 16384;  // fewer events than this: one per wave
-int filter_per(int n_events) { return n_events < kOneEvent ? 1 : (n_events < 2 * kOneEvent ? 2 : kMaxPer); }
-
 template <int PER>
-int launch_filter(const trig_raw_events* ev, const trig_filter_params* p, hipStream_t s) {
+int launch_filter(const trig_raw_events* ev, const trig_filter_params* p, bool self, hipStream_t s) {
     const int n = ev->n_events;
     const FilterLayout L = filter_layout(n, PER);
     char* ws = static_cast<char*>(p->workspace);
@@ -700,14 +690,13 @@ int launch_filter(const trig_raw_events* ev, const trig_filter_params* p, hipStr
     hipLaunchKernelGGL(k_filter_count<PER>, dim3(L.nb), dim3(kFilterThreads), 0, s, ev->offsets, n, ev->n_hits,
                        ev->station, layers, vec, counts, partials, wave_recs, ev_recs, p->out_status);
     if (hipGetLastError() != hipSuccess) return TRIG_EHIP;
-    static_assert(kOneEvent <= kSelfPrefix * kFilterWaves, "one event per wave: the waves sum the totals");
-    if (PER > 1) {
+    if (!self) {
         hipLaunchKernelGGL(k_scan_i64, dim3(1), dim3(kScanThreads), 0, s, partials, (int64_t)L.nb);
         if (hipGetLastError() != hipSuccess) return TRIG_EHIP;
     }
     hipLaunchKernelGGL(k_filter_scatter<PER>, dim3(L.nb), dim3(kFilterThreads), 0, s, ev->offsets, n, ev->n_hits,
                        ev->station, ev->x, ev->y, layers, vec, counts, partials, wave_recs, ev_recs, L.nb,
-                       p->out_capacity, p->out_layer_offsets, p->out_x, p->out_y, p->out_status);
+                       (int)self, p->out_capacity, p->out_layer_offsets, p->out_x, p->out_y, p->out_status);
     return hipGetLastError() == hipSuccess ? TRIG_OK : TRIG_EHIP;
 }
 
@@ -740,9 +729,11 @@ int trig_filter_stations(const trig_raw_events* ev, const trig_filter_params* p,
     if (!p->workspace || p->workspace_bytes < filter_layout(n, kMaxPer).total ||
         (reinterpret_cast<uintptr_t>(p->workspace) & 255))
         return TRIG_EINVAL;
-    int per = filter_per(n);
-    if (p->workspace_bytes < filter_layout(n, per).total) per = kMaxPer;
-    return per == 1 ? launch_filter<1>(ev, p, s) : per == 2 ? launch_filter<2>(ev, p, s) : launch_filter<4>(ev, p, s);
+    trig_rules::FilterShape f = trig_rules::filter_shape(n, ev->n_hits);
+    if (p->workspace_bytes < filter_layout(n, f.per).total) f = trig_rules::filter_shape_of(n, kMaxPer);
+    return f.per == 1   ? launch_filter<1>(ev, p, f.self, s)
+           : f.per == 2 ? launch_filter<2>(ev, p, f.self, s)
+                        : launch_filter<4>(ev, p, f.self, s);
 }
 
 }  // extern "C"

@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <initializer_list>
 
 namespace trig_rules {
 
@@ -106,6 +107,43 @@ inline bool blocks_z(bool aligned, bool window, int n_events, int n_hits) {
     if (!aligned || mean * kMinZEvents > kRuleFill * kZHits) return false;
     if (window) return mean <= 120.0 && n_events >= std::max(8192.0, 720.0 * mean);
     return n_events >= std::max(8192.0, 90.0 * mean);
+}
+
+// Station filter: events per wave (of kFilterWaves per workgroup, 1, 2 or
+// kFilterMaxPer) and whether the scatter's waves sum the workgroup totals
+// before their own (self) instead of a scan kernel between the two.
+//
+// Fewer events per wave keep more loads in flight while the GPU is not full;
+// more workgroups cost prologues and longer sums.  The sums of at most
+// kFilterSelf workgroups take less than the scan and its gap, 5 us: whole
+// calls with 4,000 events 13.6 us with the scan, 11.4 without, 16,000 events
+// (one per wave) 26.5 and 36.2.  So an event per wave up to 6,144 events and
+// two up to 12,288.  Then, 13,000 events of 194 hits with two and the scan or
+// four and the sums 22.0 and 20.7 us, 20,000 of 480 hits 27.9 and 26.7; of
+// large events (kFilterLarge hits) a wave has more to read, and two are the
+// better: 16,000 of 5,004 hits 33.2 and 33.7, 26,000 of 1,260 hits in random
+// station order 69.7 and 73.4.  Four per wave at 50,000 events: 50.4 and 52.7.
+constexpr int kFilterWaves = 4, kFilterMaxPer = 4;
+constexpr int kFilterSelf = 1536;       // workgroups, one or two events per wave
+constexpr int kFilterSelfFour = 2048;   // and four
+constexpr int kFilterLarge = 1000;
+constexpr int kFilterTwo = 32768;       // large events: two per wave below this many
+
+struct FilterShape {
+    int per;    // events per wave
+    bool self;
+};
+
+inline FilterShape filter_shape_of(int n_events, int per) {
+    const int64_t events = (int64_t)per * kFilterWaves, blocks = (n_events + events - 1) / events;
+    return {per, blocks <= (per == kFilterMaxPer ? kFilterSelfFour : kFilterSelf)};
+}
+
+inline FilterShape filter_shape(int n_events, int64_t n_hits) {
+    for (int per : {1, 2})
+        if (filter_shape_of(n_events, per).self) return {per, true};
+    const bool large = n_events > 0 && n_hits / n_events >= kFilterLarge;
+    return filter_shape_of(n_events, large && n_events < kFilterTwo ? 2 : kFilterMaxPer);
 }
 
 }  // namespace trig_rules
