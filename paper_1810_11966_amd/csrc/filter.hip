@@ -386,15 +386,16 @@ struct ScatterRec {
     uint32_t pad;
 };
 
-// self: each wave sums the totals of the workgroups before its own (at most
-// 16 KB from L2) instead of a scan kernel between the two (filter_shape).
-template <int PER>
+// SELF: the workgroup's waves sum the totals of the workgroups before it (a
+// quarter each, from L2) instead of a scan kernel between the two
+// (filter_shape).
+template <int PER, bool SELF>
 __global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(PER == kMaxPer ? 8 : 6))) void k_filter_scatter(
     const int64_t* __restrict__ off, int n_events, int64_t n_hits, const uint8_t* __restrict__ st,
     const float* __restrict__ x, const float* __restrict__ y, uint32_t layers, int vec,
     const int32_t* __restrict__ counts, const int64_t* __restrict__ partials,
-    const u32x4r* __restrict__ wave_recs, const int32_t* __restrict__ ev_recs, int n_blocks, int self,
-    int32_t capacity, int32_t* __restrict__ out_off, float* __restrict__ out_x, float* __restrict__ out_y, uint32_t* status) {
+    const u32x4r* __restrict__ wave_recs, const int32_t* __restrict__ ev_recs, int n_blocks, int32_t capacity,
+    int32_t* __restrict__ out_off, float* __restrict__ out_x, float* __restrict__ out_y, uint32_t* status) {
     constexpr int kFilterEvents = PER * kFilterWaves;  // events of a workgroup
     static_assert(kFilterEvents <= trig::kWave, "one lane per event in the prologue");
     constexpr int kPer = PER;
@@ -421,9 +422,34 @@ __global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(
     const uint32_t* went = reinterpret_cast<const uint32_t*>(wrec);
     const u32x4r first = wrec[min(lane, wave_windows<PER>() - 1)];
     const uint32_t first_entry = PER < kMaxPer ? went[lane] : 0u;
-    const int64_t wg_base = self ? wave_prefix_i64(partials, (int)blockIdx.x) : partials[blockIdx.x];
+    // this lane's event (prologue below), in the same round trip
+    const int j = lane;
+    const int e = e_first + j;
+    const bool in = j < kFilterEvents && e < n_events;
+    int64_t oa = 0, ob = 0;
+    int32_t c0 = 0, c1 = 0, c2 = 0, nr = 0;
+    if (in) {
+        oa = off[e];
+        ob = off[e + 1];
+        c0 = counts[3 * (int64_t)e];
+        c1 = counts[3 * (int64_t)e + 1];
+        c2 = counts[3 * (int64_t)e + 2];
+        nr = ev_recs[e];
+    }
+    int64_t wg_base;
+    if (SELF) {
+        __shared__ int64_t before_all[kFilterWaves];
+        const int nb = (int)blockIdx.x, q0 = (int)((int64_t)nb * w / kFilterWaves);
+        const int q1 = (int)((int64_t)nb * (w + 1) / kFilterWaves);
+        before_all[w] = wave_prefix_i64(partials + q0, q1 - q0);
+        __syncthreads();
+        wg_base = 0;
+        for (int k = 0; k < kFilterWaves; ++k) wg_base += before_all[k];
+    } else {
+        wg_base = partials[blockIdx.x];
+    }
     if ((int)blockIdx.x == n_blocks - 1 && threadIdx.x == 0) {
-        const int64_t total = self ? wg_base + partials[blockIdx.x] : partials[n_blocks];
+        const int64_t total = SELF ? wg_base + partials[blockIdx.x] : partials[n_blocks];
         if (total > cap && status) atomicOr(status, TRIG_FILTER_CAPACITY);
         out_off[3 * (int64_t)n_events] = (int32_t)std::min<int64_t>(total, cap);
     }
@@ -436,26 +462,12 @@ __global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(
     {
         int64_t(*cnt)[3] = cnt_all[w];
         int32_t* nrec = nrec_all[w];
-        const int j = lane;
-        const int e = e_first + j;
-        const bool in = j < kFilterEvents && e < n_events;
-        int64_t c[3] = {0, 0, 0};
-        int32_t nr = 0;
-        Range r{0, 0, false};
+        const int64_t c[3] = {c0, c1, c2};
+        Range r;
+        r.a = oa;
+        r.b = ob;
+        r.ok = in && 0 <= oa && oa <= ob && ob <= n_hits && ob - oa <= (int64_t)INT32_MAX;
         const bool mine = j < kFilterEvents && j % kFilterWaves == w;
-        if (in) {
-            // every load first (one round trip), then their uses
-            const int64_t oa = off[e], ob = off[e + 1];
-            const int32_t c0 = counts[3 * (int64_t)e], c1 = counts[3 * (int64_t)e + 1];
-            const int32_t c2 = counts[3 * (int64_t)e + 2];
-            nr = ev_recs[e];
-            c[0] = c0;
-            c[1] = c1;
-            c[2] = c2;
-            r.a = oa;
-            r.b = ob;
-            r.ok = 0 <= oa && oa <= ob && ob <= n_hits && ob - oa <= (int64_t)INT32_MAX;
-        }
         if (j < kFilterEvents) {
             cnt[j][0] = c[0];
             cnt[j][1] = c[1];
@@ -676,8 +688,8 @@ FilterLayout filter_layout(int n_events, int per) {
     return L;
 }
 
-template <int PER>
-int launch_filter(const trig_raw_events* ev, const trig_filter_params* p, bool self, hipStream_t s) {
+template <int PER, bool SELF>
+int launch_filter(const trig_raw_events* ev, const trig_filter_params* p, hipStream_t s) {
     const int n = ev->n_events;
     const FilterLayout L = filter_layout(n, PER);
     char* ws = static_cast<char*>(p->workspace);
@@ -690,13 +702,14 @@ int launch_filter(const trig_raw_events* ev, const trig_filter_params* p, bool s
     hipLaunchKernelGGL(k_filter_count<PER>, dim3(L.nb), dim3(kFilterThreads), 0, s, ev->offsets, n, ev->n_hits,
                        ev->station, layers, vec, counts, partials, wave_recs, ev_recs, p->out_status);
     if (hipGetLastError() != hipSuccess) return TRIG_EHIP;
-    if (!self) {
+    if (!SELF) {
         hipLaunchKernelGGL(k_scan_i64, dim3(1), dim3(kScanThreads), 0, s, partials, (int64_t)L.nb);
         if (hipGetLastError() != hipSuccess) return TRIG_EHIP;
     }
-    hipLaunchKernelGGL(k_filter_scatter<PER>, dim3(L.nb), dim3(kFilterThreads), 0, s, ev->offsets, n, ev->n_hits,
+    const auto scatter = k_filter_scatter<PER, SELF>;
+    hipLaunchKernelGGL(scatter, dim3(L.nb), dim3(kFilterThreads), 0, s, ev->offsets, n, ev->n_hits,
                        ev->station, ev->x, ev->y, layers, vec, counts, partials, wave_recs, ev_recs, L.nb,
-                       (int)self, p->out_capacity, p->out_layer_offsets, p->out_x, p->out_y, p->out_status);
+                       p->out_capacity, p->out_layer_offsets, p->out_x, p->out_y, p->out_status);
     return hipGetLastError() == hipSuccess ? TRIG_OK : TRIG_EHIP;
 }
 
@@ -730,10 +743,11 @@ int trig_filter_stations(const trig_raw_events* ev, const trig_filter_params* p,
         (reinterpret_cast<uintptr_t>(p->workspace) & 255))
         return TRIG_EINVAL;
     trig_rules::FilterShape f = trig_rules::filter_shape(n, ev->n_hits);
-    if (p->workspace_bytes < filter_layout(n, f.per).total) f = trig_rules::filter_shape_of(n, kMaxPer);
-    return f.per == 1   ? launch_filter<1>(ev, p, f.self, s)
-           : f.per == 2 ? launch_filter<2>(ev, p, f.self, s)
-                        : launch_filter<4>(ev, p, f.self, s);
+    if (p->workspace_bytes < filter_layout(n, f.per).total) f.per = kMaxPer;
+    return f.per == 1   ? launch_filter<1, true>(ev, p, s)
+           : f.per == 2 ? launch_filter<2, true>(ev, p, s)
+           : f.self     ? launch_filter<4, true>(ev, p, s)
+                        : launch_filter<4, false>(ev, p, s);
 }
 
 }  // extern "C"

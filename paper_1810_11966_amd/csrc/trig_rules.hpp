@@ -6,7 +6,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
-#include <initializer_list>
 
 namespace trig_rules {
 
@@ -110,40 +109,33 @@ inline bool blocks_z(bool aligned, bool window, int n_events, int n_hits) {
 }
 
 // Station filter: events per wave (of kFilterWaves per workgroup, 1, 2 or
-// kFilterMaxPer) and whether the scatter's waves sum the workgroup totals
-// before their own (self) instead of a scan kernel between the two.
+// kFilterMaxPer) and whether the scatter's workgroups sum the totals before
+// their own (self) instead of a scan kernel between the two.
 //
 // Fewer events per wave keep more loads in flight while the GPU is not full;
-// more workgroups cost prologues and longer sums.  The sums of at most
-// kFilterSelf workgroups take less than the scan and its gap, 5 us: whole
-// calls with 4,000 events 13.6 us with the scan, 11.4 without, 16,000 events
-// (one per wave) 26.5 and 36.2.  So an event per wave up to 6,144 events and
-// two up to 12,288.  Then, 13,000 events of 194 hits with two and the scan or
-// four and the sums 22.0 and 20.7 us, 20,000 of 480 hits 27.9 and 26.7; of
-// large events (kFilterLarge hits) a wave has more to read, and two are the
-// better: 16,000 of 5,004 hits 33.2 and 33.7, 26,000 of 1,260 hits in random
-// station order 69.7 and 73.4.  Four per wave at 50,000 events: 50.4 and 52.7.
+// more workgroups cost prologues and longer sums.  Whole calls at one, two and
+// four per wave with the sums, events of 194 hits: 4,000 events 11.0, 11.3 and
+// 14.7 us, 6,000 13.4, 12.9 and 16.7, 10,000 18.6, 16.0 and 18.8, 13,000 23.4,
+// 20.9 and 20.8, 20,000 32.7, 26.2 and 25.3.  Of large events (kFilterLarge
+// hits) a wave has more to read, and two are the better for longer: 16,000
+// events of 5,004 hits 36.7, 32.3 and 33.9, 32,000 of 1,260 hits in random
+// station order 93.7, 91.2 and 96.7.  The scan and its gap take 5 us: with it
+// 4,000 events take 13.3 us, 32,000 36.0 against 34.1 with the sums, 50,000
+// 50.1 and 49.8, 80,000 in random order 86.2 and 89.5.
 constexpr int kFilterWaves = 4, kFilterMaxPer = 4;
-constexpr int kFilterSelf = 1536;       // workgroups, one or two events per wave
-constexpr int kFilterSelfFour = 2048;   // and four
-constexpr int kFilterLarge = 1000;
-constexpr int kFilterTwo = 32768;       // large events: two per wave below this many
+constexpr int kFilterOne = 6144, kFilterTwo = 12288;  // at most this many events: one, two per wave
+constexpr int kFilterLarge = 1000, kFilterLargeTwo = 32768;
+constexpr int kFilterSelf = 49152;  // and at most this many: the sums
 
 struct FilterShape {
     int per;    // events per wave
-    bool self;
+    bool self;  // (one or two per wave always)
 };
 
-inline FilterShape filter_shape_of(int n_events, int per) {
-    const int64_t events = (int64_t)per * kFilterWaves, blocks = (n_events + events - 1) / events;
-    return {per, blocks <= (per == kFilterMaxPer ? kFilterSelfFour : kFilterSelf)};
-}
-
 inline FilterShape filter_shape(int n_events, int64_t n_hits) {
-    for (int per : {1, 2})
-        if (filter_shape_of(n_events, per).self) return {per, true};
     const bool large = n_events > 0 && n_hits / n_events >= kFilterLarge;
-    return filter_shape_of(n_events, large && n_events < kFilterTwo ? 2 : kFilterMaxPer);
+    const int per = n_events <= kFilterOne ? 1 : n_events <= (large ? kFilterLargeTwo : kFilterTwo) ? 2 : kFilterMaxPer;
+    return {per, n_events <= kFilterSelf};
 }
 
 }  // namespace trig_rules

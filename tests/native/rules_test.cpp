@@ -79,17 +79,17 @@ static void test_blocks_z() {
     CHECK(blocks_z(true, true, 80000, 80000 * 90) && !blocks_z(true, true, 40000, 40000 * 90));
 }
 
-// Station filter: no wave sums more totals than it is worth, at any size.
+// Station filter: no workgroup sums more totals than it is worth, and one or
+// two events per wave always go with the sums.
 static void test_filter_shape() {
-    for (int n : {1, 6143, 6144, 6145, 12288, 12289, 16384, 32767, 32768, 32769, 100000, 2000000000})
+    for (int n : {1, 6143, 6144, 6145, 12288, 12289, 16384, 32768, 32769, 49152, 49153, 2000000000})
         for (int64_t hits : {0, 10, 999, 1000, 5000}) {
             const FilterShape f = filter_shape(n, hits * n);
             const int64_t blocks = (n + (int64_t)f.per * 4 - 1) / ((int64_t)f.per * 4);
-            CHECK(f.per == 1 || f.per == 2 || f.per == 4);
-            CHECK(blocks <= 2048 || !f.self);
-            CHECK(f.per == (n <= 6144 ? 1 : n <= 12288 || (hits >= 1000 && n < 32768) ? 2 : 4));
-            CHECK(f.self == (n <= 12288 || (f.per == 4 && n <= 32768)));
+            CHECK(f.per == (n <= 6144 ? 1 : n <= 12288 || (hits >= 1000 && n <= 32768) ? 2 : 4));
+            CHECK(f.self ? blocks <= 4096 : f.per == 4 && n > 49152);
         }
+    CHECK(filter_shape(0, 0).per == 1);
 }
 
 int main() {

@@ -164,7 +164,7 @@ def test_filter_event_split(gpu, n_events):  # noqa: F811
     filter_parity(gpu, "split short output", lens, st, capacity=int(np.isin(st, (13, 14, 15)).sum()) // 2)
 
 
-@pytest.mark.parametrize("n_events", (6144, 6145, 12288, 12289, 32769))
+@pytest.mark.parametrize("n_events", (6144, 6145, 12288, 12289, 32768, 32769, 49152, 49153))
 @pytest.mark.parametrize("large", (False, True))
 def test_filter_totals(gpu, n_events, large):  # noqa: F811
     """Both ways to the workgroups' first positions, on both sides of the sizes
@@ -173,7 +173,7 @@ def test_filter_totals(gpu, n_events, large):  # noqa: F811
     rng = np.random.default_rng(n_events)
     lens = rng.integers(0, 12, n_events)
     if large:
-        lens[rng.integers(0, n_events, 16)] = -(-1000 * n_events // 12)
+        lens[rng.integers(0, n_events, 16)] = -(-1000 * n_events // 16)
     filter_parity(gpu, f"totals large={large}", lens, rng.integers(0, 256, int(lens.sum())))
 
 
