@@ -61,12 +61,13 @@ __device__ __forceinline__ int64_t from_lane_below(int64_t v, int64_t first) {
 
 typedef int64_t i64x2 __attribute__((ext_vector_type(2)));
 
-// Streams beyond this many hits (384 MiB of times) do not fit the 256 MiB
+// Streams beyond this many hits (320 MiB of times) do not fit the 256 MiB
 // last-level cache: their loads are non-temporal with two rounds in flight;
 // shorter ones keep the default policy, which finds what an earlier kernel
-// wrote there, with eight.  Whole calls, long form against short: 64 million
-// hits 93 against 110 us, 40 million 66 against 64, 4 million 20 against 13.
-constexpr int64_t kEbLongHits = (int64_t)48 << 20;
+// wrote there, with eight.  Whole calls, long form against short: 60 million
+// hits 89 against 102 us, 50 million 74 and 85, 40 million 66 and 65, 30 million
+// 47.4 and 46.9, 20 million 32.4 and 34.7, 8 million 24 and 20.
+constexpr int64_t kEbLongHits = (int64_t)40 << 20;
 
 // VEC: t is 16-byte aligned.  LONG: see kEbLongHits.
 template <bool VEC, bool LONG>
@@ -144,10 +145,12 @@ __global__ __launch_bounds__(kEbThreads) void k_eb_count(const int64_t* __restri
     }
 }
 
-// Streams of at most this many workgroups (16.8 million hits): each wave sums
-// the totals of the workgroups before its own (at most 8 KB from L2) instead
-// of a scan kernel, which with its gap takes longer (2.4 us and a launch).
-constexpr int kEbSelfPrefix = 1024;
+// Streams of at most this many workgroups (25 million hits): each wave sums
+// the totals of the workgroups before its own (at most 12 KB from L2) instead
+// of a scan kernel.  Whole calls with the sums and with the scan: 8 million
+// hits 17.3 and 19.6 us, 20 million 33.6 and 34.7, 24 million 38.0 and 38.4, 30
+// million 47.5 and 46.9.
+constexpr int kEbSelfPrefix = 1536;
 
 __global__ __launch_bounds__(kEbThreads) void k_eb_scatter(int64_t n, const uint64_t* __restrict__ masks,
                                                            const int32_t* __restrict__ wcount,

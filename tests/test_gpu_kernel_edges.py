@@ -452,3 +452,15 @@ def test_event_building_long_streams(gpu, n, off):  # noqa: F811
     gpu.cuda.synchronize()
     assert int(r.n_events.cpu()[0]) == len(want) - 1 and int(r.status.cpu()[0]) == st
     assert np.array_equal(r.offsets.cpu().numpy()[:len(want)], want)
+
+
+@pytest.mark.parametrize("n", (1536 * 16384, 1536 * 16384 + 1, 40 << 20, (40 << 20) + 1))
+def test_event_building_totals(gpu, n):  # noqa: F811
+    """Both sides of the largest stream whose waves sum the totals themselves
+    and of the largest one read with cached loads: a start every 1,000 hits."""
+    from paper_1810_11966_amd import events as EB
+    h = gpu.arange(n, dtype=gpu.int64, device="cuda")
+    r = EB.build_events(h + 5 * (h // 1000), 3)
+    k = -(-n // 1000)
+    assert int(r.n_events.cpu()[0]) == k and int(r.status.cpu()[0]) == 0
+    assert gpu.equal(r.offsets[:k], h[::1000]) and int(r.offsets[k]) == n
