@@ -68,7 +68,7 @@ __device__ __forceinline__ PreBound pre_bound(const Consts& c, const float* __re
             const int h = ev.o1 + j0 + t - (j0 + t < ev.n1 ? 0 : ev.n1);
             m = __builtin_fmaxf(m, __builtin_fmaxf(__builtin_fabsf(x[h]), __builtin_fabsf(y[h])));
         }
-        const float M = wave_max_f(m), bound = (c.fit_b0x + c.fit_b1x * M) + (c.fit_b0y + c.fit_b1y * M);
+        const float M = wave_max_f(m), bound = T::of_max(c, M);
         // (a bound this loose is not worth staging for: most |pre_k| are about |V2| M)
         return {bound, bound * T::kLoose < __builtin_fabsf(c.V2) * M};
     } else if constexpr (std::is_same<T, MsdZTest>::value) {
@@ -108,9 +108,15 @@ __global__ __launch_bounds__(WPB * kWave) void k_plain(const int32_t* __restrict
     int32_t cnt = load_event(off, e, c.n_hits, ev);
     if (cnt == 0) {
         const uint32_t tiles = pair_tiles(ev);
-        if (tiles)
-            cnt = (int32_t)wave_count<T, 2 * kChunk>(x, y, z, ev, 0, tiles, c,
-                                                     pre_bound<T>(c, x, y, z, ev, 0, ev.n0, 0, ev.n1), lds_all[w]);
+        if (tiles) {
+            bool done = false;
+            if constexpr (T::kTile) {
+                if ((done = one_tile(ev))) cnt = (int32_t)wave_count_tile<T>(x, y, ev, c);
+            }
+            if (!done)
+                cnt = (int32_t)wave_count<T, 2 * kChunk>(x, y, z, ev, 0, tiles, c,
+                                                         pre_bound<T>(c, x, y, z, ev, 0, ev.n0, 0, ev.n1), lds_all[w]);
+        }
     }
     if (lane_id() == 0) write_result(e, cnt, c, counts, accept, status);
 }
@@ -352,6 +358,13 @@ __global__ __launch_bounds__(WPB * kWave) void k_persistent(
                 EventRange ev;
                 load_event(off, e, c.n_hits, ev);  // valid: only such events own units
                 const uint32_t tiles = pair_tiles(ev);
+                if constexpr (T::kTile) {
+                    if (one_tile(ev)) {
+                        const uint32_t cnt = wave_count_tile<T>(x, y, ev, c);
+                        if (lane_id() == 0 && cnt) atomicAdd(&counts[e], (int32_t)cnt);
+                        continue;
+                    }
+                }
                 const uint32_t tb = (uint32_t)((u - ustart[e]) * tile_units);
                 const uint32_t te = min(tiles, tb + (uint32_t)tile_units);
                 // The unit's own bound, from the hits of its pairs: a bound over

@@ -200,7 +200,8 @@ __device__ __forceinline__ uint64_t lanes(bool cmp) { return __builtin_amdgcn_ba
 //   per-hit z, MSD: s_k - s_i, |.| <= (a0 + a1 M) / zmin.
 // kLoose, kNear, kShare: where the rejecting test does not pay, see wave_count;
 // kMinHits: layer-2 hits from which on it does.  kPreTests: pre_pair and pre_k
-// are all that the test itself needs (pre_pass).
+// are all that the test itself needs (pre_pass).  kTile: small events by
+// wave_count_tile, with bound().
 // Invalid pairs and padding are NaN, which fails every comparison.
 // ----------------------------------------------------------------------------
 
@@ -211,9 +212,12 @@ struct MsdBasisTest {
     static constexpr int kNear = 8, kShare = 3, kMinHits = 1;
     static constexpr bool kPreTests = false;
     static constexpr bool kZ = false;  // layer positions from the parameters
+    static constexpr bool kTile = true;
     struct Pair {
         float ax2, bx0, ay2, by0;
     };
+    // The rejecting test's bound (m: the lane's largest |layer-1 coordinate|).
+    __device__ static __forceinline__ float bound(const Consts& c, float) { return c.pre_msd; }
     __device__ static __forceinline__ void stage(const Consts& c, float x, float y, float* h) {
         h[0] = c.V2 * x;
         h[1] = c.V2 * y;
@@ -256,9 +260,14 @@ struct MsdFitTest {
     static constexpr int kNear = 8, kShare = 3, kMinHits = 1;
     static constexpr bool kPreTests = false;
     static constexpr bool kZ = false;  // layer positions from the parameters
+    static constexpr bool kTile = true;
     struct Pair {
         float xi, xj, sx01, yi, yj, sy01;
     };
+    __device__ static __forceinline__ float bound(const Consts& c, float m) { return of_max(c, wave_max_f(m)); }
+    __device__ static __forceinline__ float of_max(const Consts& c, float M) {
+        return (c.fit_b0x + c.fit_b1x * M) + (c.fit_b0y + c.fit_b1y * M);
+    }
     __device__ static __forceinline__ void stage(const Consts& c, float x, float y, float* h) {
         h[0] = x;
         h[1] = y;
@@ -302,7 +311,7 @@ struct WindowTest {
     static constexpr int HF = 2;
     static constexpr float kLoose = 3.0f;
     static constexpr int kNear = 16, kShare = 3, kMinHits = 5;
-    static constexpr bool kPreTests = true;
+    static constexpr bool kPreTests = true, kTile = false;
     static constexpr bool kZ = false;  // layer positions from the parameters
     struct Pair {
         float sxi, syi;  // NaN when the layer-1 window already fails
@@ -346,7 +355,7 @@ struct MsdZTest {
     static constexpr int HF = 6;
     static constexpr float kLoose = 6.0f;
     static constexpr int kNear = 8, kShare = 3, kMinHits = 1;
-    static constexpr bool kPreTests = false;
+    static constexpr bool kPreTests = false, kTile = false;
     static constexpr bool kZ = true;
     struct Pair {
         float xi, xj, sx01, yi, yj, sy01, zi, zj, szz01;
@@ -400,7 +409,7 @@ struct WindowZTest {
     static constexpr int HF = 2;
     static constexpr float kLoose = 3.0f;
     static constexpr int kNear = 16, kShare = 3, kMinHits = 5;
-    static constexpr bool kPreTests = true;
+    static constexpr bool kPreTests = true, kTile = false;
     static constexpr bool kZ = true;
     struct Pair {
         float sxi, syi;  // NaN when the layer-1 window already fails
@@ -711,6 +720,53 @@ __device__ __forceinline__ bool wave_count_pre(const float* __restrict__ x, cons
     return true;
 }
 
+// Passing triplets of a small event, one tile of pairs and at most kTileHits
+// layer-2 hits (T::kTile tests): lane p holds pair p and layer-2 hit p, all in
+// one round trip and without LDS; the layer-2 values reach the lanes through
+// scalar registers.  Bound by instructions and that round trip: 450,000 events
+// of 4 hits per layer, whole call, MSD 147 us by wave_count, 97 here, basis form
+// 137 and 91; of 6 hits 157 and 120, 146 and 111.  At more layer-2 hits the two
+// meet (9 hits, of which some events still are one tile: 180 and 171).
+constexpr int kTileHits = 16;
+
+__device__ __forceinline__ bool one_tile(const EventRange& ev) {
+    return (uint64_t)ev.n0 * (uint64_t)ev.n1 <= (uint64_t)kWave && ev.n2 <= kTileHits;
+}
+
+// (n0, n1, n2 > 0)
+template <class T>
+__device__ __forceinline__ uint32_t wave_count_tile(const float* __restrict__ x, const float* __restrict__ y,
+                                                    const EventRange& ev, const Consts& c) {
+    const int lane = (int)lane_id();
+    // lane / n1: the quotient's distance from a whole number, 0.5 / n1, is far
+    // above its error
+    const int i = (int)(((float)lane + 0.5f) * __builtin_amdgcn_rcpf((float)ev.n1)), j = lane - i * ev.n1;
+    const bool v = i < ev.n0;
+    const int hi = ev.o0 + min(i, ev.n0 - 1), hj = ev.o1 + j, hk = ev.o2 + min(lane, ev.n2 - 1);
+    const float xi = x[hi], yi = y[hi], xj = x[hj], yj = y[hj], xk = x[hk], yk = y[hk];
+    const float2 p = T::pre_pair(c, xi, yi, xj, yj), w = T::pre_k(c, xk, yk);
+    const float bound = T::bound(c, __builtin_fmaxf(__builtin_fabsf(xj), __builtin_fabsf(yj)));
+    auto of_hit = [](float f, int k) {
+        return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(f), k));
+    };
+    float m = __builtin_nanf("");  // fmin drops NaN; all NaN fails
+    for (int k = 0; k < ev.n2; ++k)
+        m = __builtin_fminf(m, __builtin_fabsf(p.x + of_hit(w.x, k)) + __builtin_fabsf(p.y + of_hit(w.y, k)));
+    if (!wave_any(v && m <= bound) && bound < __builtin_inff()) return 0u;
+    const typename T::Pair pr = v ? T::pair(c, xi, yi, xj, yj) : T::invalid();
+    float own[T::HF];
+    T::stage(c, xk, yk, own);
+    uint32_t cnt = 0;
+#pragma unroll 2
+    for (int k = 0; k < ev.n2; ++k) {
+        float h[T::HF];
+#pragma unroll
+        for (int f = 0; f < T::HF; ++f) h[f] = of_hit(own[f], k);
+        cnt += (uint32_t)__builtin_popcountll(T::pass(c, pr, h));
+    }
+    return cnt;
+}
+
 // Passing triplets of one event over pair tiles [t_begin, t_end); each tile
 // is 64 consecutive (i, j) pairs in row-major order (pair p -> i = p / n1,
 // j = p % n1), one pair per lane, looping over every layer-2 hit staged in
@@ -743,8 +799,7 @@ __device__ __forceinline__ bool wave_count_pre(const float* __restrict__ x, cons
 // on.  20,000 events of 30 hits per layer, cuts 1, 10 and 100 times the default
 // in cm, us: MSD 58, 129, 329 (always the full test: 326), basis form 56, 101,
 // 126 (124), window 81, 87, 116 (115); each hit on a track: MSD 130 (280),
-// window 81 (94).  Small events gain less: 200,000 of 3 hits per layer 63, 60
-// and 60 us (68, 57, 60).
+// window 81 (94).
 template <class T, int LF>
 __device__ uint32_t wave_count(const float* __restrict__ x, const float* __restrict__ y,
                                const float* __restrict__ z, const EventRange& ev, uint32_t t_begin,

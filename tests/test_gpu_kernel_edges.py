@@ -177,6 +177,28 @@ def test_filter_totals(gpu, n_events, large):  # noqa: F811
     filter_parity(gpu, f"totals large={large}", lens, rng.integers(0, 256, int(lens.sum())))
 
 
+# -------------------------------------------------- every-triplet forms ---
+
+@pytest.mark.parametrize("test", ("msd", "msd_basis"))
+@pytest.mark.parametrize("form", ("plain", "persistent"))
+def test_one_tile_events(gpu, form, test):  # noqa: F811
+    """Events on both sides of one tile of pairs and of sixteen layer-2 hits,
+    at cuts that pass few, many and all triplets; with a NaN or infinite hit,
+    and with hits at the top of binary32 in every other event."""
+    sizes = [(a, b, c) for a, b in ((1, 1), (1, 64), (64, 1), (1, 65), (65, 1), (8, 8), (9, 7), (5, 13), (7, 9), (2, 32),
+                                    (3, 21), (63, 1), (0, 4), (4, 0)) for c in (0, 1, 2, 15, 16, 17)]
+    s = helpers.ragged_sizes_set(sizes * 4, seed=91)
+    passing = []
+    for f in (1.0, 100.0, 1e6):
+        cuts = dict(msd_max=(0.03 * f * f, 0.025 * f * f))
+        passing.append(int(assert_parity(gpu, s, test, form, f"one tile x{f}", **cuts).sum()))
+        for k, bad in enumerate((np.nan, np.inf, -3.4028235e38)):
+            x = s.x.copy()
+            x[k::7] = bad
+            assert_parity(gpu, synth.EventSet(s.offsets, x, s.y, s.n_tracks), test, form, f"one tile x{f} {bad}", **cuts)
+    assert passing[0] < passing[1] <= passing[2]
+
+
 # ------------------------------------------------------------ per-hit z ---
 
 @pytest.mark.parametrize("test", ("msd", "window"))
