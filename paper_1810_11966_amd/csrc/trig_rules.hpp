@@ -117,14 +117,15 @@ inline bool blocks_z(bool aligned, bool window, int n_events, int n_hits) {
 // four per wave with the sums, events of 194 hits: 4,000 events 11.0, 11.3 and
 // 14.7 us, 6,000 13.4, 12.9 and 16.7, 10,000 18.6, 16.0 and 18.8, 13,000 23.4,
 // 20.9 and 20.8, 20,000 32.7, 26.2 and 25.3.  Of large events (kFilterLarge
-// hits) a wave has more to read, and two are the better for longer: 16,000
-// events of 5,004 hits 36.7, 32.3 and 33.9, 32,000 of 1,260 hits in random
-// station order 93.7, 91.2 and 96.7.  The scan and its gap take 5 us: with it
+// hits) a wave has more to read, and fewer are the better for longer: 8,000
+// events of 5,004 hits 23.1, 21.6 and 25.4, in random station order 42.5, 44.1
+// and 48.6, 16,000 36.7, 32.3 and 33.9, 32,000 of 1,260 hits in random order
+// 93.7, 91.2 and 96.7.  The scan and its gap take 5 us: with it
 // 4,000 events take 13.3 us, 32,000 36.0 against 34.1 with the sums, 50,000
 // 50.1 and 49.8, 80,000 in random order 86.2 and 89.5.
 constexpr int kFilterWaves = 4, kFilterMaxPer = 4;
 constexpr int kFilterOne = 6144, kFilterTwo = 12288;  // at most this many events: one, two per wave
-constexpr int kFilterLarge = 1000, kFilterLargeTwo = 32768;
+constexpr int kFilterLarge = 1000, kFilterLargeOne = 8192, kFilterLargeTwo = 32768;
 constexpr int kFilterSelf = 49152;  // and at most this many: the sums
 
 struct FilterShape {
@@ -134,7 +135,9 @@ struct FilterShape {
 
 inline FilterShape filter_shape(int n_events, int64_t n_hits) {
     const bool large = n_events > 0 && n_hits / n_events >= kFilterLarge;
-    const int per = n_events <= kFilterOne ? 1 : n_events <= (large ? kFilterLargeTwo : kFilterTwo) ? 2 : kFilterMaxPer;
+    const int per = n_events <= (large ? kFilterLargeOne : kFilterOne)   ? 1
+                    : n_events <= (large ? kFilterLargeTwo : kFilterTwo) ? 2
+                                                                         : kFilterMaxPer;
     return {per, n_events <= kFilterSelf};
 }
 

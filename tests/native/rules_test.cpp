@@ -82,11 +82,11 @@ static void test_blocks_z() {
 // Station filter: no workgroup sums more totals than it is worth, and one or
 // two events per wave always go with the sums.
 static void test_filter_shape() {
-    for (int n : {1, 6143, 6144, 6145, 12288, 12289, 16384, 32768, 32769, 49152, 49153, 2000000000})
+    for (int n : {1, 6143, 6144, 6145, 8192, 8193, 12288, 12289, 16384, 32768, 32769, 49152, 49153, 2000000000})
         for (int64_t hits : {0, 10, 999, 1000, 5000}) {
             const FilterShape f = filter_shape(n, hits * n);
             const int64_t blocks = (n + (int64_t)f.per * 4 - 1) / ((int64_t)f.per * 4);
-            CHECK(f.per == (n <= 6144 ? 1 : n <= 12288 || (hits >= 1000 && n <= 32768) ? 2 : 4));
+            CHECK(f.per == (n <= (hits >= 1000 ? 8192 : 6144) ? 1 : n <= 12288 || (hits >= 1000 && n <= 32768) ? 2 : 4));
             CHECK(f.self ? blocks <= 4096 : f.per == 4 && n > 49152);
         }
     CHECK(filter_shape(0, 0).per == 1);
