@@ -62,8 +62,15 @@ inline int spread_events(int eb, int nw, int n_events, int cus, int blocks) {
 // better: one per CU in small batches (4,000 events of 15 hits per layer: 16.5 us,
 // at four per CU 40.8), and kLargeHits where they still give every CU one
 // (100,000 events of 25 hits per layer: 62 against 90 us; 8,000: 24.5 against
-// 23.3) and hold more than ten events (40,000 of 140 hits, window test: 236
-// against 224).
+// 23.3) or four events come near kRuleHits (50,000 of 200 hits: 357 against
+// 398; 40,000 of 140 hits, window test, 236 against 224, but uneven events of
+// 200 hits 375 against 398).  A claim of many large events, or a block that is
+// cut up, holds its workgroup for long, so batches of few and large events take
+// kLargeHits and four of them at a time, or eight where there are more and they
+// fit (events of 100 to 150 hits per layer, four, eight and twelve at a time:
+// 4,000 uneven ones 64, 71 and 98 us, 20,000 116, 119 and 137; 6,000 even ones of
+// 100 hits, MSD 61, 57 and 57, window 61, 62 and 69; 1,900 of 200 hits 65, 104
+// and, with 2048, 89).
 struct BlockShape {
     int hb, nw, eb;
 };
@@ -73,11 +80,19 @@ inline BlockShape choose_block_shape(int hb, int nw, int eb, bool stealing, int 
     const double mean = mean_hits(n_events, n_hits);
     if (hb <= 0) {
         hb = kRuleHits;
-        if (stealing) {
-            if (n_hits >= (double)cus * kRuleFill * kLargeHits && mean * 10.0 <= kRuleFill * kLargeHits) hb = kLargeHits;
-        } else if (nw <= 0 && eb <= 0 && mean * kRuleWaves > 0.6 * kRuleHits && n_events <= 4 * kRuleWaves * cus) {
+        const double four = mean * kRuleWaves, waves = (double)kRuleWaves * cus;  // hits of four events
+        const bool choose = nw <= 0 && eb <= 0;
+        if (!stealing) {
+            if (choose && four > 0.6 * kRuleHits && n_events <= 4 * waves) {
+                hb = kLargeHits;
+                eb = kRuleWaves;
+            }
+        } else if (choose && four > 0.4 * kRuleHits && n_events <= (four > 0.55 * kRuleHits ? 20 : 8) * waves) {
             hb = kLargeHits;
-            eb = kRuleWaves;
+            eb = n_events <= (four > 0.55 * kRuleHits ? 4 : 2) * waves || 2.0 * four > 0.6 * kLargeHits ? kRuleWaves
+                                                                                                     : 2 * kRuleWaves;
+        } else if (n_hits >= (double)cus * kRuleFill * kLargeHits || four > 0.75 * kRuleHits) {
+            hb = kLargeHits;
         }
     }
     if (nw <= 0) nw = std::min(kRuleWaves, hb / 512);

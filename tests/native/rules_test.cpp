@@ -62,7 +62,14 @@ static void test_small_batches() {
     // stealing: 4096 where they fill the CUs
     CHECK(choose_block_shape(0, 0, 0, true, 100000, 100000 * 75, kCus).hb == 4096);
     CHECK(choose_block_shape(0, 0, 0, true, 8000, 8000 * 75, kCus).hb == 2048);
-    CHECK(choose_block_shape(0, 0, 0, true, 40000, 40000 * 420, kCus).hb == 2048);
+    CHECK(choose_block_shape(0, 0, 0, true, 40000, 40000 * 420, kCus).hb == 4096);
+    // or where events are few and large, four or eight at a time
+    for (int n : {300, 1900, 4000, 20000})
+        for (int hits : {300, 450}) {
+            const BlockShape s = choose_block_shape(0, 0, 0, true, n, n * hits, kCus);
+            CHECK(s.hb == 4096 && s.nw == 4 && s.eb == (n <= 4096 || hits > 307 ? 4 : 8));
+        }
+    CHECK(choose_block_shape(0, 0, 0, true, 100000, 100000 * 600, kCus).hb == 4096);
 }
 
 // Per-hit z: a wave per event for arrays off a 16-byte boundary, small batches
