@@ -64,8 +64,13 @@ inline int spread_events(int eb, int nw, int n_events, int cus, int blocks) {
 // (100,000 events of 25 hits per layer: 62 against 90 us; 8,000: 24.5 against
 // 23.3) or four events come near kRuleHits (50,000 of 200 hits: 357 against
 // 398; 40,000 of 140 hits, window test, 236 against 224, but uneven events of
-// 200 hits 375 against 398).  A claim of many large events, or a block that is
-// cut up, holds its workgroup for long, so batches of few and large events take
+// 200 hits 375 against 398).  Those hold kStealEvents, or 0.6 of what fits,
+// while a CU has fewer than kStealParts blocks: stealing is for batches whose heavy events lie
+// together, in blocks that are cut up (300,000 events, the first 2 % of 240
+// hits per layer and the rest of 10: 84 events per block 966 us, 48 of them 589,
+// 2048 hits and 40 events 666; even events lose less, 100,000 of 25 hits 78 for
+// 62; a million of 30 would take 309 for 278, 50,000 of 100 at four 187 for 130).  A claim of many large events
+// holds its workgroup for long, so batches of few and large events take
 // kLargeHits and four of them at a time, or eight where there are more and they
 // fit (events of 100 to 150 hits per layer, four, eight and twelve at a time:
 // 4,000 uneven ones 64, 71 and 98 us, 20,000 116, 119 and 137; 6,000 even ones of
@@ -74,7 +79,7 @@ inline int spread_events(int eb, int nw, int n_events, int cus, int blocks) {
 struct BlockShape {
     int hb, nw, eb;
 };
-constexpr int kSmallBlocks = 8, kStealBlocks = 1;
+constexpr int kSmallBlocks = 8, kStealBlocks = 1, kStealParts = 40, kStealEvents = 28;
 
 inline BlockShape choose_block_shape(int hb, int nw, int eb, bool stealing, int n_events, int n_hits, int cus) {
     const double mean = mean_hits(n_events, n_hits);
@@ -96,9 +101,14 @@ inline BlockShape choose_block_shape(int hb, int nw, int eb, bool stealing, int 
         }
     }
     if (nw <= 0) nw = std::min(kRuleWaves, hb / 512);
-    if (eb <= 0)
+    if (eb <= 0) {
         eb = spread_events(events_for_fill(kRuleFill, hb, nw, n_events, n_hits), nw, n_events, cus,
                            stealing ? kStealBlocks : kSmallBlocks);
+        if (stealing && hb == kLargeHits) {
+            const int most = n_events / (kStealParts * cus) / nw * nw;
+            eb = std::min(eb, std::max({events_for_fill(0.6 * kRuleFill, hb, nw, n_events, n_hits), most, kStealEvents}));
+        }
+    }
     return {hb, nw, eb};
 }
 

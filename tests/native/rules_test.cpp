@@ -63,6 +63,9 @@ static void test_small_batches() {
     CHECK(choose_block_shape(0, 0, 0, true, 100000, 100000 * 75, kCus).hb == 4096);
     CHECK(choose_block_shape(0, 0, 0, true, 8000, 8000 * 75, kCus).hb == 2048);
     CHECK(choose_block_shape(0, 0, 0, true, 40000, 40000 * 420, kCus).hb == 4096);
+    // not quite full while a CU has few of them: heavy events may lie together
+    CHECK(choose_block_shape(0, 0, 0, true, 300000, 300000 * 44, kCus).eb == 48);
+    CHECK(choose_block_shape(0, 0, 0, true, 1000000, 1000000 * 90, kCus).eb == 40);
     // or where events are few and large, four or eight at a time
     for (int n : {300, 1900, 4000, 20000})
         for (int hits : {300, 450}) {
