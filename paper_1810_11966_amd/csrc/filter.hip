@@ -390,7 +390,8 @@ struct ScatterRec {
 // quarter each, from L2) instead of a scan kernel between the two
 // (filter_shape).
 template <int PER, bool SELF>
-__global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(PER == kMaxPer ? 8 : 6))) void k_filter_scatter(
+__global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(PER == kMaxPer ? 8 : 6)))
+void k_filter_scatter(
     const int64_t* __restrict__ off, int n_events, int64_t n_hits, const uint8_t* __restrict__ st,
     const float* __restrict__ x, const float* __restrict__ y, uint32_t layers, int vec,
     const int32_t* __restrict__ counts, const int64_t* __restrict__ partials,
@@ -399,7 +400,7 @@ __global__ __launch_bounds__(kFilterThreads) __attribute__((amdgpu_waves_per_eu(
     constexpr int kFilterEvents = PER * kFilterWaves;  // events of a workgroup
     static_assert(kFilterEvents <= trig::kWave, "one lane per event in the prologue");
     constexpr int kPer = PER;
-    // Per wave, its own copies: no wave waits for another.
+    // Per wave, its own copies: after the totals no wave waits for another.
     __shared__ ScatterEvent ev_all[kFilterWaves][kPer];  // the wave's events w, w + 4, ...
     __shared__ int64_t cnt_all[kFilterWaves][kFilterEvents][3];
     __shared__ int32_t nrec_all[kFilterWaves][kFilterEvents];

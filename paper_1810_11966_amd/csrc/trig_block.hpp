@@ -9,9 +9,10 @@
 //   MSD test (the fit written out): a = f32(U0*c_i + U1*c_j) depends on
 //              (i, j) only, and a triplet that passes a plane has
 //              |a| <= a0 + a1 M for any M >= |c_j| (csrc/trig_bounds.hpp: a
-//              rigorous bound on the fit's binary32 rounding).  M is the
-//              largest |x|, |y| among the staged hits (per block, or per event
-//              for events read from HBM).
+//              rigorous bound on the fit's binary32 rounding).  M is a
+//              bound on |x|, |y| of the staged hits, at most about twice the
+//              largest (mag2; per block, or exact per event for events read
+//              from HBM).
 //   MSD_BASIS: Q = f32(A + f32(b*b)) >= A = f32(a*a) in binary32 (rounding is
 //              monotone and b*b >= 0), so a triplet can pass only if
 //              f32(a*a) <= Qmax in both planes, i.e. |a| <= beta with beta the
@@ -59,9 +60,9 @@ __device__ __forceinline__ int div_small(int a, int n) {
 // floor(lane / n) for 0 <= lane < 64 and 1 <= n <= 64: (lane * r) >> 16 with
 // r = ceil(2^16 / n) (a 24-bit multiply and a shift).  With r n = 2^16 + d,
 // 0 <= d < n, the product is 2^16 lane / n + lane d / n, and lane d / n < 64
-// < 2^16 / n, which never reaches the next multiple of 2^16 / n.  r is
-// computed once per event in the descriptor pass (recip16) and travels with
-// the event's descriptor.
+// < 2^16 / n, which never reaches the next multiple of 2^16 / n.  For events
+// read from HBM (wave_event_z); the staged events' descriptors hold
+// direct_recip instead.
 __device__ __forceinline__ uint32_t recip16(int n) { return (65536u + (uint32_t)n - 1u) / (uint32_t)n; }
 __device__ __forceinline__ int div_lane(int lane, uint32_t r) { return (int)(__umul24((unsigned)lane, r) >> 16); }
 
@@ -716,7 +717,7 @@ __device__ uint32_t fast_exact(const Consts& c, const PairBounds& pb, const H& h
 // in the orientation S (S = 0: layer 1 in the lanes, as wave_event_pruned;
 // S = 1: layer 0): the computation of wave_event_pruned with its loops taken
 // once, and the prefilter minimum (fast_score, per lane) taken over the whole
-// event before one vote.  R, T and S come from the per-event descriptor (event_layout).
+// event before one vote.  R, T and S come from event_layout.
 template <class P>
 __device__ __forceinline__ float fast_score(const float* px, const float* py, int T, int g, float2 q) {
     const float4* ppx = reinterpret_cast<const float4*>(px + g * T);
@@ -984,8 +985,8 @@ __device__ __forceinline__ uint32_t mag4(uint32_t m, float a, float b, float c, 
 }
 __device__ __forceinline__ float mag_of(uint32_t m) { return __builtin_bit_cast(float, min(m, 0x7f800000u)); }
 
-// Returns the largest |x|, |y| among the hits this thread staged (and a few
-// neighbours of the range: only an upper bound is needed).
+// Returns a bound (mag4) on |x|, |y| of the hits this thread staged (and a few
+// neighbours of the range).
 template <int HB, int NT>
 __device__ __forceinline__ uint32_t stage_hits(const float* __restrict__ x, const float* __restrict__ y,
                                                int base, int nh, int n_hits, bool vec, float2* st) {
@@ -1053,7 +1054,7 @@ struct BlockLds {
     uint32_t da[EB], db[EB], dc[EB], dr[EB];
     int32_t soff[3 * EB + 1];
     int32_t sres[EB];
-    float wmag[NW];  // per wave: largest |x|, |y| it staged (TRIG_TEST_MSD bounds)
+    float wmag[NW];  // per wave: bound on |x|, |y| of what it staged (mag_of)
     int s_block, s_next, s_bad;
 };
 
@@ -1072,8 +1073,8 @@ constexpr int block_waves_per_simd() {
 constexpr int kSmallEB = 52;
 static_assert(block_waves_per_simd<2048, 4, kSmallEB>() == 8, "eight 2048-hit workgroups per CU");
 
-// Each wave's largest staged |x|, |y| into L.wmag (whole waves; read after
-// the next barrier by block_mag).  m: mag4 bits.
+// Each wave's bound on its staged |x|, |y| into L.wmag (whole waves; read
+// after the next barrier by block_mag).  m: mag4 bits.
 template <int HB, int NW, int EB>
 __device__ __forceinline__ void publish_mag(BlockLds<HB, NW, EB>& L, uint32_t m) {
     const uint32_t wm = wave_max_u(m);
@@ -1299,7 +1300,7 @@ struct HitGroups {
         vy = *reinterpret_cast<const f32x4*>(y + a0 + 4 * q);
         rest.load(x, y, a0, nq_full);
     }
-    // Returns the largest |x|, |y| of the groups (and m), as mag4 bits.
+    // Returns the mag4 bits of the groups (and m).
     __device__ __forceinline__ uint32_t store(int nq_full, float2* st, uint32_t m) const {
         const int q = (int)threadIdx.x + (K - 1) * NT;
         if (q < nq_full) {
@@ -1342,7 +1343,7 @@ struct HitPrefetch {
         nq_full = nq;
         g.load(x, y, base & ~3, nq);
     }
-    // Stores the block's hits; returns the largest |x|, |y| this thread
+    // Stores the block's hits; returns the mag4 bits of what this thread
     // stored (the groups of a block with nq_full <= 0 are not loaded: 0).
     __device__ __forceinline__ uint32_t store(const float* __restrict__ x, const float* __restrict__ y, int base,
                                               int nh, float2* st) const {
@@ -1491,7 +1492,8 @@ __device__ __forceinline__ uint32_t direct_pairs_z(const Consts& c, const PairBo
         for (int k = 0; k < 8 && t0 + (k >> 1) < T; ++k) {  // lane hits j and j2 of each step
             const int t = t0 + (k >> 1);
             const float2 v = b[t];
-            const float dx = __builtin_fabsf(v.x - (k & 1 ? q2.x : q.x)), dy = __builtin_fabsf(v.y - (k & 1 ? q2.y : q.y));
+            const float dx = __builtin_fabsf(v.x - (k & 1 ? q2.x : q.x));
+            const float dy = __builtin_fabsf(v.y - (k & 1 ? q2.y : q.y));
             const bool in = (k & 1 ? jv2 : jv) && from + t >= own && dx <= bx && dy <= by;
             const uint64_t sure = lanes(in && (P::kMag || (dx < pb.bx - slack && dy < pb.by - slack)));
             for (uint64_t left = lanes(in); left; left &= left - 1u) {
@@ -1515,7 +1517,7 @@ __device__ __forceinline__ uint32_t direct_pairs_z(const Consts& c, const PairBo
 // triplet; the close pairs of the others (a few events in a hundred at the
 // default MSD cuts) are completed from HBM (direct_pairs_z), events too large
 // for one lane pass or expected to have many are counted there
-// (wave_event_z).  With M the block's largest |x|, |y| and zmin its smallest z, s' is
+// (wave_event_z).  With M the block's bound on |x|, |y| and zmin its smallest z, s' is
 // within 2^-21 M / zmin of the slope c / z rounded to binary32 (reciprocal
 // within one step, one product), so |s'_j - s'_i| exceeds |f32(s_j - s_i)| by
 // less than 2^-19 M / zmin, which `pre` adds per plane.  Blocks whose z (window:

@@ -65,12 +65,11 @@ struct Consts {
 };
 
 // The count an event's result holds (errors, negative, unchanged).
-__device__ __forceinline__ int32_t capped(int32_t cnt, const Consts& c) { return cnt < c.count_cap ? cnt : c.count_cap; }
+__device__ __forceinline__ int32_t capped(int32_t cnt, const Consts& c) {
+    return cnt < c.count_cap ? cnt : c.count_cap;
+}
 
 __device__ __forceinline__ int uniform_i(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ float uniform_f(float v) {
-    return __builtin_bit_cast(float, uniform_i(__builtin_bit_cast(int, v)));
-}
 // cond ? a : b for wave-uniform operands, on the scalar unit (a compare
 // and a scalar select; the compiler would otherwise select per lane).
 __device__ __forceinline__ float select_uniform(int cond, float a, float b) {
@@ -93,12 +92,6 @@ __device__ __forceinline__ void wave_lds_sync() {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_wave_barrier();
     asm volatile("" ::: "memory");
-}
-
-// Number of lanes of the wave with pred set (the lane mask goes straight to
-// scalar registers: one compare per predicate, popcount on the scalar unit).
-__device__ __forceinline__ uint32_t wave_popc(bool pred) {
-    return (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(pred));
 }
 
 __device__ __forceinline__ bool wave_any(bool pred) { return __builtin_amdgcn_ballot_w64(pred) != 0ull; }
