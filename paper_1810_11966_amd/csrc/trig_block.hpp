@@ -1059,13 +1059,14 @@ struct BlockLds {
 };
 
 // Waves per SIMD that a workgroup's BlockLds allows on a CU (160 KB of LDS,
-// at most eight waves per SIMD): the register budget k_block is held to.
+// at most eight waves per SIMD, seven where the basis form's 128-entry table
+// at 1024 hits would spill): the register budget k_block is held to.
 template <int HB, int NW, int EB>
 constexpr int block_waves_per_simd() {
     int wg = (int)(163840 / sizeof(BlockLds<HB, NW, EB>));
     if (wg * NW > 4 * 8) wg = 4 * 8 / NW;
     const int w = wg * NW / 4;
-    return w < 1 ? 1 : w;
+    return w < 1 ? 1 : (w > 7 && HB == 1024 ? 7 : w);
 }
 // An event table small enough that eight 2048-hit workgroups of four waves
 // fit on a CU (seven with the full kMaxEB table); blocks of at most kSmallEB
