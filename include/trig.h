@@ -133,11 +133,11 @@ enum {
                                    every-triplet loop from a global counter;
                                    with TRIG_EXEC_PRUNED: workgroups steal event
                                    blocks; with TRIG_EXEC_BINNED: waves steal
-                                   runs of events from 64 slices of the batch.
+                                   runs of events, dealt out to 64 counters.
                                    Needs workspace */
     TRIG_EXEC_BINNED = 2u,      /* binned form for high-multiplicity events:
                                    one wave per event sorts layer 1 (and layer
-                                   2 of events with more than 64 surviving
+                                   2 of events with more than a few surviving
                                    pairs) into cells of a slope-proportional key
                                    in LDS and tests only hits in the cells whose
                                    key interval can pass (MSD tests: bounds on

@@ -106,7 +106,8 @@ inline BlockShape choose_block_shape(int hb, int nw, int eb, bool stealing, int 
                            stealing ? kStealBlocks : kSmallBlocks);
         if (stealing && hb == kLargeHits) {
             const int most = n_events / (kStealParts * cus) / nw * nw;
-            eb = std::min(eb, std::max({events_for_fill(0.6 * kRuleFill, hb, nw, n_events, n_hits), most, kStealEvents}));
+            const int part = events_for_fill(0.6 * kRuleFill, hb, nw, n_events, n_hits);
+            eb = std::min(eb, std::max({part, most, kStealEvents}));
         }
     }
     return {hb, nw, eb};
